@@ -197,3 +197,93 @@ def tolerance(case):
     norm against float64.  Lists: a few selections may fall on ties of the
     float32 scores."""
     return {"rel": 1e-2, "max": 0.4, "differ": 5e-3}
+
+
+# float64 values of the same calls in plain torch, by explicit masks.
+
+def _exact_topk(score, k):
+    """Positions of the k largest entries, ascending; ties go to the lower one."""
+    return torch.sort(torch.sort(score, descending=True, stable=True).indices[:k]).values
+
+
+def _exact_vs_index(q, k, c):
+    """(verticals, cover of the slash tiles over t + 64 for t in -64 .. N - 1) of one head."""
+    N, dev = k.shape[0], k.device
+    rows = torch.arange(N - LAST_Q, N, device=dev)[:, None]
+    off = rows - torch.arange(N, device=dev)[None, :]
+    a = (q[N - LAST_Q:] @ k.T / math.sqrt(D)).masked_fill_(off < 0, -math.inf).softmax(1)
+    ok = off >= 0
+    diag = torch.zeros(N, dtype=torch.float64, device=dev).index_add_(0, off[ok], a[ok])
+    kept = _exact_topk(diag, min(c["ns"], N))
+    edge = torch.zeros(N + BLOCK + 1, dtype=torch.int64, device=dev)
+    edge.index_add_(0, kept + 1, torch.ones_like(kept))              # slash o covers the offsets o - 63 .. o
+    edge.index_add_(0, kept + BLOCK + 1, -torch.ones_like(kept))
+    return _exact_topk(a.sum(0), min(c["nv"], N)), (edge.cumsum(0) > 0)[:N + BLOCK]
+
+
+def _exact_blocks(q, k, topk):
+    """Kept key blocks per query block, ascending, -1 past the end."""
+    s = q.view(-1, BLOCK, D).mean(1) @ k.view(-1, BLOCK, D).mean(1).T
+    NB = s.shape[0]
+    out = torch.full((NB, topk), -1, dtype=torch.int64, device=q.device)
+    for b in range(NB):
+        n = min(topk, b + 1)
+        out[b, :n] = _exact_topk(s[b, :b + 1], n)
+    return out
+
+
+def _exact_rows(q, k, v, i0, mask):
+    """Attention of the rows i0 .. under the mask; a row without a key gives zeros."""
+    used = mask.any(0).nonzero()[:, 0]
+    s = (q[i0:i0 + mask.shape[0]] @ k[used].T / math.sqrt(D)).masked_fill_(~mask[:, used], -math.inf)
+    return s.softmax(1).nan_to_num_(0.0) @ v[used]
+
+
+def exact(case, seed):
+    N, c = case["N"], case
+    heads = c["n_vs"] + c["n_bs"] + c["n_dense"]
+    if c["batch"] * heads * N * N > 32 * 66000 ** 2:
+        return None
+    s = prepare(case, seed)
+    vs, bs, ash, dense = (s[n] for n in ("vs", "bs", "ash", "dense"))
+    Q, K, V = (s[n] if s[n].dim() == 4 else s[n][None] for n in "qkv")
+    hq, group = Q.shape[1], Q.shape[1] // K.shape[1]
+    o = torch.zeros(Q.shape, dtype=torch.float64, device="cuda")
+    blocks, bits = [], []
+    for b in range(c["batch"]):
+        for h in range(hq):
+            q, k, v = (x.double().contiguous() for x in (Q[b, h], K[b, h // group], V[b, h // group]))
+            if h in vs:
+                vert, cover = _exact_vs_index(q, k, c)
+                bits.append((b, vs.index(h), cover))
+            elif h in bs:
+                kept = _exact_blocks(q, k, c["topk"])
+                blocks.append((b, bs.index(h), kept))
+                keep = torch.zeros(N // BLOCK, N // BLOCK + 1, dtype=torch.bool, device="cuda")
+                keep.scatter_(1, kept.where(kept >= 0, kept.new_tensor(N // BLOCK)), True)
+            for i0 in range(0, N, 1024):
+                i = torch.arange(i0, min(i0 + 1024, N), device="cuda")[:, None]
+                j = torch.arange(i0 + len(i), device="cuda")[None, :]
+                if h in vs:
+                    q0 = torch.arange(i0, i0 + len(i), BLOCK, device="cuda")[:, None]
+                    m = cover[(q0 - j + BLOCK).clamp_min(0)].repeat_interleave(BLOCK, 0)
+                    m[:, vert[vert < m.shape[1]]] = True
+                elif h in bs:
+                    m = keep[i0 // BLOCK:(i0 + len(i)) // BLOCK, :j.shape[1] // BLOCK]
+                    m = m.repeat_interleave(BLOCK, 0).repeat_interleave(BLOCK, 1)
+                elif h in ash:
+                    m = (j < c["n_init"]) | (i - j < c["n_local"])
+                else:
+                    m = torch.ones(len(i), j.shape[1], dtype=torch.bool, device="cuda")
+                o[b, h, i0:i0 + len(i)] = _exact_rows(q, k, v, i0, m & (j <= i))
+    out = {"o": o.view(s["q"].shape)}
+    if vs:
+        words = s["vs_index"].cover_words
+        full = torch.zeros(c["batch"] * len(vs), 32 * words, dtype=torch.int64, device="cuda")
+        for b, r, cover in bits:
+            full[b * len(vs) + r, :len(cover)] = cover
+        w = (full.view(-1, words, 32) << torch.arange(32, device="cuda")).sum(2)
+        out["slash_bits"] = torch.where(w >= 1 << 31, w - (1 << 32), w).to(torch.int32)
+    if bs:
+        out["blocks"] = torch.stack([x for _, _, x in sorted(blocks, key=lambda t: t[:2])]).to(torch.int32)
+    return out
