@@ -1035,6 +1035,94 @@ struct StepBuf {
   __device__ inline char *v(int s) const { return lds + (2 + s) * HALF_BYTES; }
 };
 
+constexpr int RING_BYTES = 5 * HALF_BYTES;
+
+// End of the optimistic pass when NW waves of a workgroup have each taken a share of ONE query
+// block's steps: every wave has its own reference m, row sums l and sums O; the row is
+//   O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w,   M = max_w (m_w + log2 l_w)
+// (M is the largest share's mass, so the weighted row sum lies in [1, NW]).  The waves put their O
+// (fp32, 32 KiB) and m, l into their own rings; wave w then writes the rows 64 w / NW ...  Returns
+// false, without having written anything, if some row must be redone exactly: a share overflowed,
+// or a share that may have lost terms to underflow (l_w < 2^-100: at most 2^20 keys of less than
+// 2^(m_w - 100) each) is not below 2^-20 of the row's mass; a row without a key is one.
+template <int NW>
+__device__ inline bool split_finish(const WaveState &st, bf16_t *oh, int64_t o_st, int q0, char *lds, int wave,
+                                    int lane) {
+  constexpr int ML_OFS = 64 * 512, ROWS = 64 / NW;
+  const int n = lane & 31, h = lane >> 5;
+  char *mine = lds + wave * RING_BYTES;
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    const int row = 32 * nb + n;
+    const float l = st.l[nb] + __shfl_xor(st.l[nb], 32);
+    if (h == 0) *reinterpret_cast<float2 *>(mine + ML_OFS + 8 * row) = make_float2(st.m[nb], l);
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)          // 16-byte chunk c of a row at chunk c ^ (row % 32)
+        *reinterpret_cast<float4 *>(mine + row * 512 + (((8 * db + 2 * g + h) ^ n) << 4)) =
+            make_float4(st.o[db][nb][4 * g], st.o[db][nb][4 * g + 1], st.o[db][nb][4 * g + 2], st.o[db][nb][4 * g + 3]);
+  }
+  __syncthreads();
+  float wgt[ROWS / 4][NW];
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < ROWS / 4; ++i) {
+    const int row = ROWS * wave + 4 * i + (lane >> 4);
+    float2 ml[NW];
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      ml[w] = *reinterpret_cast<const float2 *>(lds + w * RING_BYTES + ML_OFS + 8 * row);
+      bad = bad || !(ml[w].y < L_LIMIT);
+      if (ml[w].y > 0.f) M = fmaxf(M, ml[w].x + __builtin_amdgcn_logf(ml[w].y));
+    }
+    float L = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      bad = bad || (ml[w].y < L_TINY && !(M > ml[w].x - 60.f));
+      wgt[i][w] = ml[w].y > 0.f ? fast_exp2(ml[w].x - M) : 0.f;
+      L += wgt[i][w] * ml[w].y;
+    }
+    const float inv = 1.0f / L;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) wgt[i][w] *= inv;
+  }
+  const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+  if (lane == 0) *reinterpret_cast<int *>(mine + ML_OFS + 512) = wave_bad;
+  __syncthreads();
+  int any_bad = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) any_bad |= *reinterpret_cast<const int *>(lds + w * RING_BYTES + ML_OFS + 512);
+  if (__builtin_amdgcn_readfirstlane(any_bad)) {
+    __syncthreads();       // every wave has read the flags: wave 0 may overwrite its ring
+    return false;
+  }
+#pragma unroll
+  for (int i = 0; i < ROWS / 4; ++i) {
+    const int row = ROWS * wave + 4 * i + (lane >> 4), c = lane & 15;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const char *src = lds + w * RING_BYTES + row * 512;
+      const float4 a = *reinterpret_cast<const float4 *>(src + (((2 * c) ^ (row & 31)) << 4));
+      const float4 b = *reinterpret_cast<const float4 *>(src + (((2 * c + 1) ^ (row & 31)) << 4));
+      const float f = wgt[i][w];
+      acc[0] += f * a.x; acc[1] += f * a.y; acc[2] += f * a.z; acc[3] += f * a.w;
+      acc[4] += f * b.x; acc[5] += f * b.y; acc[6] += f * b.z; acc[7] += f * b.w;
+    }
+    uint4 out;
+    unsigned *o32 = reinterpret_cast<unsigned *>(&out);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x2 two = {acc[2 * j], acc[2 * j + 1]};
+      o32[j] = __builtin_bit_cast(unsigned, __builtin_convertvector(two, bf16x2));
+    }
+    *reinterpret_cast<uint4 *>(oh + (int64_t)(q0 + row) * o_st + 8 * c) = out;
+  }
+  return true;
+}
+
 template <bool CONTIG, class Buf>
 __device__ inline void fetch_step(const Buf &sb, int s, const bf16_t *kh, const bf16_t *vh, int64_t k_st,
                                   int64_t v_st, int kbase, const int *cols, int N, int lane) {
@@ -1379,8 +1467,12 @@ struct WavePipe3 {
     if (d.cls == 2 || !has_ref) {
       MaskP m = mp;
       m.lo = d.lo; m.hi = d.hi;
-      if (d.cls == 2) window_mask<1>(s, d.kbase, m, lane);
-      if (!has_ref) special_tile<1>(s, st, d.kbase, m, false, true, c_log2, lane);
+      if (Gen::SINK_MASK) {
+        special_tile<1>(s, st, d.kbase, m, d.cls == 2, !has_ref, c_log2, lane);
+      } else {
+        if (d.cls == 2) window_mask<1>(s, d.kbase, m, lane);
+        if (!has_ref) special_tile<1>(s, st, d.kbase, m, false, true, c_log2, lane);
+      }
     }
     has_ref = true;
   }
@@ -1608,6 +1700,7 @@ __device__ inline void bs_pass(const BsCtx &c, WaveState &st, const LaneOfs &lo,
 // holds a key some row may attend (ids outside [0, NB) and blocks past the
 // diagonal are dropped).
 struct BsGen {
+  static constexpr bool SINK_MASK = false;
   int mine;             // lane i: entry i of the current chunk of the block list
   int n, NB;
   const MaskP &mp;
@@ -1631,8 +1724,9 @@ struct BsGen {
   }
 };
 
-// One work item = one wave: query block b (a position in the processing order, if there is one) of list slot `slot`.
-template <bool ROWS256>
+// One work item = query block b (a position in the processing order, if there is one) of list slot `slot`:
+// one wave, or NW waves of which wave w takes the list entries w, w + NW, ...
+template <bool ROWS256, int NW>
 __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const int32_t *blk_idx,
                                         const int32_t *blk_cnt, const int32_t *order, int topk, int slot, int b,
                                         char *lds) {
@@ -1646,7 +1740,7 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh;
   bf16_t *oh = x.o + head * x.o_sh;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q0 = b * BQ;
 
   WaveState st;
@@ -1657,7 +1751,7 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
   mp.q0 = q0; mp.lo = 0; mp.hi = x.N; mp.n_init = KEY_NONE; mp.n_local = 1;
   BsCtx c;
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
-  c.N = x.N; c.NB = NB; c.buf = StepBuf{lds}; c.c_log2 = x.c_log2;
+  c.N = x.N; c.NB = NB; c.buf = StepBuf{lds + wave * RING_BYTES}; c.c_log2 = x.c_log2;
   // the block list of this query block is walked 64 ids at a time, one per lane
   const int32_t *glist = blk_idx + ((int64_t)slot * NB + b) * topk;
   c.cnt = min(max(blk_cnt[(int64_t)slot * NB + b], 0), topk);
@@ -1670,16 +1764,19 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
   dma_lane_init(dv, x.v_st, lane);
   const int total = c.cnt;
   bool has_ref = false;
-  for (int r0 = 0; r0 < total; r0 += 64) {
-    const int n = min(total - r0, 64);
-    const int mine = lane < n ? glist[r0 + lane] : -1;
+  for (int r0 = wave; r0 < total; r0 += 64 * NW) {
+    const int n = min((total - r0 + NW - 1) / NW, 64);
+    const int mine = lane < n ? glist[r0 + NW * lane] : -1;
     BsGen gen{mine, n, NB, mp, 0, 0};
     WavePipe3<BsGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, reinterpret_cast<const char *>(c.kh),
                                    reinterpret_cast<const char *>(c.vh), (unsigned)x.k_st * 2u,
                                    (unsigned)x.v_st * 2u, dk, dv, mp, c.c_log2, lane};
     pipe.run();
   }
-  if (needs_exact(st)) {
+  if (NW > 1) {
+    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+  }
+  if (NW > 1 || needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
     bs_pass<PASS_MAX>(c, st, lo, mp, lane);
@@ -1696,7 +1793,7 @@ __global__ __launch_bounds__(64) void bs_kernel(QKV x, HeadList hl, const int32_
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  bs_item<ROWS256>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+  bs_item<ROWS256, 1>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1802,7 +1899,12 @@ __device__ inline void vs_pass(const VsCtx &c, WaveState &st, const LaneOfs &lo,
 
 // Generators of the Vertical-Slash steps for the pipelined pass.
 // Slash runs: a chunk of 64 runs held one per lane, each walked 32 keys at a time.
+// NW waves share the walk: each takes every NW-th step of the concatenated runs.  pos may start
+// 32 x (steps of the other waves before this wave's first one) past ke = 0: what lies behind the
+// end of a run is carried into the next.
+template <int NW>
 struct VsRunGen {
+  static constexpr bool SINK_MASK = false;
   int2 mine;            // lane i: run i of the chunk
   int n, q0, N;
   int iv, ks, ke, pos;
@@ -1816,17 +1918,20 @@ struct VsRunGen {
         // the run is causal up to q0 + 63 by construction; only the key window and
         // the diagonal can mask elements
         d.cls = (d.kbase == pos && pos + 31 < ke && pos + 31 <= q0) ? 1 : 2;
-        pos += 32;
+        pos += 32 * NW;
         return true;
       }
       if (iv >= n) return false;
       const int rx = __builtin_amdgcn_readlane(mine.x, iv), ry = __builtin_amdgcn_readlane(mine.y, iv);
       ++iv;
+      const int over = NW == 1 ? 0 : left_over();
       ks = max(q0 - ry + 1, 0);
       ke = min(q0 - rx + 1, N);
-      pos = ks;
+      pos = ks + 32 * over;
     }
   }
+  // steps of the other waves that precede this wave's next one, once pos >= ke
+  __device__ inline int left_over() const { return (pos - ke) >> 5; }
 };
 
 // Gathered verticals: steps of 32 entries of the compacted column list (LDS).
@@ -1846,16 +1951,17 @@ struct VsColGen {
 // Phase B of the optimistic pass: the kept verticals that are causal for the block and outside
 // every run, compacted into this wave's column list and gathered 32 per step through this wave's
 // own ring.  No workgroup barrier: every wave has its own list length.
-template <bool ROWS256>
+// NW waves share the list: wave w takes the chunks w, w + NW, ... of 64 entries.
+template <bool ROWS256, int NW>
 __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QAcc &qa, bool &has_ref,
                                          const LaneOfs &lo, const MaskP &mp, const DmaLane &dk,
-                                         const DmaLane &dv, int lane) {
+                                         const DmaLane &dv, int wave, int lane) {
   const int q0 = c.q0;
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
   const int qlast = q0 + BQ - 1;
   int *cols = c.cols;
-  int vpos = 0;
+  int vpos = 64 * wave;
   while (vpos < c.n_v) {
     int ncol = 0;
     while (vpos < c.n_v && ncol <= VCAP - 64) {
@@ -1870,7 +1976,7 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
       const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
       if (ok) cols[ncol + before] = v;
       ncol += __builtin_popcountll(bal);
-      vpos += 64;
+      vpos += 64 * NW;
       if (__shfl(v, 0) > qlast) { vpos = c.n_v; break; }
     }
     if (ncol == 0) continue;
@@ -1885,9 +1991,9 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
 }
 
 // Optimistic pass of the Vertical-Slash kernel, software pipelined.
-template <bool ROWS256>
+template <bool ROWS256, int NW>
 __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp,
-                                         int lane) {
+                                         int wave, int lane) {
   const int q0 = c.q0;
   bool has_ref = false;
   QAcc qa;
@@ -1898,6 +2004,7 @@ __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const La
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
   // ---- phase A: slash runs, 64 at a time, one per lane (the run list takes no LDS)
+  int over = wave;           // steps of the other waves before this wave's first one
   for (int r0 = 0; r0 < c.n_c; r0 += 64) {
     const int n = min(c.n_c - r0, 64);
     int2 mine = make_int2(KEY_NONE, KEY_NONE);
@@ -1905,16 +2012,17 @@ __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const La
     // runs ascend: those that reach a key >= 0 (t0 <= q0) form a prefix
     const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
     if (usable == 0) break;
-    VsRunGen gen{mine, usable, q0, c.N, 0, 0, 0, 0};
-    WavePipe3<VsRunGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
+    VsRunGen<NW> gen{mine, usable, q0, c.N, 0, 0, 0, 32 * over};
+    WavePipe3<VsRunGen<NW>, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
     pipe.run();
     if (usable < n) break;
+    if (NW > 1) over = gen.left_over();
   }
-  vs_cols_pipelined<ROWS256>(c, st, qa, has_ref, lo, mp, dk, dv, lane);
+  vs_cols_pipelined<ROWS256, NW>(c, st, qa, has_ref, lo, mp, dk, dv, wave, lane);
 }
 
-// One work item = one wave: query block b of list slot `slot`.
-template <bool ROWS256>
+// One work item = query block b of list slot `slot`: one wave, or NW waves that share its steps.
+template <bool ROWS256, int NW>
 __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
                                         const int32_t *cover, const uint32_t *cover_bits,
                                         const int32_t *counts, int nv, int ns, int cover_words, int slot, int b,
@@ -1923,14 +2031,15 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh;
   bf16_t *oh = x.o + head * x.o_sh;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q0 = b * BQ;
+  char *ring = lds + wave * RING_BYTES;
 
   VsCtx c;
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
   // The column list of the vertical phase, which runs two deep on V slots 0 and 1, lives in V slot 2.
-  c.N = x.N; c.q0 = q0; c.buf = StepBuf{lds}; c.c_log2 = x.c_log2;
-  c.cols = reinterpret_cast<int *>(lds + 4 * HALF_BYTES);   // [VCAP + 64]
+  c.N = x.N; c.q0 = q0; c.buf = StepBuf{ring}; c.c_log2 = x.c_log2;
+  c.cols = reinterpret_cast<int *>(ring + 4 * HALF_BYTES);   // [VCAP + 64]
   c.n_v = min(max(counts[slot * 4 + 0], 0), nv);
   c.n_c = min(max(counts[slot * 4 + 2], 0), ns);
   c.vlist = v_idx + (int64_t)slot * nv;
@@ -1944,8 +2053,11 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   MaskP mp;
   mp.q0 = q0; mp.n_init = KEY_NONE; mp.n_local = 1; mp.lo = 0; mp.hi = 0;
 
-  vs_pass_pipelined<ROWS256>(c, st, lo, mp, lane);
-  if (needs_exact(st)) {
+  vs_pass_pipelined<ROWS256, NW>(c, st, lo, mp, wave, lane);
+  if (NW > 1) {
+    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+  }
+  if (NW > 1 || needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
     vs_pass<PASS_MAX>(c, st, lo, mp, lane);
@@ -1963,7 +2075,113 @@ __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  vs_item<ROWS256>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+  vs_item<ROWS256, 1>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+}
+
+// Few work items: four waves per query block, each with a quarter of its steps (and its own ring;
+// 160 KiB, one workgroup per CU).  The time is the longest item's: 128 steps of 32 keys at 4K tokens
+// took 100 us as one wave and take 37 us as four (bound by the CU's load path, 1.3 us per step of
+// all four waves against 0.8 us for one wave alone).  The shares meet once, in split_finish.
+constexpr int SPLIT = 4;
+template <bool ROWS256>
+__global__ __launch_bounds__(64 * SPLIT) void vs_split_kernel(QKV x, HeadList hl, const int32_t *v_idx,
+                                                              const int32_t *cover, const uint32_t *cover_bits,
+                                                              const int32_t *counts, int nv, int ns, int cover_words,
+                                                              Sched sched) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  int slot, b;
+  if (!decode_wg(sched, slot, b)) return;
+  vs_item<ROWS256, SPLIT>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+}
+template <bool ROWS256>
+__global__ __launch_bounds__(64 * SPLIT) void bs_split_kernel(QKV x, HeadList hl, const int32_t *blk_idx,
+                                                              const int32_t *blk_cnt, const int32_t *order, int topk,
+                                                              Sched sched) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  int slot, b;
+  if (!decode_wg(sched, slot, b)) return;
+  bs_item<ROWS256, SPLIT>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+}
+
+// A-shape / dense steps of one query block, 32 keys each: the sink [0, e1), then the window [s2, q0 + 64)
+// (both 64-aligned); each of NW waves takes every NW-th step.
+template <int NW>
+struct AshapeGen {
+  static constexpr bool SINK_MASK = true;
+  const MaskP &mp;
+  int e1, s2, end;
+  int pos;              // 32 x step number
+  __device__ inline AshapeGen(const MaskP &m, int wave) : mp(m), pos(32 * wave) {
+    end = m.q0 + BQ;
+    e1 = min((m.n_init + BK - 1) / BK * BK, end);
+    s2 = max(m.q0 - m.n_local + 1, 0) / BK * BK;
+    if (s2 <= e1) { s2 = 0; e1 = 0; }
+  }
+  __device__ inline bool next(Step &d) {
+    while (true) {
+      const int kbase = pos < e1 ? pos : s2 + (pos - e1);
+      if (kbase >= end) return false;
+      pos += 32 * NW;
+      const int cls = classify_step<32>(kbase, mp);
+      if (cls == 0) continue;
+      d.kbase = kbase; d.lo = mp.lo; d.hi = mp.hi; d.cls = cls; d.cols = nullptr;
+      return true;
+    }
+  }
+};
+
+template <int PASS>
+__device__ inline void ashape_wave_pass(const AshapeGen<1> &gen0, WaveState &st, const LaneOfs &lo, const StepBuf &buf,
+                                        const bf16_t *kh, const bf16_t *vh, const QKV &x, const MaskP &mp, int lane) {
+  AshapeGen<1> gen = gen0;
+  bool has_ref = false;
+  Step d;
+  while (gen.next(d)) {
+    fetch_step<true>(buf, 0, kh, vh, x.k_st, x.v_st, d.kbase, nullptr, x.N, lane);
+    MINF_WAIT_VMCNT(0);
+    contiguous_step<1, PASS>(st, has_ref, lo, buf.k(0), buf.v(0), d.kbase, mp, x.c_log2, lane);
+  }
+}
+
+// A-shape and dense with few work items: four waves per query block instead of one each.
+template <bool ROWS256>
+__global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadList hl, int n_init, int n_local,
+                                                                  Sched sched) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  int slot, b;
+  if (!decode_wg(sched, slot, b)) return;
+  const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
+  const int kvh = to_sgpr(head / x.group);
+  const bf16_t *qh = x.q + head * x.q_sh, *kh = x.k + kvh * x.k_sh, *vh = x.v + kvh * x.v_sh;
+  bf16_t *oh = x.o + head * x.o_sh;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q0 = b * BQ;
+  WaveState st;
+  wave_init(st, qh, x.q_st, q0, lane);
+  LaneOfs lo;
+  lane_offsets(lo, lane);
+  MaskP mp;
+  mp.q0 = q0; mp.lo = 0; mp.hi = x.N; mp.n_init = n_init; mp.n_local = n_local;
+  const StepBuf buf{lds + wave * RING_BYTES};
+  QAcc qa;
+  pin_q(qa, st);
+  DmaLane dk, dv;
+  dma_lane_init(dk, x.k_st, lane);
+  dma_lane_init(dv, x.v_st, lane);
+  bool has_ref = false;
+  AshapeGen<SPLIT> gen(mp, wave);
+  WavePipe3<AshapeGen<SPLIT>, ROWS256> pipe{gen, st, qa, has_ref, lo, buf, reinterpret_cast<const char *>(kh),
+                                            reinterpret_cast<const char *>(vh), (unsigned)x.k_st * 2u,
+                                            (unsigned)x.v_st * 2u, dk, dv, mp, x.c_log2, lane};
+  pipe.run();
+  if (split_finish<SPLIT>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+  load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
+  reset_for_max_pass(st);
+  const AshapeGen<1> all(mp, 0);
+  ashape_wave_pass<PASS_MAX>(all, st, lo, buf, kh, vh, x, mp, lane);
+  finish_max_pass(st, x.c_log2);
+  ashape_wave_pass<PASS_FIX>(all, st, lo, buf, kh, vh, x, mp, lane);
+  wave_finish(st, oh, x.o_st, q0, lds, lane);
 }
 
 // Vertical-Slash and Block-Sparse heads of a layer in ONE launch (the layers of the paper's models
@@ -1990,9 +2208,9 @@ __global__ __launch_bounds__(64) void vs_bs_kernel(QKV x, HeadList hv, VsArgs va
   int kind, slot, b;
   if (!decode_mixed(sv, sb, blockIdx.x, kind, slot, b)) return;
   if (kind == 0)
-    vs_item<ROWS256>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_item<ROWS256, 1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
   else
-    bs_item<ROWS256>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+    bs_item<ROWS256, 1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -2007,7 +2225,6 @@ __global__ __launch_bounds__(64) void vs_bs_kernel(QKV x, HeadList hv, VsArgs va
 // LDS: four rings of 2 K + 3 V slots of 8 KiB (160 KiB); ring slots are
 // indexed by the step number, which is common to the four waves.
 // ---------------------------------------------------------------------------
-constexpr int RING_BYTES = 5 * HALF_BYTES;
 
 // The runs of a head, 64 at a time one per lane; the next 64 are fetched when the schedule
 // reaches them (once per 64 runs; the load waits for the tile loads in flight).
@@ -2314,7 +2531,7 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   }
   if (!active) return;       // no workgroup barrier below this line
   // ---- phase B: verticals, per wave
-  vs_cols_pipelined<ROWS256>(c, st, qa, has_ref, lo, mp, dk, dv, lane);
+  vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
   if (needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
@@ -2332,8 +2549,36 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Largest number of work items (heads x query blocks) for which four waves share an item.  One wave
+// per item leaves SIMDs idle below 1024 items (256 CUs x 4) and ends with the longest item alone; a
+// CU whose four waves all load their own tiles is at its load path, so above that the split only
+// adds its epilogue.  Measured, one wave -> four: Vertical-Slash 256 items of 4K tokens 101 -> 37
+// us, 1024 of 8K 213 -> 163 (short lists 172 -> 136), 4096 of 8K 595 -> 626 (412 -> 500);
+// Block-Sparse 256 items 105 -> 39, 1024 183 -> 160, 4096 720 -> 763.
+constexpr int SPLIT_MAX_ITEMS = 1024;
+// A-shape and dense, whose alternative shares its tiles between four blocks and needs a quarter of
+// the loads: 512 items of 8K tokens 134 -> 83 us (dense 177 -> 86), 1024 items 148 -> 149, with a
+// short window (128, 1024) 62 -> 74.
+constexpr int ASHAPE_SPLIT_MAX_ITEMS = 512;
+
 hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
+  if (hl.n * NB <= ASHAPE_SPLIT_MAX_ITEMS) {
+    const Sched s = make_sched(hl, x.group, NB);
+    const size_t lds = SPLIT * RING_BYTES;
+    const bool rows256 = x.k_st == D && x.v_st == D;
+    const void *fn = rows256 ? reinterpret_cast<const void *>(ashape_split_kernel<true>)
+                             : reinterpret_cast<const void *>(ashape_split_kernel<false>);
+    hipError_t e = set_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    if (rows256)
+      hipLaunchKernelGGL(ashape_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
+                         n_local, s);
+    else
+      hipLaunchKernelGGL(ashape_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
+                         n_local, s);
+    return hipGetLastError();
+  }
   const Sched s = make_sched(hl, x.group, NSB);
   const size_t lds = 8 * TILE_BYTES;   // four K and four V slots
   // rows 256 bytes apart in both K and V (the [head][token][128] layout): cheaper tile fetch
@@ -2353,8 +2598,22 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
                      const int32_t *order, int topk, hipStream_t st) {
   const int NB = x.N / BQ;
   const Sched s = make_sched(hl, x.group, NB);
-  const size_t lds = 5 * HALF_BYTES;
   const bool rows256 = x.k_st == D && x.v_st == D;
+  if (hl.n * NB <= SPLIT_MAX_ITEMS) {
+    const size_t lds = SPLIT * RING_BYTES;
+    const void *fn = rows256 ? reinterpret_cast<const void *>(bs_split_kernel<true>)
+                             : reinterpret_cast<const void *>(bs_split_kernel<false>);
+    hipError_t e = set_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    if (rows256)
+      hipLaunchKernelGGL(bs_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
+                         blk_cnt, order, topk, s);
+    else
+      hipLaunchKernelGGL(bs_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
+                         blk_cnt, order, topk, s);
+    return hipGetLastError();
+  }
+  const size_t lds = 5 * HALF_BYTES;
   const void *fn = rows256 ? reinterpret_cast<const void *>(bs_kernel<true>)
                            : reinterpret_cast<const void *>(bs_kernel<false>);
   hipError_t e = set_lds(fn, lds);
@@ -2392,6 +2651,20 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     return hipGetLastError();
   }
   const Sched s = make_sched(hl, x.group, NB);
+  if (hl.n * NB <= SPLIT_MAX_ITEMS) {
+    const size_t lds = SPLIT * RING_BYTES;
+    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_split_kernel<true>)
+                             : reinterpret_cast<const void *>(vs_split_kernel<false>);
+    hipError_t e = set_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    if (rows256)
+      hipLaunchKernelGGL(vs_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
+                         cover_bits, counts, nv, ns, cover_words, s);
+    else
+      hipLaunchKernelGGL(vs_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
+                         cover_bits, counts, nv, ns, cover_words, s);
+    return hipGetLastError();
+  }
   const size_t lds = 5 * HALF_BYTES;
   const void *fn = rows256 ? reinterpret_cast<const void *>(vs_kernel<true>)
                            : reinterpret_cast<const void *>(vs_kernel<false>);
@@ -2411,6 +2684,11 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
+  if (hv.n * NB <= SPLIT_MAX_ITEMS || hb.n * NB <= SPLIT_MAX_ITEMS) {
+    // few items of a kind: the split kernels (see SPLIT_MAX_ITEMS), one launch per kind
+    const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
+    return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);
+  }
   const Sched sv = make_sched(hv, x.group, NB), sb = make_sched(hb, x.group, NB);
   const VsArgs va{v_idx, cover, cover_bits, counts, nv, ns, cover_words};
   const BsArgs ba{blk_idx, blk_cnt, order, topk};

@@ -1,0 +1,101 @@
+"""The attention kernels that let four waves share a query block (few work items) beside the ones
+that give every block one wave (many), on the same heads, against the oracle.
+
+The number of listed heads decides: 66 heads of 1024 tokens are 1056 items, 2 heads are 32.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import minference_oracle as O
+from tests.helpers import assert_close_rows, random_qkv, to_f64
+from tests.test_gpu_attention import random_bs_index, run_heads, token_major
+
+pytestmark = pytest.mark.gpu
+
+MANY, FEW = list(range(66)), [0, 65]
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2407_02490_amd import binding
+    binding.lib()
+    return binding
+
+
+def inputs(kind, N):
+    q, k, v = random_qkv(91, 66, 2, N)
+    if kind == "overflow":              # late keys outgrow every reference taken before them
+        k = k.clone()
+        k[:, 700:] *= 60.0
+    if kind == "underflow":             # every logit about -228 in the base-2 domain
+        g = torch.Generator().manual_seed(78)
+        u = torch.randn(128, generator=g)
+        u = u / u.norm() * 128 ** 0.5
+        q = (u + 0.3 * torch.randn(66, N, 128, generator=g)).to(torch.bfloat16).cuda()
+        k = (-14.0 * u + 0.3 * torch.randn(2, N, 128, generator=g)).to(torch.bfloat16).cuda()
+    return q, k, v
+
+
+@pytest.mark.parametrize("layout", ["head", "token"])
+@pytest.mark.parametrize("kind", ["normal", "overflow", "underflow"])
+def test_few_and_many_items(B, rng, kind, layout):
+    N = 1024
+    q, k, v = inputs(kind, N)
+    Vl, Sl = sorted(rng.choice(N, 200, replace=False).tolist()), list(range(0, 96)) + [300, 301, 700]
+    idx, cnt = random_bs_index(rng, N // 64, 7)
+    calls = {
+        "dense": (lambda heads, *a: B.minf_dense_attn(*a, heads), lambda Q, K, V: O.dense_attention(Q, K, V)),
+        "ashape": (lambda heads, *a: B.minf_ashape_attn(*a, heads, 100, 200),
+                   lambda Q, K, V: O.ashape_attention(Q, K, V, 100, 200)),
+        "window": (lambda heads, *a: B.minf_ashape_attn(*a, heads, 0, 65),
+                   lambda Q, K, V: O.ashape_attention(Q, K, V, 0, 65)),
+        "vs": (lambda heads, *a: B.minf_vs_attn(*a, heads, B.vs_index_from_host([Vl] * len(heads), [Sl] * len(heads), N)),
+               lambda Q, K, V: O.vs_attention(Q, K, V, Vl, Sl, Bm=64)),
+        "bs": (lambda heads, *a: B.minf_bs_attn(*a, heads, B.bs_index_from_host(np.stack([idx] * len(heads)),
+                                                                               np.stack([cnt] * len(heads)))),
+               lambda Q, K, V: O.bs_attention(Q, K, V, idx, cnt)),
+    }
+    tq, tk, tv = (token_major(t) if layout == "token" else t for t in (q, k, v))
+    for name, (call, oracle) in calls.items():
+        want = {h: oracle(to_f64(q[h]), to_f64(k[h // 33]), to_f64(v[h // 33])) for h in FEW}
+        for heads in (MANY, FEW):
+            o = torch.full_like(q, float("nan"))
+            o = token_major(o) if layout == "token" else o
+            call(heads, tq, tk, tv, o)
+            torch.cuda.synchronize()
+            for h in FEW:
+                assert_close_rows(o[h], want[h], f"{name} {kind} {layout} {len(heads)} heads, head {h}")
+            assert len(heads) == 66 or bool(torch.isnan(o[1:65].float()).all())
+
+
+@pytest.mark.parametrize("Sl", [[0], [0, 70], list(range(0, 8000, 70)), [5000] + list(range(6000, 6300))])
+def test_shares_of_short_and_many_runs(B, rng, Sl):
+    """Runs of fewer steps than waves, more than one chunk of 64 runs, blocks without a run key."""
+    N = 8192
+    q, k, v = random_qkv(92, 1, 1, N)
+    Vl = sorted(rng.choice(N, 700, replace=False).tolist())
+    dev = B.vs_index_from_host([Vl], [Sl], N)
+    o = run_heads(B.minf_vs_attn, q, k, v, [0], dev)
+    Qh, Kh, Vh = to_f64(q[0]), to_f64(k[0]), to_f64(v[0])
+    for b in (0, 1, 2, 63, 77, 78, 93, 94, 126, 127):
+        want = O.vs_attention(Qh, Kh, Vh, Vl, Sl, 64 * b, 64 * b + 64, Bm=64)
+        assert_close_rows(o[0, 64 * b:64 * b + 64], want, f"block {b}")
+
+
+def test_one_launch_of_both_kinds_with_many_items(B, rng):
+    """minf_vs_bs_attn interleaves the two kinds when both have many items: the same bits as the two calls."""
+    N, n = 4160, 17
+    q, k, v = random_qkv(93, 2 * n, 2, N)
+    vs_heads, bs_heads = list(range(n)), list(range(n, 2 * n))
+    Vl, Sl = sorted(rng.choice(N, 200, replace=False).tolist()), list(range(0, 200)) + [300, 301, 2100]
+    vidx = B.vs_index_from_host([Vl] * n, [Sl] * n, N)
+    idx, cnt = random_bs_index(rng, N // 64, 9)
+    bidx = B.bs_index_from_host(np.stack([idx] * n), np.stack([cnt] * n))
+    o1, o2 = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    B.minf_vs_attn(q, k, v, o1, vs_heads, vidx)
+    B.minf_bs_attn(q, k, v, o1, bs_heads, bidx)
+    B.minf_vs_bs_attn(q, k, v, o2, vs_heads, vidx, bs_heads, bidx)
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2)
+    assert_close_rows(o2[3], O.vs_attention(to_f64(q[3]), to_f64(k[0]), to_f64(v[0]), Vl, Sl, Bm=64), "vs")
