@@ -672,7 +672,12 @@ struct AshapeCls {
   }
 };
 
-// Optimistic pass of the shared-tile kernel, software pipelined three deep.
+// Tiles that every row of the workgroup attends (the common part of a long slash run).
+struct AllCls {
+  __device__ inline int of(int) const { return 1; }
+};
+
+// Optimistic pass of the shared-tile kernels, software pipelined three deep.
 // Iteration t: the matrix cores alternate between the logits of tile t+1
 // (K Q^T) and the output update of tile t-1 (V^T P^T) while the vector ALU turns
 // the logits of tile t into P(t), so all exp / convert / row-sum work runs in
@@ -700,14 +705,14 @@ struct AshapeCls {
 //    infinite reference.  The body is one straight path, which keeps the 128
 //    output accumulators in place; the first iteration multiplies a zero P(-1)
 //    with V(0), the last two form logits nobody consumes.
-template <bool ROWS256>
+template <bool ROWS256, class Cls>
 struct AshapeLoop {
   WaveState &st;
   const QAcc &qa;
   const LaneOfs &lo;
   const MaskP &mp;
   const WaveDma &d;
-  AshapeCls cls;
+  Cls cls;
   float c_log2;
   int lane;
   int T, T1, s2;
@@ -721,7 +726,7 @@ struct AshapeLoop {
   static constexpr unsigned v_slot(int i) { return (unsigned)(4 + (i & 3)) * TILE_BYTES; }
   int kb1, kb2, kb3, ti3;    // key bases of tiles t+1, t+2, t+3 (indices clamped to T-1); index of the last
   int cls_cur;
-  bool has_ref;
+  bool &has_ref;
 
   // scalar operands of the coming iteration
   const char *kt_, *vt_;
@@ -900,15 +905,11 @@ struct AshapeLoop {
   }
 };
 
-template <bool ROWS256>
-__device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &d, WaveState &st,
-                                             const LaneOfs &lo, const MaskP &mp, int lane) {
-  QAcc qa;
-  pin_q(qa, st);
-  AshapeLoop<ROWS256> lp{st, qa, lo, mp, d};
-  lp.cls.init(mp);
-  lp.c_log2 = c.c_log2; lp.lane = lane; lp.T = c.T; lp.T1 = c.T1; lp.s2 = c.s2; lp.lds = c.lds;
-  lp.has_ref = false;
+template <bool ROWS256, class Cls>
+__device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &d, WaveState &st, const QAcc &qa,
+                                             bool &has_ref, const LaneOfs &lo, const MaskP &mp, const Cls &cls,
+                                             int lane) {
+  AshapeLoop<ROWS256, Cls> lp{st, qa, lo, mp, d, cls, c.c_log2, lane, c.T, c.T1, c.s2, c.lds, 0, 0, 0, 0, 0, has_ref};
   const int last = c.T - 1;
   const int kb0 = lp.tile_base(0);
   lp.kb1 = lp.tile_base(min(1, last)); lp.kb2 = lp.tile_base(min(2, last));
@@ -932,12 +933,12 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
   // also for a tile this wave does not attend: its (finite) logits are turned into P = 0
   qk_tile_v(sa, qa, lo, c.lds);
   if (lp.cls_cur != 0) {
-    special_tile<2>(sa, st, kb0, mp, lp.cls_cur == 2, true, c.c_log2, lane);
-    lp.has_ref = true;
+    if (lp.cls_cur == 2 || !has_ref) special_tile<2>(sa, st, kb0, mp, lp.cls_cur == 2, !has_ref, c.c_log2, lane);
+    has_ref = true;
   }
   __syncthreads();   // all waves are done with K(0) before iteration 0 overwrites it with K(3)
   lp.prepare(0);
-  typename AshapeLoop<ROWS256>::Lead lead;
+  typename AshapeLoop<ROWS256, Cls>::Lead lead;
   lp.template read_lead<0, true>(lead);
   // iterations t = 0 .. T (the last one finishes the output update of tile T-1); T is the same
   // for the four waves, which meet at the barrier of every iteration
@@ -999,7 +1000,12 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   d.vw = reinterpret_cast<const char *>(c.vh) + (size_t)(16 * wave) * d.v_rb;
   d.lds_w = wave * 4096;
 
-  ashape_pass_pipelined<ROWS256>(c, d, st, lo, mp, lane);
+  QAcc qa;
+  pin_q(qa, st);
+  bool has_ref = false;
+  AshapeCls cls;
+  cls.init(mp);
+  ashape_pass_pipelined<ROWS256, AshapeCls>(c, d, st, qa, has_ref, lo, mp, cls, lane);
   if (__syncthreads_or(needs_exact(st) ? 1 : 0)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
@@ -2130,6 +2136,155 @@ struct AshapeGen {
   }
 };
 
+// ---------------------------------------------------------------------------
+// Vertical-Slash with long runs: a workgroup is four waves = four consecutive query blocks of a
+// head.  The keys of a long run that ALL four blocks attend whole are walked first, in 64-key tiles
+// fetched once for the four waves (the loop of ashape_kernel, no masks); then every wave takes its
+// own two ends of those runs, the short runs and the verticals through its private ring as
+// vs_kernel does.  No wave computes a tile it would not have computed alone.  (vs_kernel is at the
+// CU's load path, 16 KiB per wave and 32 keys; the shared tiles need a quarter of that and run at
+// the rate of ashape_kernel.  8K tokens, 32 heads, one run per head: 638 -> 519 us.)
+// ---------------------------------------------------------------------------
+// A run's common part costs the pipeline's fill (about three tiles) on top; from this many tiles on
+// it is taken out.
+constexpr int SHARE_MIN_TILES = 8;
+// Common whole tiles [lo, lo + 64 T) of the run [t0, t1) for the blocks whose first rows are Q0 ..
+// Q0 + 192: T, or 0 if they are too few.  0 <= lo and lo + 64 T <= Q0 + 1 <= N.
+__device__ inline int share_tiles(int t0, int t1, int Q0, int &lo) {
+  lo = max(Q0 + 3 * BQ - t1 + 1, 0);
+  const int hi = min(Q0 - t0, Q0) + 1;
+  const int T = (hi - lo) >> 6;
+  return T >= SHARE_MIN_TILES ? T : 0;
+}
+
+// The steps of VsRunGen without the common parts of long runs.
+struct VsEdgeGen {
+  static constexpr bool SINK_MASK = false;
+  int2 mine;            // lane i: run i of the chunk
+  int n, q0, Q0, N;
+  int iv, ke, pos, ks2, ke2;    // [ks2, ke2): the part behind the common one, if not empty
+  __device__ inline bool next(Step &d) {
+    while (true) {
+      if (pos < ke) {
+        d.kbase = min(pos, N - 32); d.lo = pos; d.hi = ke; d.cols = nullptr;
+        d.cls = (d.kbase == pos && pos + 31 < ke && pos + 31 <= q0) ? 1 : 2;
+        pos += 32;
+        return true;
+      }
+      if (ks2 < ke2) {
+        pos = ks2; ke = ke2; ke2 = 0;
+        continue;
+      }
+      if (iv >= n) return false;
+      const int rx = __builtin_amdgcn_readlane(mine.x, iv), ry = __builtin_amdgcn_readlane(mine.y, iv);
+      ++iv;
+      pos = max(q0 - ry + 1, 0);
+      ke = min(q0 - rx + 1, N);
+      int lo;
+      const int T = share_tiles(rx, ry, Q0, lo);
+      if (T > 0) {
+        ks2 = lo + BK * T; ke2 = ke;
+        ke = lo;
+      }
+    }
+  }
+};
+
+template <bool ROWS256>
+__global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const int32_t *v_idx, const int32_t *cover,
+                                                       const uint32_t *cover_bits, const int32_t *counts, int nv,
+                                                       int ns, int cover_words, Sched sched) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int NB = x.N / BQ;
+  int slot, sb;
+  if (!decode_wg(sched, slot, sb)) return;
+  const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
+  const int kvh = to_sgpr(head / x.group);
+  const bf16_t *qh = x.q + head * x.q_sh;
+  bf16_t *oh = x.o + head * x.o_sh;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int blk = sb * 4 + wave;
+  const bool active = blk < NB;
+  const int Q0 = sb * 4 * BQ, q0 = (active ? blk : NB - 1) * BQ;   // an idle wave helps to fetch, writes nothing
+  char *ring = lds + wave * RING_BYTES;
+
+  VsCtx c;
+  c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
+  c.N = x.N; c.q0 = q0; c.buf = StepBuf{ring}; c.c_log2 = x.c_log2;
+  c.cols = reinterpret_cast<int *>(ring + 4 * HALF_BYTES);   // [VCAP + 64]
+  c.n_v = min(max(counts[slot * 4 + 0], 0), nv);
+  c.n_c = min(max(counts[slot * 4 + 2], 0), ns);
+  c.vlist = v_idx + (int64_t)slot * nv;
+  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)slot * ns;
+  c.bits = cover_bits + (int64_t)slot * cover_words;
+
+  WaveState st;
+  wave_init(st, qh, x.q_st, q0, lane);
+  LaneOfs lo;
+  lane_offsets(lo, lane);
+  MaskP mp;
+  mp.q0 = q0; mp.n_init = KEY_NONE; mp.n_local = 1; mp.lo = 0; mp.hi = 0;
+  bool has_ref = false;
+  QAcc qa;
+  pin_q(qa, st);
+  DmaLane dk, dv;
+  dma_lane_init(dk, c.k_st, lane);
+  dma_lane_init(dv, c.v_st, lane);
+  const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
+  const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
+
+  // ---- common parts of the long runs (the same for the four waves; every pass ends with a barrier)
+  {
+    WaveDma d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { d.k_voff[i] = dk.voff[i]; d.v_voff[i] = dv.voff[i]; }
+    d.k_rb = k_rb; d.v_rb = v_rb;
+    d.kw = khb + (size_t)(16 * wave) * k_rb;
+    d.vw = vhb + (size_t)(16 * wave) * v_rb;
+    d.lds_w = wave * 4096;
+    AshapeCtx a;
+    a.lds = lds; a.c_log2 = x.c_log2; a.T1 = 0;
+    for (int r0 = 0; r0 < c.n_c; r0 += 64) {
+      int2 mine = make_int2(KEY_NONE, KEY_NONE);
+      if (r0 + lane < c.n_c) mine = c.runs[r0 + lane];
+      int klo = 0;
+      const int T = r0 + lane < c.n_c && mine.x <= Q0 ? share_tiles(mine.x, mine.y, Q0, klo) : 0;
+      unsigned long long todo = __builtin_amdgcn_ballot_w64(T > 0);
+      while (todo) {
+        const int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        a.T = __builtin_amdgcn_readlane(T, i);
+        a.s2 = __builtin_amdgcn_readlane(klo, i);
+        ashape_pass_pipelined<ROWS256, AllCls>(a, d, st, qa, has_ref, lo, mp, AllCls{}, lane);
+      }
+      if (__builtin_amdgcn_readlane(mine.x, 63) > Q0) break;      // runs ascend
+    }
+  }
+  if (!active) return;       // no workgroup barrier below this line
+  // ---- the rest of the runs, and the verticals, per wave
+  for (int r0 = 0; r0 < c.n_c; r0 += 64) {
+    const int n = min(c.n_c - r0, 64);
+    int2 mine = make_int2(KEY_NONE, KEY_NONE);
+    if (lane < n) mine = c.runs[r0 + lane];
+    const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
+    if (usable == 0) break;
+    VsEdgeGen gen{mine, usable, q0, Q0, c.N, 0, 0, 0, 0, 0};
+    WavePipe3<VsEdgeGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
+    pipe.run();
+    if (usable < n) break;
+  }
+  vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
+  if (needs_exact(st)) {
+    load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
+    reset_for_max_pass(st);
+    vs_pass<PASS_MAX>(c, st, lo, mp, lane);
+    finish_max_pass(st, x.c_log2);
+    vs_pass<PASS_FIX>(c, st, lo, mp, lane);
+  }
+  wave_finish(st, oh, x.o_st, q0, ring, lane);
+}
+
 template <int PASS>
 __device__ inline void ashape_wave_pass(const AshapeGen<1> &gen0, WaveState &st, const LaneOfs &lo, const StepBuf &buf,
                                         const bf16_t *kh, const bf16_t *vh, const QKV &x, const MaskP &mp, int lane) {
@@ -2556,6 +2711,17 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
 // us, 1024 of 8K 213 -> 163 (short lists 172 -> 136), 4096 of 8K 595 -> 626 (412 -> 500);
 // Block-Sparse 256 items 105 -> 39, 1024 183 -> 160, 4096 720 -> 763.
 constexpr int SPLIT_MAX_ITEMS = 1024;
+// Whether a workgroup takes four consecutive blocks (vs_share_kernel) instead of one (vs_kernel):
+//  - short rows and rows of which a large part is kept, where the slash tiles merge into long runs.
+//    32 heads, us: 8K tokens 638 -> 519, 16K 1958 -> 1782, 32K 5485 -> 5253, 64K 13269 -> 13137;
+//    at 128K (6096 slashes) 30796 -> 30797, and 1500 slashes at 64K lose, 4018 -> 4100;
+//  - many runs of a row whose K and V do not stay in the 256 MB memory-side cache: the four waves
+//    walk neighbouring keys at the same time and meet in the L2.  24 heads of 1M tokens 299.5 ->
+//    252.6 ms, 8 of 512K 42.3 -> 38.3, 256K 15.98 -> 15.72, 192K 12.54 -> 12.73; 1500 slashes at
+//    512K lose, 8.42 -> 8.72.
+static bool vs_share(int N, int ns) {
+  return N <= 16384 || (int64_t)ns * 12 >= N || (N >= 262144 && ns >= 4096);
+}
 // A-shape and dense, whose alternative shares its tiles between four blocks and needs a quarter of
 // the loads: 512 items of 8K tokens 134 -> 83 us (dense 177 -> 86), 1024 items 148 -> 149, with a
 // short window (128, 1024) 62 -> 74.
@@ -2665,6 +2831,21 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
                          cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
+  if (vs_share(x.N, ns)) {
+    const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4);
+    const size_t lds = 4 * RING_BYTES;
+    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_share_kernel<true>)
+                             : reinterpret_cast<const void *>(vs_share_kernel<false>);
+    hipError_t e = set_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    if (rows256)
+      hipLaunchKernelGGL(vs_share_kernel<true>, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+                         cover_bits, counts, nv, ns, cover_words, s4);
+    else
+      hipLaunchKernelGGL(vs_share_kernel<false>, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+                         cover_bits, counts, nv, ns, cover_words, s4);
+    return hipGetLastError();
+  }
   const size_t lds = 5 * HALF_BYTES;
   const void *fn = rows256 ? reinterpret_cast<const void *>(vs_kernel<true>)
                            : reinterpret_cast<const void *>(vs_kernel<false>);
@@ -2684,8 +2865,8 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  if (hv.n * NB <= SPLIT_MAX_ITEMS || hb.n * NB <= SPLIT_MAX_ITEMS) {
-    // few items of a kind: the split kernels (see SPLIT_MAX_ITEMS), one launch per kind
+  if (hv.n * NB <= SPLIT_MAX_ITEMS || hb.n * NB <= SPLIT_MAX_ITEMS || vs_share(x.N, ns)) {
+    // not one wave per block for both kinds: one launch per kind, the kernels the two calls take
     const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
     return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);
   }

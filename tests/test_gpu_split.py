@@ -85,10 +85,10 @@ def test_shares_of_short_and_many_runs(B, rng, Sl):
 
 def test_one_launch_of_both_kinds_with_many_items(B, rng):
     """minf_vs_bs_attn interleaves the two kinds when both have many items: the same bits as the two calls."""
-    N, n = 4160, 17
+    N, n = 33024, 3          # 516 blocks; short and dense rows take other kernels
     q, k, v = random_qkv(93, 2 * n, 2, N)
     vs_heads, bs_heads = list(range(n)), list(range(n, 2 * n))
-    Vl, Sl = sorted(rng.choice(N, 200, replace=False).tolist()), list(range(0, 200)) + [300, 301, 2100]
+    Vl, Sl = sorted(rng.choice(N, 200, replace=False).tolist()), list(range(0, 200)) + [300, 301, 21000]
     vidx = B.vs_index_from_host([Vl] * n, [Sl] * n, N)
     idx, cnt = random_bs_index(rng, N // 64, 9)
     bidx = B.bs_index_from_host(np.stack([idx] * n), np.stack([cnt] * n))
@@ -98,4 +98,31 @@ def test_one_launch_of_both_kinds_with_many_items(B, rng):
     B.minf_vs_bs_attn(q, k, v, o2, vs_heads, vidx, bs_heads, bidx)
     torch.cuda.synchronize()
     assert torch.equal(o1, o2)
-    assert_close_rows(o2[3], O.vs_attention(to_f64(q[3]), to_f64(k[0]), to_f64(v[0]), Vl, Sl, Bm=64), "vs")
+    for b in (0, 17, 515):
+        want = O.vs_attention(to_f64(q[2]), to_f64(k[0]), to_f64(v[0]), Vl, Sl, 64 * b, 64 * b + 64, Bm=64)
+        assert_close_rows(o2[2, 64 * b:64 * b + 64], want, f"vs block {b}")
+
+
+# common part of a run for four blocks = width - 192 keys in whole 64-key tiles, at least 8 of them
+@pytest.mark.parametrize("Sl", [list(range(0, 642, 60)), list(range(0, 640)), list(range(0, 641)), list(range(0, 705)),
+                                list(range(0, 2100)), list(range(90, 1500)), list(range(0, 700)) + list(range(1000, 2700))])
+@pytest.mark.parametrize("layout,kind", [("head", "normal"), ("token", "normal"), ("head", "overflow")])
+def test_common_part_of_long_runs(B, rng, Sl, layout, kind):
+    """Four blocks per workgroup: runs just short of and just at the width from which their common
+    part is shared, a run that starts past the diagonal, two long runs, blocks that reach key 0, an
+    odd number of blocks (4160 tokens: a workgroup with one block)."""
+    N = 4160
+    q0, k0, v0 = random_qkv(94, 17, 1, N)
+    if kind == "overflow":
+        k0 = k0.clone()
+        k0[:, 2500:] *= 60.0
+    Vl = sorted(rng.choice(N, 150, replace=False).tolist())
+    q, k, v = (token_major(t) if layout == "token" else t for t in (q0, k0, v0))
+    o = torch.full_like(q0, float("nan"))
+    o = token_major(o) if layout == "token" else o
+    B.minf_vs_attn(q, k, v, o, list(range(17)), B.vs_index_from_host([Vl] * 17, [Sl] * 17, N))
+    torch.cuda.synchronize()
+    for h in (0, 16):
+        want = O.vs_attention(to_f64(q0[h]), to_f64(k0[0]), to_f64(v0[0]), Vl, Sl, Bm=64)
+        for b in range(0, 65):
+            assert_close_rows(o[h, 64 * b:64 * b + 64], want[64 * b:64 * b + 64], f"head {h} block {b}")
