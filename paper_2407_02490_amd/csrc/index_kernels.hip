@@ -30,11 +30,12 @@ namespace minf {
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-constexpr int VS_CHUNK = 1024;      // keys / offsets owned by one workgroup of the score kernels ...
-constexpr int VS_CHUNK_SHORT = 256;  // ... for sequences up to VS_SHORT_N, where 1024 would leave most of the chip idle,
-constexpr int VS_SHORT_N = 32768;
-constexpr int VS_CHUNK_TINY = 128;   // ... and up to VS_TINY_N
-constexpr int VS_TINY_N = 8192;
+// Keys / offsets owned by one workgroup of the score kernels: the largest of the three that gives
+// every CU its two workgroups, else the smallest (a chunk also meets 64 keys beyond its own, so
+// small ones cost more work).  4 K/V heads of 40K tokens: 160 workgroups of 1024 keys took 33 + 69
+// us, 632 of 256 take 25 + 53.
+constexpr int VS_CHUNK = 1024, VS_CHUNK_SHORT = 256, VS_CHUNK_TINY = 128;
+constexpr int VS_MIN_GROUPS = 512;
 
 struct KvMap {                      // pooling work list of the Block-Sparse build
   int32_t n_kv;                     // distinct KV heads used by the call
@@ -265,6 +266,164 @@ __device__ inline void ordered_select(const float *data, int n, unsigned thr, in
       eq_before += __builtin_popcountll(eb);
     }
   }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// Exact top-k of a row of up to 1024 E scores by one workgroup of 1024 threads that reads it
+// once and holds it in registers.  Wave w owns `per` consecutive elements (per = n / 16, rounded
+// up to 256), round j of them the elements w per + 256 j .. + 255, lane L four of those.  Bound by
+// latency and LDS atomics.  With the runs from a bit set (vs_runs_from_bits), vs_select_kernel takes
+// 28 us on 32K scores of 32 heads, 13 on 8K, 10 on 4K and 37 on the candidates of 128K; a radix over
+// memory (four passes of eight bits and two of the ordered compaction, counts aggregated per wave)
+// took 63, 25, 15 and 111.
+// ---------------------------------------------------------------------------
+constexpr int REG_BINS = 2048;
+template <int E>                           // scores a thread holds
+struct RegRow {
+  static constexpr int REG_E = E;
+  unsigned u[E];                           // order keys, at least 1; 0 where the row has no element
+  int per;
+  __device__ inline int pos(int j) const { return (int)(threadIdx.x >> 6) * per + 256 * j + 4 * (int)(threadIdx.x & 63); }
+};
+
+// load4(i): the scores i .. i + 3 as a float4 (i a multiple of 4; those at n and behind are ignored)
+template <int REG_E, class Load>
+__device__ inline void reg_load(RegRow<REG_E> &row, int n, Load load4) {
+  row.per = __builtin_amdgcn_readfirstlane((n + 4095) / 4096 * 256);
+#pragma unroll
+  for (int j = 0; j < REG_E / 4; ++j)
+    if (256 * j < row.per) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (row.pos(j) < n) a = load4(row.pos(j));
+      const float e[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) row.u[4 * j + c] = row.pos(j) + c < n ? max(order_key(e[c]), 1u) : 0u;
+    }
+}
+
+// k-th largest key (1 <= k <= n), as the pair (thr, take_eq) of radix_select: the top-k are the keys
+// above thr and the first take_eq of those equal to it.  Each pass counts the keys of [lo, hi] -- at
+// first the range that occurs -- in 2048 equal bins and goes on with the bin that holds the k-th: at
+// most three passes.  take_eq is 0 if a bin ended exactly with the k-th key: then thr + 1 is a bound
+// that exactly k keys reach.  hist: REG_BINS ints of LDS, sh: 40 ints.
+template <int REG_E>
+__device__ inline void reg_threshold(const RegRow<REG_E> &row, int k, unsigned *thr, int *take_eq, int *hist, int *sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int j = 0; j < REG_E / 4; ++j)
+    if (256 * j < row.per) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        lo = min(lo, row.u[4 * j + c] - 1u);           // no element: 0 - 1 wraps to the top
+        hi = max(hi, row.u[4 * j + c]);
+      }
+    }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    lo = min(lo, (unsigned)__shfl_xor((int)lo, off));
+    hi = max(hi, (unsigned)__shfl_xor((int)hi, off));
+  }
+  if (lane == 0) { sh[wave] = (int)lo; sh[16 + wave] = (int)hi; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) { lo = min(lo, (unsigned)sh[w]); hi = max(hi, (unsigned)sh[16 + w]); }
+  lo += 1u;
+  __syncthreads();
+  int krem = k;
+  while (true) {                           // uniform: every thread sees the same lo, hi, krem
+    const unsigned width = hi - lo;
+    const int shift = width < (unsigned)REG_BINS ? 0 : 21 - __builtin_clz(width);   // (width >> shift) < 2048
+    hist[tid] = 0; hist[tid + 1024] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < REG_E / 4; ++j)
+      if (256 * j < row.per) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const unsigned u = row.u[4 * j + c];
+          if (u - lo <= width) atomicAdd(&hist[(u - lo) >> shift], 1);
+        }
+      }
+    __syncthreads();
+    // suffix sums: thread t owns the bins 2 t, 2 t + 1
+    const int b0 = hist[2 * tid], b1 = hist[2 * tid + 1];
+    int suf = b0 + b1;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_down(suf, off);
+      if (lane + off < 64) suf += o;
+    }
+    if (lane == 0) sh[wave] = suf;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w) suf += w > wave ? sh[w] : 0;
+    // suf: keys in the bins >= 2 t
+    const int s1 = suf - b0, s2 = s1 - b1;            // ... >= 2 t + 1, >= 2 t + 2
+    if (suf >= krem && s1 < krem) { sh[32] = 2 * tid; sh[33] = krem - s1; sh[34] = b0; }
+    else if (s1 >= krem && s2 < krem) { sh[32] = 2 * tid + 1; sh[33] = krem - s2; sh[34] = b1; }
+    __syncthreads();
+    const unsigned bin = (unsigned)sh[32];
+    krem = sh[33];
+    const int inside = sh[34];
+    lo += bin << shift;
+    hi = min(hi, lo + ((1u << shift) - 1u));
+    if (shift == 0) { *thr = lo; *take_eq = krem; break; }
+    if (inside == krem && lo > 0u) { *thr = lo - 1u; *take_eq = 0; break; }
+  }
+  __syncthreads();                         // every thread has read sh
+}
+
+// Calls emit(p, i) for every kept element: i its place in the row, p its rank among the kept, ascending.
+// sh: 32 ints of LDS.
+template <int REG_E, class Emit>
+__device__ inline void reg_emit(const RegRow<REG_E> &row, unsigned thr, int take_eq, int *sh, Emit emit) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int gt = 0, eq = 0;
+#pragma unroll
+  for (int j = 0; j < REG_E / 4; ++j)
+    if (256 * j < row.per) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        gt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(row.u[4 * j + c] > thr));
+        eq += __builtin_popcountll(__builtin_amdgcn_ballot_w64(row.u[4 * j + c] == thr));
+      }
+    }
+  if (lane == 0) { sh[wave] = gt; sh[16 + wave] = eq; }
+  __syncthreads();
+  int pos = 0, eq_before = 0;
+  for (int w = 0; w < wave; ++w) {
+    const int e = sh[16 + w];
+    pos += sh[w] + max(0, min(e, take_eq - eq_before));
+    eq_before += e;
+  }
+#pragma unroll
+  for (int j = 0; j < REG_E / 4; ++j)
+    if (256 * j < row.per) {
+      bool sel[4];
+      int rank = eq_before;
+      unsigned long long be[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        be[c] = __builtin_amdgcn_ballot_w64(row.u[4 * j + c] == thr);
+        rank += __builtin_popcountll(be[c] & lanes_below(lane));
+        eq_before += __builtin_popcountll(be[c]);
+      }
+      int p = pos;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool e = (be[c] >> lane) & 1ull;
+        sel[c] = row.u[4 * j + c] > thr || (e && rank < take_eq);
+        rank += e;
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(sel[c]);
+        p += __builtin_popcountll(b & lanes_below(lane));
+        pos += __builtin_popcountll(b);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (sel[c]) emit(p++, row.pos(j) + c);
+    }
   __syncthreads();
 }
 
@@ -823,8 +982,8 @@ __global__ __launch_bounds__(256) void vs_gmax_kernel(int N, int log_gv, int log
 __global__ __launch_bounds__(1024) void vs_bound_kernel(int N, int nv, int ns, int log_gv, int log_gs,
                                                         const float *gmax_v, const float *gmax_s,
                                                         VsSelState *state) {
-  __shared__ int hist[256];
-  __shared__ int sh[16];
+  __shared__ int hist[REG_BINS];
+  __shared__ int sh[40];
   const int slot = blockIdx.x, which = blockIdx.y;
   const int log_g = which == 0 ? log_gv : log_gs;
   VsSelState *st = state + slot * 2 + which;
@@ -833,7 +992,12 @@ __global__ __launch_bounds__(1024) void vs_bound_kernel(int N, int nv, int ns, i
     const float *gm = (which == 0 ? gmax_v : gmax_s) + (int64_t)slot * (N >> 2);
     const int n_g = N >> log_g, k = min(which == 0 ? nv : ns, N);
     int take_eq;
-    if ((n_g & 3) == 0) radix_select<1024, true>(gm, n_g, k, &thr, &take_eq, hist, sh);
+    if ((n_g & 3) == 0 && n_g <= 1024 * 40) {
+      RegRow<40> row;                                // N / G < 8 k, so 6096 slashes fit
+      reg_load(row, n_g, [&](int i) { return *reinterpret_cast<const float4 *>(gm + i); });
+      reg_threshold(row, k, &thr, &take_eq, hist, sh);
+      if (take_eq == 0) ++thr;
+    } else if ((n_g & 3) == 0) radix_select<1024, true>(gm, n_g, k, &thr, &take_eq, hist, sh);
     else radix_select<1024, false>(gm, n_g, k, &thr, &take_eq, hist, sh);
   }
   if (threadIdx.x == 0) {
@@ -926,8 +1090,62 @@ __global__ __launch_bounds__(256) void vs_filter_kernel(int N, int cap, int n_sl
   }
 }
 
+// The runs and the run bitmap of vs_merge_runs from the bit set of the kept offsets (sel: n_sel words
+// of LDS, bit o = offset o): the run bitmap's word w (bits b = t + 64, covered by an offset in
+// b - 64 .. b - 1) follows from three words of the set, and the runs are its stretches of ones.
+// One scan over the words instead of one per 1024 offsets.  Returns the number of runs.
+__device__ inline int vs_runs_from_bits(const unsigned *sel, int n_sel, int2 *runs, uint32_t *bits, int cover_words,
+                                        int *sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto at = [&](int w) { return w >= 0 && w < n_sel ? sel[w] : 0u; };
+  auto cover = [&](int w) {
+    const unsigned far = at(w - 2), all = at(w - 1), own = at(w);
+    unsigned c = 0u;
+    if (far) c |= 0xffffffffu >> __builtin_clz(far);                   // bits up to the highest of two words back
+    if (own) c |= ~((own & -own) | ((own & -own) - 1u));               // bits above this word's lowest
+    return all ? 0xffffffffu : c;
+  };
+  const int per = (cover_words + 1023) / 1024, w0 = tid * per, w1 = min(w0 + per, cover_words);
+  int starts = 0, ends = 0;
+  unsigned prev = w0 < cover_words && w0 > 0 ? cover(w0 - 1) >> 31 : 0u;
+  const unsigned prev0 = prev;
+  for (int w = w0; w < w1; ++w) {
+    const unsigned c = cover(w), shifted = (c << 1) | prev;
+    bits[w] = c;
+    starts += __builtin_popcount(c & ~shifted);
+    ends += __builtin_popcount(~c & shifted);
+    prev = c >> 31;
+  }
+  int is = starts, ie = ends;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int a = __shfl_up(is, off), b = __shfl_up(ie, off);
+    if (lane >= off) { is += a; ie += b; }
+  }
+  if (lane == 63) { sh[wave] = is; sh[16 + wave] = ie; }
+  __syncthreads();
+  int total = 0;
+  is -= starts; ie -= ends;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    if (w < wave) { is += sh[w]; ie += sh[16 + w]; }
+    total += sh[w];
+  }
+  prev = prev0;
+  if (starts | ends)
+    for (int w = w0; w < w1; ++w) {
+      const unsigned c = cover(w), shifted = (c << 1) | prev;
+      for (unsigned m = c & ~shifted; m; m &= m - 1u) runs[is++].x = 32 * w + __builtin_ctz(m) - 64;
+      for (unsigned m = ~c & shifted; m; m &= m - 1u) runs[ie++].y = 32 * w + __builtin_ctz(m) - 64;
+      prev = c >> 31;
+    }
+  return total;
+}
+constexpr int VS_BITS_MAX_N = 262144;               // longest row whose kept offsets are collected as bits in LDS (32 KiB)
+
 // Top-k + "sparseformat".  blockIdx.y = 0: verticals from the column sums;
 // blockIdx.y = 1: slashes from the diagonal sums, their runs and the run bitmap.
+template <int E>
 __global__ __launch_bounds__(1024) void vs_select_kernel(int N, int nv, int ns, const float *colsum,
                                                          const float *diagsum, int32_t *v_idx,
                                                          int32_t *s_idx, int32_t *cover,
@@ -936,9 +1154,11 @@ __global__ __launch_bounds__(1024) void vs_select_kernel(int N, int nv, int ns, 
                                                          const VsSelState *state, const float *cand_val,
                                                          const int32_t *cand_idx, const int2 *seg,
                                                          float *list_val, int32_t *list_idx) {
-  __shared__ int hist[256];
+  __shared__ int hist[REG_BINS];
   __shared__ int sh[40];
-  __shared__ int seg_pos[256];
+  __shared__ int seg_pos[257];                      // list position of every slice's part; behind the last: the count
+  __shared__ int2 seg_at[256];
+  __shared__ unsigned sel_bits[VS_BITS_MAX_N / 32];
   const int slot = blockIdx.x, which = blockIdx.y, tid = threadIdx.x;
   const float *data = (which == 0 ? colsum : diagsum) + (int64_t)slot * N;
   const int kcap = which == 0 ? nv : ns;
@@ -950,26 +1170,65 @@ __global__ __launch_bounds__(1024) void vs_select_kernel(int N, int nv, int ns, 
   VsSelState st;
   st.bound = 0u; st.count = 0; st.overflow = 1; st.log_g = -1;
   if (n_slices > 0) st = state[slot * 2 + which];
+  const bool as_bits = which == 1 && N <= VS_BITS_MAX_N;
+  if (as_bits) {
+    for (int i = tid; i < N / 32; i += 1024) sel_bits[i] = 0u;
+    __syncthreads();
+  }
+  auto keep = [&](int p, int i) {
+    out[p] = i;
+    if (as_bits) atomicOr(&sel_bits[i >> 5], 1u << (i & 31));
+  };
+  bool listed = true;                               // every kept offset went through keep()
   // the prefilter's candidates are complete (every slice found room) and in use for this row
   const bool filtered = st.log_g >= 0 && st.overflow == 0 && st.count >= k && st.count <= cap && n_slices <= 256;
   if (filtered) {
-    // the slices' parts, in slice order, into one list (position order)
+    // the slices' parts, in slice order, are one list (position order)
     const int2 *sg = seg + (int64_t)(slot * 2 + which) * n_slices;
-    if (tid == 0) {
+    if (tid < n_slices) seg_at[tid] = sg[tid];
+    __syncthreads();
+    if (tid <= n_slices) {
       int p = 0;
-      for (int i = 0; i < n_slices; ++i) {
-        seg_pos[i] = p;
-        p += sg[i].y;
-      }
+      for (int i = 0; i < tid; ++i) p += seg_at[i].y;
+      seg_pos[tid] = p;
     }
     __syncthreads();
     const float *cv = cand_val + (int64_t)(slot * 2 + which) * cap;
     const int32_t *ci = cand_idx + (int64_t)(slot * 2 + which) * cap;
+    // candidate i of the list: its place in cv / ci
+    auto part_of = [&](int i) {            // the slice whose part holds list position i < count
+      int a = 0, b = n_slices - 1;
+      while (a < b) {
+        const int m = (a + b + 1) >> 1;
+        if (seg_pos[m] <= i) a = m; else b = m - 1;
+      }
+      return a;
+    };
+    if (st.count <= 1024 * E) {
+      RegRow<E> row;
+      reg_load(row, st.count, [&](int i) {
+        int part = part_of(i);
+        float e[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int ic = min(i + c, st.count - 1);
+          while (seg_pos[part + 1] <= ic) ++part;
+          e[c] = cv[seg_at[part].x + ic - seg_pos[part]];
+        }
+        return make_float4(e[0], e[1], e[2], e[3]);
+      });
+      reg_threshold(row, k, &thr, &take_eq, hist, sh);
+      reg_emit(row, thr, take_eq, sh, [&](int p, int i) {
+        const int part = part_of(i);
+        keep(p, ci[seg_at[part].x + i - seg_pos[part]]);
+      });
+    } else {
+    listed = false;
     float *lv = list_val + (int64_t)(slot * 2 + which) * cap;
     int32_t *li = list_idx + (int64_t)(slot * 2 + which) * cap;
     const int wave = tid >> 6, lane = tid & 63;
     for (int i = wave; i < n_slices; i += 16) {
-      const int2 g = sg[i];
+      const int2 g = seg_at[i];
       for (int e = lane; e < g.y; e += 64) {
         lv[seg_pos[i] + e] = cv[g.x + e];
         li[seg_pos[i] + e] = ci[g.x + e];
@@ -979,7 +1238,14 @@ __global__ __launch_bounds__(1024) void vs_select_kernel(int N, int nv, int ns, 
     __syncthreads();
     radix_select<1024, false>(lv, st.count, k, &thr, &take_eq, hist, sh);
     ordered_select<1024, false>(lv, st.count, thr, take_eq, out, sh + 8, li);
+    }
+  } else if (N <= 1024 * E) {
+    RegRow<E> row;
+    reg_load(row, N, [&](int i) { return *reinterpret_cast<const float4 *>(data + i); });
+    reg_threshold(row, k, &thr, &take_eq, hist, sh);
+    reg_emit(row, thr, take_eq, sh, keep);
   } else {
+    listed = false;
     radix_select<1024, true>(data, N, k, &thr, &take_eq, hist, sh);      // N % 64 == 0, rows 256-byte aligned
     ordered_select<1024, true>(data, N, thr, take_eq, out, sh + 8);
   }
@@ -988,8 +1254,17 @@ __global__ __launch_bounds__(1024) void vs_select_kernel(int N, int nv, int ns, 
     if (tid == 0) counts[slot * 4 + 0] = k;
     return;
   }
-  const int n_runs = vs_merge_runs(out, k, N, reinterpret_cast<int2 *>(cover) + (int64_t)slot * ns,
-                                   cover_bits + (int64_t)slot * cover_words, cover_words, sh + 8);
+  int2 *runs = reinterpret_cast<int2 *>(cover) + (int64_t)slot * ns;
+  uint32_t *bits = cover_bits + (int64_t)slot * cover_words;
+  int n_runs;
+  if (as_bits) {
+    if (!listed)
+      for (int i = tid; i < k; i += 1024) atomicOr(&sel_bits[out[i] >> 5], 1u << (out[i] & 31));
+    __syncthreads();
+    n_runs = vs_runs_from_bits(sel_bits, N / 32, runs, bits, cover_words, sh);
+  } else {
+    n_runs = vs_merge_runs(out, k, N, runs, bits, cover_words, sh + 8);
+  }
   if (tid == 0) {
     counts[slot * 4 + 1] = k;
     counts[slot * 4 + 2] = n_runs;
@@ -1237,7 +1512,7 @@ __global__ __launch_bounds__(256) void bs_select_kernel(int NB, int slot0, int t
 
 // ---------------------------------------------------------------------------
 // Block logits and per-row top-k in one kernel (Alg. 3): the NB x NB logits are never stored.
-// Workgroup = 128 query blocks of one head, 16 per wave, eight waves: two per SIMD, so that one
+// Workgroup = 16 query blocks of one head per wave, eight waves (two if there are few blocks): two per SIMD, so that one
 // wave's selection work runs while the other's MFMAs occupy the matrix pipeline (a single wave
 // issues in order and gets no such overlap).  Per 32-key tile (pooled K vectors staged in LDS,
 // shared by the eight waves, double buffered) a wave forms its 32 x 16 logits transposed,
@@ -1659,8 +1934,18 @@ __global__ __launch_bounds__(1024) void bs_order_kernel(int NB, int topk, const 
 // ---------------------------------------------------------------------------
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
-static int vs_chunk_keys(int N) { return N <= VS_TINY_N ? VS_CHUNK_TINY : N <= VS_SHORT_N ? VS_CHUNK_SHORT : VS_CHUNK; }
-static int vs_chunks(int N) { return (N + vs_chunk_keys(N) - 1) / vs_chunk_keys(N); }
+static int vs_chunks(int N, int keys) { return (N + keys - 1) / keys; }
+static int vs_chunk_keys(int N, int n_groups) {
+  for (const int keys : {VS_CHUNK, VS_CHUNK_SHORT})
+    if (vs_chunks(N, keys) * n_groups >= VS_MIN_GROUPS) return keys;
+  return VS_CHUNK_TINY;
+}
+
+// Chunks the workspace has a place of their own for.  More chunks (few K/V heads) go where the
+// candidates of the top-k come later: 2 N floats per head there, at most N + 128 needed.
+static int vs_ml_chunks(int N) {
+  return vs_chunks(N, N <= 8192 ? VS_CHUNK_TINY : N <= 32768 ? VS_CHUNK_SHORT : VS_CHUNK);
+}
 
 static int vs_slices(int N) { return (N + VS_SLICE - 1) / VS_SLICE; }
 static int vs_cand_cap(int N) { return N / 4 > 1024 ? N / 4 : 1024; }        // candidates per (head, which)
@@ -1668,7 +1953,7 @@ static int vs_cand_cap(int N) { return N / 4 > 1024 ? N / 4 : 1024; }        // 
 size_t vs_index_ws_bytes(int N, int n_heads) {
   size_t b = 0;
   b += 2 * align256((size_t)n_heads * N * sizeof(float));                     // colsum, diagsum
-  b += align256((size_t)n_heads * vs_chunks(N) * 128 * sizeof(float));        // per-chunk (max, sum)
+  b += align256((size_t)n_heads * vs_ml_chunks(N) * 128 * sizeof(float));     // per-chunk (max, sum)
   b += align256((size_t)n_heads * 128 * sizeof(float));                       // final (max, 1/sum)
   b += 2 * align256((size_t)n_heads * (N / 4) * sizeof(float));               // group maxima (G >= 4)
   b += 4 * align256((size_t)n_heads * 2 * vs_cand_cap(N) * sizeof(float));    // candidates: parts and list, value and position
@@ -1680,22 +1965,7 @@ size_t vs_index_ws_bytes(int N, int n_heads) {
 hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv, int ns,
                            int32_t *v_idx, int32_t *s_idx, int32_t *cover, uint32_t *cover_bits,
                            int32_t *counts, int cover_words, void *ws, hipStream_t st) {
-  const int N = x.N, nc = vs_chunks(N);
-  char *p = static_cast<char *>(ws);
-  float *colsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
-  float *diagsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
-  float *ml_part = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * nc * 128 * sizeof(float));
-  float *ml_fin = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * 128 * sizeof(float));
-  const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
-  float *gmax_v = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
-  float *gmax_s = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
-  const size_t cand_bytes = align256((size_t)hl.n * 2 * cap * sizeof(float));
-  float *cand_val = reinterpret_cast<float *>(p); p += cand_bytes;
-  int32_t *cand_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
-  float *list_val = reinterpret_cast<float *>(p); p += cand_bytes;
-  int32_t *list_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
-  int2 *seg = reinterpret_cast<int2 *>(p); p += align256((size_t)hl.n * 2 * n_slices * sizeof(int2));
-  VsSelState *state = reinterpret_cast<VsSelState *>(p);
+  const int N = x.N;
   // the listed heads grouped by K/V head, in order of first appearance, at most four per group
   VsGroups vg;
   memset(&vg, 0, sizeof(vg));
@@ -1707,6 +1977,23 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
     if (g == vg.n) { gkv[g] = kv; ++vg.n; }
     vg.slot[g][vg.cnt[g]++] = (uint8_t)i;
   }
+  const int ck = vs_chunk_keys(N, vg.n), nc = vs_chunks(N, ck);
+  char *p = static_cast<char *>(ws);
+  float *colsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
+  float *diagsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
+  float *ml_part = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * vs_ml_chunks(N) * 128 * sizeof(float));
+  float *ml_fin = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * 128 * sizeof(float));
+  const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
+  float *gmax_v = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
+  float *gmax_s = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
+  const size_t cand_bytes = align256((size_t)hl.n * 2 * cap * sizeof(float));
+  float *cand_val = reinterpret_cast<float *>(p); p += cand_bytes;
+  int32_t *cand_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
+  float *list_val = reinterpret_cast<float *>(p); p += cand_bytes;
+  int32_t *list_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
+  int2 *seg = reinterpret_cast<int2 *>(p); p += align256((size_t)hl.n * 2 * n_slices * sizeof(int2));
+  VsSelState *state = reinterpret_cast<VsSelState *>(p);
+  if (nc > vs_ml_chunks(N)) ml_part = cand_val;
   // 48 KiB (three workgroups of four waves per CU; registers allow two) and 75 KiB (two per CU)
   const dim3 grid(nc, vg.n);
   auto score = [&](auto chunk_keys) -> hipError_t {
@@ -1723,7 +2010,6 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
                        (const float *)ml_fin, colsum, diagsum);
     return hipSuccess;
   };
-  const int ck = vs_chunk_keys(N);
   const hipError_t e = ck == VS_CHUNK_TINY    ? score(std::integral_constant<int, VS_CHUNK_TINY>{})
                        : ck == VS_CHUNK_SHORT ? score(std::integral_constant<int, VS_CHUNK_SHORT>{})
                                               : score(std::integral_constant<int, VS_CHUNK>{});
@@ -1741,10 +2027,17 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
   if (prefilter)
     hipLaunchKernelGGL(vs_filter_kernel, dim3(n_slices, hl.n, 2), dim3(256), 0, st, N, cap, n_slices,
                        (const float *)colsum, (const float *)diagsum, state, cand_val, cand_idx, seg);
-  hipLaunchKernelGGL(vs_select_kernel, dim3(hl.n, 2), dim3(1024), 0, st, N, nv, ns, (const float *)colsum,
-                     (const float *)diagsum, v_idx, s_idx, cover, cover_bits, counts, cover_words, cap,
-                     prefilter ? n_slices : 0, (const VsSelState *)state, (const float *)cand_val, (const int32_t *)cand_idx,
-                     (const int2 *)seg, list_val, list_idx);
+  auto select = [&](auto held) {
+    constexpr int E = decltype(held)::value;
+    hipLaunchKernelGGL((vs_select_kernel<E>), dim3(hl.n, 2), dim3(1024), 0, st, N, nv, ns, (const float *)colsum,
+                       (const float *)diagsum, v_idx, s_idx, cover, cover_bits, counts, cover_words, cap,
+                       prefilter ? n_slices : 0, (const VsSelState *)state, (const float *)cand_val,
+                       (const int32_t *)cand_idx, (const int2 *)seg, list_val, list_idx);
+  };
+  // scores a thread of the selection holds
+  if (N <= 8192) select(std::integral_constant<int, 8>{});
+  else if (N <= 32768) select(std::integral_constant<int, 32>{});
+  else select(std::integral_constant<int, 40>{});     // 48 would spill; longer rows without a prefilter: from memory
   return hipGetLastError();
 }
 

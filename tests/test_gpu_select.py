@@ -1,0 +1,73 @@
+"""Selection kernels of the index builds at the sizes where their dispatch changes."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import minference_oracle as O
+from tests.helpers import check_topk, random_qkv, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2407_02490_amd import binding
+    binding.lib()
+    return binding
+
+
+def build_vs(B, q, k, heads, nv, ns):
+    N = q.shape[1]
+    idx = B.alloc_vs_index(len(heads), nv, ns, N)
+    ws = torch.empty(B.minf_vs_index_workspace_bytes(q, k, len(heads), 64), dtype=torch.uint8, device="cuda")
+    B.minf_build_vs_index(q, k, heads, 64, nv, ns, idx, ws)
+    torch.cuda.synchronize()
+    return idx
+
+
+# 8192 | 32768 | 40960 scores: the steps of what a thread holds; behind the last, from memory; from
+# 131072 on the candidates of the prefilter; the run bits come from LDS up to 262144
+@pytest.mark.parametrize("N,nv,ns", [(64, 64, 64), (128, 1, 1), (4096, 256, 512), (8192, 1000, 6096), (8256, 1000, 6096),
+                                     (32768, 100, 1800), (32832, 3000, 200), (40960, 500, 1500), (41024, 500, 1500),
+                                     (131072, 1000, 6096), (262144, 30, 2048), (262208, 30, 2048)])
+def test_vs_selection_and_runs(B, N, nv, ns):
+    q, k, _ = random_qkv(61, 2, 1, N)
+    idx = build_vs(B, q, k, [0, 1], nv, ns)
+    # runs and bitmap against the builder that takes the same lines as a list
+    n_runs = idx.counts[:, 2].tolist()
+    again = B.VSIndex(2, nv, ns, N, "cuda")
+    again.v_idx.copy_(idx.v_idx), again.s_idx.copy_(idx.s_idx), again.counts.copy_(idx.counts)
+    B.minf_vs_index_from_lines(again)
+    torch.cuda.synchronize()
+    assert torch.equal(idx.counts, again.counts) and torch.equal(idx.cover_bits, again.cover_bits)
+    for r in range(2):
+        assert torch.equal(idx.cover[r, :n_runs[r]], again.cover[r, :n_runs[r]])
+    if N <= 65536:
+        col, diag = O.vs_line_scores(O.vs_estimate(to_f64(q[1]), to_f64(k[0]), 64))
+        check_topk(idx.v_idx[1].cpu().numpy(), col, nv)
+        check_topk(idx.s_idx[1].cpu().numpy(), diag, ns)
+
+
+@pytest.mark.parametrize("N", [4096, 8256, 41024])
+def test_vs_ties_go_to_the_lower_position(B, N):
+    """All logits equal: every key before the last 64 has the same column sum."""
+    q, k, _ = random_qkv(62, 1, 1, N)
+    idx = build_vs(B, q, torch.zeros_like(k), [0], 700, 10)
+    assert torch.equal(idx.v_idx[0].cpu(), torch.arange(700, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("N,topk", [(8256, 100), (8256, 7), (65600, 100)])
+def test_bs_few_and_many_rows_and_order(B, N, topk):
+    """129 blocks of 66 heads fill the chip, those of one head do not: the same index either way."""
+    NB, heads = N // 64, 66 if N < 65536 else 9
+    q, k, _ = random_qkv(63, heads, 1, N)
+    got = []
+    for hs in ([heads - 1], list(range(heads))):
+        idx = B.alloc_bs_index(len(hs), N, topk)
+        ws = torch.empty(B.minf_bs_index_workspace_bytes(q, k, len(hs), topk), dtype=torch.uint8, device="cuda")
+        B.minf_build_bs_index(q, k, hs, topk, idx, ws)
+        torch.cuda.synchronize()
+        got.append((idx.blk_idx[-1].cpu(), idx.blk_cnt[-1].cpu(), idx.order[-1].cpu()))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    first = got[0][0][:, 0].numpy()
+    assert np.array_equal(got[0][2].numpy(), np.lexsort((np.arange(NB), first)))
