@@ -1139,18 +1139,16 @@ __device__ inline void fetch_step(const Buf &sb, int s, const bf16_t *kh, const 
   dma_rows<1, 32, CONTIG>(vh, v_st, dv, kbase, cols, N, sb.v(s), 0, lane);
 }
 
+// Place of column i in the list of a gather phase: within a step of 32, column 4 b + r at 8 r + b (see GatherKeys).
+__device__ inline int gather_pos(int i) { return (i & ~31) | ((i & 3) << 3) | ((i & 31) >> 2); }
+
 // Rare path on fresh logits of a gathered step: attended iff key <= query row.
 __device__ inline void special_gather(f32x16 (&s)[1][2], WaveState &st, const int *cols, const MaskP &mp,
                                       bool first, float c_log2, int lane) {
   const int n = lane & 31, h = lane >> 5;
   int keys[16];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int4 a = *reinterpret_cast<const int4 *>(cols + 16 * t + 8 * h);
-    const int4 b = *reinterpret_cast<const int4 *>(cols + 16 * t + 8 * h + 4);
-    keys[8 * t + 0] = a.x; keys[8 * t + 1] = a.y; keys[8 * t + 2] = a.z; keys[8 * t + 3] = a.w;
-    keys[8 * t + 4] = b.x; keys[8 * t + 5] = b.y; keys[8 * t + 6] = b.z; keys[8 * t + 7] = b.w;
-  }
+  for (int r = 0; r < 16; ++r) keys[r] = cols[gather_pos(16 * (r >> 3) + 8 * h + (r & 7))];
 #pragma unroll
   for (int r = 0; r < 16; ++r)
 #pragma unroll
@@ -1191,20 +1189,30 @@ __device__ inline void dma_pair(const char *step_row0, unsigned rb, const unsign
     dma16_imm<0>(step_row0 + (size_t)(4 * B + 4) * rb, voff[(B + 1) & 3], lds_step + (B + 1) * 1024);
   }
 }
-// Gathered rows: lane L of block blk fetches chunk c of row cols[4 blk + L / 16];
-// the byte offset key * rb + 16 c fits 32 bits (checked on the host: N rb < 2^32),
-// key < 2^24.  KEY_NONE entries read the last row (the caller masks them): one unsigned minimum
-// with N - 1 instead of a compare and a select.
-template <int B>
-__device__ inline void dma_pair_gather(const char *head, unsigned rb, const int *cols, unsigned lds_step,
-                                       int lane, unsigned last_row) {
-  const int rl = lane >> 4, cpos = lane & 15;
+// Gathered rows: lane L of block blk fetches chunk c of row (column id) 4 blk + L / 16 of the step;
+// the byte offset key * rb + 16 c fits 32 bits (checked on the host: N rb < 2^32), key < 2^24.  The
+// list holds a step's 32 ids in the order a lane needs them (gather_pos), so that a lane's eight come
+// with two 16-byte reads, one step ahead (an LDS read and its wait in front of every one of a step's
+// 16 loads before: 32 heads of 128K tokens, 3000 columns, 200 slashes: 5.41 -> 5.32 ms);
+// KEY_NONE entries read the last row (the caller masks them).
+struct GatherKeys {
+  unsigned key[8];                 // of blocks 0 .. 7
+};
+__device__ inline void gather_keys(GatherKeys &g, const int *cols, int lane, unsigned last_row) {
+  const int4 a = *reinterpret_cast<const int4 *>(cols + 8 * (lane >> 4));
+  const int4 b = *reinterpret_cast<const int4 *>(cols + 8 * (lane >> 4) + 4);
+  const int v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) g.key[i] = min((unsigned)v[i], last_row);
+}
+template <bool ROWS256, int B>
+__device__ inline void dma_pair_gather(const char *head, unsigned rb, const GatherKeys &g, unsigned lds_step, int lane) {
+  const unsigned rl = lane >> 4, cpos = lane & 15;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int blk = B + j, r = 4 * blk + rl;
-    const unsigned key = min((unsigned)cols[r], last_row);
-    const unsigned ofs = __umul24(key, rb) + (unsigned)((cpos ^ swz_f(r)) << 4);
-    dma16_su(head, ofs, lds_step + blk * 1024);
+    const unsigned c16 = ((cpos ^ (rl << 2)) ^ (unsigned)((B + j) & 3)) << 4;      // cpos ^ swz_f(4 blk + rl)
+    const unsigned ofs = (ROWS256 ? g.key[B + j] << 8 : __umul24(g.key[B + j], rb)) + c16;
+    dma16_su(head, ofs, lds_step + (B + j) * 1024);
   }
 }
 
@@ -1239,6 +1247,7 @@ struct WavePipe {
   int lane;
   Step d0, d1, d2;          // steps t, t+1, t+2
   bool h0, h1, h2;
+  GatherKeys kk, kv;        // GATHER: the rows of steps t+2 (K goes out in this iteration) and t+1 (V)
 
   __device__ inline const char *row0(const char *head, unsigned rb, const Step &d) const {
     // the generators yield steps inside [0, N); step descriptors come out of LDS lists or lanes,
@@ -1247,14 +1256,13 @@ struct WavePipe {
     return head + (uint64_t)kb * rb;
   }
   template <int R>
-  __device__ inline void round_dma(const char *kt, const char *vt, const int *kcols, const int *vcols,
-                                   unsigned k_dst, unsigned v_dst) const {
+  __device__ inline void round_dma(const char *kt, const char *vt, unsigned k_dst, unsigned v_dst) const {
     // K in rounds 0..3, V in rounds 4..7: K is needed at the top of the next iteration, V not
     // before its round 2
     constexpr bool k_now = R < 4;
     if (GATHER) {
-      if (k_now) dma_pair_gather<2 * (R & 3)>(kh, k_rb, kcols, k_dst, lane, (unsigned)N - 1u);
-      else dma_pair_gather<2 * (R & 3)>(vh, v_rb, vcols, v_dst, lane, (unsigned)N - 1u);
+      if (k_now) dma_pair_gather<ROWS256, 2 * (R & 3)>(kh, k_rb, kk, k_dst, lane);
+      else dma_pair_gather<ROWS256, 2 * (R & 3)>(vh, v_rb, kv, v_dst, lane);
     } else {
       if (k_now) dma_pair<ROWS256, 2 * (R & 3)>(kt, k_rb, dk.voff, k_dst);
       else dma_pair<ROWS256, 2 * (R & 3)>(vt, v_rb, dv.voff, v_dst);
@@ -1296,7 +1304,7 @@ struct WavePipe {
     bf16x8 kf[8], vf[8], p[2][2];
     kf[0] = lds_read_k(tK, lo.k[0]);
     const char *kt = row0(kh, k_rb, d2), *vt = row0(vh, v_rb, d1);
-    const int *kcols = d2.cols, *vcols = d1.cols;     // the generator advances mid-iteration
+    GatherKeys kn;
     const float m0 = st.m[0], m1 = st.m[1];
     float lsum0 = 0.f, lsum1 = 0.f;
     auto fetch_v = [&](int i) {            // output update step i = (t, db)
@@ -1347,7 +1355,7 @@ struct WavePipe {
       for (int i = 0; i < NPV_NEXT; ++i) vf[(PV_NEXT0 + i) & 7] = fetch_v((PV_NEXT0 + i) & 7);
       constexpr int NEW = (r + 1 < 8 ? 1 : 0) + 2 * NPV_NEXT;      // LDS reads just issued
       __builtin_amdgcn_s_waitcnt(0xC07F | (NEW << 8));
-      round_dma<r>(kt, vt, kcols, vcols, k_dst, v_dst);
+      round_dma<r>(kt, vt, k_dst, v_dst);
       if (r == 1) MINF_WAIT_VMCNT(4);      // V of step t has landed: round 2 starts reading it
       if (r == 0) {
         mfma_qk_first(s_nxt[0][0], kf[0], qa.q[0][0]);
@@ -1375,6 +1383,8 @@ struct WavePipe {
         h2 = h2 && gen.next(dn);
         if (h2) d2 = dn;
       }
+      // the next iteration's rows: read here, so that no load of it waits for them
+      if (GATHER && r == 5) gather_keys(kn, d2.cols, lane, (unsigned)N - 1u);
       __builtin_amdgcn_sched_barrier(0);
     };
 #define MINF_IC(n) std::integral_constant<int, n>{}
@@ -1387,6 +1397,7 @@ struct WavePipe {
     round(MINF_IC(6), MINF_IC(16), MINF_IC(16), MINF_IC(4), MINF_IC(6));
     round(MINF_IC(7), MINF_IC(16), MINF_IC(16), MINF_IC(6), MINF_IC(8));
 #undef MINF_IC
+    if (GATHER) { kv = kk; kk = kn; }
     st.l[0] += lsum0;
     st.l[1] += lsum1;
     // after the generator advanced in round 3: d0 = the step whose logits are now in s_nxt
@@ -1397,9 +1408,10 @@ struct WavePipe {
     const char *head = IS_K ? kh : vh;
     const unsigned rb = IS_K ? k_rb : v_rb;
     if (GATHER) {
-      const unsigned last = (unsigned)N - 1u;
-      dma_pair_gather<0>(head, rb, d.cols, dst, lane, last); dma_pair_gather<2>(head, rb, d.cols, dst, lane, last);
-      dma_pair_gather<4>(head, rb, d.cols, dst, lane, last); dma_pair_gather<6>(head, rb, d.cols, dst, lane, last);
+      GatherKeys g;
+      gather_keys(g, d.cols, lane, (unsigned)N - 1u);
+      dma_pair_gather<ROWS256, 0>(head, rb, g, dst, lane); dma_pair_gather<ROWS256, 2>(head, rb, g, dst, lane);
+      dma_pair_gather<ROWS256, 4>(head, rb, g, dst, lane); dma_pair_gather<ROWS256, 6>(head, rb, g, dst, lane);
     } else {
       const char *a = row0(head, rb, d);
       const unsigned (&vo)[4] = IS_K ? dk.voff : dv.voff;
@@ -1418,6 +1430,10 @@ struct WavePipe {
     fetch_whole<true>(d0, lds_addr_of(buf.k(0)));
     fetch_whole<true>(d1, lds_addr_of(buf.k(1)));
     fetch_whole<false>(d0, lds_addr_of(buf.v(0)));
+    if (GATHER) {
+      gather_keys(kv, d1.cols, lane, (unsigned)N - 1u);
+      gather_keys(kk, d2.cols, lane, (unsigned)N - 1u);
+    }
     MINF_WAIT_VMCNT(0);
     f32x16 sa[1][2], sb[1][2];
     qk_first(sa, buf.k(0));
@@ -1940,7 +1956,7 @@ struct VsRunGen {
   __device__ inline int left_over() const { return (pos - ke) >> 5; }
 };
 
-// Gathered verticals: steps of 32 entries of the compacted column list (LDS).
+// Gathered verticals: steps of 32 entries of the compacted column list (LDS, in gather_pos order).
 struct VsColGen {
   const int *cols;
   int nstep, q0, t;
@@ -1980,14 +1996,14 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
       }
       const unsigned long long bal = __builtin_amdgcn_ballot_w64(ok);
       const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-      if (ok) cols[ncol + before] = v;
+      if (ok) cols[gather_pos(ncol + before)] = v;
       ncol += __builtin_popcountll(bal);
       vpos += 64 * NW;
       if (__shfl(v, 0) > qlast) { vpos = c.n_v; break; }
     }
     if (ncol == 0) continue;
     const int nstep = (ncol + 31) / 32;
-    if (lane + ncol < nstep * 32) cols[ncol + lane] = KEY_NONE;   // pad the last step
+    if (lane + ncol < nstep * 32) cols[gather_pos(ncol + lane)] = KEY_NONE;   // pad the last step
     wave_lds_sync();
     VsColGen gen{cols, nstep, q0, 0};
     WavePipe<VsColGen, true, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, c.N, mp, c.c_log2, lane};
