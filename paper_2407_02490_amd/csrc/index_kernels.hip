@@ -10,8 +10,9 @@
 //   normalised probabilities and reduces them along columns and diagonals.
 //   A_hat itself (64 x N) is never stored.  All reductions run in a fixed
 //   order: the scores are bit-reproducible.
-//   Top-k of the line scores: an exact radix select on the order-preserving
-//   integer image of the fp32 score (4 passes of 8 bits), ties to the lower
+//   Top-k of the line scores: an exact selection on the order-preserving
+//   integer image of the fp32 score (counts per range of keys, at most three
+//   passes over registers, or a radix select over memory), ties to the lower
 //   index, followed by an ordered compaction, so the kept indices come out
 //   ascending without a sort.  From 128K scores on, a prefilter by many
 //   workgroups (group maxima -> a lower bound of the k-th largest -> the scores
@@ -1512,7 +1513,7 @@ __global__ __launch_bounds__(256) void bs_select_kernel(int NB, int slot0, int t
 
 // ---------------------------------------------------------------------------
 // Block logits and per-row top-k in one kernel (Alg. 3): the NB x NB logits are never stored.
-// Workgroup = 16 query blocks of one head per wave, eight waves (two if there are few blocks): two per SIMD, so that one
+// Workgroup = 16 query blocks of one head per selecting wave, eight waves: two per SIMD, so that one
 // wave's selection work runs while the other's MFMAs occupy the matrix pipeline (a single wave
 // issues in order and gets no such overlap).  Per 32-key tile (pooled K vectors staged in LDS,
 // shared by the eight waves, double buffered) a wave forms its 32 x 16 logits transposed,
@@ -1528,15 +1529,26 @@ __global__ __launch_bounds__(256) void bs_select_kernel(int NB, int slot0, int t
 // step with the exact k-th largest key leaves exactly the k selected blocks, already ascending.
 // Needs topk <= BSF_MAX_TOPK and NB < 65536 (block ids are kept in 16 bits).
 // ---------------------------------------------------------------------------
-constexpr int BSF_ROWS = 128;                       // query blocks per workgroup
-constexpr int BSF_THREADS = 512;
+// Eight waves per workgroup share every pooled K tile; each selects for 16 query blocks of its own,
+// or, where that would leave CUs idle, two of them do and all eight pool the 32 blocks' Q
+// (BSF_FEW_GROUPS).
+constexpr int BSF_WAVES = 8, BSF_SEL_FEW = 2;
+// Workgroups of 128 blocks that leave at least half of the 256 CUs idle.  8 heads of 313 blocks (24
+// workgroups): 109 us; with 32 blocks per workgroup 61 (88 when the two selecting waves pool alone).
+// Full chips gain nothing from the shared pooling: 32 heads of 2048 blocks 620 -> 641 us.
+constexpr int BSF_FEW_GROUPS = 128;
 constexpr int BSF_CAP = 160;                        // candidates a row can hold
 constexpr int BSF_PITCH = 164;                      // entries between rows: a multiple of 4 (16-byte reads)
                                                     // and an odd multiple of 4 (16 rows hit 64 different banks)
 constexpr int BSF_SLACK = 16;                       // the bisection of a running cut stops at k .. k + slack entries
 constexpr int BSF_MAX_TOPK = BSF_CAP - 32 - BSF_SLACK;   // 32: what one tile can add to a row
 constexpr int BSF_TILE_BYTES = 32 * 512;            // 32 pooled vectors of 128 floats
-constexpr size_t BSF_LDS = 2 * BSF_TILE_BYTES + (size_t)BSF_ROWS * BSF_PITCH * (4 + 2);
+constexpr size_t bsf_lds(int waves) { return 2 * BSF_TILE_BYTES + (size_t)16 * waves * BSF_PITCH * (4 + 2); }
+constexpr int BSF_POOL_PITCH = 132;                 // floats between rows while Q is pooled by all waves
+constexpr size_t bsf_few_lds() {                    // per wave 16 rows of partial sums; the means of all blocks
+  const size_t pool = (size_t)(16 * BSF_WAVES + 16 * BSF_SEL_FEW) * BSF_POOL_PITCH * sizeof(float);
+  return pool > bsf_lds(BSF_SEL_FEW) ? pool : bsf_lds(BSF_SEL_FEW);
+}
 
 // the lists are addressed as LDS (not through generic pointers) also inside the functions below
 typedef __attribute__((address_space(3))) unsigned lds_u32;
@@ -1755,8 +1767,59 @@ __device__ __forceinline__ void bsf_pool_q(const bf16_t *q0, int64_t q_st, float
   for (int j = 0; j < 32; ++j) q[j] *= 1.0f / 64.0f;
 }
 
-__global__ __launch_bounds__(BSF_THREADS) void bs_topk_kernel(QKV x, HeadList hl, int NB, int NBp, int topk, KvMap km,
-                                                              const float *kpool, int32_t *blk_idx, int32_t *blk_cnt) {
+// Q_hat of the query blocks b0 .. b0 + n - 1 (clamped to NB - 1) into mean[0 .. n): the mean of a
+// block's 64 query rows, summed in the order of bs_pool_kernel (tokens r, r + 16, r + 32, r + 48
+// first, then r = 0 .. 15), so that both give the same bits.  A load takes four whole rows; the
+// partial sums of 16 lanes meet in `part`, private to the wave.
+__device__ __forceinline__ void bsf_pool_blocks(const bf16_t *qh, int64_t q_st, int b0, int n, int NB, float *part,
+                                                float *mean, int lane) {
+  const int rl = lane >> 4, c = lane & 15;
+  for (int b = 0; b < n; ++b) {
+    const bf16_t *src = qh + (int64_t)(64 * min(b0 + b, NB - 1)) * q_st + 8 * c;
+    uint4 w[4][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[g][i] = *reinterpret_cast<const uint4 *>(src + (int64_t)(4 * g + rl + 16 * i) * q_st);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {              // r = 4 g + rl
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned ww[4] = {w[g][i].x, w[g][i].y, w[g][i].z, w[g][i].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc[2 * j] += __uint_as_float(ww[j] << 16);
+          acc[2 * j + 1] += __uint_as_float(ww[j] & 0xffff0000u);
+        }
+      }
+      float4 *dst = reinterpret_cast<float4 *>(part + (4 * g + rl) * BSF_POOL_PITCH + 8 * c);
+      dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float2 e = *reinterpret_cast<const float2 *>(part + r * BSF_POOL_PITCH + 2 * lane);
+      s0 += e.x;
+      s1 += e.y;
+    }
+    *reinterpret_cast<float2 *>(mean + b * BSF_POOL_PITCH + 2 * lane) = make_float2(s0 * (1.0f / 64.0f), s1 * (1.0f / 64.0f));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// SEL: the waves that select (16 query blocks each); the others only fetch and pool.
+template <int SEL>
+__global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList hl, int NB, int NBp, int topk, KvMap km,
+                                                                 const float *kpool, int32_t *blk_idx,
+                                                                 int32_t *blk_cnt) {
+  constexpr int BSF_ROWS = 16 * SEL;                         // query blocks per workgroup
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   unsigned *ckey = reinterpret_cast<unsigned *>(lds + 2 * BSF_TILE_BYTES);
   unsigned short *cidx = reinterpret_cast<unsigned short *>(ckey + BSF_ROWS * BSF_PITCH);
@@ -1765,7 +1828,7 @@ __global__ __launch_bounds__(BSF_THREADS) void bs_topk_kernel(QKV x, HeadList hl
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, hq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row = R0 + 16 * wave + n;                        // query block of these four lanes
-  const bool row_ok = row < NB;
+  const bool row_ok = row < NB && wave < SEL;
   const int k = min(topk, row + 1);
   lds_u32 *keys = (lds_u32 *)ckey + (16 * wave + n) * BSF_PITCH;    // this row's list
   lds_u16 *idx = (lds_u16 *)cidx + (16 * wave + n) * BSF_PITCH;
@@ -1777,17 +1840,32 @@ __global__ __launch_bounds__(BSF_THREADS) void bs_topk_kernel(QKV x, HeadList hl
   // MFMA step j is 32 hq + j, for both operands), pooled here from the block's 64 query rows: the
   // pooled Q never goes through memory.
   float q[32];
-  bsf_pool_q(x.q + hl.h[slot] * x.q_sh + (int64_t)(64 * min(row, NB - 1)) * x.q_st + 32 * hq, x.q_st, q);
+  if (SEL == BSF_WAVES) {
+    bsf_pool_q(x.q + hl.h[slot] * x.q_sh + (int64_t)(64 * min(row, NB - 1)) * x.q_st + 32 * hq, x.q_st, q);
+  } else {
+    constexpr int PER = BSF_ROWS / BSF_WAVES;                // blocks a wave pools
+    float *mean = reinterpret_cast<float *>(lds);
+    bsf_pool_blocks(x.q + hl.h[slot] * x.q_sh, x.q_st, R0 + PER * wave, PER, NB,
+                    mean + (BSF_ROWS + 16 * wave) * BSF_POOL_PITCH, mean + PER * wave * BSF_POOL_PITCH, lane);
+    __syncthreads();
+    const float *src = mean + (16 * (wave % SEL) + n) * BSF_POOL_PITCH + 32 * hq;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const float4 e = *reinterpret_cast<const float4 *>(src + 4 * j);
+      q[4 * j] = e.x; q[4 * j + 1] = e.y; q[4 * j + 2] = e.z; q[4 * j + 3] = e.w;
+    }
+    __syncthreads();                                         // the tiles and lists take the pooling's LDS
+  }
   const float *kp = kpool + (int64_t)km.slot_kv[slot] * NBp * 128;
   const int last_row = min(R0 + BSF_ROWS, NB) - 1;           // last query block of the workgroup
   const int n_tiles = last_row / 32 + 1;                     // key tiles that hold a key <= last_row
   const int wave_first = R0 + 16 * wave;
-  const int t_last = wave_first < NB ? min(wave_first + 15, NB - 1) / 32 : -1;   // last tile with a causal key for this wave
+  const int t_last = wave_first < NB && wave < SEL ? min(wave_first + 15, NB - 1) / 32 : -1;   // last tile with a causal key for this wave
 
   // Tile t = pooled K rows 32 t .. 32 t + 31 (kpool is padded to whole tiles), 512 bytes each, in
   // LDS with the 16-byte chunk c of row m at chunk position c ^ (m % 16): the 16 lanes that read
   // one chunk column of 16 rows hit all 64 banks.  One load instruction fills two rows; this wave
-  // issues two of the sixteen.
+  // issues its share of the sixteen.
   auto fetch = [&](int t) {
     const float *ubase = kp + (int64_t)(32 * t) * 128;
     const unsigned base = lds_addr_of(lds + (t & 1) * BSF_TILE_BYTES);
@@ -1884,6 +1962,7 @@ __global__ __launch_bounds__(BSF_THREADS) void bs_topk_kernel(QKV x, HeadList hl
     for (int e = 0; e < 8; ++e) sc[e] = acc[e >> 2][0][e & 3] + acc[e >> 2][1][e & 3];
     select(sc, kb);
   }
+  if (wave >= SEL) return;
   // exact selection of what is left, then the row goes out (ascending; -1 behind the last entry)
   cnt = bsf_compact(keys, idx, cnt, k, true, hq, tau).cnt;
   if (row_ok) {
@@ -1899,7 +1978,7 @@ __global__ __launch_bounds__(BSF_THREADS) void bs_topk_kernel(QKV x, HeadList hl
 // two with keys above every real one).
 constexpr int BS_ORDER_MAX = 32768;
 __global__ __launch_bounds__(1024) void bs_order_kernel(int NB, int topk, const int32_t *blk_idx, int32_t *order) {
-  extern __shared__ unsigned key[];
+  extern __shared__ __attribute__((aligned(16))) unsigned key[];
   const int slot = blockIdx.x, tid = threadIdx.x;
   const int32_t *idx = blk_idx + (int64_t)slot * NB * topk;
   int32_t *out = order + (int64_t)slot * NB;
@@ -1914,6 +1993,20 @@ __global__ __launch_bounds__(1024) void bs_order_kernel(int NB, int topk, const 
     key[b] = (kf << 16) | (unsigned)(b & 0xffff);
   }
   __syncthreads();
+  if (NB <= 1024) {
+    // short rows: a block's place is the number of smaller keys (all differ).  313 blocks: 6 us, the
+    // 55 barriers of the sort 15.
+    if (tid < NB) {
+      const unsigned own = key[tid];
+      int place = 0;
+      for (int i = 0; i < NB; i += 4) {
+        const uint4 e = *reinterpret_cast<const uint4 *>(key + i);       // behind NB: keys above every real one
+        place += (e.x < own) + (e.y < own) + (e.z < own) + (e.w < own);
+      }
+      out[place] = tid;
+    }
+    return;
+  }
   for (int k = 2; k <= P; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
       for (int i = tid; i < P; i += 1024) {
@@ -2103,11 +2196,19 @@ hipError_t launch_build_bs(const QKV &x, const HeadList &hl, int topk, int32_t *
                      NBp);
   if (fused) {
     // pooling of Q, block logits and top-k in one kernel: neither the pooled Q nor anything of size NB x NB is stored
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs_topk_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)BSF_LDS);
+    auto topk_launch = [&](auto waves, size_t lds) -> hipError_t {
+      constexpr int SEL = decltype(waves)::value;
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs_topk_kernel<SEL>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((bs_topk_kernel<SEL>), dim3(hl.n, (NB + 16 * SEL - 1) / (16 * SEL)), dim3(64 * BSF_WAVES), lds,
+                         st, x, hl, NB, NBp, topk, km, (const float *)kpool, blk_idx, blk_cnt);
+      return hipSuccess;
+    };
+    const bool few = hl.n * ((NB + 16 * BSF_WAVES - 1) / (16 * BSF_WAVES)) <= BSF_FEW_GROUPS;
+    const hipError_t e = few ? topk_launch(std::integral_constant<int, BSF_SEL_FEW>{}, bsf_few_lds())
+                             : topk_launch(std::integral_constant<int, BSF_WAVES>{}, bsf_lds(BSF_WAVES));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bs_topk_kernel, dim3(hl.n, (NB + BSF_ROWS - 1) / BSF_ROWS), dim3(BSF_THREADS), BSF_LDS, st, x, hl,
-                       NB, NBp, topk, km, (const float *)kpool, blk_idx, blk_cnt);
   } else {
     // budgets beyond the candidate lists of the fused kernel: logits through memory, head batches
     const int hbmax = bs_head_batch(NB, hl.n);
