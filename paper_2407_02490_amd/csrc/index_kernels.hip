@@ -25,6 +25,7 @@
 //   through stored logits and a per-row radix select.
 #include <string.h>
 
+#include "key_range.h"
 #include "mfma_tile.h"
 
 namespace minf {
@@ -279,7 +280,6 @@ __device__ inline void ordered_select(const float *data, int n, unsigned thr, in
 // memory (four passes of eight bits and two of the ordered compaction, counts aggregated per wave)
 // took 63, 25, 15 and 111.
 // ---------------------------------------------------------------------------
-constexpr int REG_BINS = 2048;
 template <int E>                           // scores a thread holds
 struct RegRow {
   static constexpr int REG_E = E;
@@ -330,12 +330,11 @@ __device__ inline void reg_threshold(const RegRow<REG_E> &row, int k, unsigned *
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < 16; ++w) { lo = min(lo, (unsigned)sh[w]); hi = max(hi, (unsigned)sh[16 + w]); }
-  lo += 1u;
+  KeyRange range{lo + 1u, hi};
   __syncthreads();
   int krem = k;
-  while (true) {                           // uniform: every thread sees the same lo, hi, krem
-    const unsigned width = hi - lo;
-    const int shift = width < (unsigned)REG_BINS ? 0 : 21 - __builtin_clz(width);   // (width >> shift) < 2048
+  while (true) {                           // uniform: every thread sees the same range and krem
+    const int shift = key_range_shift(range);
     hist[tid] = 0; hist[tid + 1024] = 0;
     __syncthreads();
 #pragma unroll
@@ -344,7 +343,7 @@ __device__ inline void reg_threshold(const RegRow<REG_E> &row, int k, unsigned *
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const unsigned u = row.u[4 * j + c];
-          if (u - lo <= width) atomicAdd(&hist[(u - lo) >> shift], 1);
+          if (key_range_has(range, u)) atomicAdd(&hist[(u - range.lo) >> shift], 1);
         }
       }
     __syncthreads();
@@ -368,10 +367,9 @@ __device__ inline void reg_threshold(const RegRow<REG_E> &row, int k, unsigned *
     const unsigned bin = (unsigned)sh[32];
     krem = sh[33];
     const int inside = sh[34];
-    lo += bin << shift;
-    hi = min(hi, lo + ((1u << shift) - 1u));
-    if (shift == 0) { *thr = lo; *take_eq = krem; break; }
-    if (inside == krem && lo > 0u) { *thr = lo - 1u; *take_eq = 0; break; }
+    range = key_range_bin(range, bin, shift);
+    if (shift == 0) { *thr = range.lo; *take_eq = krem; break; }
+    if (inside == krem) { *thr = range.lo - 1u; *take_eq = 0; break; }
   }
   __syncthreads();                         // every thread has read sh
 }
