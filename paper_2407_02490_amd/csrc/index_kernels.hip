@@ -32,11 +32,16 @@ namespace minf {
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-// Keys / offsets owned by one workgroup of the score kernels: the largest of the three that gives
-// every CU its two workgroups, else the smallest (a chunk also meets 64 keys beyond its own, so
-// small ones cost more work).  4 K/V heads of 40K tokens: 160 workgroups of 1024 keys took 33 + 69
-// us, 632 of 256 take 25 + 53.
+// Keys / offsets owned by one workgroup of the score kernels.
+//  Pass 1 (row maxima and sums): by the length alone.  The partial sums of a row are rounded per
+//  chunk, so a chunk that followed the number of listed heads would give a head other scores, and
+//  now and then another line on a tie, when it is listed alone.
+//  Pass 2 (column and diagonal sums): every sum is taken in the same order whatever the chunk, so
+//  the chunk follows the grid: the largest that gives every CU its two workgroups, else the
+//  smallest (a chunk also meets 64 keys beyond its own, so small ones cost more work).  4 K/V heads
+//  of 40K tokens: 160 workgroups of 1024 keys took 69 us, 632 of 256 take 53.
 constexpr int VS_CHUNK = 1024, VS_CHUNK_SHORT = 256, VS_CHUNK_TINY = 128;
+constexpr int VS_SHORT_N = 32768, VS_TINY_N = 8192;
 constexpr int VS_MIN_GROUPS = 512;
 
 struct KvMap {                      // pooling work list of the Block-Sparse build
@@ -2026,17 +2031,13 @@ __global__ __launch_bounds__(1024) void bs_order_kernel(int NB, int topk, const 
 static inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 static int vs_chunks(int N, int keys) { return (N + keys - 1) / keys; }
-static int vs_chunk_keys(int N, int n_groups) {
+static int vs_ml_chunk_keys(int N) { return N <= VS_TINY_N ? VS_CHUNK_TINY : N <= VS_SHORT_N ? VS_CHUNK_SHORT : VS_CHUNK; }
+static int vs_sum_chunk_keys(int N, int n_groups) {
   for (const int keys : {VS_CHUNK, VS_CHUNK_SHORT})
     if (vs_chunks(N, keys) * n_groups >= VS_MIN_GROUPS) return keys;
   return VS_CHUNK_TINY;
 }
-
-// Chunks the workspace has a place of their own for.  More chunks (few K/V heads) go where the
-// candidates of the top-k come later: 2 N floats per head there, at most N + 128 needed.
-static int vs_ml_chunks(int N) {
-  return vs_chunks(N, N <= 8192 ? VS_CHUNK_TINY : N <= 32768 ? VS_CHUNK_SHORT : VS_CHUNK);
-}
+static int vs_ml_chunks(int N) { return vs_chunks(N, vs_ml_chunk_keys(N)); }
 
 static int vs_slices(int N) { return (N + VS_SLICE - 1) / VS_SLICE; }
 static int vs_cand_cap(int N) { return N / 4 > 1024 ? N / 4 : 1024; }        // candidates per (head, which)
@@ -2068,11 +2069,11 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
     if (g == vg.n) { gkv[g] = kv; ++vg.n; }
     vg.slot[g][vg.cnt[g]++] = (uint8_t)i;
   }
-  const int ck = vs_chunk_keys(N, vg.n), nc = vs_chunks(N, ck);
+  const int nc = vs_ml_chunks(N);
   char *p = static_cast<char *>(ws);
   float *colsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
   float *diagsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
-  float *ml_part = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * vs_ml_chunks(N) * 128 * sizeof(float));
+  float *ml_part = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * nc * 128 * sizeof(float));
   float *ml_fin = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * 128 * sizeof(float));
   const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
   float *gmax_v = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
@@ -2084,26 +2085,32 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
   int32_t *list_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
   int2 *seg = reinterpret_cast<int2 *>(p); p += align256((size_t)hl.n * 2 * n_slices * sizeof(int2));
   VsSelState *state = reinterpret_cast<VsSelState *>(p);
-  if (nc > vs_ml_chunks(N)) ml_part = cand_val;
   // 48 KiB (three workgroups of four waves per CU; registers allow two) and 75 KiB (two per CU)
-  const dim3 grid(nc, vg.n);
-  auto score = [&](auto chunk_keys) -> hipError_t {
-    constexpr int C = decltype(chunk_keys)::value;
-    const size_t lds1 = 3 * VS_TILE_BYTES;
-    const size_t lds2 = 3 * HALF_BYTES + VS_GROUP * vs_wave_floats(C) * sizeof(float);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(vs_score_kernel<2, C>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((vs_score_kernel<1, C>), grid, dim3(256), lds1, st, x, hl, vg, last_q, nc, ml_part,
-                       (const float *)nullptr, (float *)nullptr, (float *)nullptr);
-    hipLaunchKernelGGL(vs_combine_kernel, dim3(hl.n), dim3(1024), 0, st, nc, (const float *)ml_part, ml_fin);
-    hipLaunchKernelGGL((vs_score_kernel<2, C>), grid, dim3(256), lds2, st, x, hl, vg, last_q, nc, (float *)nullptr,
-                       (const float *)ml_fin, colsum, diagsum);
+  auto score = [&](auto pass, auto chunk_keys, size_t lds) -> hipError_t {
+    constexpr int P = decltype(pass)::value, C = decltype(chunk_keys)::value;
+    if (P == 2) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(vs_score_kernel<P, C>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((vs_score_kernel<P, C>), dim3(vs_chunks(N, C), vg.n), dim3(64 * VS_GROUP), lds, st, x, hl, vg,
+                       last_q, nc, ml_part, (const float *)ml_fin, colsum, diagsum);
     return hipSuccess;
   };
-  const hipError_t e = ck == VS_CHUNK_TINY    ? score(std::integral_constant<int, VS_CHUNK_TINY>{})
-                       : ck == VS_CHUNK_SHORT ? score(std::integral_constant<int, VS_CHUNK_SHORT>{})
-                                              : score(std::integral_constant<int, VS_CHUNK>{});
+  auto pass1 = [&](auto c) { return score(std::integral_constant<int, 1>{}, c, 3 * VS_TILE_BYTES); };
+  auto pass2 = [&](auto c) {
+    return score(std::integral_constant<int, 2>{}, c,
+                 3 * HALF_BYTES + VS_GROUP * vs_wave_floats(decltype(c)::value) * sizeof(float));
+  };
+  auto by_chunk = [&](int keys, auto run) -> hipError_t {
+    return keys == VS_CHUNK_TINY    ? run(std::integral_constant<int, VS_CHUNK_TINY>{})
+           : keys == VS_CHUNK_SHORT ? run(std::integral_constant<int, VS_CHUNK_SHORT>{})
+                                    : run(std::integral_constant<int, VS_CHUNK>{});
+  };
+  hipError_t e = by_chunk(vs_ml_chunk_keys(N), pass1);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(vs_combine_kernel, dim3(hl.n), dim3(1024), 0, st, nc, (const float *)ml_part, ml_fin);
+  e = by_chunk(vs_sum_chunk_keys(N, vg.n), pass2);
   if (e != hipSuccess) return e;
   // top-k of the line scores: prefilter by many workgroups, exact selection on what is left
   const int kv_ = nv < N ? nv : N, ks_ = ns < N ? ns : N;

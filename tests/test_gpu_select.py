@@ -48,6 +48,25 @@ def test_vs_selection_and_runs(B, N, nv, ns):
         check_topk(idx.s_idx[1].cpu().numpy(), diag, ns)
 
 
+@pytest.mark.parametrize("N", [1024, 4160, 12352, 33024, 65600, 131072])
+def test_vs_scores_do_not_depend_on_the_listed_heads(B, N):
+    """A head listed alone and with all others (four K/V heads): the same line scores, bit for bit
+    (they lie at the start of the workspace, [heads][N] of the columns, then of the diagonals), and
+    the same lines."""
+    heads = list(range(8))
+    q, k, _ = random_qkv(64, 8, 4, N)
+    got = []
+    for hs in (heads, [5]):
+        idx = B.alloc_vs_index(len(hs), 50, 200, N)
+        ws = torch.empty(B.minf_vs_index_workspace_bytes(q, k, len(hs), 64), dtype=torch.uint8, device="cuda")
+        B.minf_build_vs_index(q, k, hs, 64, 50, 200, idx, ws)
+        torch.cuda.synchronize()
+        scores = ws[:2 * len(hs) * N * 4].view(torch.int32).view(2, len(hs), N)
+        r = hs.index(5)
+        got.append((scores[0, r].cpu(), scores[1, r].cpu(), idx.v_idx[r].cpu(), idx.s_idx[r].cpu(), idx.counts[r].cpu()))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("N", [4096, 8256, 41024])
 def test_vs_ties_go_to_the_lower_position(B, N):
     """All logits equal: every key before the last 64 has the same column sum."""
