@@ -29,6 +29,13 @@
  *   - The head -> pattern assignment (the output of the paper's offline
  *     search, Section 3.2) is expressed by which call a head id is passed to;
  *     budgets are per call.  Each attention call writes O only for its heads.
+ *   - The results of a head do not depend on which other heads a call lists:
+ *     a layer's heads in one call or over several calls give the same bits.
+ *     The kernel of an attention call is chosen by the shape of the layer
+ *     (n_q_heads, seq_len) and the budgets, so the same head as part of a
+ *     tensor with another n_q_heads (a shard of the layer) may be summed in
+ *     another order: equal up to rounding, not bit for bit.  Indices are the
+ *     same in both cases.
  */
 #ifndef MINF_H_
 #define MINF_H_

@@ -2720,7 +2720,11 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// Largest number of work items (heads x query blocks) for which four waves share an item.  One wave
+// Work items (query heads x query blocks) of the layer.  The choice of a kernel follows them and not
+// the heads that a call lists: the kernels round differently, and a head has to come out with the
+// same bits whether its layer's heads are listed in one call or over several.
+static int64_t layer_items(const QKV &x) { return (int64_t)x.n_q * (x.N / BQ); }
+// Largest number of work items of a layer for which four waves share an item.  One wave
 // per item leaves SIMDs idle below 1024 items (256 CUs x 4) and ends with the longest item alone; a
 // CU whose four waves all load their own tiles is at its load path, so above that the split only
 // adds its epilogue.  Measured, one wave -> four: Vertical-Slash 256 items of 4K tokens 101 -> 37
@@ -2745,7 +2749,7 @@ constexpr int ASHAPE_SPLIT_MAX_ITEMS = 512;
 
 hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
-  if (hl.n * NB <= ASHAPE_SPLIT_MAX_ITEMS) {
+  if (layer_items(x) <= ASHAPE_SPLIT_MAX_ITEMS) {
     const Sched s = make_sched(hl, x.group, NB);
     const size_t lds = SPLIT * RING_BYTES;
     const bool rows256 = x.k_st == D && x.v_st == D;
@@ -2781,7 +2785,7 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
   const int NB = x.N / BQ;
   const Sched s = make_sched(hl, x.group, NB);
   const bool rows256 = x.k_st == D && x.v_st == D;
-  if (hl.n * NB <= SPLIT_MAX_ITEMS) {
+  if (layer_items(x) <= SPLIT_MAX_ITEMS) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = rows256 ? reinterpret_cast<const void *>(bs_split_kernel<true>)
                              : reinterpret_cast<const void *>(bs_split_kernel<false>);
@@ -2833,7 +2837,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     return hipGetLastError();
   }
   const Sched s = make_sched(hl, x.group, NB);
-  if (hl.n * NB <= SPLIT_MAX_ITEMS) {
+  if (layer_items(x) <= SPLIT_MAX_ITEMS) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = rows256 ? reinterpret_cast<const void *>(vs_split_kernel<true>)
                              : reinterpret_cast<const void *>(vs_split_kernel<false>);
@@ -2881,7 +2885,7 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  if (hv.n * NB <= SPLIT_MAX_ITEMS || hb.n * NB <= SPLIT_MAX_ITEMS || vs_share(x.N, ns)) {
+  if (layer_items(x) <= SPLIT_MAX_ITEMS || vs_share(x.N, ns)) {
     // not one wave per block for both kinds: one launch per kind, the kernels the two calls take
     const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
     return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);

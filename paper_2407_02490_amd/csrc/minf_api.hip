@@ -85,6 +85,7 @@ QKV view(const minf_qkv *x, int b) {
   v.o_sh = x->o_stride[1]; v.o_st = x->o_stride[2];
   v.N = x->seq_len;
   v.group = x->n_q_heads / x->n_kv_heads;
+  v.n_q = x->n_q_heads;
   v.scale = x->softmax_scale > 0.f ? x->softmax_scale : 1.0f / sqrtf((float)x->head_dim);
   v.c_log2 = v.scale * 1.4426950408889634f;
   return v;

@@ -19,7 +19,7 @@ struct QKV {
   const bf16_t *q, *k, *v;
   bf16_t *o;
   int64_t q_sh, q_st, k_sh, k_st, v_sh, v_st, o_sh, o_st;
-  int32_t N, group;
+  int32_t N, group, n_q;              // n_q: query heads of the layer (not of the call's list)
   float scale, c_log2;
 };
 

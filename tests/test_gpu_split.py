@@ -1,7 +1,8 @@
 """The attention kernels that let four waves share a query block (few work items) beside the ones
 that give every block one wave (many), on the same heads, against the oracle.
 
-The number of listed heads decides: 66 heads of 1024 tokens are 1056 items, 2 heads are 32.
+The number of query heads of the layer decides, not the list: 66 heads of 1024 tokens are 1056
+items, 3 heads are 48.
 """
 import numpy as np
 import pytest
@@ -13,7 +14,7 @@ from tests.test_gpu_attention import random_bs_index, run_heads, token_major
 
 pytestmark = pytest.mark.gpu
 
-MANY, FEW = list(range(66)), [0, 65]
+FEW = [0, 65]           # heads of the large layer that the small one holds too, as its heads 0 and 2
 
 
 @pytest.fixture(scope="module")
@@ -56,17 +57,41 @@ def test_few_and_many_items(B, rng, kind, layout):
                                                                                np.stack([cnt] * len(heads)))),
                lambda Q, K, V: O.bs_attention(Q, K, V, idx, cnt)),
     }
-    tq, tk, tv = (token_major(t) if layout == "token" else t for t in (q, k, v))
+    many = (q, k, v, list(range(66)), FEW)
+    few = (q[[0, 30, 65]], k[[0, 0, 1]], v[[0, 0, 1]], [0, 2], [0, 2])
     for name, (call, oracle) in calls.items():
-        want = {h: oracle(to_f64(q[h]), to_f64(k[h // 33]), to_f64(v[h // 33])) for h in FEW}
-        for heads in (MANY, FEW):
-            o = torch.full_like(q, float("nan"))
-            o = token_major(o) if layout == "token" else o
+        want = [oracle(to_f64(q[h]), to_f64(k[h // 33]), to_f64(v[h // 33])) for h in FEW]
+        for cq, ck, cv, heads, checked in (many, few):
+            o = torch.full_like(cq, float("nan"))
+            tq, tk, tv, o = (token_major(t) if layout == "token" else t for t in (cq, ck, cv, o))
             call(heads, tq, tk, tv, o)
             torch.cuda.synchronize()
-            for h in FEW:
-                assert_close_rows(o[h], want[h], f"{name} {kind} {layout} {len(heads)} heads, head {h}")
-            assert len(heads) == 66 or bool(torch.isnan(o[1:65].float()).all())
+            for h, w in zip(checked, want):
+                assert_close_rows(o[h], w, f"{name} {kind} {layout} {len(heads)} heads, head {h}")
+            assert len(heads) == 66 or bool(torch.isnan(o[1].float()).all())
+
+
+@pytest.mark.parametrize("nq,N", [(66, 1024), (66, 512), (5, 1024), (40, 4096)])
+def test_bits_of_a_head_do_not_depend_on_the_listed_heads(B, rng, nq, N):
+    """A head alone, in a short list and with all heads of the layer: the same bits from every call."""
+    q, k, v = random_qkv(95, nq, 1, N)
+    Vl, Sl = sorted(rng.choice(N, 60, replace=False).tolist()), list(range(0, 130)) + [300, 301]
+    idx, cnt = random_bs_index(rng, N // 64, 20)
+    calls = {
+        "dense": lambda hs, o: B.minf_dense_attn(q, k, v, o, hs),
+        "ashape": lambda hs, o: B.minf_ashape_attn(q, k, v, o, hs, 100, 200),
+        "vs": lambda hs, o: B.minf_vs_attn(q, k, v, o, hs, B.vs_index_from_host([Vl] * len(hs), [Sl] * len(hs), N)),
+        "bs": lambda hs, o: B.minf_bs_attn(q, k, v, o, hs, B.bs_index_from_host(np.stack([idx] * len(hs)),
+                                                                               np.stack([cnt] * len(hs)))),
+    }
+    for name, call in calls.items():
+        got = []
+        for hs in ([3], [4, 3, 1], list(range(nq))):
+            o = torch.full_like(q, float("nan"))
+            call(hs, o)
+            torch.cuda.synchronize()
+            got.append(o[3])
+        assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]), name
 
 
 @pytest.mark.parametrize("Sl", [[0], [0, 70], list(range(0, 8000, 70)), [5000] + list(range(6000, 6300))])
