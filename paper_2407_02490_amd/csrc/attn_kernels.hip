@@ -53,6 +53,7 @@
 #include <string.h>
 #include <type_traits>
 
+#include "dispatch.h"
 #include "mfma_tile.h"
 #include "vs_ring_sched.h"
 
@@ -2720,17 +2721,6 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// Work items (query heads x query blocks) of the layer.  The choice of a kernel follows them and not
-// the heads that a call lists: the kernels round differently, and a head has to come out with the
-// same bits whether its layer's heads are listed in one call or over several.
-static int64_t layer_items(const QKV &x) { return (int64_t)x.n_q * (x.N / BQ); }
-// Largest number of work items of a layer for which four waves share an item.  One wave
-// per item leaves SIMDs idle below 1024 items (256 CUs x 4) and ends with the longest item alone; a
-// CU whose four waves all load their own tiles is at its load path, so above that the split only
-// adds its epilogue.  Measured, one wave -> four: Vertical-Slash 256 items of 4K tokens 101 -> 37
-// us, 1024 of 8K 213 -> 163 (short lists 172 -> 136), 4096 of 8K 595 -> 626 (412 -> 500);
-// Block-Sparse 256 items 105 -> 39, 1024 183 -> 160, 4096 720 -> 763.
-constexpr int SPLIT_MAX_ITEMS = 1024;
 // Whether a workgroup takes four consecutive blocks (vs_share_kernel) instead of one (vs_kernel):
 //  - short rows and rows of which a large part is kept, where the slash tiles merge into long runs.
 //    32 heads, us: 8K tokens 638 -> 519, 16K 1958 -> 1782, 32K 5485 -> 5253, 64K 13269 -> 13137;
@@ -2742,14 +2732,10 @@ constexpr int SPLIT_MAX_ITEMS = 1024;
 static bool vs_share(int N, int ns) {
   return N <= 16384 || (int64_t)ns * 12 >= N || (N >= 262144 && ns >= 4096);
 }
-// A-shape and dense, whose alternative shares its tiles between four blocks and needs a quarter of
-// the loads: 512 items of 8K tokens 134 -> 83 us (dense 177 -> 86), 1024 items 148 -> 149, with a
-// short window (128, 1024) 62 -> 74.
-constexpr int ASHAPE_SPLIT_MAX_ITEMS = 512;
 
 hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
-  if (layer_items(x) <= ASHAPE_SPLIT_MAX_ITEMS) {
+  if (ashape_split_pays(x.n_q, x.N, n_local)) {
     const Sched s = make_sched(hl, x.group, NB);
     const size_t lds = SPLIT * RING_BYTES;
     const bool rows256 = x.k_st == D && x.v_st == D;
@@ -2785,7 +2771,7 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
   const int NB = x.N / BQ;
   const Sched s = make_sched(hl, x.group, NB);
   const bool rows256 = x.k_st == D && x.v_st == D;
-  if (layer_items(x) <= SPLIT_MAX_ITEMS) {
+  if (bs_split_pays(x.n_q, x.N, topk)) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = rows256 ? reinterpret_cast<const void *>(bs_split_kernel<true>)
                              : reinterpret_cast<const void *>(bs_split_kernel<false>);
@@ -2837,7 +2823,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     return hipGetLastError();
   }
   const Sched s = make_sched(hl, x.group, NB);
-  if (layer_items(x) <= SPLIT_MAX_ITEMS) {
+  if (vs_split_pays(x.n_q, x.N, nv, ns)) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = rows256 ? reinterpret_cast<const void *>(vs_split_kernel<true>)
                              : reinterpret_cast<const void *>(vs_split_kernel<false>);
@@ -2885,7 +2871,7 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  if (layer_items(x) <= SPLIT_MAX_ITEMS || vs_share(x.N, ns)) {
+  if (vs_split_pays(x.n_q, x.N, nv, ns) || bs_split_pays(x.n_q, x.N, topk) || vs_share(x.N, ns)) {
     // not one wave per block for both kinds: one launch per kind, the kernels the two calls take
     const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
     return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);

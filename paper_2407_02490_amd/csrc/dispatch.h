@@ -1,0 +1,68 @@
+// Rules that choose the kernel of an attention call.  Plain integer functions of the layer's shape
+// and the budgets, compiled for the host only (a test evaluates them at measured sizes).  They know
+// neither the listed heads nor the layout: the kernels round differently, and a head has to come out
+// with the same bits whether its layer's heads are listed in one call or over several.
+//
+// n_q: query heads of the layer; N: tokens.  A work item is a (query head, 64-row block).
+#ifndef MINF_DISPATCH_H_
+#define MINF_DISPATCH_H_
+
+#include <stdint.h>
+
+namespace minf {
+
+// A split launch holds one workgroup per CU (160 KiB of LDS): the layer's items in rounds of 256.
+inline int64_t split_rounds(int n_q, int N) { return ((int64_t)n_q * (N / 64) + 255) / 256; }
+constexpr int SPLIT_MAX_ROUNDS = 4;          // beyond 1024 items one wave per item fills every SIMD
+
+// Block-Sparse: four waves per block (bs_split_kernel) or one (bs_kernel).
+// One wave per item ends with its longest list, 1.55 us per listed block.  A round of the split
+// kernel costs its own start and merge, as long as about 15 listed blocks, and then 0.52 us per
+// listed block of an average list (causality shortens the first ones).  With L the longest list and
+// A the average, split iff rounds (15 + A) < 3 L + 8.  One wave -> four, us:
+//   256 items, 8K tokens:  top-2 12.2 -> 13.2, 8: 21.1 -> 15.8, 100: 163 -> 55
+//   512 items, 8K tokens:  8: 24.0 -> 30.1, 16: 37.4 -> 37.2, 24: 49.7 -> 44.0, 100: 164 -> 86
+//   768 items, 8K tokens:  37: 71.6 -> 81.9, 64: 109 -> 105, 100: 164 -> 127
+//   1024 items, 8K tokens: 8: 29.6 -> 55.9, 50: 101 -> 115, 80: 143 -> 140, 100: 176 -> 159
+//   1024 items, 4K tokens: 37: 74.1 -> 88.6, 64: 111 -> 96; 16K tokens: 110: 202 -> 205
+//   2048 items, 8K tokens: 50: 201 -> 225, 100: 330 -> 310; 2560 items: 100: 390 -> 391
+inline bool bs_split_pays(int n_q, int N, int topk) {
+  const int64_t r = split_rounds(n_q, N), NB = N / 64, L = topk < NB ? topk : NB;
+  const int64_t total = L * NB - L * (L - 1) / 2;                     // A NB
+  return r <= SPLIT_MAX_ROUNDS && r * (15 * NB + total) < (3 * L + 8) * NB;
+}
+
+// Vertical-Slash: four waves per block (vs_split_kernel).  As above, but the length of a block's walk
+// is known on the device only; nv + 4 ns stands for it (a slash brings the keys of its tile that its
+// neighbours' tiles do not hold).  One wave -> four, us, for (nv, ns):
+//   256 items:  every budget and length, e.g. 4K tokens (30, 64) 33 -> 22, (1000, 6096) 101 -> 39
+//   512 items:  (30, 64) 4K 31 -> 35, 16K 28 -> 36, 8K 44 -> 39; (30, 256) 4K 49 -> 38, 16K 57 -> 53,
+//               1K 34 -> 37; (256, 512) 4K 55 -> 40, 1K 38 -> 39; (1000, 6096) 1K 40 -> 37
+//   768 items:  2K (1000, 6096) 62 -> 63; 4K (256, 512) 60 -> 62, (30, 1024) 90 -> 78; 8K (256, 512) 91 -> 88,
+//               (30, 256) 69 -> 72; 16K (256, 512) 93 -> 96, (500, 1500) 147 -> 114
+//   1024 items: 2K (1000, 6096) 65 -> 75; 4K (256, 512) 63 -> 79, (30, 1024) 82 -> 89, (30, 2048) 110 -> 100;
+//               8K (30, 256) 87 -> 96, (1000, 256) 107 -> 111, (30, 512) 120 -> 112, (1000, 6096) 204 -> 160
+//   2048 items: 8K (30, 2048) 226 -> 238, (1000, 6096) 341 -> 311 (four blocks per workgroup: 299)
+inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
+  const int64_t r = split_rounds(n_q, N);
+  const int64_t walk = (int64_t)(nv < N ? nv : N) + 4 * (int64_t)(ns < N ? ns : N);
+  if (r <= 1) return true;
+  if (r == 2) return walk >= (N >= 1536 ? 1024 : 4096);
+  if (r > SPLIT_MAX_ROUNDS || N < 3072) return false;
+  return walk >= (N >= 8192 ? 2048 : r == 3 ? 4096 : 6000);
+}
+
+// A-shape and dense (n_local >= N): four waves per block (ashape_split_kernel) against four blocks
+// per workgroup that share their tiles and need a quarter of the loads.  Us, shared -> split:
+//   512 items:  4K tokens (1024, 4096) 98 -> 52, (128, 1024) 58 -> 40, (0, 128) 33 -> 25, dense 99 -> 53
+//   768 items:  8K tokens (1024, 4096) 134 -> 123, (0, 128) 34 -> 36, dense 177 -> 131
+//   1024 items: 8K tokens (1024, 4096) 139 -> 144, (128, 1024) 62 -> 73, dense 184 -> 162;
+//               dense of 4K 103 -> 99, 16K 345 -> 289, 2K 71 -> 74
+//   2048 items: 8K tokens dense 307 -> 311
+inline bool ashape_split_pays(int n_q, int N, int n_local) {
+  const int64_t items = (int64_t)n_q * (N / 64);
+  return items <= 512 || (n_local >= N && N >= 4096 && items <= 1024);
+}
+
+}  // namespace minf
+#endif

@@ -36,14 +36,24 @@ def test_shared_tile_vertical_slash_schedule_covers_every_run_key_once():
         assert r.returncode == 0 and r.stdout.startswith("ok cases"), r.stdout[-2000:] + r.stderr[-2000:]
 
 
-def test_selection_ranges_keep_exactly_k_keys():
-    """tests/key_range_check.cpp (host only): the range passes of the register selection on rows with
-    ties, infinities and NaN scores and with places that hold no element."""
+def run_host_check(name):
     with tempfile.TemporaryDirectory() as tmp:
-        exe = os.path.join(tmp, "key_range_check")
+        exe = os.path.join(tmp, name)
         cmd = ["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2407_02490_amd", "csrc"),
-               os.path.join(ROOT, "tests", "key_range_check.cpp"), "-o", exe]
+               os.path.join(ROOT, "tests", name + ".cpp"), "-o", exe]
         r = subprocess.run(cmd, capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
         r = subprocess.run([exe], capture_output=True, text=True)
-        assert r.returncode == 0 and r.stdout.startswith("ok cases"), r.stdout[-2000:] + r.stderr[-2000:]
+        assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout[-2000:] + r.stderr[-2000:]
+
+
+def test_selection_ranges_keep_exactly_k_keys():
+    """tests/key_range_check.cpp (host only): the range passes of the register selection on rows with
+    ties, infinities and NaN scores and with places that hold no element."""
+    run_host_check("key_range_check")
+
+
+def test_kernel_rules_take_the_faster_kernel_at_measured_sizes():
+    """tests/dispatch_check.cpp (host only): the rules of dispatch.h at sizes where both kernels
+    were timed."""
+    run_host_check("dispatch_check")
