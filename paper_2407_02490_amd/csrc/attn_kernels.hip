@@ -2721,18 +2721,6 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// Whether a workgroup takes four consecutive blocks (vs_share_kernel) instead of one (vs_kernel):
-//  - short rows and rows of which a large part is kept, where the slash tiles merge into long runs.
-//    32 heads, us: 8K tokens 638 -> 519, 16K 1958 -> 1782, 32K 5485 -> 5253, 64K 13269 -> 13137;
-//    at 128K (6096 slashes) 30796 -> 30797, and 1500 slashes at 64K lose, 4018 -> 4100;
-//  - many runs of a row whose K and V do not stay in the 256 MB memory-side cache: the four waves
-//    walk neighbouring keys at the same time and meet in the L2.  24 heads of 1M tokens 299.5 ->
-//    252.6 ms, 8 of 512K 42.3 -> 38.3, 256K 15.98 -> 15.72, 192K 12.54 -> 12.73; 1500 slashes at
-//    512K lose, 8.42 -> 8.72.
-static bool vs_share(int N, int ns) {
-  return N <= 16384 || (int64_t)ns * 12 >= N || (N >= 262144 && ns >= 4096);
-}
-
 hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
   if (ashape_split_pays(x.n_q, x.N, n_local)) {
@@ -2837,7 +2825,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
                          cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
-  if (vs_share(x.N, ns)) {
+  if (vs_share_pays(x.N, ns)) {
     const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4);
     const size_t lds = 4 * RING_BYTES;
     const void *fn = rows256 ? reinterpret_cast<const void *>(vs_share_kernel<true>)
@@ -2871,7 +2859,7 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  if (vs_split_pays(x.n_q, x.N, nv, ns) || bs_split_pays(x.n_q, x.N, topk) || vs_share(x.N, ns)) {
+  if (vs_split_pays(x.n_q, x.N, nv, ns) || bs_split_pays(x.n_q, x.N, topk) || vs_share_pays(x.N, ns)) {
     // not one wave per block for both kinds: one launch per kind, the kernels the two calls take
     const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
     return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);

@@ -52,6 +52,29 @@ inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
   return walk >= (N >= 8192 ? 2048 : r == 3 ? 4096 : 6000);
 }
 
+// Vertical-Slash: four consecutive blocks per workgroup (vs_share_kernel) or one (vs_kernel), where no
+// block is split.  The four share the common part of slash runs of at least 704 offsets, and long
+// runs are there only where many slashes are kept for the length of the row.  Without them the
+// workgroup only holds its CU until its longest block ends, and rows of up to 3K tokens leave CUs
+// idle besides.  One block -> four, 32 heads unless stated, us by number of slashes:
+//   2K (64 heads)   512: 91 -> 111, 1500: 105 -> 129, all: 110 -> 133;  1K (128 heads) 512: 71 -> 147
+//   3K (40 heads)   512: 94 -> 111, 1500: 148 -> 154, 3000: 150 -> 151
+//   4K   512: 100 -> 101, 1024: 157 -> 156, 1500: 197 -> 187, 6096: 193 -> 173;  6K  2500: 372 -> 356
+//   8K   200: 380 -> 398, 1500: 406 -> 415, 3072: 464 -> 473, 3500: 564 -> 562, 4096: 601 -> 554, 6096: 593 -> 520
+//   16K  512: 714 -> 727, 2048: 920 -> 946, 4096: 1500 -> 1499, 5000: 1755 -> 1658, 6096: 1888 -> 1707
+//   32K  2048: 1995 -> 2040, 4096: 2733 -> 2811, 5000: 4491 -> 4504, 6096: 5326 -> 5136, 12288: 7272 -> 6585
+//   64K  4096: 4862 -> 4949, 5000: 10480 -> 10613, 6096: 12996 -> 12943, 8192: 16247 -> 15764
+//   128K (8 heads)  4096: 2337 -> 2371, 6096: 8122 -> 8186, 8192: 11181 -> 11111, 12288: 16454 -> 16261
+// On very long rows with many runs four neighbours gain without common tiles.  8 heads (1M: 4), ms:
+//   256K  5000: 12.58 -> 12.79, 6096: 15.49 -> 15.47;  384K  4600: 18.28 -> 17.99, 6096: 31.4 -> 28.9
+//   512K  4096: 8.91 -> 9.23, 4600: 21.96 -> 22.33, 5000: 28.3 -> 27.7, 6096: 42.2 -> 37.6
+//   1M    4096: 9.00 -> 9.32, 5000: 47.3 -> 41.9, 6096: 65.7 -> 61.7, 12288: 168.8 -> 134.3
+inline bool vs_share_pays(int N, int ns) {
+  if (N < 4096) return false;
+  if ((int64_t)(N <= 6144 ? 3 : 2) * ns >= N) return true;
+  return (int64_t)40 * (ns - 4096) >= N || (N >= 393216 && ns >= 5000);
+}
+
 // A-shape and dense (n_local >= N): four waves per block (ashape_split_kernel) against four blocks
 // per workgroup that share their tiles and need a quarter of the loads.  Us, shared -> split:
 //   512 items:  4K tokens (1024, 4096) 98 -> 52, (128, 1024) 58 -> 40, (0, 128) 33 -> 25, dense 99 -> 53

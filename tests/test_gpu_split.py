@@ -145,9 +145,10 @@ def test_common_part_of_long_runs(B, rng, Sl, layout, kind):
     q, k, v = (token_major(t) if layout == "token" else t for t in (q0, k0, v0))
     o = torch.full_like(q0, float("nan"))
     o = token_major(o) if layout == "token" else o
-    B.minf_vs_attn(q, k, v, o, list(range(17)), B.vs_index_from_host([Vl] * 17, [Sl] * 17, N))
+    # the slashes an index has room for choose the kernel: head 0's list makes it 1400 of 4160
+    B.minf_vs_attn(q, k, v, o, list(range(17)), B.vs_index_from_host([Vl] * 17, [list(range(1400))] + [Sl] * 16, N))
     torch.cuda.synchronize()
-    for h in (0, 16):
+    for h in (1, 16):
         want = O.vs_attention(to_f64(q0[h]), to_f64(k0[0]), to_f64(v0[0]), Vl, Sl, Bm=64)
         for b in range(0, 65):
             assert_close_rows(o[h, 64 * b:64 * b + 64], want[64 * b:64 * b + 64], f"head {h} block {b}")
