@@ -1052,7 +1052,9 @@ constexpr int RING_BYTES = 5 * HALF_BYTES;
 // false, without having written anything, if some row must be redone exactly: a share overflowed,
 // or a share that may have lost terms to underflow (l_w < 2^-100: at most 2^20 keys of less than
 // 2^(m_w - 100) each) is not below 2^-20 of the row's mass; a row without a key is one.
-template <int NW>
+// EXACT: the shares come from the exact scheme, each with its own row max as the reference; always
+// true, and a row without a key gives zeros.
+template <int NW, bool EXACT = false>
 __device__ inline bool split_finish(const WaveState &st, bf16_t *oh, int64_t o_st, int q0, char *lds, int wave,
                                     int lane) {
   constexpr int ML_OFS = 64 * 512, ROWS = 64 / NW;
@@ -1082,28 +1084,30 @@ __device__ inline bool split_finish(const WaveState &st, bf16_t *oh, int64_t o_s
     for (int w = 0; w < NW; ++w) {
       ml[w] = *reinterpret_cast<const float2 *>(lds + w * RING_BYTES + ML_OFS + 8 * row);
       bad = bad || !(ml[w].y < L_LIMIT);
-      if (ml[w].y > 0.f) M = fmaxf(M, ml[w].x + __builtin_amdgcn_logf(ml[w].y));
+      if (ml[w].y != 0.f) M = fmaxf(M, ml[w].x + __builtin_amdgcn_logf(ml[w].y));
     }
     float L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       bad = bad || (ml[w].y < L_TINY && !(M > ml[w].x - 60.f));
-      wgt[i][w] = ml[w].y > 0.f ? fast_exp2(ml[w].x - M) : 0.f;
+      wgt[i][w] = ml[w].y != 0.f ? fast_exp2(ml[w].x - M) : 0.f;     // a NaN share makes the row NaN
       L += wgt[i][w] * ml[w].y;
     }
-    const float inv = 1.0f / L;
+    const float inv = EXACT && L == 0.f ? 0.f : 1.0f / L;
 #pragma unroll
     for (int w = 0; w < NW; ++w) wgt[i][w] *= inv;
   }
-  const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
-  if (lane == 0) *reinterpret_cast<int *>(mine + ML_OFS + 512) = wave_bad;
-  __syncthreads();
-  int any_bad = 0;
+  if (!EXACT) {
+    const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) *reinterpret_cast<int *>(mine + ML_OFS + 512) = wave_bad;
+    __syncthreads();
+    int any_bad = 0;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) any_bad |= *reinterpret_cast<const int *>(lds + w * RING_BYTES + ML_OFS + 512);
-  if (__builtin_amdgcn_readfirstlane(any_bad)) {
-    __syncthreads();       // every wave has read the flags: wave 0 may overwrite its ring
-    return false;
+    for (int w = 0; w < NW; ++w) any_bad |= *reinterpret_cast<const int *>(lds + w * RING_BYTES + ML_OFS + 512);
+    if (__builtin_amdgcn_readfirstlane(any_bad)) {
+      __syncthreads();       // every wave has read the flags: the rings may be overwritten
+      return false;
+    }
   }
 #pragma unroll
   for (int i = 0; i < ROWS / 4; ++i) {
@@ -2302,10 +2306,11 @@ __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const
   wave_finish(st, oh, x.o_st, q0, ring, lane);
 }
 
-template <int PASS>
-__device__ inline void ashape_wave_pass(const AshapeGen<1> &gen0, WaveState &st, const LaneOfs &lo, const StepBuf &buf,
-                                        const bf16_t *kh, const bf16_t *vh, const QKV &x, const MaskP &mp, int lane) {
-  AshapeGen<1> gen = gen0;
+// One pass of the exact scheme over this wave's share of the steps.
+template <int PASS, int NW>
+__device__ inline void ashape_wave_pass(WaveState &st, const LaneOfs &lo, const StepBuf &buf, const bf16_t *kh,
+                                        const bf16_t *vh, const QKV &x, const MaskP &mp, int wave, int lane) {
+  AshapeGen<NW> gen(mp, wave);
   bool has_ref = false;
   Step d;
   while (gen.next(d)) {
@@ -2346,14 +2351,17 @@ __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadLis
                                             reinterpret_cast<const char *>(vh), (unsigned)x.k_st * 2u,
                                             (unsigned)x.v_st * 2u, dk, dv, mp, x.c_log2, lane};
   pipe.run();
-  if (split_finish<SPLIT>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+  if (split_finish<SPLIT>(st, oh, x.o_st, q0, lds, wave, lane)) return;
+  // The four waves share both exact passes too: every share against its own row max, then the same
+  // merge.  (One wave alone, whose loads nothing overlaps, was slower than the four blocks of
+  // ashape_kernel: 4 heads of 8K tokens, dense, most blocks redone: 583 us there, 715 with one wave,
+  // 256 so.)
   load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
   reset_for_max_pass(st);
-  const AshapeGen<1> all(mp, 0);
-  ashape_wave_pass<PASS_MAX>(all, st, lo, buf, kh, vh, x, mp, lane);
+  ashape_wave_pass<PASS_MAX, SPLIT>(st, lo, buf, kh, vh, x, mp, wave, lane);
   finish_max_pass(st, x.c_log2);
-  ashape_wave_pass<PASS_FIX>(all, st, lo, buf, kh, vh, x, mp, lane);
-  wave_finish(st, oh, x.o_st, q0, lds, lane);
+  ashape_wave_pass<PASS_FIX, SPLIT>(st, lo, buf, kh, vh, x, mp, wave, lane);
+  split_finish<SPLIT, true>(st, oh, x.o_st, q0, lds, wave, lane);
 }
 
 // Vertical-Slash and Block-Sparse heads of a layer in ONE launch (the layers of the paper's models
