@@ -1693,25 +1693,26 @@ struct BsCtx {
   float c_log2;
 };
 
-template <int PASS>
-__device__ inline void bs_pass(const BsCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp, int lane) {
+// Plain pass over the list entries wave, wave + NW, ...
+template <int PASS, int NW>
+__device__ inline void bs_pass(const BsCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp, int wave, int lane) {
   // entries outside [0, NB) are skipped
   auto next_valid = [&](int i) {
     while (i < c.cnt) {
       const int b = c.list[i];
       if (b >= 0 && b < c.NB) break;
-      ++i;
+      i += NW;
     }
     return i;
   };
   bool has_ref = false;
-  int i = next_valid(0), half = 0, s = 0;
+  int i = next_valid(wave), half = 0, s = 0;
   if (i < c.cnt) fetch_step<true>(c.buf, 0, c.kh, c.vh, c.k_st, c.v_st, c.list[i] * BK, nullptr, c.N, lane);
   while (i < c.cnt) {
     const int kbase = c.list[i] * BK + 32 * half;
     int i2 = i;
     const int half2 = half ^ 1;
-    if (half == 1) i2 = next_valid(i + 1);
+    if (half == 1) i2 = next_valid(i + NW);
     if (i2 < c.cnt) {
       fetch_step<true>(c.buf, s ^ 1, c.kh, c.vh, c.k_st, c.v_st, c.list[i2] * BK + 32 * half2, nullptr, c.N, lane);
       MINF_WAIT_VMCNT(16);
@@ -1801,14 +1802,18 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
     pipe.run();
   }
   if (NW > 1) {
-    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
   if (NW > 1 || needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
-    bs_pass<PASS_MAX>(c, st, lo, mp, lane);
+    bs_pass<PASS_MAX, NW>(c, st, lo, mp, wave, lane);
     finish_max_pass(st, x.c_log2);
-    bs_pass<PASS_FIX>(c, st, lo, mp, lane);
+    bs_pass<PASS_FIX, NW>(c, st, lo, mp, wave, lane);
+  }
+  if (NW > 1) {
+    split_finish<NW, true>(st, oh, x.o_st, q0, lds, wave, lane);
+    return;
   }
   wave_finish(st, oh, x.o_st, q0, lds, lane);
 }
@@ -1843,26 +1848,28 @@ struct VsCtx {
   float c_log2;
 };
 
-template <int PASS>
-__device__ inline void vs_pass(const VsCtx &c, WaveState &st, const LaneOfs &lo, MaskP mp, int lane) {
+// Plain pass over the steps wave, wave + NW, ... of the runs and the chunks of 64 verticals wave, wave + NW, ...
+template <int PASS, int NW>
+__device__ inline void vs_pass(const VsCtx &c, WaveState &st, const LaneOfs &lo, MaskP mp, int wave, int lane) {
   const int q0 = c.q0;
   bool has_ref = false;
   // ---- phase A: slash runs -------------------------------------------------
-  int iv = 0, ks = 0, ke = 0, pos = 0;   // run index, clipped key range [ks, ke), next step start
+  int iv = 0, ks = 0, ke = 0, pos = 32 * wave;   // run index, clipped key range [ks, ke), next step start
   auto next_run_step = [&](int &kbase, int &rlo, int &rhi) -> bool {
     while (true) {
       if (pos < ke) {
         kbase = pos; rlo = ks; rhi = ke;
-        pos += 32;
+        pos += 32 * NW;
         return true;
       }
       if (iv >= c.n_c) return false;
       const int2 r = c.runs[iv];
       if (r.x > q0) { iv = c.n_c; return false; }   // runs ascend: no later run reaches key >= 0
       ++iv;
+      const int over = NW == 1 ? 0 : (pos - ke) >> 5;   // steps of the other waves before this wave's next one
       ks = max(q0 - r.y + 1, 0);
       ke = min(q0 - r.x + 1, c.N);
-      pos = ks;
+      pos = ks + 32 * over;
     }
   };
   int s = 0;
@@ -1885,7 +1892,7 @@ __device__ inline void vs_pass(const VsCtx &c, WaveState &st, const LaneOfs &lo,
   // ---- phase B: verticals ----------------------------------------------------
   const int qlast = q0 + BQ - 1;
   int *cols = c.cols;
-  int vpos = 0;                       // next entry of vlist to examine
+  int vpos = 64 * wave;               // next entry of vlist to examine
   while (vpos < c.n_v) {
     // compact up to VCAP columns into cols[]
     int ncol = 0;
@@ -1901,7 +1908,7 @@ __device__ inline void vs_pass(const VsCtx &c, WaveState &st, const LaneOfs &lo,
       const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
       if (ok) cols[ncol + before] = v;
       ncol += __builtin_popcountll(bal);
-      vpos += 64;
+      vpos += 64 * NW;
       // the list ascends: once a whole chunk is past the block nothing follows
       if (__shfl(v, 0) > qlast) { vpos = c.n_v; break; }
     }
@@ -2082,14 +2089,18 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
 
   vs_pass_pipelined<ROWS256, NW>(c, st, lo, mp, wave, lane);
   if (NW > 1) {
-    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane) || wave > 0) return;
+    if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
   if (NW > 1 || needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
-    vs_pass<PASS_MAX>(c, st, lo, mp, lane);
+    vs_pass<PASS_MAX, NW>(c, st, lo, mp, wave, lane);
     finish_max_pass(st, x.c_log2);
-    vs_pass<PASS_FIX>(c, st, lo, mp, lane);
+    vs_pass<PASS_FIX, NW>(c, st, lo, mp, wave, lane);
+  }
+  if (NW > 1) {
+    split_finish<NW, true>(st, oh, x.o_st, q0, lds, wave, lane);
+    return;
   }
   wave_finish(st, oh, x.o_st, q0, lds, lane);
 }
@@ -2299,9 +2310,9 @@ __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const
   if (needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
-    vs_pass<PASS_MAX>(c, st, lo, mp, lane);
+    vs_pass<PASS_MAX, 1>(c, st, lo, mp, 0, lane);
     finish_max_pass(st, x.c_log2);
-    vs_pass<PASS_FIX>(c, st, lo, mp, lane);
+    vs_pass<PASS_FIX, 1>(c, st, lo, mp, 0, lane);
   }
   wave_finish(st, oh, x.o_st, q0, ring, lane);
 }
@@ -2715,9 +2726,9 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   if (needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
-    vs_pass<PASS_MAX>(c, st, lo, mp, lane);
+    vs_pass<PASS_MAX, 1>(c, st, lo, mp, 0, lane);
     finish_max_pass(st, x.c_log2);
-    vs_pass<PASS_FIX>(c, st, lo, mp, lane);
+    vs_pass<PASS_FIX, 1>(c, st, lo, mp, 0, lane);
   }
   wave_finish(st, oh, x.o_st, q0, ring, lane);
 }
