@@ -2293,28 +2293,48 @@ __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const
       if (__builtin_amdgcn_readlane(mine.x, 63) > Q0) break;      // runs ascend
     }
   }
-  if (!active) return;       // no workgroup barrier below this line
-  // ---- the rest of the runs, and the verticals, per wave
-  for (int r0 = 0; r0 < c.n_c; r0 += 64) {
-    const int n = min(c.n_c - r0, 64);
-    int2 mine = make_int2(KEY_NONE, KEY_NONE);
-    if (lane < n) mine = c.runs[r0 + lane];
-    const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
-    if (usable == 0) break;
-    VsEdgeGen gen{mine, usable, q0, Q0, c.N, 0, 0, 0, 0, 0};
-    WavePipe3<VsEdgeGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
-    pipe.run();
-    if (usable < n) break;
+  // ---- the rest of the runs, and the verticals, per wave (no workgroup barrier in here)
+  bool redo = false;
+  if (active) {
+    for (int r0 = 0; r0 < c.n_c; r0 += 64) {
+      const int n = min(c.n_c - r0, 64);
+      int2 mine = make_int2(KEY_NONE, KEY_NONE);
+      if (lane < n) mine = c.runs[r0 + lane];
+      const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
+      if (usable == 0) break;
+      VsEdgeGen gen{mine, usable, q0, Q0, c.N, 0, 0, 0, 0, 0};
+      WavePipe3<VsEdgeGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
+      pipe.run();
+      if (usable < n) break;
+    }
+    vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
+    redo = needs_exact(st);
+    if (!redo) wave_finish(st, oh, x.o_st, q0, ring, lane);
   }
-  vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
-  if (needs_exact(st)) {
-    load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
+  // ---- blocks that must be redone exactly: the four waves share the steps of one after the other,
+  // and merge like the waves of vs_split_kernel.  (The workgroup keeps its CU's whole LDS until the
+  // last wave ends, so a wave that redid its block alone held the CU for itself.  26 heads of the mixed
+  // recipe, which has 0.1 to 1 % of such blocks: 32K tokens with their 6 Block-Sparse heads 7.25 ->
+  // 6.08 ms, 8K 1180 -> 905 us, 4K 397 -> 257.)
+  constexpr int FLAG_OFS = RING_BYTES - 16;      // behind what wave_finish uses of the ring
+  if (lane == 0) *reinterpret_cast<int *>(ring + FLAG_OFS) = redo;
+  __syncthreads();
+  unsigned todo = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) todo |= *reinterpret_cast<const int *>(lds + w * RING_BYTES + FLAG_OFS) ? 1u << w : 0u;
+  todo = __builtin_amdgcn_readfirstlane(todo);
+  while (todo) {
+    __syncthreads();       // every wave has read the flags, or what the last round left in the rings
+    const int w = __builtin_ctz(todo);
+    todo &= todo - 1u;
+    c.q0 = mp.q0 = Q0 + w * BQ;
+    load_q(st, qh, x.q_st, c.q0, lane);
     reset_for_max_pass(st);
-    vs_pass<PASS_MAX, 1>(c, st, lo, mp, 0, lane);
+    vs_pass<PASS_MAX, 4>(c, st, lo, mp, wave, lane);
     finish_max_pass(st, x.c_log2);
-    vs_pass<PASS_FIX, 1>(c, st, lo, mp, 0, lane);
+    vs_pass<PASS_FIX, 4>(c, st, lo, mp, wave, lane);
+    split_finish<4, true>(st, oh, x.o_st, c.q0, lds, wave, lane);
   }
-  wave_finish(st, oh, x.o_st, q0, ring, lane);
 }
 
 // One pass of the exact scheme over this wave's share of the steps.
