@@ -1044,6 +1044,46 @@ struct StepBuf {
 
 constexpr int RING_BYTES = 5 * HALF_BYTES;
 
+// One reference for the NW waves that share a query block: the row maxima of the first steps of all of
+// them (raw logits; -inf where a wave has no key for the row).  Every wave comes here exactly once, at
+// its first step or, without one, at its end.  With a reference of its own every wave of a block was
+// one more chance for logits that outgrow it.  Mixed recipe, blocks that fall back: Vertical-Slash of 1K
+// tokens 2.4 % with references of their own, none with a shared one (one wave per block: none),
+// Block-Sparse of 2K 3.1 %, none (none), Vertical-Slash of 8K 1.3 %, 0.2 % (0.9 %).  8 heads of 2K
+// tokens 99 -> 47 us; without such blocks the exchange costs 0.5 us (4 heads of 4K, 70.0 -> 70.7).
+template <int NW>
+__device__ inline void share_reference(WaveState &st, float mx0, float mx1, float c_log2, char *lds, int wave,
+                                       int lane) {
+  constexpr int OFS = RING_BYTES - 512;      // the end of V slot 2: no load goes there before the second barrier
+  const int n = lane & 31;
+  float *mine = reinterpret_cast<float *>(lds + wave * RING_BYTES + OFS);
+  if (lane < 32) { mine[n] = mx0; mine[32 + n] = mx1; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float *x = reinterpret_cast<const float *>(lds + w * RING_BYTES + OFS);
+    mx0 = fmaxf(mx0, x[n]);
+    mx1 = fmaxf(mx1, x[32 + n]);
+  }
+  __syncthreads();
+  set_reference(st, 0, mx0 == -INFINITY ? 0.f : mx0 * c_log2);
+  set_reference(st, 1, mx1 == -INFINITY ? 0.f : mx1 * c_log2);
+}
+// ... from the masked logits of a wave's first step
+template <int NW>
+__device__ inline void share_reference(WaveState &st, const f32x16 (&s)[1][2], float c_log2, char *lds, int wave,
+                                       int lane) {
+  float mx[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    mx[nb] = s[0][nb][0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx[nb] = fmaxf(mx[nb], s[0][nb][r]);
+    mx[nb] = fmaxf(mx[nb], __shfl_xor(mx[nb], 32));
+  }
+  share_reference<NW>(st, mx[0], mx[1], c_log2, lds, wave, lane);
+}
+
 // End of the optimistic pass when NW waves of a workgroup have each taken a share of ONE query
 // block's steps: every wave has its own reference m, row sums l and sums O; the row is
 //   O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w,   M = max_w (m_w + log2 l_w)
@@ -1235,7 +1275,7 @@ __device__ inline void dma_pair_gather(const char *head, unsigned rb, const Gath
 // generator advances between MFMAs.  When the generator runs dry the loads
 // repeat an earlier step into the free buffer and the MFMAs form logits nobody
 // consumes, so that the body stays one straight path.
-template <class Gen, bool GATHER, bool ROWS256>
+template <class Gen, bool GATHER, bool ROWS256, int NW = 1>
 struct WavePipe {
   Gen &gen;
   WaveState &st;
@@ -1250,6 +1290,8 @@ struct WavePipe {
   MaskP mp;
   float c_log2;
   int lane;
+  char *wg = nullptr;       // NW > 1: LDS of the workgroup, this wave's number
+  int wave = 0;
   Step d0, d1, d2;          // steps t, t+1, t+2
   bool h0, h1, h2;
   GatherKeys kk, kv;        // GATHER: the rows of steps t+2 (K goes out in this iteration) and t+1 (V)
@@ -1273,7 +1315,13 @@ struct WavePipe {
       else dma_pair<ROWS256, 2 * (R & 3)>(vt, v_rb, dv.voff, v_dst);
     }
   }
-  __device__ inline void fresh(f32x16 (&s)[1][2], const Step &d) {
+  __device__ inline void fresh(f32x16 (&s)[1][2], const Step &d, bool first_of_pass = false) {
+    if (NW > 1 && first_of_pass && !has_ref) {
+      has_ref = true;
+      fresh(s, d);
+      share_reference<NW>(st, s, c_log2, wg, wave, lane);
+      return;
+    }
     if (d.cls == 2 || !has_ref) {
       if (GATHER) {
         special_gather(s, st, d.cols, mp, !has_ref, c_log2, lane);
@@ -1442,7 +1490,7 @@ struct WavePipe {
     MINF_WAIT_VMCNT(0);
     f32x16 sa[1][2], sb[1][2];
     qk_first(sa, buf.k(0));
-    fresh(sa, d0);
+    fresh(sa, d0, true);
     // iteration t: d0 = step t (logits in hand), d1 = step t+1 (K landed), d2 = step t+2
     int t = 0;
     while (h0) {
@@ -1469,7 +1517,7 @@ struct WavePipe {
 // reference), without a next step the MFMAs form logits nobody consumes and
 // the loads repeat an earlier step into the free slots; the first iteration
 // multiplies a zero P(-1) with V(0).
-template <class Gen, bool ROWS256>
+template <class Gen, bool ROWS256, int NW = 1>
 struct WavePipe3 {
   Gen &gen;
   WaveState &st;
@@ -1483,6 +1531,8 @@ struct WavePipe3 {
   MaskP mp;
   float c_log2;
   int lane;
+  char *wg = nullptr;       // NW > 1: LDS of the workgroup, this wave's number
+  int wave = 0;
   Step d0, d1, d2;          // steps t (softmax), t+1 (logits), t+2 (K fetch)
   bool h0, h1, h2, hp;      // ... exist; hp: step t-1 exists (its P awaits the output update)
 
@@ -1490,7 +1540,13 @@ struct WavePipe3 {
     const unsigned kb = (unsigned)__builtin_amdgcn_readfirstlane(d.kbase);
     return head + (uint64_t)kb * rb;
   }
-  __device__ inline void fresh(f32x16 (&s)[1][2], const Step &d) {
+  __device__ inline void fresh(f32x16 (&s)[1][2], const Step &d, bool first_of_pass = false) {
+    if (NW > 1 && first_of_pass && !has_ref) {
+      has_ref = true;
+      fresh(s, d);
+      share_reference<NW>(st, s, c_log2, wg, wave, lane);
+      return;
+    }
     if (d.cls == 2 || !has_ref) {
       MaskP m = mp;
       m.lo = d.lo; m.hi = d.hi;
@@ -1659,7 +1715,7 @@ struct WavePipe3 {
 #pragma unroll
       for (int j = 0; j < 8; ++j) (&pa[0][0])[i][j] = (__bf16)0.f;
     qk_first(sa, buf.k(0));
-    fresh(sa, d0);
+    fresh(sa, d0, true);
     // iteration t: d0 = step t (logits in hand), d1 = step t+1 (K landed), d2 = step t+2;
     // one iteration past the last step finishes its output update
     iter<0, true>(sa, sb, pa, pb);
@@ -1796,12 +1852,13 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
     const int n = min((total - r0 + NW - 1) / NW, 64);
     const int mine = lane < n ? glist[r0 + NW * lane] : -1;
     BsGen gen{mine, n, NB, mp, 0, 0};
-    WavePipe3<BsGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, reinterpret_cast<const char *>(c.kh),
-                                   reinterpret_cast<const char *>(c.vh), (unsigned)x.k_st * 2u,
-                                   (unsigned)x.v_st * 2u, dk, dv, mp, c.c_log2, lane};
+    WavePipe3<BsGen, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, reinterpret_cast<const char *>(c.kh),
+                                       reinterpret_cast<const char *>(c.vh), (unsigned)x.k_st * 2u,
+                                       (unsigned)x.v_st * 2u, dk, dv, mp, c.c_log2, lane, lds, wave};
     pipe.run();
   }
   if (NW > 1) {
+    if (!has_ref) share_reference<NW>(st, -INFINITY, -INFINITY, c.c_log2, lds, wave, lane);
     if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
   if (NW > 1 || needs_exact(st)) {
@@ -1989,7 +2046,7 @@ struct VsColGen {
 template <bool ROWS256, int NW>
 __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QAcc &qa, bool &has_ref,
                                          const LaneOfs &lo, const MaskP &mp, const DmaLane &dk,
-                                         const DmaLane &dv, int wave, int lane) {
+                                         const DmaLane &dv, int wave, int lane, char *wg = nullptr) {
   const int q0 = c.q0;
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
@@ -2018,7 +2075,7 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
     if (lane + ncol < nstep * 32) cols[gather_pos(ncol + lane)] = KEY_NONE;   // pad the last step
     wave_lds_sync();
     VsColGen gen{cols, nstep, q0, 0};
-    WavePipe<VsColGen, true, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, c.N, mp, c.c_log2, lane};
+    WavePipe<VsColGen, true, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, c.N, mp, c.c_log2, lane, wg, wave};
     pipe.run();
     wave_lds_sync();
   }
@@ -2027,7 +2084,7 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
 // Optimistic pass of the Vertical-Slash kernel, software pipelined.
 template <bool ROWS256, int NW>
 __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp,
-                                         int wave, int lane) {
+                                         int wave, int lane, char *wg) {
   const int q0 = c.q0;
   bool has_ref = false;
   QAcc qa;
@@ -2047,12 +2104,13 @@ __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const La
     const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
     if (usable == 0) break;
     VsRunGen<NW> gen{mine, usable, q0, c.N, 0, 0, 0, 32 * over};
-    WavePipe3<VsRunGen<NW>, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
+    WavePipe3<VsRunGen<NW>, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane, wg, wave};
     pipe.run();
     if (usable < n) break;
     if (NW > 1) over = gen.left_over();
   }
-  vs_cols_pipelined<ROWS256, NW>(c, st, qa, has_ref, lo, mp, dk, dv, wave, lane);
+  vs_cols_pipelined<ROWS256, NW>(c, st, qa, has_ref, lo, mp, dk, dv, wave, lane, wg);
+  if (NW > 1 && !has_ref) share_reference<NW>(st, -INFINITY, -INFINITY, c.c_log2, wg, wave, lane);
 }
 
 // One work item = query block b of list slot `slot`: one wave, or NW waves that share its steps.
@@ -2087,7 +2145,7 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   MaskP mp;
   mp.q0 = q0; mp.n_init = KEY_NONE; mp.n_local = 1; mp.lo = 0; mp.hi = 0;
 
-  vs_pass_pipelined<ROWS256, NW>(c, st, lo, mp, wave, lane);
+  vs_pass_pipelined<ROWS256, NW>(c, st, lo, mp, wave, lane, lds);
   if (NW > 1) {
     if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
@@ -2378,10 +2436,11 @@ __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadLis
   dma_lane_init(dv, x.v_st, lane);
   bool has_ref = false;
   AshapeGen<SPLIT> gen(mp, wave);
-  WavePipe3<AshapeGen<SPLIT>, ROWS256> pipe{gen, st, qa, has_ref, lo, buf, reinterpret_cast<const char *>(kh),
-                                            reinterpret_cast<const char *>(vh), (unsigned)x.k_st * 2u,
-                                            (unsigned)x.v_st * 2u, dk, dv, mp, x.c_log2, lane};
+  WavePipe3<AshapeGen<SPLIT>, ROWS256, SPLIT> pipe{gen, st, qa, has_ref, lo, buf, reinterpret_cast<const char *>(kh),
+                                                   reinterpret_cast<const char *>(vh), (unsigned)x.k_st * 2u,
+                                                   (unsigned)x.v_st * 2u, dk, dv, mp, x.c_log2, lane, lds, wave};
   pipe.run();
+  if (!has_ref) share_reference<SPLIT>(st, -INFINITY, -INFINITY, x.c_log2, lds, wave, lane);
   if (split_finish<SPLIT>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   // The four waves share both exact passes too: every share against its own row max, then the same
   // merge.  (One wave alone, whose loads nothing overlaps, was slower than the four blocks of
