@@ -231,10 +231,11 @@ minf_status minf_bs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
  * arguments, checks and results (bit for bit) as minf_vs_attn on vs_heads
  * followed by minf_bs_attn on bs_heads; a head must not be in both lists
  * (MINF_ERR_SHAPE).  The work items of the two patterns are interleaved four
- * to one so that every part of the chip holds both kinds at once.  Measured
- * slower than the two separate calls on the mixed 1M-token layer (the
- * patterns disturb each other's cache reuse); provided as the measured
- * alternative.
+ * to one so that every part of the chip holds both kinds at once.  Sequences
+ * of more than 8192 tokens for which one of the two calls would take a block
+ * with several waves, or several blocks per workgroup, get the launches of the
+ * two calls.  Faster than the two calls up to about 8K tokens; slower from 32K
+ * on (the patterns disturb each other's cache reuse).
  */
 minf_status minf_vs_bs_attn(const minf_qkv *x, const int32_t *vs_heads, int32_t n_vs, const minf_vs_index *vs,
                             const int32_t *bs_heads, int32_t n_bs, const minf_bs_index *bs, void *hip_stream);

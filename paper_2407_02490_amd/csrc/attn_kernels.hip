@@ -2280,14 +2280,12 @@ struct VsEdgeGen {
   }
 };
 
+// One work item = the query blocks 4 sb .. 4 sb + 3 of list slot `slot`, one per wave of the workgroup.
 template <bool ROWS256>
-__global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const int32_t *v_idx, const int32_t *cover,
-                                                       const uint32_t *cover_bits, const int32_t *counts, int nv,
-                                                       int ns, int cover_words, Sched sched) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
+__device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
+                                              const int32_t *cover, const uint32_t *cover_bits, const int32_t *counts,
+                                              int nv, int ns, int cover_words, int slot, int sb, char *lds) {
   const int NB = x.N / BQ;
-  int slot, sb;
-  if (!decode_wg(sched, slot, sb)) return;
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh;
@@ -2395,6 +2393,16 @@ __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const
   }
 }
 
+template <bool ROWS256>
+__global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const int32_t *v_idx, const int32_t *cover,
+                                                       const uint32_t *cover_bits, const int32_t *counts, int nv,
+                                                       int ns, int cover_words, Sched sched) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  int slot, sb;
+  if (!decode_wg(sched, slot, sb)) return;
+  vs_share_item<ROWS256>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, sb, lds);
+}
+
 // One pass of the exact scheme over this wave's share of the steps.
 template <int PASS, int NW>
 __device__ inline void ashape_wave_pass(WaveState &st, const LaneOfs &lo, const StepBuf &buf, const bf16_t *kh,
@@ -2458,9 +2466,8 @@ __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadLis
 // mix the patterns, App. E): the work items of the two kinds are interleaved four to one in
 // launch order, each kind keeping its own XCD-aware mapping (a workgroup id's low three bits are
 // the XCD in both), so that every XCD holds both kinds at any time.  Same results as the two
-// separate launches, bit for bit; measured slower than them (the Block-Sparse items stream other
-// K/V heads through the L2s that the Vertical-Slash items share) and therefore not what
-// minf_vs_attn / minf_bs_attn do: kept as the measured alternative.
+// separate launches, bit for bit.  Faster than them on short rows; slower on long ones, where the
+// Block-Sparse items stream other K/V heads through the L2s that the Vertical-Slash items share.
 struct VsArgs {
   const int32_t *v_idx, *cover;
   const uint32_t *cover_bits;
@@ -2481,6 +2488,33 @@ __global__ __launch_bounds__(64) void vs_bs_kernel(QKV x, HeadList hv, VsArgs va
     vs_item<ROWS256, 1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
   else
     bs_item<ROWS256, 1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+}
+
+// The same for short rows on which a kind takes its blocks with four waves: workgroups of four waves
+// and 160 KiB hold an item of a kind that shares it (four waves per block, or four blocks), or four
+// items of a kind that does not.  Each kind runs the code of its own call.
+enum { TAKE_EACH = 0, TAKE_SPLIT = 1, TAKE_SHARE = 2 };
+template <bool ROWS256>
+__global__ __launch_bounds__(64 * SPLIT) void vs_bs_wide_kernel(QKV x, HeadList hv, VsArgs va, Sched sv, int vs_take,
+                                                                HeadList hb, BsArgs ba, Sched sb, int bs_take) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char *ring = lds + wave * RING_BYTES;
+  int kind, slot, b;
+  // with an item for the whole workgroup all four waves leave here, or none
+  if (!decode_wide(sv, vs_take == TAKE_EACH, sb, bs_take == TAKE_EACH, blockIdx.x, wave, kind, slot, b)) return;
+  slot = __builtin_amdgcn_readfirstlane(slot);
+  b = __builtin_amdgcn_readfirstlane(b);
+  if (kind == 1) {
+    if (bs_take == TAKE_SPLIT) bs_item<ROWS256, SPLIT>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+    else bs_item<ROWS256, 1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, ring);
+  } else if (vs_take == TAKE_SHARE) {
+    vs_share_item<ROWS256>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+  } else if (vs_take == TAKE_SPLIT) {
+    vs_item<ROWS256, SPLIT>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+  } else {
+    vs_item<ROWS256, 1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, ring);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2952,19 +2986,45 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
   return hipGetLastError();
 }
 
+// Longest row on which minf_vs_bs_attn interleaves the kinds also where one of them shares blocks among
+// waves; beyond it such layers take the launches of the two calls.  Short rows end with idle CUs, and
+// one launch ends once: both calls -> one launch, mixed recipe, us: 32 heads of 1K tokens 62 -> 52,
+// 8 of 2K 47 -> 30, 8 of 4K 83 -> 69, 32 of 4K 256 -> 216, of 8K 890 -> 588 (blocks that are redone
+// overlap with the other kind).  On long rows the kinds disturb each other's cache reuse: one wave per
+// block, one launch against two, 16K tokens 2048 against 2058 us, 32K 6352 against 5988.
+constexpr int ONE_LAUNCH_MAX_N = 8192;
+
 hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,
                         const uint32_t *cover_bits, const int32_t *counts, int nv, int ns, int cover_words,
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  if (vs_split_pays(x.n_q, x.N, nv, ns) || bs_split_pays(x.n_q, x.N, topk) || vs_share_pays(x.N, ns)) {
-    // not one wave per block for both kinds: one launch per kind, the kernels the two calls take
+  const int vs_take = vs_split_pays(x.n_q, x.N, nv, ns) ? TAKE_SPLIT : vs_share_pays(x.N, ns) ? TAKE_SHARE : TAKE_EACH;
+  const int bs_take = bs_split_pays(x.n_q, x.N, topk) ? TAKE_SPLIT : TAKE_EACH;
+  const bool wide = vs_take != TAKE_EACH || bs_take != TAKE_EACH;
+  if (wide && x.N > ONE_LAUNCH_MAX_N) {
     const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
     return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);
   }
-  const Sched sv = make_sched(hv, x.group, NB), sb = make_sched(hb, x.group, NB);
+  const Sched sv = make_sched(hv, x.group, vs_take == TAKE_SHARE ? (NB + 3) / 4 : NB), sb = make_sched(hb, x.group, NB);
   const VsArgs va{v_idx, cover, cover_bits, counts, nv, ns, cover_words};
   const BsArgs ba{blk_idx, blk_cnt, order, topk};
+  if (wide) {
+    const size_t lds = SPLIT * RING_BYTES;
+    const bool rows256 = x.k_st == D && x.v_st == D;
+    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_bs_wide_kernel<true>)
+                             : reinterpret_cast<const void *>(vs_bs_wide_kernel<false>);
+    hipError_t e = set_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    const int groups = mixed_groups(wide_per_xcd(sv, vs_take == TAKE_EACH), wide_per_xcd(sb, bs_take == TAKE_EACH));
+    if (rows256)
+      hipLaunchKernelGGL(vs_bs_wide_kernel<true>, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
+                         hb, ba, sb, bs_take);
+    else
+      hipLaunchKernelGGL(vs_bs_wide_kernel<false>, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
+                         hb, ba, sb, bs_take);
+    return hipGetLastError();
+  }
   const size_t lds = 5 * HALF_BYTES;
   const bool rows256 = x.k_st == D && x.v_st == D;
   const void *fn = rows256 ? reinterpret_cast<const void *>(vs_bs_kernel<true>)

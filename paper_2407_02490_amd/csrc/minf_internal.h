@@ -97,15 +97,31 @@ __host__ __device__ inline bool decode_item(const Sched &s, int hw, int &slot, i
 // 40 = 32 positions of the first launch order and 8 of the second, so that the two kinds are interleaved
 // four to one and a position's low three bits stay the XCD of the hardware id.  kind 0: first, 1: second.
 // Returns false if the id holds no item.  groups = max(ceil(8 a.per_xcd / 32), b.per_xcd), grid = 40 groups.
-__host__ __device__ inline int mixed_groups(const Sched &a, const Sched &b) {
-  const int ga = (8 * a.per_xcd + 31) / 32;
-  return ga > b.per_xcd ? ga : b.per_xcd;
+__host__ __device__ inline int mixed_groups(int a_per_xcd, int b_per_xcd) {
+  const int ga = (8 * a_per_xcd + 31) / 32;
+  return ga > b_per_xcd ? ga : b_per_xcd;
 }
-__host__ __device__ inline bool decode_mixed(const Sched &a, const Sched &b, int w, int &kind, int &slot, int &blk) {
+__host__ __device__ inline int mixed_groups(const Sched &a, const Sched &b) { return mixed_groups(a.per_xcd, b.per_xcd); }
+__host__ __device__ inline void mixed_position(int w, int &kind, int &hw) {
   const int g = w / 40, r = w - 40 * g, xcd = r & 7, q = r >> 3;
   kind = q < 4 ? 0 : 1;
+  hw = kind == 0 ? (4 * g + q) * 8 + xcd : g * 8 + xcd;
+}
+__host__ __device__ inline bool decode_mixed(const Sched &a, const Sched &b, int w, int &kind, int &slot, int &blk) {
+  int hw;
+  mixed_position(w, kind, hw);
   const Sched &s = kind == 0 ? a : b;
-  const int hw = kind == 0 ? (4 * g + q) * 8 + xcd : g * 8 + xcd;
+  return hw < 8 * s.per_xcd && decode_item(s, hw, slot, blk);
+}
+// The same with workgroups of four waves: an item of a kind is taken by the four waves together, or
+// (each = true) every wave takes its own, four consecutive positions of the workgroup's XCD.
+__host__ __device__ inline int wide_per_xcd(const Sched &s, bool each) { return each ? (s.per_xcd + 3) / 4 : s.per_xcd; }
+__host__ __device__ inline bool decode_wide(const Sched &a, bool a_each, const Sched &b, bool b_each, int w, int wave,
+                                            int &kind, int &slot, int &blk) {
+  int hw;
+  mixed_position(w, kind, hw);
+  const Sched &s = kind == 0 ? a : b;
+  if (kind == 0 ? a_each : b_each) hw = ((4 * (hw >> 3) + wave) << 3) | (hw & 7);
   return hw < 8 * s.per_xcd && decode_item(s, hw, slot, blk);
 }
 // Returns false if this workgroup has no work item.

@@ -80,8 +80,46 @@ static int check_mixed(const std::vector<int> &ha, const std::vector<int> &hb, i
   return 0;
 }
 
+// Workgroups of four waves (decode_wide): every item of both lists exactly once -- by all four waves where
+// they share it, by one wave where each takes its own -- and no workgroup id beyond the grid needed.
+static int check_wide(const std::vector<int> &ha, const std::vector<int> &hb, int group, int nb_a, int nb_b, bool a_each,
+                      bool b_each) {
+  HeadList la, lb;
+  memset(&la, 0, sizeof(la));
+  memset(&lb, 0, sizeof(lb));
+  la.n = (int)ha.size();
+  lb.n = (int)hb.size();
+  for (int i = 0; i < la.n; ++i) la.h[i] = ha[i];
+  for (int i = 0; i < lb.n; ++i) lb.h[i] = hb[i];
+  const Sched sa = make_sched(la, group, nb_a), sb = make_sched(lb, group, nb_b);
+  std::vector<int> seen_a((size_t)la.n * nb_a, 0), seen_b((size_t)lb.n * nb_b, 0);
+  const int grid = 40 * mixed_groups(wide_per_xcd(sa, a_each), wide_per_xcd(sb, b_each));
+  for (int w = 0; w < grid; ++w)
+    for (int wave = 0; wave < 4; ++wave) {
+      int kind = -1, slot = -1, blk = -1;
+      if (!decode_wide(sa, a_each, sb, b_each, w, wave, kind, slot, blk)) continue;
+      const int n = kind == 0 ? la.n : lb.n, nb = kind == 0 ? nb_a : nb_b;
+      if (kind < 0 || kind > 1 || slot < 0 || slot >= n || blk < 0 || blk >= nb) {
+        printf("FAIL wide out of range: w %d -> kind %d slot %d blk %d\n", w, kind, slot, blk);
+        return 1;
+      }
+      ++(kind == 0 ? seen_a : seen_b)[(size_t)slot * nb + blk];
+    }
+  for (int s : seen_a)
+    if (s != (a_each ? 1 : 4)) { printf("FAIL wide: first list item seen %d times\n", s); return 1; }
+  for (int s : seen_b)
+    if (s != (b_each ? 1 : 4)) { printf("FAIL wide: second list item seen %d times\n", s); return 1; }
+  printf("ok wide heads %d + %d blocks %d %d grid %d\n", la.n, lb.n, nb_a, nb_b, grid);
+  return 0;
+}
+
 int main() {
   int bad = 0;
+  for (int nb : {1, 4, 7, 33, 128})
+    for (int take = 0; take < 3; ++take) {      // (shared, shared), (shared, each), (each, shared); four blocks: nb / 4
+      bad |= check_wide({0, 1, 2, 4, 5, 6}, {3, 7}, 4, nb, nb, take == 2, take == 1);
+      bad |= check_wide({9}, {0, 1, 2, 3, 4, 5, 6, 7, 8}, 4, (nb + 3) / 4, nb, take == 2, take == 1);
+    }
   for (int nb : {1, 7, 64, 513, 16384}) {
     bad |= check_mixed({0, 1, 2, 4, 5, 6}, {3, 7}, 4, nb);
     bad |= check_mixed({9}, {0, 1, 2, 3, 4, 5, 6, 7, 8}, 4, nb);

@@ -108,24 +108,51 @@ def test_shares_of_short_and_many_runs(B, rng, Sl):
         assert_close_rows(o[0, 64 * b:64 * b + 64], want, f"block {b}")
 
 
-def test_one_launch_of_both_kinds_with_many_items(B, rng):
-    """minf_vs_bs_attn interleaves the two kinds when both have many items: the same bits as the two calls."""
-    N, n = 33024, 3          # 516 blocks; short and dense rows take other kernels
-    q, k, v = random_qkv(93, 2 * n, 2, N)
-    vs_heads, bs_heads = list(range(n)), list(range(n, 2 * n))
-    Vl, Sl = sorted(rng.choice(N, 200, replace=False).tolist()), list(range(0, 200)) + [300, 301, 21000]
-    vidx = B.vs_index_from_host([Vl] * n, [Sl] * n, N)
-    idx, cnt = random_bs_index(rng, N // 64, 9)
-    bidx = B.bs_index_from_host(np.stack([idx] * n), np.stack([cnt] * n))
+# (query heads, tokens, verticals, slashes, blocks): how each kind takes its blocks
+ONE_LAUNCH = {
+    "one wave, one wave": (6, 33024, 200, 203, 9),
+    "four waves, four waves": (4, 1024, 100, 300, 9),
+    "four waves, one wave": (4, 4096, 100, 300, 2),
+    "one wave, four waves": (8, 4096, 48, 100, 24),
+    "four blocks, one wave": (17, 4160, 60, 1400, 9),
+    "four blocks, one wave, a launch each": (9, 8256, 60, 4200, 9),
+}
+
+
+@pytest.mark.parametrize("layout", ["head", "token"])
+@pytest.mark.parametrize("take", ONE_LAUNCH)
+def test_one_launch_of_both_kinds(B, rng, take, layout):
+    """minf_vs_bs_attn, for every way the two kinds take their blocks: the same bits as the two calls,
+    and the oracle's values on some blocks."""
+    nq, N, nv, ns, topk = ONE_LAUNCH[take]
+    NB, nb = N // 64, nq // 3
+    q, k, v = random_qkv(93, nq, 1, N)
+    vs_heads, bs_heads = list(range(nq - nb - 1)), list(range(nq - nb, nq))       # one head in neither list
+    Vl = sorted(rng.choice(N, nv, replace=False).tolist())
+    Sl = sorted(set(range(0, ns - 40)) | set(rng.choice(N, 40, replace=False).tolist()))
+    vidx = B.vs_index_from_host([Vl] * len(vs_heads), [Sl] * len(vs_heads), N)
+    idx, cnt = random_bs_index(rng, NB, topk)
+    bidx = B.bs_index_from_host(np.stack([idx] * nb), np.stack([cnt] * nb))
     o1, o2 = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
-    B.minf_vs_attn(q, k, v, o1, vs_heads, vidx)
-    B.minf_bs_attn(q, k, v, o1, bs_heads, bidx)
-    B.minf_vs_bs_attn(q, k, v, o2, vs_heads, vidx, bs_heads, bidx)
+    tq, tk, tv, o1, o2 = (token_major(t) if layout == "token" else t for t in (q, k, v, o1, o2))
+    B.minf_vs_attn(tq, tk, tv, o1, vs_heads, vidx)
+    B.minf_bs_attn(tq, tk, tv, o1, bs_heads, bidx)
+    B.minf_vs_bs_attn(tq, tk, tv, o2, vs_heads, vidx, bs_heads, bidx)
     torch.cuda.synchronize()
-    assert torch.equal(o1, o2)
-    for b in (0, 17, 515):
-        want = O.vs_attention(to_f64(q[2]), to_f64(k[0]), to_f64(v[0]), Vl, Sl, 64 * b, 64 * b + 64, Bm=64)
-        assert_close_rows(o2[2, 64 * b:64 * b + 64], want, f"vs block {b}")
+    assert torch.equal(o1, o2) and bool((o2[nq - nb - 1] == 7.0).all())
+    Kh, Vh = to_f64(k[0]), to_f64(v[0])
+    for b in (0, NB // 2, NB - 1):
+        rows = slice(64 * b, 64 * b + 64)
+        for h in (vs_heads[0], vs_heads[-1]):
+            want = O.vs_attention(to_f64(q[h]), Kh, Vh, Vl, Sl, 64 * b, 64 * b + 64, Bm=64)
+            assert_close_rows(o2[h, rows], want, f"{take} {layout} vs head {h} block {b}")
+        cols = (64 * idx[b, :cnt[b]][:, None] + np.arange(64)).ravel()
+        mask = np.where(cols[None, :] <= 64 * b + np.arange(64)[:, None], 0.0, -np.inf)
+        s = to_f64(q[bs_heads[0], rows]) @ Kh[cols].T / 128 ** 0.5 + mask
+        p = np.exp(s - np.max(s, axis=1, keepdims=True, initial=-1e30))
+        den = p.sum(1, keepdims=True)
+        want = np.divide(p @ Vh[cols], den, out=np.zeros((64, 128)), where=den > 0)
+        assert_close_rows(o2[bs_heads[0], rows], want, f"{take} {layout} bs block {b}")
 
 
 # common part of a run for four blocks = width - 192 keys in whole 64-key tiles, at least 8 of them
