@@ -10,7 +10,7 @@ import torch
 
 from oracle import minference_oracle as O
 from tests.helpers import assert_close_rows, random_qkv, to_f64
-from tests.test_gpu_attention import random_bs_index, run_heads, token_major
+from tests.test_gpu_attention import VS_CASES, random_bs_index, run_heads, token_major
 
 pytestmark = pytest.mark.gpu
 
@@ -94,11 +94,74 @@ def test_bits_of_a_head_do_not_depend_on_the_listed_heads(B, rng, nq, N):
         assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]), name
 
 
+# items of a layer beyond which no kernel splits its blocks (and rows too short for four blocks per workgroup)
+def many_heads(N):
+    return 1025 // (N // 64) + 1
+
+
+@pytest.mark.parametrize("layout", ["head", "token"])
+@pytest.mark.parametrize("N,Vl,Sl", VS_CASES)
+def test_degenerate_masks_with_one_wave_per_block(B, N, Vl, Sl, layout):
+    nq = many_heads(N)
+    q0, k0, v0 = random_qkv(96, nq, 1, N)
+    q, k, v, o = (token_major(t) if layout == "token" else t for t in (q0, k0, v0, torch.full_like(q0, float("nan"))))
+    B.minf_vs_attn(q, k, v, o, [0, nq - 1], B.vs_index_from_host([Vl] * 2, [Sl] * 2, N))
+    torch.cuda.synchronize()
+    for h in (0, nq - 1):
+        want = O.vs_attention(to_f64(q0[h]), to_f64(k0[0]), to_f64(v0[0]), Vl, Sl, Bm=64)
+        assert_close_rows(o[h], want, f"{layout} head {h}")
+
+
+@pytest.mark.parametrize("layout", ["head", "token"])
+@pytest.mark.parametrize("kind", ["normal", "overflow"])
+def test_more_than_one_round_of_columns_with_one_wave_per_block(B, rng, kind, layout):
+    """1500 kept verticals: two rounds of the column list, also in the exact passes."""
+    N = 2048
+    nq = many_heads(N)
+    q0, k0, v0 = random_qkv(97, nq, 1, N)
+    if kind == "overflow":
+        k0[:, 1400:] *= 60.0
+    Vl, Sl = sorted(rng.choice(N, 1500, replace=False).tolist()), [0, 777]
+    q, k, v, o = (token_major(t) if layout == "token" else t for t in (q0, k0, v0, torch.full_like(q0, float("nan"))))
+    B.minf_vs_attn(q, k, v, o, [nq - 1], B.vs_index_from_host([Vl], [Sl], N))
+    torch.cuda.synchronize()
+    want = O.vs_attention(to_f64(q0[nq - 1]), to_f64(k0[0]), to_f64(v0[0]), Vl, Sl, Bm=64)
+    assert_close_rows(o[nq - 1], want, f"{kind} {layout}")
+
+
+@pytest.mark.parametrize("nq", [1, 70])
+@pytest.mark.parametrize("kind", ["normal", "overflow"])
+def test_bad_block_ids(B, rng, nq, kind):
+    """Ids outside [0, NB) anywhere in a list, with four waves per block and with one."""
+    N, topk = 1024, 12
+    NB = N // 64
+    q, k, v = random_qkv(98, nq, 1, N)
+    if kind == "overflow":
+        k[:, 700:] *= 60.0
+    idx = -np.ones((NB, topk), np.int64)
+    clean = -np.ones((NB, topk), np.int64)
+    cnt = np.zeros(NB, np.int64)
+    for b in range(NB):
+        good = np.sort(rng.choice(b + 1, min(topk // 2, b + 1), replace=False))
+        mixed = [int(x) for x in good]
+        for bad in (-1, NB, 99, -5):
+            mixed.insert(int(rng.integers(0, len(mixed) + 1)), bad)
+        idx[b, :len(mixed)] = mixed
+        clean[b, :len(good)], cnt[b] = good, len(good)
+    dev = B.bs_index_from_host(idx[None], np.full((1, NB), topk))
+    o = run_heads(B.minf_bs_attn, q, k, v, [nq - 1], dev)
+    want = O.bs_attention(to_f64(q[nq - 1]), to_f64(k[0]), to_f64(v[0]), clean, cnt)
+    assert_close_rows(o[nq - 1], want, f"bs bad ids {nq} heads {kind}")
+
+
+@pytest.mark.parametrize("kind", ["normal", "overflow"])
 @pytest.mark.parametrize("Sl", [[0], [0, 70], list(range(0, 8000, 70)), [5000] + list(range(6000, 6300))])
-def test_shares_of_short_and_many_runs(B, rng, Sl):
+def test_shares_of_short_and_many_runs(B, rng, Sl, kind):
     """Runs of fewer steps than waves, more than one chunk of 64 runs, blocks without a run key."""
     N = 8192
     q, k, v = random_qkv(92, 1, 1, N)
+    if kind == "overflow":
+        k[:, 4000:] *= 60.0
     Vl = sorted(rng.choice(N, 700, replace=False).tolist())
     dev = B.vs_index_from_host([Vl], [Sl], N)
     o = run_heads(B.minf_vs_attn, q, k, v, [0], dev)
