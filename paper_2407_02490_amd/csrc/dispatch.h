@@ -47,7 +47,7 @@ inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
   const int64_t r = split_rounds(n_q, N);
   const int64_t walk = (int64_t)(nv < N ? nv : N) + 4 * (int64_t)(ns < N ? ns : N);
   if (r <= 1) return true;
-  if (r == 2) return walk >= (N >= 1536 ? 1024 : 4096);
+  if (r == 2) return walk >= (N >= 1536 ? 1024 : 1536);
   if (r > SPLIT_MAX_ROUNDS || N < 3072) return false;
   return walk >= (N >= 8192 ? 2048 : r == 3 ? 4096 : 6000);
 }
