@@ -108,7 +108,7 @@ class Layer:
             with t["ashape_attn"]:
                 B.minf_ashape_attn(x.q, x.k, x.v, self.o, self.a_heads, c["n_init"], c["n_local"])
         if self.one_launch and self.vs_heads and self.bs_heads:
-            with t["vs_bs_attn"]:           # both patterns in one launch (measured alternative, --one-launch)
+            with t["vs_bs_attn"]:           # both patterns in one call (--one-launch)
                 B.minf_vs_bs_attn(x.q, x.k, x.v, self.o, self.vs_heads, self.vs_idx, self.bs_heads, self.bs_idx)
             return
         if self.vs_heads:
@@ -457,8 +457,9 @@ def main():
     ap.add_argument("--no-dense", action="store_true", help="skip the dense causal baseline")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle timing")
     ap.add_argument("--one-launch", action="store_true",
-                    help="run the Vertical-Slash and the Block-Sparse heads of the layer in one launch "
-                         "(minf_vs_bs_attn: the measured, slower alternative) instead of two")
+                    help="run the Vertical-Slash and the Block-Sparse heads of the layer in one call "
+                         "(minf_vs_bs_attn) instead of two; one launch up to 8192 tokens and for longer layers "
+                         "that take one wave per block, else the launches of the two calls")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a plain 1 GiB device-to-device copy (known HBM bytes) so that "
                          "rocprofv3 FETCH_SIZE / WRITE_SIZE readings can be scaled")

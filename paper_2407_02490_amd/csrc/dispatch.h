@@ -37,7 +37,8 @@ inline bool bs_split_pays(int n_q, int N, int topk) {
 // neighbours' tiles do not hold).  One wave -> four, us, for (nv, ns):
 //   256 items:  every budget and length, e.g. 4K tokens (30, 64) 33 -> 22, (1000, 6096) 101 -> 39
 //   512 items:  (30, 64) 4K 31 -> 35, 16K 28 -> 36, 8K 44 -> 39; (30, 256) 4K 49 -> 38, 16K 57 -> 53,
-//               1K 34 -> 37; (256, 512) 4K 55 -> 40, 1K 38 -> 39; (1000, 6096) 1K 40 -> 37
+//               1K 34 -> 37; (256, 512) 4K 55 -> 40, 1K 38 -> 39; (1000, 6096) 1K 40 -> 37;
+//               16 heads of 1088 tokens, (1088, 200), 272 items: layer 83 -> 71
 //   768 items:  2K (1000, 6096) 62 -> 63; 4K (256, 512) 60 -> 62, (30, 1024) 90 -> 78; 8K (256, 512) 91 -> 88,
 //               (30, 256) 69 -> 72; 16K (256, 512) 93 -> 96, (500, 1500) 147 -> 114
 //   1024 items: 2K (1000, 6096) 65 -> 75; 4K (256, 512) 63 -> 79, (30, 1024) 82 -> 89, (30, 2048) 110 -> 100;
@@ -68,7 +69,9 @@ inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
 // On very long rows with many runs four neighbours gain without common tiles.  8 heads (1M: 4), ms:
 //   256K  5000: 12.58 -> 12.79, 6096: 15.49 -> 15.47;  384K  4600: 18.28 -> 17.99, 6096: 31.4 -> 28.9
 //   512K  4096: 8.91 -> 9.23, 4600: 21.96 -> 22.33, 5000: 28.3 -> 27.7, 6096: 42.2 -> 37.6
-//   1M    4096: 9.00 -> 9.32, 5000: 47.3 -> 41.9, 6096: 65.7 -> 61.7, 12288: 168.8 -> 134.3
+//   1M    4096: 9.00 -> 9.32, 5000: 47.3 -> 41.9, 6096: 65.7 -> 61.7, 12288: 168.8 -> 134.3; 24 heads of the
+//         mixed recipe, four seeds: 291 -> 260, 231 -> 224, 289 -> 260, 207 -> 211 (69.5 % of the L2 requests
+//         hit instead of 66.2 %, 0.87 TB from the fabric instead of 1.00)
 inline bool vs_share_pays(int N, int ns) {
   if (N < 4096) return false;
   if ((int64_t)(N <= 6144 ? 3 : 2) * ns >= N) return true;

@@ -1536,9 +1536,11 @@ __global__ __launch_bounds__(256) void bs_select_kernel(int NB, int slot0, int t
 // or, where that would leave CUs idle, two of them do and all eight pool the 32 blocks' Q
 // (BSF_FEW_GROUPS).
 constexpr int BSF_WAVES = 8, BSF_SEL_FEW = 2;
-// Workgroups of 128 blocks that leave at least half of the 256 CUs idle.  8 heads of 313 blocks (24
-// workgroups): 109 us; with 32 blocks per workgroup 61 (88 when the two selecting waves pool alone).
-// Full chips gain nothing from the shared pooling: 32 heads of 2048 blocks 620 -> 641 us.
+// Workgroups of 128 blocks that leave at least half of the 256 CUs idle.  Index build, all eight waves
+// selecting -> two, us: 8 heads of 313 blocks (24 workgroups) 125 -> 73 (top-k kernel 109 -> 61; 88 when
+// the two selecting waves pool alone), of 1024 (64) 289 -> 174, of 2048 (128) 470 -> 340; 32 heads of
+// 512 blocks (128) 208 -> 165; 1 head of 16384 (128) 2153 -> 1421.  Full chips gain nothing from the
+// shared pooling: 32 heads of 2048 blocks 620 -> 641 (top-k kernel).
 constexpr int BSF_FEW_GROUPS = 128;
 constexpr int BSF_CAP = 160;                        // candidates a row can hold
 constexpr int BSF_PITCH = 164;                      // entries between rows: a multiple of 4 (16-byte reads)
