@@ -49,6 +49,10 @@
 //    32-key steps through private rings (2 K + 3 V slots, 40 KiB); 4 workgroups
 //    share a CU.  Both loops are unrolled over their rings (4x and 6x), so that
 //    every LDS slot address is an immediate.
+//  * Layers with few query blocks: four waves share a block (the *_split_kernels),
+//    each with a quarter of its steps, one reference for the four and one merge.
+//    Vertical-Slash rows with long slash runs: four blocks per workgroup share the
+//    tiles that all of them attend (vs_share_kernel).  dispatch.h holds the rules.
 #include <stdlib.h>
 #include <string.h>
 #include <type_traits>
@@ -1050,7 +1054,7 @@ constexpr int RING_BYTES = 5 * HALF_BYTES;
 // one more chance for logits that outgrow it.  Mixed recipe, blocks that fall back: Vertical-Slash of 1K
 // tokens 2.4 % with references of their own, none with a shared one (one wave per block: none),
 // Block-Sparse of 2K 3.1 %, none (none), Vertical-Slash of 8K 1.3 %, 0.2 % (0.9 %).  8 heads of 2K
-// tokens 99 -> 47 us; without such blocks the exchange costs 0.5 us (4 heads of 4K, 70.0 -> 70.7).
+// tokens 99 -> 47 us; without such blocks the exchange costs 0.5 to 1.2 us (4 heads of 4K 70.0 -> 70.7, A-shape 22.6 -> 23.8).
 template <int NW>
 __device__ inline void share_reference(WaveState &st, float mx0, float mx1, float c_log2, char *lds, int wave,
                                        int lane) {

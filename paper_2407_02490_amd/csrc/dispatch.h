@@ -11,9 +11,15 @@
 
 namespace minf {
 
-// A split launch holds one workgroup per CU (160 KiB of LDS): the layer's items in rounds of 256.
-inline int64_t split_rounds(int n_q, int N) { return ((int64_t)n_q * (N / 64) + 255) / 256; }
-constexpr int SPLIT_MAX_ROUNDS = 4;          // beyond 1024 items one wave per item fills every SIMD
+// A split launch holds one workgroup per CU (160 KiB of LDS): the layer's items in rounds of 256.  A
+// rest of less than 96 items does not count: these are the shortest ones, taken last (514 items of 16K
+// tokens, top-37: 117 -> 107 us with the index).
+inline int64_t split_rounds(int n_q, int N) {
+  const int64_t r = ((int64_t)n_q * (N / 64) + 160) / 256;
+  return r < 1 ? 1 : r;
+}
+// Beyond 1024 items one wave per item fills every SIMD.
+inline bool split_fits(int n_q, int N) { return (int64_t)n_q * (N / 64) <= 1024; }
 
 // Block-Sparse: four waves per block (bs_split_kernel) or one (bs_kernel).
 // One wave per item ends with its longest list, 1.55 us per listed block.  A round of the split
@@ -29,7 +35,7 @@ constexpr int SPLIT_MAX_ROUNDS = 4;          // beyond 1024 items one wave per i
 inline bool bs_split_pays(int n_q, int N, int topk) {
   const int64_t r = split_rounds(n_q, N), NB = N / 64, L = topk < NB ? topk : NB;
   const int64_t total = L * NB - L * (L - 1) / 2;                     // A NB
-  return r <= SPLIT_MAX_ROUNDS && r * (15 * NB + total) < (3 * L + 8) * NB;
+  return split_fits(n_q, N) && r * (15 * NB + total) < (3 * L + 8) * NB;
 }
 
 // Vertical-Slash: four waves per block (vs_split_kernel).  As above, but the length of a block's walk
@@ -47,19 +53,23 @@ inline bool bs_split_pays(int n_q, int N, int topk) {
 inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
   const int64_t r = split_rounds(n_q, N);
   const int64_t walk = (int64_t)(nv < N ? nv : N) + 4 * (int64_t)(ns < N ? ns : N);
+  if (!split_fits(n_q, N)) return false;
   if (r <= 1) return true;
   if (r == 2) return walk >= (N >= 1536 ? 1024 : 1536);
-  if (r > SPLIT_MAX_ROUNDS || N < 3072) return false;
+  if (N < 3072) return false;
   return walk >= (N >= 8192 ? 2048 : r == 3 ? 4096 : 6000);
 }
 
 // Vertical-Slash: four consecutive blocks per workgroup (vs_share_kernel) or one (vs_kernel), where no
 // block is split.  The four share the common part of slash runs of at least 704 offsets, and long
 // runs are there only where many slashes are kept for the length of the row.  Without them the
-// workgroup only holds its CU until its longest block ends, and rows of up to 3K tokens leave CUs
-// idle besides.  One block -> four, 32 heads unless stated, us by number of slashes:
+// workgroup only holds its CU until its longest block ends, and on the shortest rows whether its
+// rounds come out even decides (32, 40 and 64 heads of 2560 tokens: 98 -> 81, 118 -> 132, 153 -> 154).
+// One block -> four, 32 heads unless stated, us by number of slashes:
 //   2K (64 heads)   512: 91 -> 111, 1500: 105 -> 129, all: 110 -> 133;  1K (128 heads) 512: 71 -> 147
-//   3K (40 heads)   512: 94 -> 111, 1500: 148 -> 154, 3000: 150 -> 151
+//   3K   512: 79 -> 82, 1800: 122 -> 103, all: 126 -> 106;  24 heads 512: 70 -> 79, all: 100 -> 94
+//        40 heads 512: 94 -> 112, 1800: 142 -> 148, all: 148 -> 152;  64 heads 512: 122 -> 134, all: 195 -> 178
+//   3.5K 512: 97 -> 103, 1200: 165 -> 156, 1800: 158 -> 141;  40 heads 1200: 186 -> 190, 1800: 180 -> 179
 //   4K   512: 100 -> 101, 1024: 157 -> 156, 1500: 197 -> 187, 6096: 193 -> 173;  6K  2500: 372 -> 356
 //   8K   200: 380 -> 398, 1500: 406 -> 415, 3072: 464 -> 473, 3500: 564 -> 562, 4096: 601 -> 554, 6096: 593 -> 520
 //   16K  512: 714 -> 727, 2048: 920 -> 946, 4096: 1500 -> 1499, 5000: 1755 -> 1658, 6096: 1888 -> 1707
@@ -73,8 +83,8 @@ inline bool vs_split_pays(int n_q, int N, int nv, int ns) {
 //         mixed recipe, four seeds: 291 -> 260, 231 -> 224, 289 -> 260, 207 -> 211 (69.5 % of the L2 requests
 //         hit instead of 66.2 %, 0.87 TB from the fabric instead of 1.00)
 inline bool vs_share_pays(int N, int ns) {
-  if (N < 4096) return false;
-  if ((int64_t)(N <= 6144 ? 3 : 2) * ns >= N) return true;
+  if (N < 3072) return false;
+  if ((int64_t)(N >= 3584 && N <= 6144 ? 3 : 2) * ns >= N) return true;
   return (int64_t)40 * (ns - 4096) >= N || (N >= 393216 && ns >= 5000);
 }
 
