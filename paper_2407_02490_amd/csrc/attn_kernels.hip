@@ -306,44 +306,26 @@ __device__ inline void qk_tile(f32x16 (&s)[MB][2], const WaveState &st, const La
   }
 }
 
-// Rare path on fresh logits of a contiguous tile: element mask and / or taking
-// the exponent reference from this tile's row max.
+// Takes the exponent reference from the row maxima of a step's masked logits (once per block).
 template <int MB>
-__device__ inline void special_tile(f32x16 (&s)[MB][2], WaveState &st, int kbase, const MaskP &mp,
-                                    bool need_mask, bool first, float c_log2, int lane) {
-  const int n = lane & 31, h = lane >> 5;
-  if (need_mask) {
+__device__ inline void take_reference(const f32x16 (&s)[MB][2], WaveState &st, float c_log2) {
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb) {
+    float mx = s[0][nb][0];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kbase + 32 * mb + 16 * (r >> 3) + 8 * h + (r & 7);
-        const bool okk = key >= mp.lo && key < mp.hi;
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const int qi = mp.q0 + 32 * nb + n;
-          const bool ok = okk && key <= qi && (key < mp.n_init || key + mp.n_local > qi);
-          s[mb][nb][r] = ok ? s[mb][nb][r] : -INFINITY;
-        }
-      }
-  }
-  if (first) {
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      float mx = s[0][nb][0];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[mb][nb][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32)) * c_log2;
-      set_reference(st, nb, mx == -INFINITY ? 0.f : mx);
-    }
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[mb][nb][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32)) * c_log2;
+    set_reference(st, nb, mx == -INFINITY ? 0.f : mx);
   }
 }
 
 // Cheap element mask for steps whose only constraints are a key window and
-// causality (Block-Sparse, Vertical-Slash, dense): attended iff
-// lo <= key < min(hi, query row + 1), one unsigned compare per element.
+// causality (Block-Sparse, Vertical-Slash): attended iff
+// lo <= key < min(hi, query row + 1), one unsigned compare per element.  (As the
+// thresholds below, 4 instructions per element pair instead of 5, with the path out of line, it cost
+// the one-wave loop 1 to 3 % at 32K and 128K tokens.)
 template <int MB>
 __device__ inline void window_mask(f32x16 (&s)[MB][2], int kbase, const MaskP &mp, int lane) {
   const int n = lane & 31, h = lane >> 5;
@@ -359,6 +341,58 @@ __device__ inline void window_mask(f32x16 (&s)[MB][2], int kbase, const MaskP &m
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) s[mb][nb][r] = d < span[nb] ? s[mb][nb][r] : -INFINITY;
     }
+}
+
+// A wave-uniform condition whose parts the compiler must not look into.  The masks change the logits in
+// place; when it splits a rare path into one path per part of its condition, it also gives the logits a
+// second home and copies all of them on the path without masks (64 registers per tile).  With the whole
+// rare path out of line four iterations of the A-shape loop are 2109 instructions, 5284 before.
+__device__ inline bool opaque(bool c) {
+  int v = c;
+  asm volatile("" : "+s"(v));
+  return v != 0;
+}
+
+// Element masks as thresholds.  Register r of s[mb][nb] holds key index c(r) + 8 h of the step,
+// c(r) = 32 mb + 16 (r / 8) + r % 8 <= 55, so a bound on the key is a bound on c(r): one compare of a
+// lane's value with an inline constant and one select per element.  (The masks run on few steps, but
+// at one wave per SIMD every instruction of theirs is time, and in the shared-tile loop the four waves
+// wait at a barrier for the one that masks.  With the three comparisons of the A-shape mask spelt out
+// for every element a tile that masks cost 1.7 us, as much as its matrix work: of 58 us per workgroup at
+// (128, 1024) 23 went into the masks of four diagonals and four window edges.  Us before -> after:
+// 8 heads of 128K tokens at (0, 64) 493 -> 354, (128, 1024) 929 -> 745, (1024, 4096) 2419 -> 2372;
+// 32 heads at (1024, 4096) 9969 -> 9455, 8 heads of 16448 tokens 295 -> 275, dense of 16K 1822 -> 1795.)
+// Four elements of each query half at a time: the scheduler would form all comparisons of a tile first
+// and spill their 64-bit results.
+enum { KEEP_UPTO = 0, KEEP_OUTSIDE = 1 };   // c <= t;  not t <= c < t + span
+// t0, t1 (and spans): of the query halves 0 and 1
+template <int MB, int KEEP>
+__device__ inline void threshold_mask(f32x16 (&s)[MB][2], int t0, int t1, unsigned span0 = 0, unsigned span1 = 0) {
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int c = 32 * mb + 16 * (r >> 3) + (r & 7);
+      const bool k0 = KEEP == KEEP_UPTO ? t0 >= c : (unsigned)(c - t0) >= span0;
+      const bool k1 = KEEP == KEEP_UPTO ? t1 >= c : (unsigned)(c - t1) >= span1;
+      s[mb][0][r] = k0 ? s[mb][0][r] : -INFINITY;
+      s[mb][1][r] = k1 ? s[mb][1][r] : -INFINITY;
+      if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Tiles of the A-shape and dense kernels that are attended in part (classify_step / AshapeCls::of: 2):
+// of a row's keys up to the diagonal, n_init .. row - n_local are cut out.  One form for every such
+// tile: the shared-tile loop holds a copy per phase, and a loop that outgrows the instruction cache is
+// slower on every tile (with a branch of its own for each case dense attention lost 2 %).
+template <int MB>
+__device__ inline void ashape_mask(f32x16 (&s)[MB][2], int kbase, const MaskP &mp, int lane) {
+  const int n = lane & 31, first = kbase + 8 * (lane >> 5), klast = kbase + 32 * MB - 1;
+  if (klast >= mp.n_init && kbase + mp.n_local <= mp.q0 + BQ - 1) {
+    const int len = mp.q0 + n - mp.n_local + 1 - mp.n_init;
+    threshold_mask<MB, KEEP_OUTSIDE>(s, mp.n_init - first, mp.n_init - first, max(len, 0), max(len + 32, 0));
+  }
+  if (klast > mp.q0) threshold_mask<MB, KEEP_UPTO>(s, mp.q0 + n - first, mp.q0 + n - first + 32);
 }
 
 template <int MB>
@@ -663,6 +697,7 @@ __device__ inline void dma_block(const char *tile_w, unsigned rb, unsigned voff,
 // the A-shape mask, with the comparisons' constants taken out of the loop:
 // 0 = nothing to attend, 1 = all attended, 2 = mixed.
 struct AshapeCls {
+  static constexpr bool PARTIAL = true;
   int qlast, n_init, a, b, c, d;
   __device__ inline void init(const MaskP &mp) {
     qlast = mp.q0 + BQ - 1; n_init = mp.n_init;
@@ -679,6 +714,7 @@ struct AshapeCls {
 
 // Tiles that every row of the workgroup attends (the common part of a long slash run).
 struct AllCls {
+  static constexpr bool PARTIAL = false;
   __device__ inline int of(int) const { return 1; }
 };
 
@@ -902,8 +938,9 @@ struct AshapeLoop {
       st.l[1] += lsum1;
     }
     // logits of tile t+1: element mask and / or the exponent reference (rare)
-    if (cls_nxt == 2 || (cls_nxt != 0 && !has_ref)) {
-      special_tile<2>(s_nxt, st, kb_nxt, mp, cls_nxt == 2, !has_ref, c_log2, lane);
+    if (opaque(cls_nxt == 2 || (cls_nxt != 0 && !has_ref))) {
+      if (Cls::PARTIAL) ashape_mask<2>(s_nxt, kb_nxt, mp, lane);     // leaves a tile that is attended whole as it is
+      if (!has_ref) take_reference<2>(s_nxt, st, c_log2);
       has_ref = true;
     }
     cls_cur = cls_nxt;
@@ -938,7 +975,8 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
   // also for a tile this wave does not attend: its (finite) logits are turned into P = 0
   qk_tile_v(sa, qa, lo, c.lds);
   if (lp.cls_cur != 0) {
-    if (lp.cls_cur == 2 || !has_ref) special_tile<2>(sa, st, kb0, mp, lp.cls_cur == 2, !has_ref, c.c_log2, lane);
+    if (Cls::PARTIAL && lp.cls_cur == 2) ashape_mask<2>(sa, kb0, mp, lane);
+    if (!has_ref) take_reference<2>(sa, st, c.c_log2);
     has_ref = true;
   }
   __syncthreads();   // all waves are done with K(0) before iteration 0 overwrites it with K(3)
@@ -1202,10 +1240,7 @@ __device__ inline void special_gather(f32x16 (&s)[1][2], WaveState &st, const in
   for (int r = 0; r < 16; ++r)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) s[0][nb][r] = keys[r] <= mp.q0 + 32 * nb + n ? s[0][nb][r] : -INFINITY;
-  if (first) {
-    MaskP none = mp;
-    special_tile<1>(s, st, 0, none, false, true, c_log2, lane);
-  }
+  if (first) take_reference<1>(s, st, c_log2);
 }
 
 // One 32-key step of a single-wave kernel.  cols == nullptr: keys kbase .. kbase+31
@@ -1333,7 +1368,7 @@ struct WavePipe {
         MaskP m = mp;
         m.lo = d.lo; m.hi = d.hi;
         if (d.cls == 2) window_mask<1>(s, d.kbase, m, lane);
-        if (!has_ref) special_tile<1>(s, st, d.kbase, m, false, true, c_log2, lane);
+        if (!has_ref) take_reference<1>(s, st, c_log2);
       }
     }
     has_ref = true;
@@ -1554,12 +1589,11 @@ struct WavePipe3 {
     if (d.cls == 2 || !has_ref) {
       MaskP m = mp;
       m.lo = d.lo; m.hi = d.hi;
-      if (Gen::SINK_MASK) {
-        special_tile<1>(s, st, d.kbase, m, d.cls == 2, !has_ref, c_log2, lane);
-      } else {
-        if (d.cls == 2) window_mask<1>(s, d.kbase, m, lane);
-        if (!has_ref) special_tile<1>(s, st, d.kbase, m, false, true, c_log2, lane);
+      if (d.cls == 2) {
+        if (Gen::SINK_MASK) ashape_mask<1>(s, d.kbase, m, lane);
+        else window_mask<1>(s, d.kbase, m, lane);
       }
+      if (!has_ref) take_reference<1>(s, st, c_log2);
     }
     has_ref = true;
   }
@@ -2597,7 +2631,7 @@ struct RingPipe3 {
       MaskP m = mp;
       m.lo = d.lo; m.hi = d.hi;
       if (d.mask) window_mask<1>(s, d.kbase, m, lane);
-      if (!has_ref) special_tile<1>(s, st, d.kbase, m, false, true, c_log2, lane);
+      if (!has_ref) take_reference<1>(s, st, c_log2);
     }
     has_ref = has_ref || d.work;
   }

@@ -71,6 +71,22 @@ def test_few_and_many_items(B, rng, kind, layout):
             assert len(heads) == 66 or bool(torch.isnan(o[1].float()).all())
 
 
+@pytest.mark.parametrize("n_init,n_local", [(0, 1), (0, 64), (1, 31), (63, 33), (64, 65), (65, 127), (100, 129),
+                                            (130, 1), (200, 300), (704, 1)])
+def test_window_edges(B, n_init, n_local):
+    """Tiles that hold the end of the sink, the start of the window, the diagonal or several of them,
+    with four blocks per workgroup (52 heads of 11 blocks) and with four waves per block (3 heads)."""
+    N = 704
+    q, k, v = random_qkv(97, 52, 2, N)
+    want = {h: O.ashape_attention(to_f64(q[h]), to_f64(k[h // 26]), to_f64(v[h // 26]), n_init, n_local) for h in (0, 51)}
+    for cq, ck, cv, heads, at in ((q, k, v, [0, 51], (0, 51)), (q[[0, 7, 51]], k[[0, 0, 1]], v[[0, 0, 1]], [0, 2], (0, 2))):
+        o = torch.full_like(cq, float("nan"))
+        B.minf_ashape_attn(cq, ck, cv, o, heads, n_init, n_local)
+        torch.cuda.synchronize()
+        for h, w in zip(at, want.values()):
+            assert_close_rows(o[h], w, f"({n_init}, {n_local}) {len(cq)} heads, head {h}")
+
+
 @pytest.mark.parametrize("nq,N", [(66, 1024), (66, 512), (5, 1024), (40, 4096)])
 def test_bits_of_a_head_do_not_depend_on_the_listed_heads(B, rng, nq, N):
     """A head alone, in a short list and with all heads of the layer: the same bits from every call."""
