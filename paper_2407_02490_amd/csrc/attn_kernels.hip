@@ -649,6 +649,15 @@ __device__ inline void pin_q(QAcc &qa, const WaveState &st) {
     }
 }
 
+// Keeps the output accumulators in accumulator registers here: as known zeros they get other homes,
+// and copies between them, when the first iteration of a pipeline does not touch them.
+__device__ inline void pin_o(WaveState &st) {
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) asm volatile("" : "+a"(st.o[db][nb]));
+}
+
 // K Q^T of one tile into vector registers (start of the pipeline).
 __device__ inline void qk_tile_v(f32x16 (&s)[2][2], const QAcc &qa, const LaneOfs &lo, const char *tK) {
 #pragma unroll
@@ -744,8 +753,8 @@ struct AllCls {
 //    also on tiles outside its own rows' mask (the four waves meet at a barrier
 //    each iteration, so skipping would only idle): such a tile gets P = 0 via an
 //    infinite reference.  The body is one straight path, which keeps the 128
-//    output accumulators in place; the first iteration multiplies a zero P(-1)
-//    with V(0), the last two form logits nobody consumes.
+//    output accumulators in place; the first iteration has no output update,
+//    the last two form logits nobody consumes.
 template <bool ROWS256, class Cls>
 struct AshapeLoop {
   WaveState &st;
@@ -782,26 +791,18 @@ struct AshapeLoop {
     cls_nxt_ = t + 1 < T ? cls.of(kb1) : 0;
   }
 
-  template <int I>
-  __device__ inline void load_k(int kb, unsigned slot_ofs) const {
-    dma_block<ROWS256, I>(d.kw + (size_t)kb * d.k_rb, d.k_rb, d.k_voff[I], lds_addr_of(lds) + slot_ofs + d.lds_w);
-  }
-  template <int I>
-  __device__ inline void load_v(int kb, unsigned slot_ofs) const {
-    dma_block<ROWS256, I>(d.vw + (size_t)kb * d.v_rb, d.v_rb, d.v_voff[I],
-                          lds_addr_of(lds) + 4 * TILE_BYTES + slot_ofs + d.lds_w);
-  }
   // first operands of an iteration (k-step 0 of both key blocks, output update steps 0, 1): read
   // during the last round of the iteration before
   struct Lead {
     bf16x8 k[2], v[2];
   };
-  // for the iteration of phase PH: K(t+1) and V(t-1) (V(0) in the very first one: zero P(-1))
+  // for the iteration of phase PH: K(t+1) and V(t-1)
   template <int PH, bool FIRST>
   __device__ inline void read_lead(Lead &ld) const {
-    const char *tK = lds + k_slot(PH + 1), *tV = lds + v_slot(FIRST ? 0 : PH + 3);
+    const char *tK = lds + k_slot(PH + 1), *tV = lds + v_slot(PH + 3);
     ld.k[0] = lds_read_k(tK, lo.k[0]);
     ld.k[1] = lds_read_k(tK, lo.k[0] + HALF_BYTES);
+    if (FIRST) return;
     ld.v[0] = lds_read_vt(tV, lo.v[0][0], lo.v[0][1]);
     ld.v[1] = lds_read_vt(tV, lo.v[1][0], lo.v[1][1]);
   }
@@ -810,7 +811,7 @@ struct AshapeLoop {
   template <int PH, bool FIRST>
   __device__ inline void iter(int t, f32x16 (&s_cur)[2][2], f32x16 (&s_nxt)[2][2], bf16x8 (&p_prev)[2][2][2],
                               bf16x8 (&p_cur)[2][2][2], Lead &lead) {
-    const char *tK = lds + k_slot(PH + 1), *tV = lds + v_slot(FIRST ? 0 : PH + 3);
+    const char *tK = lds + k_slot(PH + 1), *tV = lds + v_slot(PH + 3);
     auto fetch_v = [&](int i) {            // PV step i = (mb, t, db)
       const int mb = i / 8, tt = (i / 4) & 1, db = i & 3;
       const int base = (32 * mb + 16 * tt) * ROW_BYTES;
@@ -819,8 +820,10 @@ struct AshapeLoop {
     bf16x8 kf[8][2], vf[16];
     kf[0][0] = lead.k[0];
     kf[0][1] = lead.k[1];
-    vf[0] = lead.v[0];
-    vf[1] = lead.v[1];
+    if (!FIRST) {
+      vf[0] = lead.v[0];
+      vf[1] = lead.v[1];
+    }
     // the iteration's scalar operands were prepared during the previous one
     const char *kt = kt_, *vt = vt_;
     const unsigned k_dst = lds_addr_of(lds) + k_slot(PH + 3) + d.lds_w;
@@ -890,7 +893,7 @@ struct AshapeLoop {
       if (r == 0) mfma_qk_first(s_nxt[1][0], kf[0][1], qa.q[0][0]);
       else mfma_qk_acc(s_nxt[1][0], kf[r][1], qa.q[0][r]);
       exp_pair(8 * r + 2);
-      if (r + 1 < 8) {
+      if (!FIRST && r + 1 < 8) {
         vf[(2 * r + 2) & 15] = fetch_v((2 * r + 2) & 15);
         vf[(2 * r + 3) & 15] = fetch_v((2 * r + 3) & 15);
       }
@@ -906,10 +909,10 @@ struct AshapeLoop {
       for (int g = 0; g < 2; ++g) {
         const int i = 2 * r + g;
         const int mb = i / 8, tt = (i / 4) & 1, db = i & 3;
-        st.o[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], p_prev[0][mb][tt], st.o[db][0], 0, 0, 0);
+        if (!FIRST) st.o[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], p_prev[0][mb][tt], st.o[db][0], 0, 0, 0);
         exp_pair(8 * r + 4 + 2 * g);
         __builtin_amdgcn_sched_barrier(0);
-        st.o[db][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], p_prev[1][mb][tt], st.o[db][1], 0, 0, 0);
+        if (!FIRST) st.o[db][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], p_prev[1][mb][tt], st.o[db][1], 0, 0, 0);
         sum_pair(8 * r + 4 + 2 * g);
         if (r == 7 && g == 1) finish_pair(62);
         // the first operands of the next iteration (its tiles were confirmed at this iteration's barrier)
@@ -947,6 +950,25 @@ struct AshapeLoop {
   }
 };
 
+// The first loads of a pass, in the order in which they are needed: K(0), K(1), V(0), K(2).  They go out
+// before the Q rows are awaited, and the pass starts on K(0) alone: with every load of the prologue
+// awaited behind Q, and a zero output update in the first iteration, windows of (0, 64) took 333 us
+// instead of 323 and (128, 1024) 714 instead of 705 (8 heads of 128K tokens); longer ones the same.
+template <bool ROWS256>
+__device__ inline void ashape_first_loads(const AshapeCtx &c, const WaveDma &d) {
+  const unsigned dst = lds_addr_of(c.lds) + d.lds_w;
+  auto tile = [&](const char *w, unsigned rb, const unsigned (&voff)[4], int t, unsigned to) {
+    const char *row0 = w + (size_t)c.tile_base(min(t, c.T - 1)) * rb;
+    dma_block<ROWS256, 0>(row0, rb, voff[0], to); dma_block<ROWS256, 1>(row0, rb, voff[1], to);
+    dma_block<ROWS256, 2>(row0, rb, voff[2], to); dma_block<ROWS256, 3>(row0, rb, voff[3], to);
+  };
+  tile(d.kw, d.k_rb, d.k_voff, 0, dst);
+  tile(d.kw, d.k_rb, d.k_voff, 1, dst + TILE_BYTES);
+  tile(d.vw, d.v_rb, d.v_voff, 0, dst + 4 * TILE_BYTES);
+  tile(d.kw, d.k_rb, d.k_voff, 2, dst + 2 * TILE_BYTES);
+}
+
+// After ashape_first_loads.
 template <bool ROWS256, class Cls>
 __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &d, WaveState &st, const QAcc &qa,
                                              bool &has_ref, const LaneOfs &lo, const MaskP &mp, const Cls &cls,
@@ -958,18 +980,7 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
   lp.ti3 = min(3, last); lp.kb3 = lp.tile_base(lp.ti3);
   f32x16 sa[2][2], sb[2][2];
   bf16x8 pa[2][2][2], pb[2][2][2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) (&pa[0][0][0])[i][j] = (__bf16)0.f;
-  // K(0), K(1), K(2) into K slots 0, 1, 2 and V(0) into V slot 0
-  lp.template load_k<0>(kb0, 0); lp.template load_k<1>(kb0, 0); lp.template load_k<2>(kb0, 0); lp.template load_k<3>(kb0, 0);
-  lp.template load_k<0>(lp.kb1, TILE_BYTES); lp.template load_k<1>(lp.kb1, TILE_BYTES);
-  lp.template load_k<2>(lp.kb1, TILE_BYTES); lp.template load_k<3>(lp.kb1, TILE_BYTES);
-  lp.template load_k<0>(lp.kb2, 2 * TILE_BYTES); lp.template load_k<1>(lp.kb2, 2 * TILE_BYTES);
-  lp.template load_k<2>(lp.kb2, 2 * TILE_BYTES); lp.template load_k<3>(lp.kb2, 2 * TILE_BYTES);
-  lp.template load_v<0>(kb0, 0); lp.template load_v<1>(kb0, 0); lp.template load_v<2>(kb0, 0); lp.template load_v<3>(kb0, 0);
-  MINF_WAIT_VMCNT(0);
+  MINF_WAIT_VMCNT(12);      // K(0)
   __syncthreads();
   lp.cls_cur = lp.cls.of(kb0);
   // also for a tile this wave does not attend: its (finite) logits are turned into P = 0
@@ -979,12 +990,15 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
     if (!has_ref) take_reference<2>(sa, st, c.c_log2);
     has_ref = true;
   }
-  __syncthreads();   // all waves are done with K(0) before iteration 0 overwrites it with K(3)
+  MINF_WAIT_VMCNT(4);       // K(1), V(0); K(2) is awaited at the barrier of iteration 0
+  __syncthreads();          // all waves are done with K(0)
   lp.prepare(0);
   typename AshapeLoop<ROWS256, Cls>::Lead lead;
   lp.template read_lead<0, true>(lead);
-  // iterations t = 0 .. T (the last one finishes the output update of tile T-1); T is the same
-  // for the four waves, which meet at the barrier of every iteration
+  // iterations t = 0 .. T (the last one finishes the output update of tile T-1; an update alone behind
+  // the loop makes the compiler spill); T is the same for the four waves, which meet at the barrier of
+  // every iteration
+  pin_o(st);
   lp.template iter<0, true>(0, sa, sb, pa, pb, lead);
   for (int t = 1; t <= c.T;) {
     lp.template iter<1, false>(t, sb, sa, pb, pa, lead);
@@ -996,7 +1010,7 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
     lp.template iter<0, false>(t, sa, sb, pa, pb, lead);
     ++t;
   }
-  MINF_WAIT_VMCNT(0);   // the repeated loads of the last iterations
+  MINF_WAIT_VMCNT(0);       // the repeated loads of the last iterations
   __syncthreads();
 }
 
@@ -1018,13 +1032,6 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   const bool active = blk < NB;
   const int q0 = (active ? blk : NB - 1) * BQ;   // an idle wave shadows the last block, writes nothing
 
-  WaveState st;
-  wave_init(st, qh, x.q_st, q0, lane);
-  LaneOfs lo;
-  lane_offsets(lo, lane);
-  MaskP mp;
-  mp.q0 = q0; mp.lo = 0; mp.hi = x.N; mp.n_init = n_init; mp.n_local = n_local;
-
   // key ranges of the workgroup, 64-aligned: sink [0, e1) and window [s2, e2)
   const int wq0 = sb * 4 * BQ, wq1 = min(wq0 + 4 * BQ, x.N);
   int e1 = min(((n_init + BK - 1) / BK) * BK, wq1);
@@ -1042,7 +1049,14 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   d.kw = reinterpret_cast<const char *>(c.kh) + (size_t)(16 * wave) * d.k_rb;
   d.vw = reinterpret_cast<const char *>(c.vh) + (size_t)(16 * wave) * d.v_rb;
   d.lds_w = wave * 4096;
+  ashape_first_loads<ROWS256>(c, d);      // before Q: one memory latency for both
 
+  WaveState st;
+  wave_init(st, qh, x.q_st, q0, lane);
+  LaneOfs lo;
+  lane_offsets(lo, lane);
+  MaskP mp;
+  mp.q0 = q0; mp.lo = 0; mp.hi = x.N; mp.n_init = n_init; mp.n_local = n_local;
   QAcc qa;
   pin_q(qa, st);
   bool has_ref = false;
@@ -2382,6 +2396,7 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
         todo &= todo - 1;
         a.T = __builtin_amdgcn_readlane(T, i);
         a.s2 = __builtin_amdgcn_readlane(klo, i);
+        ashape_first_loads<ROWS256>(a, d);
         ashape_pass_pipelined<ROWS256, AllCls>(a, d, st, qa, has_ref, lo, mp, AllCls{}, lane);
       }
       if (__builtin_amdgcn_readlane(mine.x, 63) > Q0) break;      // runs ascend
