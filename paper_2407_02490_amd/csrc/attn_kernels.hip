@@ -588,7 +588,6 @@ __device__ inline void finish_max_pass(WaveState &st, float c_log2) {
 struct AshapeCtx {
   const bf16_t *kh, *vh;
   int64_t k_st, v_st;
-  DmaLane dk, dv;
   int N, T1, T, s2;
   char *lds;
   float c_log2;
@@ -598,10 +597,13 @@ struct AshapeCtx {
 template <int PASS>
 __device__ inline void ashape_pass(const AshapeCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp,
                                    int wave, int lane) {
+  DmaLane dk, dv;
+  dma_lane_init(dk, c.k_st, lane);
+  dma_lane_init(dv, c.v_st, lane);
   auto fetch = [&](int t) {
     char *stg = c.lds + (t & 1) * 2 * TILE_BYTES;
-    dma_rows<4, 64, true>(c.kh, c.k_st, c.dk, c.tile_base(t), nullptr, c.N, stg, wave, lane);
-    dma_rows<4, 64, true>(c.vh, c.v_st, c.dv, c.tile_base(t), nullptr, c.N, stg + TILE_BYTES, wave, lane);
+    dma_rows<4, 64, true>(c.kh, c.k_st, dk, c.tile_base(t), nullptr, c.N, stg, wave, lane);
+    dma_rows<4, 64, true>(c.vh, c.v_st, dv, c.tile_base(t), nullptr, c.N, stg + TILE_BYTES, wave, lane);
   };
   bool has_ref = false;
   fetch(0);
@@ -677,14 +679,27 @@ __device__ inline void qk_tile_v(f32x16 (&s)[2][2], const QAcc &qa, const LaneOf
   asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
 }
 
+// Per-lane offsets of the pipelines' tile loads, for any distance between rows.  The four 1 KiB blocks
+// (four rows each) of 16 rows go out with one base pair and one M0 value: the immediate offset of the
+// load shifts the global and the LDS address alike, so block j has its row distance in the lane offset,
+// less the 1024 j that the immediate adds (rows are at least 256 bytes apart: never negative, and
+// 15 rows of at most 2^25 bytes fit).  (With a base per block, which rows more than 256 bytes apart took
+// before, every load costs four scalar instructions and an M0 write, and the scalars that did not fit
+// were spilled into vector lanes inside the loops, up to 100 of them: two prompts of 40K tokens,
+// token-major, 3755 -> 3648 us; token-major layers drawn at random up to 10 %; 256-byte rows the same.)
+struct DmaRows {
+  unsigned voff[4];
+  __device__ inline void init(unsigned row_bytes, int lane) {
+    const unsigned rl = lane >> 4, cpos = lane & 15;
+#pragma unroll
+    for (unsigned j = 0; j < 4; ++j) voff[j] = (4 * j + rl) * row_bytes + (((cpos ^ (rl << 2)) ^ j) << 4) - 1024 * j;
+  }
+};
+
 // This wave's quarter of the fetch of a 64-row tile that lies wholly inside
 // [0, N): rows 16w .. 16w+15, i.e. the 1 KiB blocks 4w .. 4w+3 of the tile in LDS.
-// ROWS256: rows are 256 bytes apart in global memory as they are in LDS, so the
-// four blocks are 1 KiB apart on both sides and one base pair and one M0 value
-// serve all four loads through the instruction's immediate offset (it shifts the
-// global and the LDS address alike).  Otherwise each block gets its own base.
 struct WaveDma {
-  unsigned k_voff[4], v_voff[4];   // per lane, block 4w + i
+  DmaRows k, v;
   unsigned k_rb, v_rb;             // bytes between rows
   const char *kw, *vw;             // head base + 16 w rows
   unsigned lds_w;                  // 4 w KiB
@@ -696,12 +711,6 @@ __device__ inline void dma16_imm(const char *ubase, unsigned voff, unsigned lds_
   if (I == 2) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:2048" :: "v"(voff), "s"(ubase), "s"(lds_addr) : "memory");
   if (I == 3) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072" :: "v"(voff), "s"(ubase), "s"(lds_addr) : "memory");
 }
-template <bool ROWS256, int I>
-__device__ inline void dma_block(const char *tile_w, unsigned rb, unsigned voff, unsigned lds_tile_w) {
-  if (ROWS256) dma16_imm<I>(tile_w, voff, lds_tile_w);
-  else dma16_imm<0>(tile_w + (size_t)(4 * I) * rb, voff, lds_tile_w + I * 1024);
-}
-
 // Class of the 64-key tile at kb for the wave whose rows are q0 .. q0+63 under
 // the A-shape mask, with the comparisons' constants taken out of the loop:
 // 0 = nothing to attend, 1 = all attended, 2 = mixed.
@@ -755,7 +764,7 @@ struct AllCls {
 //    infinite reference.  The body is one straight path, which keeps the 128
 //    output accumulators in place; the first iteration has no output update,
 //    the last two form logits nobody consumes.
-template <bool ROWS256, class Cls>
+template <class Cls>
 struct AshapeLoop {
   WaveState &st;
   const QAcc &qa;
@@ -888,7 +897,7 @@ struct AshapeLoop {
       if (r == 0) mfma_qk_first(s_nxt[0][1], kf[0][0], qa.q[1][0]);
       else mfma_qk_acc(s_nxt[0][1], kf[r][0], qa.q[1][r]);
       sum_pair(8 * r);
-      if (r >= 4) dma_block<ROWS256, r & 3>(kt, d.k_rb, d.k_voff[r & 3], k_dst);
+      if (r >= 4) dma16_imm<(r & 3)>(kt, d.k.voff[r & 3], k_dst);
       __builtin_amdgcn_sched_barrier(0);
       if (r == 0) mfma_qk_first(s_nxt[1][0], kf[0][1], qa.q[0][0]);
       else mfma_qk_acc(s_nxt[1][0], kf[r][1], qa.q[0][r]);
@@ -901,7 +910,7 @@ struct AshapeLoop {
       if (r == 0) mfma_qk_first(s_nxt[1][1], kf[0][1], qa.q[1][0]);
       else mfma_qk_acc(s_nxt[1][1], kf[r][1], qa.q[1][r]);
       sum_pair(8 * r + 2);
-      if (r >= 4) dma_block<ROWS256, r & 3>(vt, d.v_rb, d.v_voff[r & 3], v_dst);
+      if (r >= 4) dma16_imm<(r & 3)>(vt, d.v.voff[r & 3], v_dst);
       if (r == 5) prepare_next();
       __builtin_amdgcn_sched_barrier(0);
       // groups 4..7: output update steps 2r, 2r + 1 of the previous tile
@@ -954,26 +963,25 @@ struct AshapeLoop {
 // before the Q rows are awaited, and the pass starts on K(0) alone: with every load of the prologue
 // awaited behind Q, and a zero output update in the first iteration, windows of (0, 64) took 333 us
 // instead of 323 and (128, 1024) 714 instead of 705 (8 heads of 128K tokens); longer ones the same.
-template <bool ROWS256>
 __device__ inline void ashape_first_loads(const AshapeCtx &c, const WaveDma &d) {
   const unsigned dst = lds_addr_of(c.lds) + d.lds_w;
-  auto tile = [&](const char *w, unsigned rb, const unsigned (&voff)[4], int t, unsigned to) {
+  auto tile = [&](const char *w, unsigned rb, const DmaRows &rows, int t, unsigned to) {
     const char *row0 = w + (size_t)c.tile_base(min(t, c.T - 1)) * rb;
-    dma_block<ROWS256, 0>(row0, rb, voff[0], to); dma_block<ROWS256, 1>(row0, rb, voff[1], to);
-    dma_block<ROWS256, 2>(row0, rb, voff[2], to); dma_block<ROWS256, 3>(row0, rb, voff[3], to);
+    dma16_imm<0>(row0, rows.voff[0], to); dma16_imm<1>(row0, rows.voff[1], to);
+    dma16_imm<2>(row0, rows.voff[2], to); dma16_imm<3>(row0, rows.voff[3], to);
   };
-  tile(d.kw, d.k_rb, d.k_voff, 0, dst);
-  tile(d.kw, d.k_rb, d.k_voff, 1, dst + TILE_BYTES);
-  tile(d.vw, d.v_rb, d.v_voff, 0, dst + 4 * TILE_BYTES);
-  tile(d.kw, d.k_rb, d.k_voff, 2, dst + 2 * TILE_BYTES);
+  tile(d.kw, d.k_rb, d.k, 0, dst);
+  tile(d.kw, d.k_rb, d.k, 1, dst + TILE_BYTES);
+  tile(d.vw, d.v_rb, d.v, 0, dst + 4 * TILE_BYTES);
+  tile(d.kw, d.k_rb, d.k, 2, dst + 2 * TILE_BYTES);
 }
 
 // After ashape_first_loads.
-template <bool ROWS256, class Cls>
+template <class Cls>
 __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &d, WaveState &st, const QAcc &qa,
                                              bool &has_ref, const LaneOfs &lo, const MaskP &mp, const Cls &cls,
                                              int lane) {
-  AshapeLoop<ROWS256, Cls> lp{st, qa, lo, mp, d, cls, c.c_log2, lane, c.T, c.T1, c.s2, c.lds, 0, 0, 0, 0, 0, has_ref};
+  AshapeLoop<Cls> lp{st, qa, lo, mp, d, cls, c.c_log2, lane, c.T, c.T1, c.s2, c.lds, 0, 0, 0, 0, 0, has_ref};
   const int last = c.T - 1;
   const int kb0 = lp.tile_base(0);
   lp.kb1 = lp.tile_base(min(1, last)); lp.kb2 = lp.tile_base(min(2, last));
@@ -993,7 +1001,7 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
   MINF_WAIT_VMCNT(4);       // K(1), V(0); K(2) is awaited at the barrier of iteration 0
   __syncthreads();          // all waves are done with K(0)
   lp.prepare(0);
-  typename AshapeLoop<ROWS256, Cls>::Lead lead;
+  typename AshapeLoop<Cls>::Lead lead;
   lp.template read_lead<0, true>(lead);
   // iterations t = 0 .. T (the last one finishes the output update of tile T-1; an update alone behind
   // the loop makes the compiler spill); T is the same for the four waves, which meet at the barrier of
@@ -1014,7 +1022,6 @@ __device__ inline void ashape_pass_pipelined(const AshapeCtx &c, const WaveDma &
   __syncthreads();
 }
 
-template <bool ROWS256>
 __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_init, int n_local,
                                                      Sched sched) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -1040,16 +1047,14 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   AshapeCtx c;
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
   c.N = x.N; c.T1 = e1 / BK; c.T = c.T1 + (wq1 - s2) / BK; c.s2 = s2; c.lds = lds; c.c_log2 = x.c_log2;
-  dma_lane_init(c.dk, x.k_st, lane);
-  dma_lane_init(c.dv, x.v_st, lane);
   WaveDma d;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { d.k_voff[i] = c.dk.voff[i]; d.v_voff[i] = c.dv.voff[i]; }
   d.k_rb = (unsigned)x.k_st * 2u; d.v_rb = (unsigned)x.v_st * 2u;
+  d.k.init(d.k_rb, lane);
+  d.v.init(d.v_rb, lane);
   d.kw = reinterpret_cast<const char *>(c.kh) + (size_t)(16 * wave) * d.k_rb;
   d.vw = reinterpret_cast<const char *>(c.vh) + (size_t)(16 * wave) * d.v_rb;
   d.lds_w = wave * 4096;
-  ashape_first_loads<ROWS256>(c, d);      // before Q: one memory latency for both
+  ashape_first_loads(c, d);      // before Q: one memory latency for both
 
   WaveState st;
   wave_init(st, qh, x.q_st, q0, lane);
@@ -1062,7 +1067,7 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   bool has_ref = false;
   AshapeCls cls;
   cls.init(mp);
-  ashape_pass_pipelined<ROWS256, AshapeCls>(c, d, st, qa, has_ref, lo, mp, cls, lane);
+  ashape_pass_pipelined<AshapeCls>(c, d, st, qa, has_ref, lo, mp, cls, lane);
   if (__syncthreads_or(needs_exact(st) ? 1 : 0)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
@@ -1267,25 +1272,19 @@ struct Step {
 
 // Two loads of one round of the single-wave pipeline: blocks B and B + 1 of the
 // eight 1 KiB blocks of a 32-row step, both with the M0 value set here.
-// ROWS256 (rows 256 bytes apart in global memory, as in LDS): blocks 0..3 hang off
-// base and M0 through the immediate offset, blocks 4..7 off base + 4096.
-template <bool ROWS256, int B>
-__device__ inline void dma_pair(const char *step_row0, unsigned rb, const unsigned (&voff)[4], unsigned lds_step) {
-  if (ROWS256) {
-    const char *base = step_row0 + (B >= 4 ? 4096 : 0);
-    const unsigned m = lds_step + (B >= 4 ? 4096 : 0);
-    if ((B & 3) == 0)
-      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
-                   "global_load_lds_dwordx4 %1, %2 offset:1024"
-                   :: "v"(voff[0]), "v"(voff[1]), "s"(base), "s"(m) : "memory");
-    else
-      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\t"
-                   "global_load_lds_dwordx4 %1, %2 offset:3072"
-                   :: "v"(voff[2]), "v"(voff[3]), "s"(base), "s"(m) : "memory");
-  } else {
-    dma16_imm<0>(step_row0 + (size_t)(4 * B) * rb, voff[B & 3], lds_step + B * 1024);
-    dma16_imm<0>(step_row0 + (size_t)(4 * B + 4) * rb, voff[(B + 1) & 3], lds_step + (B + 1) * 1024);
-  }
+// Blocks 0..3 hang off the step's first row, blocks 4..7 off its row 16.
+template <int B>
+__device__ inline void dma_pair(const char *step_row0, unsigned rb, const DmaRows &rows, unsigned lds_step) {
+  const char *base = B >= 4 ? step_row0 + (size_t)16 * rb : step_row0;
+  const unsigned m = lds_step + (B >= 4 ? 4096 : 0);
+  if ((B & 3) == 0)
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:1024"
+                 :: "v"(rows.voff[0]), "v"(rows.voff[1]), "s"(base), "s"(m) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:3072"
+                 :: "v"(rows.voff[2]), "v"(rows.voff[3]), "s"(base), "s"(m) : "memory");
 }
 // Gathered rows: lane L of block blk fetches chunk c of row (column id) 4 blk + L / 16 of the step;
 // the byte offset key * rb + 16 c fits 32 bits (checked on the host: N rb < 2^32), key < 2^24.  The
@@ -1303,13 +1302,13 @@ __device__ inline void gather_keys(GatherKeys &g, const int *cols, int lane, uns
 #pragma unroll
   for (int i = 0; i < 8; ++i) g.key[i] = min((unsigned)v[i], last_row);
 }
-template <bool ROWS256, int B>
+template <int B>
 __device__ inline void dma_pair_gather(const char *head, unsigned rb, const GatherKeys &g, unsigned lds_step, int lane) {
   const unsigned rl = lane >> 4, cpos = lane & 15;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const unsigned c16 = ((cpos ^ (rl << 2)) ^ (unsigned)((B + j) & 3)) << 4;      // cpos ^ swz_f(4 blk + rl)
-    const unsigned ofs = (ROWS256 ? g.key[B + j] << 8 : __umul24(g.key[B + j], rb)) + c16;
+    const unsigned ofs = __umul24(g.key[B + j], rb) + c16;
     dma16_su(head, ofs, lds_step + (B + j) * 1024);
   }
 }
@@ -1328,7 +1327,7 @@ __device__ inline void dma_pair_gather(const char *head, unsigned rb, const Gath
 // generator advances between MFMAs.  When the generator runs dry the loads
 // repeat an earlier step into the free buffer and the MFMAs form logits nobody
 // consumes, so that the body stays one straight path.
-template <class Gen, bool GATHER, bool ROWS256, int NW = 1>
+template <class Gen, bool GATHER, int NW = 1>
 struct WavePipe {
   Gen &gen;
   WaveState &st;
@@ -1338,7 +1337,7 @@ struct WavePipe {
   StepBuf buf;
   const char *kh, *vh;       // head bases (bytes)
   unsigned k_rb, v_rb;
-  const DmaLane &dk, &dv;
+  const DmaRows &dk, &dv;
   int N;
   MaskP mp;
   float c_log2;
@@ -1361,11 +1360,11 @@ struct WavePipe {
     // before its round 2
     constexpr bool k_now = R < 4;
     if (GATHER) {
-      if (k_now) dma_pair_gather<ROWS256, 2 * (R & 3)>(kh, k_rb, kk, k_dst, lane);
-      else dma_pair_gather<ROWS256, 2 * (R & 3)>(vh, v_rb, kv, v_dst, lane);
+      if (k_now) dma_pair_gather<2 * (R & 3)>(kh, k_rb, kk, k_dst, lane);
+      else dma_pair_gather<2 * (R & 3)>(vh, v_rb, kv, v_dst, lane);
     } else {
-      if (k_now) dma_pair<ROWS256, 2 * (R & 3)>(kt, k_rb, dk.voff, k_dst);
-      else dma_pair<ROWS256, 2 * (R & 3)>(vt, v_rb, dv.voff, v_dst);
+      if (k_now) dma_pair<2 * (R & 3)>(kt, k_rb, dk, k_dst);
+      else dma_pair<2 * (R & 3)>(vt, v_rb, dv, v_dst);
     }
   }
   __device__ inline void fresh(f32x16 (&s)[1][2], const Step &d, bool first_of_pass = false) {
@@ -1516,13 +1515,13 @@ struct WavePipe {
     if (GATHER) {
       GatherKeys g;
       gather_keys(g, d.cols, lane, (unsigned)N - 1u);
-      dma_pair_gather<ROWS256, 0>(head, rb, g, dst, lane); dma_pair_gather<ROWS256, 2>(head, rb, g, dst, lane);
-      dma_pair_gather<ROWS256, 4>(head, rb, g, dst, lane); dma_pair_gather<ROWS256, 6>(head, rb, g, dst, lane);
+      dma_pair_gather<0>(head, rb, g, dst, lane); dma_pair_gather<2>(head, rb, g, dst, lane);
+      dma_pair_gather<4>(head, rb, g, dst, lane); dma_pair_gather<6>(head, rb, g, dst, lane);
     } else {
       const char *a = row0(head, rb, d);
-      const unsigned (&vo)[4] = IS_K ? dk.voff : dv.voff;
-      dma_pair<ROWS256, 0>(a, rb, vo, dst); dma_pair<ROWS256, 2>(a, rb, vo, dst);
-      dma_pair<ROWS256, 4>(a, rb, vo, dst); dma_pair<ROWS256, 6>(a, rb, vo, dst);
+      const DmaRows &vo = IS_K ? dk : dv;
+      dma_pair<0>(a, rb, vo, dst); dma_pair<2>(a, rb, vo, dst);
+      dma_pair<4>(a, rb, vo, dst); dma_pair<6>(a, rb, vo, dst);
     }
   }
   __device__ inline void run() {
@@ -1570,7 +1569,7 @@ struct WavePipe {
 // reference), without a next step the MFMAs form logits nobody consumes and
 // the loads repeat an earlier step into the free slots; the first iteration
 // multiplies a zero P(-1) with V(0).
-template <class Gen, bool ROWS256, int NW = 1>
+template <class Gen, int NW = 1>
 struct WavePipe3 {
   Gen &gen;
   WaveState &st;
@@ -1580,7 +1579,7 @@ struct WavePipe3 {
   StepBuf buf;
   const char *kh, *vh;       // head bases (bytes)
   unsigned k_rb, v_rb;
-  const DmaLane &dk, &dv;
+  const DmaRows &dk, &dv;
   MaskP mp;
   float c_log2;
   int lane;
@@ -1629,9 +1628,9 @@ struct WavePipe3 {
   __device__ inline void fetch_whole(const Step &d, unsigned dst) const {
     const char *a = row0(IS_K ? kh : vh, IS_K ? k_rb : v_rb, d);
     const unsigned rb = IS_K ? k_rb : v_rb;
-    const unsigned (&vo)[4] = IS_K ? dk.voff : dv.voff;
-    dma_pair<ROWS256, 0>(a, rb, vo, dst); dma_pair<ROWS256, 2>(a, rb, vo, dst);
-    dma_pair<ROWS256, 4>(a, rb, vo, dst); dma_pair<ROWS256, 6>(a, rb, vo, dst);
+    const DmaRows &vo = IS_K ? dk : dv;
+    dma_pair<0>(a, rb, vo, dst); dma_pair<2>(a, rb, vo, dst);
+    dma_pair<4>(a, rb, vo, dst); dma_pair<6>(a, rb, vo, dst);
   }
 
   // Iteration t with PH = t mod 6: K of step s lives in K slot s mod 2, V of step s in V slot
@@ -1703,8 +1702,8 @@ struct WavePipe3 {
       if (r == 0) mfma_qk_first(s_nxt[0][1], kf[0], qa.q[1][0]);
       else mfma_qk_acc(s_nxt[0][1], kf[r], qa.q[1][r]);
       sum_pair(2 * r);
-      if (r < 4) dma_pair<ROWS256, 2 * (r & 3)>(kt, k_rb, dk.voff, k_dst);
-      else dma_pair<ROWS256, 2 * (r & 3)>(vt, v_rb, dv.voff, v_dst);
+      if (r < 4) dma_pair<2 * (r & 3)>(kt, k_rb, dk, k_dst);
+      else dma_pair<2 * (r & 3)>(vt, v_rb, dv, v_dst);
       __builtin_amdgcn_sched_barrier(0);
       // group 2: output update step r, query block 0; exponentials of pair 2r + 1
       {
@@ -1862,7 +1861,7 @@ struct BsGen {
 
 // One work item = query block b (a position in the processing order, if there is one) of list slot `slot`:
 // one wave, or NW waves of which wave w takes the list entries w, w + NW, ...
-template <bool ROWS256, int NW>
+template <int NW>
 __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const int32_t *blk_idx,
                                         const int32_t *blk_cnt, const int32_t *order, int topk, int slot, int b,
                                         char *lds) {
@@ -1895,16 +1894,16 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
 
   QAcc qa;
   pin_q(qa, st);
-  DmaLane dk, dv;
-  dma_lane_init(dk, x.k_st, lane);
-  dma_lane_init(dv, x.v_st, lane);
+  DmaRows dk, dv;
+  dk.init((unsigned)x.k_st * 2u, lane);
+  dv.init((unsigned)x.v_st * 2u, lane);
   const int total = c.cnt;
   bool has_ref = false;
   for (int r0 = wave; r0 < total; r0 += 64 * NW) {
     const int n = min((total - r0 + NW - 1) / NW, 64);
     const int mine = lane < n ? glist[r0 + NW * lane] : -1;
     BsGen gen{mine, n, NB, mp, 0, 0};
-    WavePipe3<BsGen, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, reinterpret_cast<const char *>(c.kh),
+    WavePipe3<BsGen, NW> pipe{gen, st, qa, has_ref, lo, c.buf, reinterpret_cast<const char *>(c.kh),
                                        reinterpret_cast<const char *>(c.vh), (unsigned)x.k_st * 2u,
                                        (unsigned)x.v_st * 2u, dk, dv, mp, c.c_log2, lane, lds, wave};
     pipe.run();
@@ -1927,14 +1926,13 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
   wave_finish(st, oh, x.o_st, q0, lds, lane);
 }
 
-template <bool ROWS256>
 __global__ __launch_bounds__(64) void bs_kernel(QKV x, HeadList hl, const int32_t *blk_idx,
                                                 const int32_t *blk_cnt, const int32_t *order, int topk,
                                                 Sched sched) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  bs_item<ROWS256, 1>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+  bs_item<1>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -2095,10 +2093,10 @@ struct VsColGen {
 // every run, compacted into this wave's column list and gathered 32 per step through this wave's
 // own ring.  No workgroup barrier: every wave has its own list length.
 // NW waves share the list: wave w takes the chunks w, w + NW, ... of 64 entries.
-template <bool ROWS256, int NW>
+template <int NW>
 __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QAcc &qa, bool &has_ref,
-                                         const LaneOfs &lo, const MaskP &mp, const DmaLane &dk,
-                                         const DmaLane &dv, int wave, int lane, char *wg = nullptr) {
+                                         const LaneOfs &lo, const MaskP &mp, const DmaRows &dk,
+                                         const DmaRows &dv, int wave, int lane, char *wg = nullptr) {
   const int q0 = c.q0;
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
@@ -2127,23 +2125,23 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
     if (lane + ncol < nstep * 32) cols[gather_pos(ncol + lane)] = KEY_NONE;   // pad the last step
     wave_lds_sync();
     VsColGen gen{cols, nstep, q0, 0};
-    WavePipe<VsColGen, true, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, c.N, mp, c.c_log2, lane, wg, wave};
+    WavePipe<VsColGen, true, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, c.N, mp, c.c_log2, lane, wg, wave};
     pipe.run();
     wave_lds_sync();
   }
 }
 
 // Optimistic pass of the Vertical-Slash kernel, software pipelined.
-template <bool ROWS256, int NW>
+template <int NW>
 __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const LaneOfs &lo, const MaskP &mp,
                                          int wave, int lane, char *wg) {
   const int q0 = c.q0;
   bool has_ref = false;
   QAcc qa;
   pin_q(qa, st);
-  DmaLane dk, dv;
-  dma_lane_init(dk, c.k_st, lane);
-  dma_lane_init(dv, c.v_st, lane);
+  DmaRows dk, dv;
+  dk.init((unsigned)c.k_st * 2u, lane);
+  dv.init((unsigned)c.v_st * 2u, lane);
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
   // ---- phase A: slash runs, 64 at a time, one per lane (the run list takes no LDS)
@@ -2156,17 +2154,17 @@ __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const La
     const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
     if (usable == 0) break;
     VsRunGen<NW> gen{mine, usable, q0, c.N, 0, 0, 0, 32 * over};
-    WavePipe3<VsRunGen<NW>, ROWS256, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane, wg, wave};
+    WavePipe3<VsRunGen<NW>, NW> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane, wg, wave};
     pipe.run();
     if (usable < n) break;
     if (NW > 1) over = gen.left_over();
   }
-  vs_cols_pipelined<ROWS256, NW>(c, st, qa, has_ref, lo, mp, dk, dv, wave, lane, wg);
+  vs_cols_pipelined<NW>(c, st, qa, has_ref, lo, mp, dk, dv, wave, lane, wg);
   if (NW > 1 && !has_ref) share_reference<NW>(st, -INFINITY, -INFINITY, c.c_log2, wg, wave, lane);
 }
 
 // One work item = query block b of list slot `slot`: one wave, or NW waves that share its steps.
-template <bool ROWS256, int NW>
+template <int NW>
 __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
                                         const int32_t *cover, const uint32_t *cover_bits,
                                         const int32_t *counts, int nv, int ns, int cover_words, int slot, int b,
@@ -2197,7 +2195,7 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   MaskP mp;
   mp.q0 = q0; mp.n_init = KEY_NONE; mp.n_local = 1; mp.lo = 0; mp.hi = 0;
 
-  vs_pass_pipelined<ROWS256, NW>(c, st, lo, mp, wave, lane, lds);
+  vs_pass_pipelined<NW>(c, st, lo, mp, wave, lane, lds);
   if (NW > 1) {
     if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
@@ -2215,7 +2213,6 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   wave_finish(st, oh, x.o_st, q0, lds, lane);
 }
 
-template <bool ROWS256>
 __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_t *v_idx,
                                                 const int32_t *cover, const uint32_t *cover_bits,
                                                 const int32_t *counts, int nv, int ns, int cover_words,
@@ -2223,7 +2220,7 @@ __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  vs_item<ROWS256, 1>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+  vs_item<1>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
 }
 
 // Few work items: four waves per query block, each with a quarter of its steps (and its own ring;
@@ -2231,7 +2228,6 @@ __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_
 // took 100 us as one wave and take 37 us as four (bound by the CU's load path, 1.3 us per step of
 // all four waves against 0.8 us for one wave alone).  The shares meet once, in split_finish.
 constexpr int SPLIT = 4;
-template <bool ROWS256>
 __global__ __launch_bounds__(64 * SPLIT) void vs_split_kernel(QKV x, HeadList hl, const int32_t *v_idx,
                                                               const int32_t *cover, const uint32_t *cover_bits,
                                                               const int32_t *counts, int nv, int ns, int cover_words,
@@ -2239,16 +2235,15 @@ __global__ __launch_bounds__(64 * SPLIT) void vs_split_kernel(QKV x, HeadList hl
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  vs_item<ROWS256, SPLIT>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+  vs_item<SPLIT>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
 }
-template <bool ROWS256>
 __global__ __launch_bounds__(64 * SPLIT) void bs_split_kernel(QKV x, HeadList hl, const int32_t *blk_idx,
                                                               const int32_t *blk_cnt, const int32_t *order, int topk,
                                                               Sched sched) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  bs_item<ROWS256, SPLIT>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+  bs_item<SPLIT>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
 }
 
 // A-shape / dense steps of one query block, 32 keys each: the sink [0, e1), then the window [s2, q0 + 64)
@@ -2333,7 +2328,6 @@ struct VsEdgeGen {
 };
 
 // One work item = the query blocks 4 sb .. 4 sb + 3 of list slot `slot`, one per wave of the workgroup.
-template <bool ROWS256>
 __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
                                               const int32_t *cover, const uint32_t *cover_bits, const int32_t *counts,
                                               int nv, int ns, int cover_words, int slot, int sb, char *lds) {
@@ -2368,17 +2362,16 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
   bool has_ref = false;
   QAcc qa;
   pin_q(qa, st);
-  DmaLane dk, dv;
-  dma_lane_init(dk, c.k_st, lane);
-  dma_lane_init(dv, c.v_st, lane);
+  DmaRows dk, dv;
+  dk.init((unsigned)c.k_st * 2u, lane);
+  dv.init((unsigned)c.v_st * 2u, lane);
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
 
   // ---- common parts of the long runs (the same for the four waves; every pass ends with a barrier)
   {
     WaveDma d;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { d.k_voff[i] = dk.voff[i]; d.v_voff[i] = dv.voff[i]; }
+    d.k = dk; d.v = dv;
     d.k_rb = k_rb; d.v_rb = v_rb;
     d.kw = khb + (size_t)(16 * wave) * k_rb;
     d.vw = vhb + (size_t)(16 * wave) * v_rb;
@@ -2396,8 +2389,8 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
         todo &= todo - 1;
         a.T = __builtin_amdgcn_readlane(T, i);
         a.s2 = __builtin_amdgcn_readlane(klo, i);
-        ashape_first_loads<ROWS256>(a, d);
-        ashape_pass_pipelined<ROWS256, AllCls>(a, d, st, qa, has_ref, lo, mp, AllCls{}, lane);
+        ashape_first_loads(a, d);
+        ashape_pass_pipelined<AllCls>(a, d, st, qa, has_ref, lo, mp, AllCls{}, lane);
       }
       if (__builtin_amdgcn_readlane(mine.x, 63) > Q0) break;      // runs ascend
     }
@@ -2412,11 +2405,11 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
       const int usable = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && mine.x <= q0));
       if (usable == 0) break;
       VsEdgeGen gen{mine, usable, q0, Q0, c.N, 0, 0, 0, 0, 0};
-      WavePipe3<VsEdgeGen, ROWS256> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
+      WavePipe3<VsEdgeGen> pipe{gen, st, qa, has_ref, lo, c.buf, khb, vhb, k_rb, v_rb, dk, dv, mp, c.c_log2, lane};
       pipe.run();
       if (usable < n) break;
     }
-    vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
+    vs_cols_pipelined<1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
     redo = needs_exact(st);
     if (!redo) wave_finish(st, oh, x.o_st, q0, ring, lane);
   }
@@ -2446,14 +2439,13 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
   }
 }
 
-template <bool ROWS256>
 __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const int32_t *v_idx, const int32_t *cover,
                                                        const uint32_t *cover_bits, const int32_t *counts, int nv,
                                                        int ns, int cover_words, Sched sched) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, sb;
   if (!decode_wg(sched, slot, sb)) return;
-  vs_share_item<ROWS256>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, sb, lds);
+  vs_share_item(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, sb, lds);
 }
 
 // One pass of the exact scheme over this wave's share of the steps.
@@ -2471,7 +2463,6 @@ __device__ inline void ashape_wave_pass(WaveState &st, const LaneOfs &lo, const 
 }
 
 // A-shape and dense with few work items: four waves per query block instead of one each.
-template <bool ROWS256>
 __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadList hl, int n_init, int n_local,
                                                                   Sched sched) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -2492,12 +2483,12 @@ __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadLis
   const StepBuf buf{lds + wave * RING_BYTES};
   QAcc qa;
   pin_q(qa, st);
-  DmaLane dk, dv;
-  dma_lane_init(dk, x.k_st, lane);
-  dma_lane_init(dv, x.v_st, lane);
+  DmaRows dk, dv;
+  dk.init((unsigned)x.k_st * 2u, lane);
+  dv.init((unsigned)x.v_st * 2u, lane);
   bool has_ref = false;
   AshapeGen<SPLIT> gen(mp, wave);
-  WavePipe3<AshapeGen<SPLIT>, ROWS256, SPLIT> pipe{gen, st, qa, has_ref, lo, buf, reinterpret_cast<const char *>(kh),
+  WavePipe3<AshapeGen<SPLIT>, SPLIT> pipe{gen, st, qa, has_ref, lo, buf, reinterpret_cast<const char *>(kh),
                                                    reinterpret_cast<const char *>(vh), (unsigned)x.k_st * 2u,
                                                    (unsigned)x.v_st * 2u, dk, dv, mp, x.c_log2, lane, lds, wave};
   pipe.run();
@@ -2531,23 +2522,21 @@ struct BsArgs {
   const int32_t *blk_idx, *blk_cnt, *order;
   int topk;
 };
-template <bool ROWS256>
 __global__ __launch_bounds__(64) void vs_bs_kernel(QKV x, HeadList hv, VsArgs va, Sched sv, HeadList hb, BsArgs ba,
                                                    Sched sb) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int kind, slot, b;
   if (!decode_mixed(sv, sb, blockIdx.x, kind, slot, b)) return;
   if (kind == 0)
-    vs_item<ROWS256, 1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
   else
-    bs_item<ROWS256, 1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+    bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
 }
 
 // The same for short rows on which a kind takes its blocks with four waves: workgroups of four waves
 // and 160 KiB hold an item of a kind that shares it (four waves per block, or four blocks), or four
 // items of a kind that does not.  Each kind runs the code of its own call.
 enum { TAKE_EACH = 0, TAKE_SPLIT = 1, TAKE_SHARE = 2 };
-template <bool ROWS256>
 __global__ __launch_bounds__(64 * SPLIT) void vs_bs_wide_kernel(QKV x, HeadList hv, VsArgs va, Sched sv, int vs_take,
                                                                 HeadList hb, BsArgs ba, Sched sb, int bs_take) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -2559,14 +2548,14 @@ __global__ __launch_bounds__(64 * SPLIT) void vs_bs_wide_kernel(QKV x, HeadList 
   slot = __builtin_amdgcn_readfirstlane(slot);
   b = __builtin_amdgcn_readfirstlane(b);
   if (kind == 1) {
-    if (bs_take == TAKE_SPLIT) bs_item<ROWS256, SPLIT>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
-    else bs_item<ROWS256, 1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, ring);
+    if (bs_take == TAKE_SPLIT) bs_item<SPLIT>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+    else bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, ring);
   } else if (vs_take == TAKE_SHARE) {
-    vs_share_item<ROWS256>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_share_item(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
   } else if (vs_take == TAKE_SPLIT) {
-    vs_item<ROWS256, SPLIT>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_item<SPLIT>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
   } else {
-    vs_item<ROWS256, 1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, ring);
+    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, ring);
   }
 }
 
@@ -2612,7 +2601,7 @@ struct RunLanes {
 //  - a step with nothing to attend (the idle steps of the skew, steps of a run that lie
 //    before key 0 for this wave only) is run with P = 0.  The rings are zero-filled at the start
 //    and only ever receive K/V rows, so what such a step multiplies by zero is finite.
-template <class Gen, bool ROWS256>
+template <class Gen>
 struct RingPipe3 {
   Gen &gen;
   WaveState &st;
@@ -2623,7 +2612,7 @@ struct RingPipe3 {
   int wave;
   const char *kh, *vh;       // head bases (bytes)
   unsigned k_rb, v_rb;
-  const DmaLane &dk, &dv;
+  const DmaRows &dk, &dv;
   MaskP mp;
   float c_log2;
   int lane;
@@ -2668,9 +2657,9 @@ struct RingPipe3 {
   __device__ inline void fetch_whole(const RStep &d, unsigned dst) const {
     const char *a = row0(IS_K ? kh : vh, IS_K ? k_rb : v_rb, d);
     const unsigned rb = IS_K ? k_rb : v_rb;
-    const unsigned (&vo)[4] = IS_K ? dk.voff : dv.voff;
-    dma_pair<ROWS256, 0>(a, rb, vo, dst); dma_pair<ROWS256, 2>(a, rb, vo, dst);
-    dma_pair<ROWS256, 4>(a, rb, vo, dst); dma_pair<ROWS256, 6>(a, rb, vo, dst);
+    const DmaRows &vo = IS_K ? dk : dv;
+    dma_pair<0>(a, rb, vo, dst); dma_pair<2>(a, rb, vo, dst);
+    dma_pair<4>(a, rb, vo, dst); dma_pair<6>(a, rb, vo, dst);
   }
 
   // Iteration t with PH = t mod 6: K of step s lives in K slot s mod 2, V of step s in V slot
@@ -2735,9 +2724,9 @@ struct RingPipe3 {
       else mfma_qk_acc(s_nxt[0][1], kf[r], qa.q[1][r]);
       sum_pair(2 * r);
       if (r < 4) {
-        if (ld_k) dma_pair<ROWS256, 2 * (r & 3)>(kt, k_rb, dk.voff, k_dst);
+        if (ld_k) dma_pair<2 * (r & 3)>(kt, k_rb, dk, k_dst);
       } else {
-        if (ld_v) dma_pair<ROWS256, 2 * (r & 3)>(vt, v_rb, dv.voff, v_dst);
+        if (ld_v) dma_pair<2 * (r & 3)>(vt, v_rb, dv, v_dst);
       }
       __builtin_amdgcn_sched_barrier(0);
       {
@@ -2824,7 +2813,6 @@ struct RingPipe3 {
   }
 };
 
-template <bool ROWS256>
 __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const int32_t *v_idx,
                                                       const int32_t *cover, const uint32_t *cover_bits,
                                                       const int32_t *counts, int nv, int ns, int cover_words,
@@ -2872,15 +2860,15 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   bool has_ref = false;
   QAcc qa;
   pin_q(qa, st);
-  DmaLane dk, dv;
-  dma_lane_init(dk, c.k_st, lane);
-  dma_lane_init(dv, c.v_st, lane);
+  DmaRows dk, dv;
+  dk.init((unsigned)c.k_st * 2u, lane);
+  dv.init((unsigned)c.v_st * 2u, lane);
   {
     // ---- phase A: slash runs, shared between the four waves
     RunLanes rl{c.runs, c.n_c, lane, 0, make_int2(KEY_NONE, KEY_NONE)};
     rl.load(0);
     VsRingGen<RunLanes> gen(rl, sb * 4 * BQ, wave, c.N);
-    RingPipe3<VsRingGen<RunLanes>, ROWS256> pipe{gen, st, qa, has_ref, lo, lds, wave,
+    RingPipe3<VsRingGen<RunLanes>> pipe{gen, st, qa, has_ref, lo, lds, wave,
                                                  reinterpret_cast<const char *>(c.kh),
                                                  reinterpret_cast<const char *>(c.vh), (unsigned)c.k_st * 2u,
                                                  (unsigned)c.v_st * 2u, dk, dv, mp, c.c_log2, lane};
@@ -2888,7 +2876,7 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   }
   if (!active) return;       // no workgroup barrier below this line
   // ---- phase B: verticals, per wave
-  vs_cols_pipelined<ROWS256, 1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
+  vs_cols_pipelined<1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
   if (needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
@@ -2911,31 +2899,19 @@ hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_loc
   if (ashape_split_pays(x.n_q, x.N, n_local)) {
     const Sched s = make_sched(hl, x.group, NB);
     const size_t lds = SPLIT * RING_BYTES;
-    const bool rows256 = x.k_st == D && x.v_st == D;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(ashape_split_kernel<true>)
-                             : reinterpret_cast<const void *>(ashape_split_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(ashape_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    if (rows256)
-      hipLaunchKernelGGL(ashape_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
-                         n_local, s);
-    else
-      hipLaunchKernelGGL(ashape_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
-                         n_local, s);
+    hipLaunchKernelGGL(ashape_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
+                       n_local, s);
     return hipGetLastError();
   }
   const Sched s = make_sched(hl, x.group, NSB);
   const size_t lds = 8 * TILE_BYTES;   // four K and four V slots
-  // rows 256 bytes apart in both K and V (the [head][token][128] layout): cheaper tile fetch
-  const bool rows256 = x.k_st == D && x.v_st == D;
-  const void *fn = rows256 ? reinterpret_cast<const void *>(ashape_kernel<true>)
-                           : reinterpret_cast<const void *>(ashape_kernel<false>);
+  const void *fn = reinterpret_cast<const void *>(ashape_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  if (rows256)
-    hipLaunchKernelGGL(ashape_kernel<true>, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, n_init, n_local, s);
-  else
-    hipLaunchKernelGGL(ashape_kernel<false>, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, n_init, n_local, s);
+  hipLaunchKernelGGL(ashape_kernel, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, n_init, n_local, s);
   return hipGetLastError();
 }
 
@@ -2943,30 +2919,20 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
                      const int32_t *order, int topk, hipStream_t st) {
   const int NB = x.N / BQ;
   const Sched s = make_sched(hl, x.group, NB);
-  const bool rows256 = x.k_st == D && x.v_st == D;
   if (bs_split_pays(x.n_q, x.N, topk)) {
     const size_t lds = SPLIT * RING_BYTES;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(bs_split_kernel<true>)
-                             : reinterpret_cast<const void *>(bs_split_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(bs_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    if (rows256)
-      hipLaunchKernelGGL(bs_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
-                         blk_cnt, order, topk, s);
-    else
-      hipLaunchKernelGGL(bs_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
-                         blk_cnt, order, topk, s);
+    hipLaunchKernelGGL(bs_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
+                       blk_cnt, order, topk, s);
     return hipGetLastError();
   }
   const size_t lds = 5 * HALF_BYTES;
-  const void *fn = rows256 ? reinterpret_cast<const void *>(bs_kernel<true>)
-                           : reinterpret_cast<const void *>(bs_kernel<false>);
+  const void *fn = reinterpret_cast<const void *>(bs_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  if (rows256)
-    hipLaunchKernelGGL(bs_kernel<true>, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, blk_idx, blk_cnt, order, topk, s);
-  else
-    hipLaunchKernelGGL(bs_kernel<false>, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, blk_idx, blk_cnt, order, topk, s);
+  hipLaunchKernelGGL(bs_kernel, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, blk_idx, blk_cnt, order, topk, s);
   return hipGetLastError();
 }
 
@@ -2975,7 +2941,6 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
                      int cover_words, hipStream_t st) {
   const int NB = x.N / BQ;
   // gathered rows are addressed with 32-bit byte offsets from the head base (checked by the caller)
-  const bool rows256 = x.k_st == D && x.v_st == D;
   // MINF_VS_ENGINE=ring selects the shared-tile engine (four waves per workgroup, slash-run tiles
   // fetched once per group of waves); it is slower than the default on every measured workload
   // and kept as a measured alternative.
@@ -2983,59 +2948,39 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
   if (use_ring) {
     const Sched s = make_sched(hl, x.group, (NB + 3) / 4);
     const size_t lds = 4 * RING_BYTES;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_ring_kernel<true>)
-                             : reinterpret_cast<const void *>(vs_ring_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(vs_ring_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    if (rows256)
-      hipLaunchKernelGGL(vs_ring_kernel<true>, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s);
-    else
-      hipLaunchKernelGGL(vs_ring_kernel<false>, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s);
+    hipLaunchKernelGGL(vs_ring_kernel, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+                       cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
   const Sched s = make_sched(hl, x.group, NB);
   if (vs_split_pays(x.n_q, x.N, nv, ns)) {
     const size_t lds = SPLIT * RING_BYTES;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_split_kernel<true>)
-                             : reinterpret_cast<const void *>(vs_split_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(vs_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    if (rows256)
-      hipLaunchKernelGGL(vs_split_kernel<true>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s);
-    else
-      hipLaunchKernelGGL(vs_split_kernel<false>, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s);
+    hipLaunchKernelGGL(vs_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
+                       cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
   if (vs_share_pays(x.N, ns)) {
     const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4);
     const size_t lds = 4 * RING_BYTES;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_share_kernel<true>)
-                             : reinterpret_cast<const void *>(vs_share_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(vs_share_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    if (rows256)
-      hipLaunchKernelGGL(vs_share_kernel<true>, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s4);
-    else
-      hipLaunchKernelGGL(vs_share_kernel<false>, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
-                         cover_bits, counts, nv, ns, cover_words, s4);
+    hipLaunchKernelGGL(vs_share_kernel, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+                       cover_bits, counts, nv, ns, cover_words, s4);
     return hipGetLastError();
   }
   const size_t lds = 5 * HALF_BYTES;
-  const void *fn = rows256 ? reinterpret_cast<const void *>(vs_kernel<true>)
-                           : reinterpret_cast<const void *>(vs_kernel<false>);
+  const void *fn = reinterpret_cast<const void *>(vs_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  if (rows256)
-    hipLaunchKernelGGL(vs_kernel<true>, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, v_idx, cover, cover_bits,
-                       counts, nv, ns, cover_words, s);
-  else
-    hipLaunchKernelGGL(vs_kernel<false>, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, v_idx, cover, cover_bits,
-                       counts, nv, ns, cover_words, s);
+  hipLaunchKernelGGL(vs_kernel, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, v_idx, cover, cover_bits,
+                     counts, nv, ns, cover_words, s);
   return hipGetLastError();
 }
 
@@ -3064,32 +3009,21 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
   const BsArgs ba{blk_idx, blk_cnt, order, topk};
   if (wide) {
     const size_t lds = SPLIT * RING_BYTES;
-    const bool rows256 = x.k_st == D && x.v_st == D;
-    const void *fn = rows256 ? reinterpret_cast<const void *>(vs_bs_wide_kernel<true>)
-                             : reinterpret_cast<const void *>(vs_bs_wide_kernel<false>);
+    const void *fn = reinterpret_cast<const void *>(vs_bs_wide_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
     const int groups = mixed_groups(wide_per_xcd(sv, vs_take == TAKE_EACH), wide_per_xcd(sb, bs_take == TAKE_EACH));
-    if (rows256)
-      hipLaunchKernelGGL(vs_bs_wide_kernel<true>, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
-                         hb, ba, sb, bs_take);
-    else
-      hipLaunchKernelGGL(vs_bs_wide_kernel<false>, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
-                         hb, ba, sb, bs_take);
+    hipLaunchKernelGGL(vs_bs_wide_kernel, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
+                       hb, ba, sb, bs_take);
     return hipGetLastError();
   }
   const size_t lds = 5 * HALF_BYTES;
-  const bool rows256 = x.k_st == D && x.v_st == D;
-  const void *fn = rows256 ? reinterpret_cast<const void *>(vs_bs_kernel<true>)
-                           : reinterpret_cast<const void *>(vs_bs_kernel<false>);
+  const void *fn = reinterpret_cast<const void *>(vs_bs_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
   // groups of 40 workgroup ids: 32 Vertical-Slash positions and 8 Block-Sparse positions
   const int groups = mixed_groups(sv, sb);
-  if (rows256)
-    hipLaunchKernelGGL(vs_bs_kernel<true>, dim3(40 * groups), dim3(64), lds, st, x, hv, va, sv, hb, ba, sb);
-  else
-    hipLaunchKernelGGL(vs_bs_kernel<false>, dim3(40 * groups), dim3(64), lds, st, x, hv, va, sv, hb, ba, sb);
+  hipLaunchKernelGGL(vs_bs_kernel, dim3(40 * groups), dim3(64), lds, st, x, hv, va, sv, hb, ba, sb);
   return hipGetLastError();
 }
 
