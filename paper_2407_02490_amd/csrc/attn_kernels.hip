@@ -1028,6 +1028,7 @@ __global__ __launch_bounds__(256) void ashape_kernel(QKV x, HeadList hl, int n_i
   const int NB = x.N / BQ;
   int slot, sb;
   if (!decode_wg(sched, slot, sb)) return;
+  x = at_batch(x, blockIdx.y);
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh;
@@ -1863,12 +1864,12 @@ struct BsGen {
 // one wave, or NW waves of which wave w takes the list entries w, w + NW, ...
 template <int NW>
 __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const int32_t *blk_idx,
-                                        const int32_t *blk_cnt, const int32_t *order, int topk, int slot, int b,
-                                        char *lds) {
+                                        const int32_t *blk_cnt, const int32_t *order, int topk, int slot, int row,
+                                        int b, char *lds) {
   const int NB = x.N / BQ;
   if (order) {
     // position in the processing order -> query block (a permutation: every block is taken once)
-    b = __builtin_amdgcn_readfirstlane(order[(int64_t)slot * NB + b]);
+    b = __builtin_amdgcn_readfirstlane(order[(int64_t)row * NB + b]);
     if (b < 0 || b >= NB) return;
   }
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
@@ -1888,8 +1889,8 @@ __device__ __forceinline__ void bs_item(const QKV &x, const HeadList &hl, const 
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
   c.N = x.N; c.NB = NB; c.buf = StepBuf{lds + wave * RING_BYTES}; c.c_log2 = x.c_log2;
   // the block list of this query block is walked 64 ids at a time, one per lane
-  const int32_t *glist = blk_idx + ((int64_t)slot * NB + b) * topk;
-  c.cnt = min(max(blk_cnt[(int64_t)slot * NB + b], 0), topk);
+  const int32_t *glist = blk_idx + ((int64_t)row * NB + b) * topk;
+  c.cnt = min(max(blk_cnt[(int64_t)row * NB + b], 0), topk);
   c.list = glist;
 
   QAcc qa;
@@ -1932,7 +1933,7 @@ __global__ __launch_bounds__(64) void bs_kernel(QKV x, HeadList hl, const int32_
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  bs_item<1>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+  bs_item<1>(at_batch(x, blockIdx.y), hl, blk_idx, blk_cnt, order, topk, slot, slot + blockIdx.y * hl.n, b, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -2167,7 +2168,7 @@ __device__ inline void vs_pass_pipelined(const VsCtx &c, WaveState &st, const La
 template <int NW>
 __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
                                         const int32_t *cover, const uint32_t *cover_bits,
-                                        const int32_t *counts, int nv, int ns, int cover_words, int slot, int b,
+                                        const int32_t *counts, int nv, int ns, int cover_words, int slot, int row, int b,
                                         char *lds) {
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
@@ -2182,11 +2183,11 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   // The column list of the vertical phase, which runs two deep on V slots 0 and 1, lives in V slot 2.
   c.N = x.N; c.q0 = q0; c.buf = StepBuf{ring}; c.c_log2 = x.c_log2;
   c.cols = reinterpret_cast<int *>(ring + 4 * HALF_BYTES);   // [VCAP + 64]
-  c.n_v = min(max(counts[slot * 4 + 0], 0), nv);
-  c.n_c = min(max(counts[slot * 4 + 2], 0), ns);
-  c.vlist = v_idx + (int64_t)slot * nv;
-  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)slot * ns;
-  c.bits = cover_bits + (int64_t)slot * cover_words;
+  c.n_v = min(max(counts[row * 4 + 0], 0), nv);
+  c.n_c = min(max(counts[row * 4 + 2], 0), ns);
+  c.vlist = v_idx + (int64_t)row * nv;
+  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)row * ns;
+  c.bits = cover_bits + (int64_t)row * cover_words;
 
   WaveState st;
   wave_init(st, qh, x.q_st, q0, lane);
@@ -2220,7 +2221,8 @@ __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  vs_item<1>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+  vs_item<1>(at_batch(x, blockIdx.y), hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot,
+             slot + blockIdx.y * hl.n, b, lds);
 }
 
 // Few work items: four waves per query block, each with a quarter of its steps (and its own ring;
@@ -2235,7 +2237,8 @@ __global__ __launch_bounds__(64 * SPLIT) void vs_split_kernel(QKV x, HeadList hl
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  vs_item<SPLIT>(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, b, lds);
+  vs_item<SPLIT>(at_batch(x, blockIdx.y), hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot,
+             slot + blockIdx.y * hl.n, b, lds);
 }
 __global__ __launch_bounds__(64 * SPLIT) void bs_split_kernel(QKV x, HeadList hl, const int32_t *blk_idx,
                                                               const int32_t *blk_cnt, const int32_t *order, int topk,
@@ -2243,7 +2246,7 @@ __global__ __launch_bounds__(64 * SPLIT) void bs_split_kernel(QKV x, HeadList hl
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
-  bs_item<SPLIT>(x, hl, blk_idx, blk_cnt, order, topk, slot, b, lds);
+  bs_item<SPLIT>(at_batch(x, blockIdx.y), hl, blk_idx, blk_cnt, order, topk, slot, slot + blockIdx.y * hl.n, b, lds);
 }
 
 // A-shape / dense steps of one query block, 32 keys each: the sink [0, e1), then the window [s2, q0 + 64)
@@ -2330,7 +2333,8 @@ struct VsEdgeGen {
 // One work item = the query blocks 4 sb .. 4 sb + 3 of list slot `slot`, one per wave of the workgroup.
 __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, const int32_t *v_idx,
                                               const int32_t *cover, const uint32_t *cover_bits, const int32_t *counts,
-                                              int nv, int ns, int cover_words, int slot, int sb, char *lds) {
+                                              int nv, int ns, int cover_words, int slot, int row, int sb,
+                                              char *lds) {
   const int NB = x.N / BQ;
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
@@ -2347,11 +2351,11 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
   c.N = x.N; c.q0 = q0; c.buf = StepBuf{ring}; c.c_log2 = x.c_log2;
   c.cols = reinterpret_cast<int *>(ring + 4 * HALF_BYTES);   // [VCAP + 64]
-  c.n_v = min(max(counts[slot * 4 + 0], 0), nv);
-  c.n_c = min(max(counts[slot * 4 + 2], 0), ns);
-  c.vlist = v_idx + (int64_t)slot * nv;
-  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)slot * ns;
-  c.bits = cover_bits + (int64_t)slot * cover_words;
+  c.n_v = min(max(counts[row * 4 + 0], 0), nv);
+  c.n_c = min(max(counts[row * 4 + 2], 0), ns);
+  c.vlist = v_idx + (int64_t)row * nv;
+  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)row * ns;
+  c.bits = cover_bits + (int64_t)row * cover_words;
 
   WaveState st;
   wave_init(st, qh, x.q_st, q0, lane);
@@ -2445,7 +2449,8 @@ __global__ __launch_bounds__(256) void vs_share_kernel(QKV x, HeadList hl, const
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, sb;
   if (!decode_wg(sched, slot, sb)) return;
-  vs_share_item(x, hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot, sb, lds);
+  vs_share_item(at_batch(x, blockIdx.y), hl, v_idx, cover, cover_bits, counts, nv, ns, cover_words, slot,
+                slot + blockIdx.y * hl.n, sb, lds);
 }
 
 // One pass of the exact scheme over this wave's share of the steps.
@@ -2468,6 +2473,7 @@ __global__ __launch_bounds__(64 * SPLIT) void ashape_split_kernel(QKV x, HeadLis
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int slot, b;
   if (!decode_wg(sched, slot, b)) return;
+  x = at_batch(x, blockIdx.y);
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh, *kh = x.k + kvh * x.k_sh, *vh = x.v + kvh * x.v_sh;
@@ -2527,10 +2533,12 @@ __global__ __launch_bounds__(64) void vs_bs_kernel(QKV x, HeadList hv, VsArgs va
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int kind, slot, b;
   if (!decode_mixed(sv, sb, blockIdx.x, kind, slot, b)) return;
+  x = at_batch(x, blockIdx.y);
+  const int row = slot + blockIdx.y * (kind == 0 ? hv.n : hb.n);
   if (kind == 0)
-    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, row, b, lds);
   else
-    bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
+    bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, row, b, lds);
 }
 
 // The same for short rows on which a kind takes its blocks with four waves: workgroups of four waves
@@ -2547,15 +2555,17 @@ __global__ __launch_bounds__(64 * SPLIT) void vs_bs_wide_kernel(QKV x, HeadList 
   if (!decode_wide(sv, vs_take == TAKE_EACH, sb, bs_take == TAKE_EACH, blockIdx.x, wave, kind, slot, b)) return;
   slot = __builtin_amdgcn_readfirstlane(slot);
   b = __builtin_amdgcn_readfirstlane(b);
+  x = at_batch(x, blockIdx.y);
+  const int row = slot + blockIdx.y * __builtin_amdgcn_readfirstlane(kind == 0 ? hv.n : hb.n);
   if (kind == 1) {
-    if (bs_take == TAKE_SPLIT) bs_item<SPLIT>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, lds);
-    else bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, b, ring);
+    if (bs_take == TAKE_SPLIT) bs_item<SPLIT>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, row, b, lds);
+    else bs_item<1>(x, hb, ba.blk_idx, ba.blk_cnt, ba.order, ba.topk, slot, row, b, ring);
   } else if (vs_take == TAKE_SHARE) {
-    vs_share_item(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_share_item(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, row, b, lds);
   } else if (vs_take == TAKE_SPLIT) {
-    vs_item<SPLIT>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, lds);
+    vs_item<SPLIT>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, row, b, lds);
   } else {
-    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, b, ring);
+    vs_item<1>(x, hv, va.v_idx, va.cover, va.cover_bits, va.counts, va.nv, va.ns, va.cover_words, slot, row, b, ring);
   }
 }
 
@@ -2821,6 +2831,8 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   const int NB = x.N / BQ;
   int slot, sb;
   if (!decode_wg(sched, slot, sb)) return;
+  x = at_batch(x, blockIdx.y);
+  const int row = slot + blockIdx.y * hl.n;
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
   const bf16_t *qh = x.q + head * x.q_sh;
@@ -2843,11 +2855,11 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   c.kh = x.k + kvh * x.k_sh; c.vh = x.v + kvh * x.v_sh; c.k_st = x.k_st; c.v_st = x.v_st;
   c.N = x.N; c.q0 = q0; c.buf = StepBuf{ring}; c.c_log2 = x.c_log2;
   c.cols = reinterpret_cast<int *>(ring + 4 * HALF_BYTES);   // [VCAP + 64], third V slot
-  c.n_v = min(max(counts[slot * 4 + 0], 0), nv);
-  c.n_c = min(max(counts[slot * 4 + 2], 0), ns);
-  c.vlist = v_idx + (int64_t)slot * nv;
-  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)slot * ns;
-  c.bits = cover_bits + (int64_t)slot * cover_words;
+  c.n_v = min(max(counts[row * 4 + 0], 0), nv);
+  c.n_c = min(max(counts[row * 4 + 2], 0), ns);
+  c.vlist = v_idx + (int64_t)row * nv;
+  c.runs = reinterpret_cast<const int2 *>(cover) + (int64_t)row * ns;
+  c.bits = cover_bits + (int64_t)row * cover_words;
 
   WaveState st;
   wave_init(st, qh, x.q_st, active ? q0 : (NB - 1) * BQ, lane);
@@ -2894,7 +2906,7 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
+hipError_t launch_ashape(const QKV &x, int nb, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
   if (ashape_split_pays(x.n_q, x.N, n_local)) {
     const Sched s = make_sched(hl, x.group, NB);
@@ -2902,7 +2914,7 @@ hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_loc
     const void *fn = reinterpret_cast<const void *>(ashape_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ashape_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, n_init,
+    hipLaunchKernelGGL(ashape_split_kernel, dim3(s.per_xcd * 8, nb), dim3(64 * SPLIT), lds, st, x, hl, n_init,
                        n_local, s);
     return hipGetLastError();
   }
@@ -2911,11 +2923,11 @@ hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_loc
   const void *fn = reinterpret_cast<const void *>(ashape_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(ashape_kernel, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, n_init, n_local, s);
+  hipLaunchKernelGGL(ashape_kernel, dim3(s.per_xcd * 8, nb), dim3(256), lds, st, x, hl, n_init, n_local, s);
   return hipGetLastError();
 }
 
-hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, const int32_t *blk_cnt,
+hipError_t launch_bs(const QKV &x, int nb, const HeadList &hl, const int32_t *blk_idx, const int32_t *blk_cnt,
                      const int32_t *order, int topk, hipStream_t st) {
   const int NB = x.N / BQ;
   const Sched s = make_sched(hl, x.group, NB);
@@ -2924,7 +2936,7 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
     const void *fn = reinterpret_cast<const void *>(bs_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bs_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
+    hipLaunchKernelGGL(bs_split_kernel, dim3(s.per_xcd * 8, nb), dim3(64 * SPLIT), lds, st, x, hl, blk_idx,
                        blk_cnt, order, topk, s);
     return hipGetLastError();
   }
@@ -2932,11 +2944,11 @@ hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, c
   const void *fn = reinterpret_cast<const void *>(bs_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bs_kernel, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, blk_idx, blk_cnt, order, topk, s);
+  hipLaunchKernelGGL(bs_kernel, dim3(s.per_xcd * 8, nb), dim3(64), lds, st, x, hl, blk_idx, blk_cnt, order, topk, s);
   return hipGetLastError();
 }
 
-hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, const int32_t *cover,
+hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_idx, const int32_t *cover,
                      const uint32_t *cover_bits, const int32_t *counts, int nv, int ns,
                      int cover_words, hipStream_t st) {
   const int NB = x.N / BQ;
@@ -2951,7 +2963,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     const void *fn = reinterpret_cast<const void *>(vs_ring_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(vs_ring_kernel, dim3(s.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+    hipLaunchKernelGGL(vs_ring_kernel, dim3(s.per_xcd * 8, nb), dim3(256), lds, st, x, hl, v_idx, cover,
                        cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
@@ -2961,7 +2973,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     const void *fn = reinterpret_cast<const void *>(vs_split_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(vs_split_kernel, dim3(s.per_xcd * 8), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
+    hipLaunchKernelGGL(vs_split_kernel, dim3(s.per_xcd * 8, nb), dim3(64 * SPLIT), lds, st, x, hl, v_idx, cover,
                        cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
@@ -2971,7 +2983,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
     const void *fn = reinterpret_cast<const void *>(vs_share_kernel);
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(vs_share_kernel, dim3(s4.per_xcd * 8), dim3(256), lds, st, x, hl, v_idx, cover,
+    hipLaunchKernelGGL(vs_share_kernel, dim3(s4.per_xcd * 8, nb), dim3(256), lds, st, x, hl, v_idx, cover,
                        cover_bits, counts, nv, ns, cover_words, s4);
     return hipGetLastError();
   }
@@ -2979,7 +2991,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
   const void *fn = reinterpret_cast<const void *>(vs_kernel);
   hipError_t e = set_lds(fn, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(vs_kernel, dim3(s.per_xcd * 8), dim3(64), lds, st, x, hl, v_idx, cover, cover_bits,
+  hipLaunchKernelGGL(vs_kernel, dim3(s.per_xcd * 8, nb), dim3(64), lds, st, x, hl, v_idx, cover, cover_bits,
                      counts, nv, ns, cover_words, s);
   return hipGetLastError();
 }
@@ -2992,7 +3004,7 @@ hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, con
 // block, one launch against two, 16K tokens 2048 against 2058 us, 32K 6352 against 5988.
 constexpr int ONE_LAUNCH_MAX_N = 8192;
 
-hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,
+hipError_t launch_vs_bs(const QKV &x, int nb, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,
                         const uint32_t *cover_bits, const int32_t *counts, int nv, int ns, int cover_words,
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st) {
@@ -3001,8 +3013,8 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
   const int bs_take = bs_split_pays(x.n_q, x.N, topk) ? TAKE_SPLIT : TAKE_EACH;
   const bool wide = vs_take != TAKE_EACH || bs_take != TAKE_EACH;
   if (wide && x.N > ONE_LAUNCH_MAX_N) {
-    const hipError_t e = launch_vs(x, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
-    return e != hipSuccess ? e : launch_bs(x, hb, blk_idx, blk_cnt, order, topk, st);
+    const hipError_t e = launch_vs(x, nb, hv, v_idx, cover, cover_bits, counts, nv, ns, cover_words, st);
+    return e != hipSuccess ? e : launch_bs(x, nb, hb, blk_idx, blk_cnt, order, topk, st);
   }
   const Sched sv = make_sched(hv, x.group, vs_take == TAKE_SHARE ? (NB + 3) / 4 : NB), sb = make_sched(hb, x.group, NB);
   const VsArgs va{v_idx, cover, cover_bits, counts, nv, ns, cover_words};
@@ -3013,7 +3025,7 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
     hipError_t e = set_lds(fn, lds);
     if (e != hipSuccess) return e;
     const int groups = mixed_groups(wide_per_xcd(sv, vs_take == TAKE_EACH), wide_per_xcd(sb, bs_take == TAKE_EACH));
-    hipLaunchKernelGGL(vs_bs_wide_kernel, dim3(40 * groups), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
+    hipLaunchKernelGGL(vs_bs_wide_kernel, dim3(40 * groups, nb), dim3(64 * SPLIT), lds, st, x, hv, va, sv, vs_take,
                        hb, ba, sb, bs_take);
     return hipGetLastError();
   }
@@ -3023,7 +3035,7 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
   if (e != hipSuccess) return e;
   // groups of 40 workgroup ids: 32 Vertical-Slash positions and 8 Block-Sparse positions
   const int groups = mixed_groups(sv, sb);
-  hipLaunchKernelGGL(vs_bs_kernel, dim3(40 * groups), dim3(64), lds, st, x, hv, va, sv, hb, ba, sb);
+  hipLaunchKernelGGL(vs_bs_kernel, dim3(40 * groups, nb), dim3(64), lds, st, x, hv, va, sv, hb, ba, sb);
   return hipGetLastError();
 }
 

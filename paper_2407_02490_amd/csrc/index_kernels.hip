@@ -589,12 +589,13 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
   const bool active = wave < vg.cnt[grp];
   // a wave without a head takes the group's first one for its addresses; it only helps to fetch
   const int slot = __builtin_amdgcn_readfirstlane((int)vg.slot[grp][active ? wave : 0]);
+  const int row0 = slot + blockIdx.z * hl.n;         // index row: batch element blockIdx.z, list slot
   float *dacc = reinterpret_cast<float *>(lds + 3 * HALF_BYTES) + wave * vs_wave_floats(C);   // [VS_DPAD + C + VS_DPAD], pass 2
   float *skew = dacc + C + 2 * VS_DPAD;                                // [32][VS_SKEW_PITCH], pass 2
 
   const int head = __builtin_amdgcn_readfirstlane(hl.h[slot]);
   const int kvh = to_sgpr(head / x.group);
-  const bf16_t *qh = x.q + head * x.q_sh, *kh = x.k + kvh * x.k_sh;
+  const bf16_t *qh = x.q + blockIdx.z * x.q_sb + head * x.q_sh, *kh = x.k + blockIdx.z * x.k_sb + kvh * x.k_sh;
   const int n = lane & 31, h = lane >> 5;
   const int N = x.N;
   const int r_min = 64 - last_q;
@@ -624,7 +625,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = 32 * nb + 8 * (r >> 2) + 4 * h + (r & 3);
-        const float mx = ml_fin[(slot * 64 + row) * 2 + 0], inv = ml_fin[(slot * 64 + row) * 2 + 1];
+        const float mx = ml_fin[(row0 * 64 + row) * 2 + 0], inv = ml_fin[(row0 * 64 + row) * 2 + 1];
         off[nb][r] = (row >= r_min && inv > 0.f) ? mx - __builtin_amdgcn_logf(inv) : INFINITY;
       }
     for (int i = lane; i < C + 2 * VS_DPAD + 32 * VS_SKEW_PITCH; i += 64) dacc[i] = 0.f;   // dacc and skew
@@ -790,7 +791,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
       // the two lane halves hold the two halves of the rows of the same key
       const float other = __shfl_xor(cs, 32);
       const float tot = h == 0 ? cs + other : other + cs;   // same operand order in both
-      if (active && h == 0 && m < C / 32) colsum[(int64_t)slot * N + kt + n] = tot;
+      if (active && h == 0 && m < C / 32) colsum[(int64_t)row0 * N + kt + n] = tot;
     }
     // the upper rows of the last half tile
     vs_skew_reduce(carry, skew, dacc + VS_DPAD + 32 * n_half, n, h);
@@ -808,7 +809,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
       const float a = h == 0 ? l_run * fast_exp2(m_run - Mu) : lo2 * fast_exp2(mo - Mu);
       const float b = h == 0 ? lo2 * fast_exp2(mo - Mu) : l_run * fast_exp2(m_run - Mu);
       if (active && h == 0) {
-        float *dst = ml_part + (((int64_t)slot * n_chunks + chunk) * 64 + 32 * nb + n) * 2;
+        float *dst = ml_part + (((int64_t)row0 * n_chunks + chunk) * 64 + 32 * nb + n) * 2;
         dst[0] = M;
         dst[1] = a + b;
       }
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
     __syncthreads();
     for (int i = lane; i < C; i += 64) {
       const int o = chunk * C + i;
-      if (active && o < N) diagsum[(int64_t)slot * N + o] = dacc[VS_DPAD + i];
+      if (active && o < N) diagsum[(int64_t)row0 * N + o] = dacc[VS_DPAD + i];
     }
   }
 }
@@ -1301,7 +1302,8 @@ __global__ __launch_bounds__(1024) void vs_lines_kernel(int N, int nv, int ns, c
 // ---------------------------------------------------------------------------
 // grid (NB, n_heads + n_kv): y < n_heads pools Q of head slot y, else K of kv[y - n_heads]
 // (the pooled K vectors of a K/V head are NBp >= NB rows apart: padded to whole 32-row tiles)
-// grid (NB, n_q + n_kv): n_q = the listed query heads, or 0 (qpool == nullptr) when the caller pools Q itself.
+// grid (NB, n_q + n_kv, batch): n_q = the listed query heads, or 0 (qpool == nullptr) when the caller pools Q
+// itself (Q is pooled for one batch element at a time).
 __global__ __launch_bounds__(256) void bs_pool_kernel(QKV x, HeadList hl, KvMap km, float *qpool, float *kpool,
                                                       int NBp) {
   __shared__ float red[16][132];
@@ -1313,7 +1315,8 @@ __global__ __launch_bounds__(256) void bs_pool_kernel(QKV x, HeadList hl, KvMap 
   if (y < hl.n) {
     src = x.q + hl.h[y] * x.q_sh; st = x.q_st; dst = qpool + ((int64_t)y * NB + b) * 128;
   } else {
-    src = x.k + km.kv[y - hl.n] * x.k_sh; st = x.k_st; dst = kpool + ((int64_t)(y - hl.n) * NBp + b) * 128;
+    src = x.k + blockIdx.z * x.k_sb + km.kv[y - hl.n] * x.k_sh; st = x.k_st;
+    dst = kpool + ((int64_t)(blockIdx.z * km.n_kv + y - hl.n) * NBp + b) * 128;
   }
   const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1829,6 +1832,8 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
   unsigned *ckey = reinterpret_cast<unsigned *>(lds + 2 * BSF_TILE_BYTES);
   unsigned short *cidx = reinterpret_cast<unsigned short *>(ckey + BSF_ROWS * BSF_PITCH);
   const int slot = blockIdx.x;
+  const int64_t list0 = (int64_t)(slot + blockIdx.z * gridDim.x) * NB;     // first list of (batch element, slot)
+  const bf16_t *qh = x.q + blockIdx.z * x.q_sb + hl.h[slot] * x.q_sh;
   const int R0 = (gridDim.y - 1 - blockIdx.y) * BSF_ROWS;    // the longest rows of every head first
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, hq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1846,11 +1851,11 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
   // pooled Q never goes through memory.
   float q[32];
   if (SEL == BSF_WAVES) {
-    bsf_pool_q(x.q + hl.h[slot] * x.q_sh + (int64_t)(64 * min(row, NB - 1)) * x.q_st + 32 * hq, x.q_st, q);
+    bsf_pool_q(qh + (int64_t)(64 * min(row, NB - 1)) * x.q_st + 32 * hq, x.q_st, q);
   } else {
     constexpr int PER = BSF_ROWS / BSF_WAVES;                // blocks a wave pools
     float *mean = reinterpret_cast<float *>(lds);
-    bsf_pool_blocks(x.q + hl.h[slot] * x.q_sh, x.q_st, R0 + PER * wave, PER, NB,
+    bsf_pool_blocks(qh, x.q_st, R0 + PER * wave, PER, NB,
                     mean + (BSF_ROWS + 16 * wave) * BSF_POOL_PITCH, mean + PER * wave * BSF_POOL_PITCH, lane);
     __syncthreads();
     const float *src = mean + (16 * (wave % SEL) + n) * BSF_POOL_PITCH + 32 * hq;
@@ -1861,7 +1866,7 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
     }
     __syncthreads();                                         // the tiles and lists take the pooling's LDS
   }
-  const float *kp = kpool + (int64_t)km.slot_kv[slot] * NBp * 128;
+  const float *kp = kpool + (int64_t)(blockIdx.z * km.n_kv + km.slot_kv[slot]) * NBp * 128;
   const int last_row = min(R0 + BSF_ROWS, NB) - 1;           // last query block of the workgroup
   const int n_tiles = last_row / 32 + 1;                     // key tiles that hold a key <= last_row
   const int wave_first = R0 + 16 * wave;
@@ -1971,9 +1976,9 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
   // exact selection of what is left, then the row goes out (ascending; -1 behind the last entry)
   cnt = bsf_compact(keys, idx, cnt, k, true, hq, tau).cnt;
   if (row_ok) {
-    int32_t *out = blk_idx + ((int64_t)slot * NB + row) * topk;
+    int32_t *out = blk_idx + (list0 + row) * topk;
     for (int i = hq; i < topk; i += 4) out[i] = i < cnt ? (int32_t)idx[i] : -1;
-    if (hq == 0) blk_cnt[(int64_t)slot * NB + row] = cnt;
+    if (hq == 0) blk_cnt[list0 + row] = cnt;
   }
 }
 
@@ -2044,19 +2049,56 @@ static int vs_ml_chunks(int N) { return vs_chunks(N, vs_ml_chunk_keys(N)); }
 static int vs_slices(int N) { return (N + VS_SLICE - 1) / VS_SLICE; }
 static int vs_cand_cap(int N) { return N / 4 > 1024 ? N / 4 : 1024; }        // candidates per (head, which)
 
-size_t vs_index_ws_bytes(int N, int n_heads) {
-  size_t b = 0;
-  b += 2 * align256((size_t)n_heads * N * sizeof(float));                     // colsum, diagsum
-  b += align256((size_t)n_heads * vs_ml_chunks(N) * 128 * sizeof(float));     // per-chunk (max, sum)
-  b += align256((size_t)n_heads * 128 * sizeof(float));                       // final (max, 1/sum)
-  b += 2 * align256((size_t)n_heads * (N / 4) * sizeof(float));               // group maxima (G >= 4)
-  b += 4 * align256((size_t)n_heads * 2 * vs_cand_cap(N) * sizeof(float));    // candidates: parts and list, value and position
-  b += align256((size_t)n_heads * 2 * vs_slices(N) * sizeof(int2));           // where every slice put its part
-  b += align256((size_t)n_heads * 2 * sizeof(VsSelState));
-  return b;
+// Scratch of a build over `rows` = batch elements x listed heads.  The prefilter's arrays are left out
+// where it does not run and several batch elements share the workspace; the partial sums of pass 1 then
+// lie in the place of the line scores, which pass 2 writes after they have been combined.  (A workspace
+// of the reported size, 18.5 bytes per head and token and more, so holds at least two elements.)
+struct VsScratch {
+  float *colsum, *diagsum, *ml_part, *ml_fin, *gmax_v, *gmax_s, *cand_val, *list_val;
+  int32_t *cand_idx, *list_idx;
+  int2 *seg;
+  VsSelState *state;
+  size_t bytes;
+};
+static VsScratch vs_scratch(int N, int rows, bool whole, char *base) {
+  VsScratch w;
+  memset(&w, 0, sizeof(w));
+  char *p = base;
+  auto take = [&](size_t bytes) { char *q = p; p += align256(bytes); return q; };
+  const size_t score = (size_t)rows * N * sizeof(float), ml = (size_t)rows * vs_ml_chunks(N) * 128 * sizeof(float);
+  w.colsum = reinterpret_cast<float *>(take(score));
+  w.diagsum = reinterpret_cast<float *>(take(score));
+  w.ml_part = whole ? reinterpret_cast<float *>(take(ml)) : w.colsum;   // ml <= 2 score: at least 64 keys per chunk
+  w.ml_fin = reinterpret_cast<float *>(take((size_t)rows * 128 * sizeof(float)));
+  if (whole) {
+    const size_t cand = (size_t)rows * 2 * vs_cand_cap(N) * sizeof(float);
+    w.gmax_v = reinterpret_cast<float *>(take((size_t)rows * (N / 4) * sizeof(float)));      // group maxima (G >= 4)
+    w.gmax_s = reinterpret_cast<float *>(take((size_t)rows * (N / 4) * sizeof(float)));
+    w.cand_val = reinterpret_cast<float *>(take(cand));                 // candidates: parts and list, value and position
+    w.cand_idx = reinterpret_cast<int32_t *>(take(cand));
+    w.list_val = reinterpret_cast<float *>(take(cand));
+    w.list_idx = reinterpret_cast<int32_t *>(take(cand));
+    w.seg = reinterpret_cast<int2 *>(take((size_t)rows * 2 * vs_slices(N) * sizeof(int2)));  // where every slice put its part
+    w.state = reinterpret_cast<VsSelState *>(take((size_t)rows * 2 * sizeof(VsSelState)));
+  }
+  w.bytes = (size_t)(p - base);
+  return w;
+}
+static bool vs_prefilters(int N, int nv, int ns) {
+  return vs_log_group(N, nv < N ? nv : N) >= 0 || vs_log_group(N, ns < N ? ns : N) >= 0;
 }
 
-hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv, int ns,
+size_t vs_index_ws_bytes(int N, int n_heads) { return vs_scratch(N, n_heads, true, nullptr).bytes; }
+
+int vs_index_batch(int N, int n_heads, int nv, int ns, size_t ws_bytes, int batch) {
+  const size_t most = ws_bytes / ((size_t)n_heads * N * 2 * sizeof(float));
+  int nb = (size_t)batch < most ? batch : (int)most;
+  if (nb > 65535 / n_heads) nb = 65535 / n_heads;            // rows are a grid dimension
+  while (nb > 1 && vs_scratch(N, n_heads * nb, vs_prefilters(N, nv, ns), nullptr).bytes > ws_bytes) --nb;
+  return nb < 1 ? 1 : nb;
+}
+
+hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q, int nv, int ns,
                            int32_t *v_idx, int32_t *s_idx, int32_t *cover, uint32_t *cover_bits,
                            int32_t *counts, int cover_words, void *ws, hipStream_t st) {
   const int N = x.N;
@@ -2071,22 +2113,9 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
     if (g == vg.n) { gkv[g] = kv; ++vg.n; }
     vg.slot[g][vg.cnt[g]++] = (uint8_t)i;
   }
-  const int nc = vs_ml_chunks(N);
-  char *p = static_cast<char *>(ws);
-  float *colsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
-  float *diagsum = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * N * sizeof(float));
-  float *ml_part = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * nc * 128 * sizeof(float));
-  float *ml_fin = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * 128 * sizeof(float));
+  const int nc = vs_ml_chunks(N), rows = hl.n * nb;
+  const VsScratch w = vs_scratch(N, rows, nb == 1 || vs_prefilters(N, nv, ns), static_cast<char *>(ws));
   const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
-  float *gmax_v = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
-  float *gmax_s = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * (N / 4) * sizeof(float));
-  const size_t cand_bytes = align256((size_t)hl.n * 2 * cap * sizeof(float));
-  float *cand_val = reinterpret_cast<float *>(p); p += cand_bytes;
-  int32_t *cand_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
-  float *list_val = reinterpret_cast<float *>(p); p += cand_bytes;
-  int32_t *list_idx = reinterpret_cast<int32_t *>(p); p += cand_bytes;
-  int2 *seg = reinterpret_cast<int2 *>(p); p += align256((size_t)hl.n * 2 * n_slices * sizeof(int2));
-  VsSelState *state = reinterpret_cast<VsSelState *>(p);
   // 48 KiB (three workgroups of four waves per CU; registers allow two) and 75 KiB (two per CU)
   auto score = [&](auto pass, auto chunk_keys, size_t lds) -> hipError_t {
     constexpr int P = decltype(pass)::value, C = decltype(chunk_keys)::value;
@@ -2095,8 +2124,8 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((vs_score_kernel<P, C>), dim3(vs_chunks(N, C), vg.n), dim3(64 * VS_GROUP), lds, st, x, hl, vg,
-                       last_q, nc, ml_part, (const float *)ml_fin, colsum, diagsum);
+    hipLaunchKernelGGL((vs_score_kernel<P, C>), dim3(vs_chunks(N, C), vg.n, nb), dim3(64 * VS_GROUP), lds, st, x, hl, vg,
+                       last_q, nc, w.ml_part, (const float *)w.ml_fin, w.colsum, w.diagsum);
     return hipSuccess;
   };
   auto pass1 = [&](auto c) { return score(std::integral_constant<int, 1>{}, c, 3 * VS_TILE_BYTES); };
@@ -2111,28 +2140,28 @@ hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv,
   };
   hipError_t e = by_chunk(vs_ml_chunk_keys(N), pass1);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(vs_combine_kernel, dim3(hl.n), dim3(1024), 0, st, nc, (const float *)ml_part, ml_fin);
-  e = by_chunk(vs_sum_chunk_keys(N, vg.n), pass2);
+  hipLaunchKernelGGL(vs_combine_kernel, dim3(rows), dim3(1024), 0, st, nc, (const float *)w.ml_part, w.ml_fin);
+  e = by_chunk(vs_sum_chunk_keys(N, vg.n * nb), pass2);
   if (e != hipSuccess) return e;
   // top-k of the line scores: prefilter by many workgroups, exact selection on what is left
   const int kv_ = nv < N ? nv : N, ks_ = ns < N ? ns : N;
   const int log_gv = vs_log_group(N, kv_), log_gs = vs_log_group(N, ks_);
   if (log_gv >= 0 || log_gs >= 0)
-    hipLaunchKernelGGL(vs_gmax_kernel, dim3((N + 4095) / 4096, hl.n, 2), dim3(256), 0, st, N, log_gv, log_gs,
-                       (const float *)colsum, (const float *)diagsum, gmax_v, gmax_s);
+    hipLaunchKernelGGL(vs_gmax_kernel, dim3((N + 4095) / 4096, rows, 2), dim3(256), 0, st, N, log_gv, log_gs,
+                       (const float *)w.colsum, (const float *)w.diagsum, w.gmax_v, w.gmax_s);
   const bool prefilter = log_gv >= 0 || log_gs >= 0;
   if (prefilter)
-    hipLaunchKernelGGL(vs_bound_kernel, dim3(hl.n, 2), dim3(1024), 0, st, N, nv, ns, log_gv, log_gs,
-                       (const float *)gmax_v, (const float *)gmax_s, state);
+    hipLaunchKernelGGL(vs_bound_kernel, dim3(rows, 2), dim3(1024), 0, st, N, nv, ns, log_gv, log_gs,
+                       (const float *)w.gmax_v, (const float *)w.gmax_s, w.state);
   if (prefilter)
-    hipLaunchKernelGGL(vs_filter_kernel, dim3(n_slices, hl.n, 2), dim3(256), 0, st, N, cap, n_slices,
-                       (const float *)colsum, (const float *)diagsum, state, cand_val, cand_idx, seg);
+    hipLaunchKernelGGL(vs_filter_kernel, dim3(n_slices, rows, 2), dim3(256), 0, st, N, cap, n_slices,
+                       (const float *)w.colsum, (const float *)w.diagsum, w.state, w.cand_val, w.cand_idx, w.seg);
   auto select = [&](auto held) {
     constexpr int E = decltype(held)::value;
-    hipLaunchKernelGGL((vs_select_kernel<E>), dim3(hl.n, 2), dim3(1024), 0, st, N, nv, ns, (const float *)colsum,
-                       (const float *)diagsum, v_idx, s_idx, cover, cover_bits, counts, cover_words, cap,
-                       prefilter ? n_slices : 0, (const VsSelState *)state, (const float *)cand_val,
-                       (const int32_t *)cand_idx, (const int2 *)seg, list_val, list_idx);
+    hipLaunchKernelGGL((vs_select_kernel<E>), dim3(rows, 2), dim3(1024), 0, st, N, nv, ns, (const float *)w.colsum,
+                       (const float *)w.diagsum, v_idx, s_idx, cover, cover_bits, counts, cover_words, cap,
+                       prefilter ? n_slices : 0, (const VsSelState *)w.state, (const float *)w.cand_val,
+                       (const int32_t *)w.cand_idx, (const int2 *)w.seg, w.list_val, w.list_idx);
   };
   // scores a thread of the selection holds
   if (N <= 8192) select(std::integral_constant<int, 8>{});
@@ -2173,33 +2202,48 @@ size_t bs_index_ws_bytes(int N, int n_heads, int topk) {
   return b;
 }
 
-static __global__ void iota_kernel(int n, int period, int32_t *out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = i % period;
-}
-
-hipError_t launch_build_bs(const QKV &x, const HeadList &hl, int topk, int32_t *blk_idx,
-                           int32_t *blk_cnt, int32_t *order, void *ws, hipStream_t st) {
-  const int NB = x.N / 64;
+static KvMap kv_map(const HeadList &hl, int group) {
   KvMap km;
-  km.n_kv = 0;
+  memset(&km, 0, sizeof(km));
   for (int i = 0; i < hl.n; ++i) {
-    const int kv = hl.h[i] / x.group;
+    const int kv = hl.h[i] / group;
     int j = 0;
     while (j < km.n_kv && km.kv[j] != kv) ++j;
     if (j == km.n_kv) km.kv[km.n_kv++] = kv;
     km.slot_kv[i] = j;
   }
-  for (int i = hl.n; i < MINF_MAX_HEADS; ++i) km.slot_kv[i] = 0;
-  for (int i = km.n_kv; i < MINF_MAX_HEADS; ++i) km.kv[i] = 0;
+  return km;
+}
+
+// The workspace holds pooled K rows per listed head; one set per K/V head and batch element is needed.
+int bs_index_batch(int N, const HeadList &hl, int group, int topk, size_t ws_bytes, int batch) {
+  const int NB = N / 64;
+  if (!bs_fused(NB, topk)) return 1;
+  const size_t most = ws_bytes / ((size_t)kv_map(hl, group).n_kv * bs_rows_padded(NB) * 128 * sizeof(float));
+  const int nb = (size_t)batch < most ? batch : (int)most;
+  return nb < 1 ? 1 : nb;
+}
+
+static __global__ void iota_kernel(int n, int period, int32_t *out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = i % period;
+}
+
+hipError_t launch_build_bs(const QKV &x, int nb, const HeadList &hl, int topk, int32_t *blk_idx,
+                           int32_t *blk_cnt, int32_t *order, void *ws, hipStream_t st) {
+  const int NB = x.N / 64;
+  const KvMap km = kv_map(hl, x.group);
   const int NBp = bs_rows_padded(NB);
   char *p = static_cast<char *>(ws);
   const bool fused = bs_fused(NB, topk);
   float *kpool = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * NBp * 128 * sizeof(float));
   float *qpool = nullptr;
-  if (!fused) { qpool = reinterpret_cast<float *>(p); p += align256((size_t)hl.n * NB * 128 * sizeof(float)); }
+  if (!fused) {                        // nb is 1
+    qpool = reinterpret_cast<float *>(p);
+    p += align256((size_t)hl.n * NB * 128 * sizeof(float));
+  }
   float *scores = reinterpret_cast<float *>(p);
-  hipLaunchKernelGGL(bs_pool_kernel, dim3(NB, (fused ? 0 : hl.n) + km.n_kv), dim3(256), 0, st, x, hl, km, qpool, kpool,
+  hipLaunchKernelGGL(bs_pool_kernel, dim3(NB, (fused ? 0 : hl.n) + km.n_kv, nb), dim3(256), 0, st, x, hl, km, qpool, kpool,
                      NBp);
   if (fused) {
     // pooling of Q, block logits and top-k in one kernel: neither the pooled Q nor anything of size NB x NB is stored
@@ -2208,11 +2252,11 @@ hipError_t launch_build_bs(const QKV &x, const HeadList &hl, int topk, int32_t *
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs_topk_kernel<SEL>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((bs_topk_kernel<SEL>), dim3(hl.n, (NB + 16 * SEL - 1) / (16 * SEL)), dim3(64 * BSF_WAVES), lds,
+      hipLaunchKernelGGL((bs_topk_kernel<SEL>), dim3(hl.n, (NB + 16 * SEL - 1) / (16 * SEL), nb), dim3(64 * BSF_WAVES), lds,
                          st, x, hl, NB, NBp, topk, km, (const float *)kpool, blk_idx, blk_cnt);
       return hipSuccess;
     };
-    const bool few = hl.n * ((NB + 16 * BSF_WAVES - 1) / (16 * BSF_WAVES)) <= BSF_FEW_GROUPS;
+    const bool few = nb * hl.n * ((NB + 16 * BSF_WAVES - 1) / (16 * BSF_WAVES)) <= BSF_FEW_GROUPS;
     const hipError_t e = few ? topk_launch(std::integral_constant<int, BSF_SEL_FEW>{}, bsf_few_lds())
                              : topk_launch(std::integral_constant<int, BSF_WAVES>{}, bsf_lds(BSF_WAVES));
     if (e != hipSuccess) return e;
@@ -2236,10 +2280,10 @@ hipError_t launch_build_bs(const QKV &x, const HeadList &hl, int topk, int32_t *
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs_order_kernel),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(bs_order_kernel, dim3(hl.n), dim3(1024), lds, st, NB, topk, (const int32_t *)blk_idx, order);
+      hipLaunchKernelGGL(bs_order_kernel, dim3(hl.n * nb), dim3(1024), lds, st, NB, topk, (const int32_t *)blk_idx, order);
     }
     else      // longer than the sort holds: natural order
-      hipLaunchKernelGGL(iota_kernel, dim3((hl.n * NB + 255) / 256), dim3(256), 0, st, hl.n * NB, NB, order);
+      hipLaunchKernelGGL(iota_kernel, dim3((nb * hl.n * NB + 255) / 256), dim3(256), 0, st, nb * hl.n * NB, NB, order);
   }
   return hipGetLastError();
 }

@@ -73,22 +73,35 @@ minf_status check_heads(const minf_qkv *x, const int32_t *heads, int32_t n_heads
   return MINF_OK;
 }
 
+// From batch element b on.
 QKV view(const minf_qkv *x, int b) {
   QKV v;
   v.q = static_cast<const bf16_t *>(x->q) + b * x->q_stride[0];
   v.k = static_cast<const bf16_t *>(x->k) + b * x->k_stride[0];
   v.v = x->v ? static_cast<const bf16_t *>(x->v) + b * x->v_stride[0] : nullptr;
   v.o = x->o ? static_cast<bf16_t *>(x->o) + b * x->o_stride[0] : nullptr;
-  v.q_sh = x->q_stride[1]; v.q_st = x->q_stride[2];
-  v.k_sh = x->k_stride[1]; v.k_st = x->k_stride[2];
-  v.v_sh = x->v_stride[1]; v.v_st = x->v_stride[2];
-  v.o_sh = x->o_stride[1]; v.o_st = x->o_stride[2];
+  v.q_sb = x->q_stride[0]; v.q_sh = x->q_stride[1]; v.q_st = x->q_stride[2];
+  v.k_sb = x->k_stride[0]; v.k_sh = x->k_stride[1]; v.k_st = x->k_stride[2];
+  v.v_sb = x->v_stride[0]; v.v_sh = x->v_stride[1]; v.v_st = x->v_stride[2];
+  v.o_sb = x->o_stride[0]; v.o_sh = x->o_stride[1]; v.o_st = x->o_stride[2];
   v.N = x->seq_len;
   v.group = x->n_q_heads / x->n_kv_heads;
   v.n_q = x->n_q_heads;
   v.scale = x->softmax_scale > 0.f ? x->softmax_scale : 1.0f / sqrtf((float)x->head_dim);
   v.c_log2 = v.scale * 1.4426950408889634f;
   return v;
+}
+
+// Batch elements that may run at the same time: outputs laid over each other are written in batch order.
+int outputs_apart(const minf_qkv *x) { return x->o_stride[0] == 0 ? 1 : x->batch; }
+
+// Calls launch(first batch element, how many) for groups of at most `most` elements.
+template <class Launch>
+minf_status over_batch(const minf_qkv *x, int most, Launch launch) {
+  if (most > MAX_BATCH_LAUNCH) most = MAX_BATCH_LAUNCH;
+  for (int b = 0; b < x->batch; b += most)
+    if (launch(b, x->batch - b < most ? x->batch - b : most) != hipSuccess) return MINF_ERR_HIP;
+  return MINF_OK;
 }
 
 inline minf_status from_hip(hipError_t e) { return e == hipSuccess ? MINF_OK : MINF_ERR_HIP; }
@@ -144,20 +157,18 @@ static minf_status build_vs_common(const minf_qkv *x, const int32_t *heads, int3
     if (need > (size_t)MINF_NOALLOC_SCRATCH_BYTES) return MINF_ERR_WORKSPACE;
     ws = scratch_on_current_device();
     if (!ws) return MINF_ERR_HIP;
+    ws_bytes = (size_t)MINF_NOALLOC_SCRATCH_BYTES;
   } else {
     if (!ws || ws_bytes < need) return MINF_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return MINF_ERR_WORKSPACE;
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  for (int b = 0; b < x->batch; ++b) {
+  return over_batch(x, vs_index_batch(x->seq_len, n_heads, nv, ns, ws_bytes, x->batch), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
-    hipError_t e = launch_build_vs(view(x, b), hl, last_q, nv, ns, out->v_idx + r * nv,
-                                   out->s_idx + r * ns, out->cover + r * ns * 2,
-                                   out->cover_bits + r * out->cover_words, out->counts + r * 4,
-                                   out->cover_words, ws, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+    return launch_build_vs(view(x, b), nb, hl, last_q, nv, ns, out->v_idx + r * nv, out->s_idx + r * ns,
+                           out->cover + r * ns * 2, out->cover_bits + r * out->cover_words, out->counts + r * 4,
+                           out->cover_words, ws, st);
+  });
 }
 
 minf_status minf_build_vs_index(const minf_qkv *x, const int32_t *heads, int32_t n_heads,
@@ -198,13 +209,11 @@ minf_status minf_build_bs_index(const minf_qkv *x, const int32_t *heads, int32_t
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return MINF_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int64_t NB = x->seq_len / MINF_BLOCK;
-  for (int b = 0; b < x->batch; ++b) {
+  return over_batch(x, bs_index_batch(x->seq_len, hl, x->n_q_heads / x->n_kv_heads, topk, ws_bytes, x->batch), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
-    hipError_t e = launch_build_bs(view(x, b), hl, topk, out->blk_idx + r * NB * topk,
+    return launch_build_bs(view(x, b), nb, hl, topk, out->blk_idx + r * NB * topk,
                                    out->blk_cnt + r * NB, out->order ? out->order + r * NB : nullptr, ws, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+  });
 }
 
 minf_status minf_ashape_attn(const minf_qkv *x, const int32_t *heads, int32_t n_heads,
@@ -217,11 +226,9 @@ minf_status minf_ashape_attn(const minf_qkv *x, const int32_t *heads, int32_t n_
   n_init = n_init < x->seq_len ? n_init : x->seq_len;
   n_local = n_local < x->seq_len ? n_local : x->seq_len;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  for (int b = 0; b < x->batch; ++b) {
-    hipError_t e = launch_ashape(view(x, b), hl, n_init, n_local, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
+    return launch_ashape(view(x, b), nb, hl, n_init, n_local, st);
+  });
 }
 
 minf_status minf_dense_attn(const minf_qkv *x, const int32_t *heads, int32_t n_heads,
@@ -245,14 +252,12 @@ minf_status minf_vs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
       (uint64_t)x->seq_len * (uint64_t)x->v_stride[2] * 2u >= (1ull << 32))
     return MINF_ERR_SHAPE;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  for (int b = 0; b < x->batch; ++b) {
+  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
-    hipError_t e = launch_vs(view(x, b), hl, idx->v_idx + r * idx->nv, idx->cover + r * idx->ns * 2,
+    return launch_vs(view(x, b), nb, hl, idx->v_idx + r * idx->nv, idx->cover + r * idx->ns * 2,
                              idx->cover_bits + r * idx->cover_words, idx->counts + r * 4, idx->nv,
                              idx->ns, idx->cover_words, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+  });
 }
 
 minf_status minf_bs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_heads,
@@ -266,13 +271,11 @@ minf_status minf_bs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
   if (idx->topk < 1) return MINF_ERR_BUDGET;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int64_t NB = x->seq_len / MINF_BLOCK;
-  for (int b = 0; b < x->batch; ++b) {
+  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
-    hipError_t e = launch_bs(view(x, b), hl, idx->blk_idx + r * NB * idx->topk, idx->blk_cnt + r * NB,
-                             idx->order ? idx->order + r * NB : nullptr, idx->topk, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+    return launch_bs(view(x, b), nb, hl, idx->blk_idx + r * NB * idx->topk, idx->blk_cnt + r * NB,
+                     idx->order ? idx->order + r * NB : nullptr, idx->topk, st);
+  });
 }
 
 minf_status minf_vs_bs_attn(const minf_qkv *x, const int32_t *vs_heads, int32_t n_vs, const minf_vs_index *vs,
@@ -296,15 +299,13 @@ minf_status minf_vs_bs_attn(const minf_qkv *x, const int32_t *vs_heads, int32_t 
       if (vs_heads[i] == bs_heads[j]) return MINF_ERR_SHAPE;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int64_t NB = x->seq_len / MINF_BLOCK;
-  for (int b = 0; b < x->batch; ++b) {
+  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
     const int64_t rv = (int64_t)b * n_vs, rb = (int64_t)b * n_bs;
-    hipError_t e = launch_vs_bs(view(x, b), hv, vs->v_idx + rv * vs->nv, vs->cover + rv * vs->ns * 2,
-                                vs->cover_bits + rv * vs->cover_words, vs->counts + rv * 4, vs->nv, vs->ns,
-                                vs->cover_words, hb, bs->blk_idx + rb * NB * bs->topk, bs->blk_cnt + rb * NB,
-                                bs->order ? bs->order + rb * NB : nullptr, bs->topk, st);
-    if (e != hipSuccess) return MINF_ERR_HIP;
-  }
-  return MINF_OK;
+    return launch_vs_bs(view(x, b), nb, hv, vs->v_idx + rv * vs->nv, vs->cover + rv * vs->ns * 2,
+                        vs->cover_bits + rv * vs->cover_words, vs->counts + rv * 4, vs->nv, vs->ns,
+                        vs->cover_words, hb, bs->blk_idx + rb * NB * bs->topk, bs->blk_cnt + rb * NB,
+                        bs->order ? bs->order + rb * NB : nullptr, bs->topk, st);
+  });
 }
 
 }  // extern "C"

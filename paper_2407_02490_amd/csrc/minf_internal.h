@@ -12,13 +12,13 @@ namespace minf {
 
 typedef __bf16 bf16_t;
 
-// Per-call view of Q/K/V/O for one batch element (device pointers, strides in
-// elements).  c_log2 = softmax_scale * log2(e): logits are scaled into the
+// Per-call view of Q/K/V/O: the first of the launch's batch elements (device pointers, strides in
+// elements; _sb: to the next batch element).  c_log2 = softmax_scale * log2(e): logits are scaled into the
 // base-2 domain so that exp is a bare v_exp_f32.
 struct QKV {
   const bf16_t *q, *k, *v;
   bf16_t *o;
-  int64_t q_sh, q_st, k_sh, k_st, v_sh, v_st, o_sh, o_st;
+  int64_t q_sb, q_sh, q_st, k_sb, k_sh, k_st, v_sb, v_sh, v_st, o_sb, o_sh, o_st;
   int32_t N, group, n_q;              // n_q: query heads of the layer (not of the call's list)
   float scale, c_log2;
 };
@@ -129,15 +129,26 @@ __device__ inline bool decode_wg(const Sched &s, int &slot, int &blk) {
   return decode_item(s, blockIdx.x, slot, blk);
 }
 
-// attention launches (attn_kernels.hip)
-hipError_t launch_ashape(const QKV &x, const HeadList &hl, int n_init, int n_local, hipStream_t st);
-hipError_t launch_bs(const QKV &x, const HeadList &hl, const int32_t *blk_idx, const int32_t *blk_cnt,
+// The batch elements of a call run in one launch: grid dimension y of the attention kernels, z of the index
+// kernels.  A launch per element leaves the chip to drain, and the index kernels of short prompts do not
+// fill it: two prompts of 40256 tokens, 16 heads, 3 % of 3.65 ms; pairs of short ones 188 -> 139 us and
+// 147 -> 112.  The kernels are chosen as for one element, so an element has the same bits alone.  Index row of (batch element b, list slot s) in the index arrays and the
+// workspace: b n + s, n listed heads.
+constexpr int MAX_BATCH_LAUNCH = 16384;             // batch elements per launch (grid limit 65535)
+__device__ inline QKV at_batch(QKV x, int b) {
+  x.q += b * x.q_sb; x.k += b * x.k_sb; x.v += b * x.v_sb; x.o += b * x.o_sb;
+  return x;
+}
+
+// attention launches (attn_kernels.hip); nb: batch elements
+hipError_t launch_ashape(const QKV &x, int nb, const HeadList &hl, int n_init, int n_local, hipStream_t st);
+hipError_t launch_bs(const QKV &x, int nb, const HeadList &hl, const int32_t *blk_idx, const int32_t *blk_cnt,
                      const int32_t *order, int topk, hipStream_t st);
-hipError_t launch_vs(const QKV &x, const HeadList &hl, const int32_t *v_idx, const int32_t *cover,
+hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_idx, const int32_t *cover,
                      const uint32_t *cover_bits, const int32_t *counts, int nv, int ns,
                      int cover_words, hipStream_t st);
 
-hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,
+hipError_t launch_vs_bs(const QKV &x, int nb, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,
                         const uint32_t *cover_bits, const int32_t *counts, int nv, int ns, int cover_words,
                         const HeadList &hb, const int32_t *blk_idx, const int32_t *blk_cnt, const int32_t *order,
                         int topk, hipStream_t st);
@@ -145,12 +156,15 @@ hipError_t launch_vs_bs(const QKV &x, const HeadList &hv, const int32_t *v_idx, 
 // index launches (index_kernels.hip)
 size_t vs_index_ws_bytes(int N, int n_heads);
 size_t bs_index_ws_bytes(int N, int n_heads, int topk);
-hipError_t launch_build_vs(const QKV &x, const HeadList &hl, int last_q, int nv, int ns,
+// batch elements (1 .. batch) whose rows a workspace of at least the bytes above holds at a time
+int vs_index_batch(int N, int n_heads, int nv, int ns, size_t ws_bytes, int batch);
+int bs_index_batch(int N, const HeadList &hl, int group, int topk, size_t ws_bytes, int batch);
+hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q, int nv, int ns,
                            int32_t *v_idx, int32_t *s_idx, int32_t *cover, uint32_t *cover_bits,
                            int32_t *counts, int cover_words, void *ws, hipStream_t st);
 hipError_t launch_vs_lines(int N, int rows, int nv, int ns, const int32_t *s_idx, int32_t *cover,
                            uint32_t *cover_bits, int32_t *counts, int cover_words, hipStream_t st);
-hipError_t launch_build_bs(const QKV &x, const HeadList &hl, int topk, int32_t *blk_idx,
+hipError_t launch_build_bs(const QKV &x, int nb, const HeadList &hl, int topk, int32_t *blk_idx,
                            int32_t *blk_cnt, int32_t *order, void *ws, hipStream_t st);
 
 }  // namespace minf

@@ -258,3 +258,45 @@ def test_common_part_of_long_runs(B, rng, Sl, layout, kind):
         want = O.vs_attention(to_f64(q0[h]), to_f64(k0[0]), to_f64(v0[0]), Vl, Sl, Bm=64)
         for b in range(0, 65):
             assert_close_rows(o[h, 64 * b:64 * b + 64], want[64 * b:64 * b + 64], f"head {h} block {b}")
+
+
+@pytest.mark.parametrize("layout", ["head", "token"])
+@pytest.mark.parametrize("nq,nkv,N", [(2, 1, 704), (4, 1, 6208), (3, 3, 8256), (12, 2, 12352)])
+def test_batch_elements_are_the_calls_alone(B, nq, nkv, N, layout):
+    """Three prompts in one call: indices and outputs have the bits of three calls, with workspaces of
+    the reported size (which hold one, two or three elements at a time) and larger ones."""
+    nb, heads = 3, list(range(nq))[::-1]
+    x = [random_qkv(300 + b, nq, nkv, N) for b in range(nb)]
+    q, k, v = (torch.stack([e[t] for e in x]) for t in range(3))
+    if layout == "token":
+        q, k, v = (t.transpose(1, 2).contiguous().transpose(1, 2) for t in (q, k, v))
+    nv, ns, topk = min(300, N), min(2000, N), 20
+
+    def layer(q, k, v, n, extra):
+        o = [torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+        vi, bi = B.alloc_vs_index(n * nq, nv, ns, N), B.alloc_bs_index(n * nq, N, topk)
+        for t in (vi.v_idx, vi.s_idx, vi.cover, vi.cover_bits, bi.blk_idx, bi.blk_cnt, bi.order):
+            t.fill_(-7)
+        B.minf_build_vs_index(q, k, heads, 64, nv, ns, vi, torch.empty(
+            extra * B.minf_vs_index_workspace_bytes(q, k, nq, 64), dtype=torch.uint8, device="cuda"))
+        B.minf_build_bs_index(q, k, heads, topk, bi, torch.empty(
+            extra * B.minf_bs_index_workspace_bytes(q, k, nq, topk), dtype=torch.uint8, device="cuda"))
+        B.minf_vs_attn(q, k, v, o[0], heads, vi)
+        B.minf_bs_attn(q, k, v, o[1], heads, bi)
+        B.minf_ashape_attn(q, k, v, o[2], heads, 100, 500)
+        B.minf_dense_attn(q, k, v, o[3], heads)
+        torch.cuda.synchronize()
+        runs = vi.counts[:, 2].tolist()
+        return ([vi.v_idx, vi.s_idx, vi.cover_bits, vi.counts, bi.blk_idx, bi.blk_cnt, bi.order] +
+                [vi.cover[r, :c] for r, c in enumerate(runs)], o)
+
+    alone = [layer(q[b], k[b], v[b], 1, 1) for b in range(nb)]
+    for extra in (1, 4):
+        idx, out = layer(q, k, v, nb, extra)
+        for b in range(nb):
+            for t, (got, want) in enumerate(zip(idx[:7], alone[b][0][:7])):
+                assert torch.equal(got[b * nq:(b + 1) * nq], want), f"index array {t} of element {b}"
+            for r in range(nq):
+                assert torch.equal(idx[7 + b * nq + r], alone[b][0][7 + r]), f"runs of element {b}, head {r}"
+            for t, (got, want) in enumerate(zip(out, alone[b][1])):
+                assert torch.equal(got[b].view(torch.int16), want.view(torch.int16)), f"output {t} of element {b}"
