@@ -2909,7 +2909,7 @@ static hipError_t set_lds(const void *fn, size_t bytes) {
 hipError_t launch_ashape(const QKV &x, int nb, const HeadList &hl, int n_init, int n_local, hipStream_t st) {
   const int NB = x.N / BQ, NSB = (NB + 3) / 4;
   if (ashape_split_pays(x.n_q, x.N, n_local)) {
-    const Sched s = make_sched(hl, x.group, NB);
+    const Sched s = make_sched(hl, x.group, NB, split_order(x.N));
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(ashape_split_kernel);
     hipError_t e = set_lds(fn, lds);
@@ -2918,7 +2918,7 @@ hipError_t launch_ashape(const QKV &x, int nb, const HeadList &hl, int n_init, i
                        n_local, s);
     return hipGetLastError();
   }
-  const Sched s = make_sched(hl, x.group, NSB);
+  const Sched s = make_sched(hl, x.group, NSB, ashape_order(x.N));
   const size_t lds = 8 * TILE_BYTES;   // four K and four V slots
   const void *fn = reinterpret_cast<const void *>(ashape_kernel);
   hipError_t e = set_lds(fn, lds);
@@ -2930,8 +2930,9 @@ hipError_t launch_ashape(const QKV &x, int nb, const HeadList &hl, int n_init, i
 hipError_t launch_bs(const QKV &x, int nb, const HeadList &hl, const int32_t *blk_idx, const int32_t *blk_cnt,
                      const int32_t *order, int topk, hipStream_t st) {
   const int NB = x.N / BQ;
-  const Sched s = make_sched(hl, x.group, NB);
-  if (bs_split_pays(x.n_q, x.N, topk)) {
+  const bool split = bs_split_pays(x.n_q, x.N, topk);
+  const Sched s = make_sched(hl, x.group, NB, split ? split_order(x.N) : bs_order(x.N));
+  if (split) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(bs_split_kernel);
     hipError_t e = set_lds(fn, lds);
@@ -2967,8 +2968,9 @@ hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_
                        cover_bits, counts, nv, ns, cover_words, s);
     return hipGetLastError();
   }
-  const Sched s = make_sched(hl, x.group, NB);
-  if (vs_split_pays(x.n_q, x.N, nv, ns)) {
+  const bool split = vs_split_pays(x.n_q, x.N, nv, ns);
+  const Sched s = make_sched(hl, x.group, NB, split ? split_order(x.N) : vs_order(x.N, false));
+  if (split) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(vs_split_kernel);
     hipError_t e = set_lds(fn, lds);
@@ -2978,7 +2980,7 @@ hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_
     return hipGetLastError();
   }
   if (vs_share_pays(x.N, ns)) {
-    const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4);
+    const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4, vs_order(x.N, true));
     const size_t lds = 4 * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(vs_share_kernel);
     hipError_t e = set_lds(fn, lds);

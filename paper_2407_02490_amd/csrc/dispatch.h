@@ -100,5 +100,38 @@ inline bool ashape_split_pays(int n_q, int N, int n_local) {
   return items <= 512 || (n_local >= N && N >= 4096 && items <= 1024);
 }
 
+// Order of a launch's work items (minf_internal.h: ORDER_*).  apart: chunks that are equal and 2, 4 or 8
+// get XCDs of their own; together: the largest number of other chunks that are mixed; round: workgroups an
+// XCD holds, if a chunk that fills whole rounds of them by itself loses by either (0: it does not).
+// Chunk after chunk -> apart, us (query heads / K/V heads, tokens):
+//   dense   8/8 4K 72 -> 52, 8K 191 -> 163, 16K 673 -> 456, 32K 2295 -> 1746; 4/4 32K 1234 -> 884; 16/4 8K 301 -> 238;
+//           32/8 4K 171 -> 133, 8K 514 -> 467, 20K 2779 -> 2712; 8/2 8K..32K, 16/4 16K, 4/4 64K the same;
+//           whole rounds of four-wave blocks (or nearly): 16/4 4K 96.7 -> 98.6; VS 16/4 3200 tokens, layer 104 -> 109
+//   A-shape 32/8 4K 172 -> 133, 8K 458 -> 420, 32K 2215 -> 2162, 64K 4864 -> 4548, 128K 9750 -> 9398; 8/4 11K 249 -> 188;
+//           16/4 64K 2331 -> 2263; worst 6/2 16K 260 -> 265
+//   BS      32/8 4K 198 -> 147, 8K 578 -> 540, 16K 1417 -> 1391, 32K 3140 -> 3091; 8/8 20K 578 -> 469, 32K 924 -> 832;
+//           8/2 16K 391 -> 386, 32K 814 -> 815, 64K 1710 -> 1797; 4/4 64K 959 -> 990
+//   VS, four blocks per workgroup: 32/8 4K 182 -> 135, 8K 517 -> 467; 16/8 13K 676 -> 581; 8/8 16K 599 -> 452, 20K 733 -> 678;
+//           16/8 26K 1871 -> 1970; 8/8 64K 3430 -> 3818; whole rounds: 16/4 16K 869 -> 867, 32K 2768 -> 2949
+//   VS, others: 8/8 4K 72 -> 54, 8K 189 -> 164; 4/4 8K 111 -> 87; (500, 1500) 16/4 8K 320 -> 257, 32/8 8K 518 -> 500,
+//           16K 1194 -> 1256; 8/8 32K 731 -> 783
+// Chunk after chunk -> together, 12 heads of 3 K/V heads unless stated:
+//   dense 4K 84 -> 77, 8K 217 -> 207, 16K 768 -> 698; A-shape 4K 85 -> 77, 8K..64K within 1 %
+//   BS    4K 88 -> 81, 8K 243 -> 212, 16K 591 -> 567, 32K 1226 -> 1372; 8 chunks of 16K 413 -> 529
+//   VS, four blocks per workgroup: 8K 217 -> 205, 16K 735 -> 681, 32K 2213 -> 2134; others: 4K 91 -> 89,
+//         (500, 1500) 8K 220 -> 236; four-wave blocks of 7 chunks 8K 318 -> 328 (mixed layer)
+struct OrderRule {
+  int apart, together, round;
+};
+constexpr int XCD_CUS = 32;                        // workgroups of 128 KiB and more that an XCD holds
+inline OrderRule split_order(int N) {              // four waves per block, any kind; three K/V heads of 16K fit the L2s
+  return OrderRule{N <= 16384, 49152 / N, XCD_CUS};
+}
+inline OrderRule vs_order(int N, bool share) {
+  return share ? OrderRule{N <= 20480, N <= 32768 ? 64 : 0, XCD_CUS} : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
+}
+inline OrderRule bs_order(int N) { return OrderRule{N <= 32768, N <= 16384 ? 49152 / N : 0, 0}; }
+inline OrderRule ashape_order(int N) { return OrderRule{N <= 131072, N <= 65536 ? 64 : 0, 0}; }
+
 }  // namespace minf
 #endif

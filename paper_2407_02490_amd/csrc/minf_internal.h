@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.h"
 #include "minf.h"
 
 namespace minf {
@@ -44,14 +45,21 @@ struct HeadList {
 // the same K/V head at once, and the K/V heads in flight stay few enough for the
 // memory-side cache (measured at 1M tokens: chunks that mix K/V heads cost 6% on
 // Vertical-Slash and 11% on Block-Sparse attention).
+// That is ORDER_BY_CHUNK.  Its price is the end of the launch: the heaviest blocks of the last chunk
+// start last.  Where the caches hold the K/V heads anyway, the blocks of all heads are taken heaviest
+// first: ORDER_APART gives every one of 2, 4 or 8 equal chunks its own XCDs (whose L2s then see one K/V
+// head, or two), ORDER_TOGETHER goes through all heads at every block, for other lists.  OrderRule
+// (dispatch.h) says where which pays.  No influence on the results.
+enum { ORDER_BY_CHUNK = 0, ORDER_APART = 1, ORDER_TOGETHER = 2 };
 struct Sched {
   int32_t n_heads, n_blk, stripe, ls;   // ls = stripes per XCD per chunk
   int32_t per_xcd;                      // workgroups per XCD (grid = 8 * per_xcd)
+  int32_t order, apart;                 // ORDER_*; XCDs per chunk of ORDER_APART
   uint8_t cstart[MINF_MAX_HEADS];       // per list slot: first slot of its chunk
   uint8_t csize[MINF_MAX_HEADS];        // per list slot: size of its chunk
 };
 constexpr int SCHED_MAX_CHUNK = 8;
-inline Sched make_sched(const HeadList &hl, int group, int n_blk) {
+inline Sched make_sched(const HeadList &hl, int group, int n_blk, const OrderRule &rule = OrderRule{0, 0, 0}) {
   Sched s;
   s.n_heads = hl.n;
   s.n_blk = n_blk;
@@ -61,6 +69,10 @@ inline Sched make_sched(const HeadList &hl, int group, int n_blk) {
   s.ls = (n_stripes + 7) / 8;
   s.per_xcd = s.ls * s.stripe * hl.n;      // sum over chunks of ls * stripe * chunk size
   for (int i = 0; i < MINF_MAX_HEADS; ++i) s.cstart[i] = s.csize[i] = 0;
+  s.order = ORDER_BY_CHUNK;
+  s.apart = 0;
+  int chunks = 0;
+  bool equal = true, whole = rule.round > 0;
   for (int i = 0; i < hl.n;) {
     int j = i + 1;
     while (j < hl.n && j - i < SCHED_MAX_CHUNK && hl.h[j] / group == hl.h[i] / group) ++j;
@@ -68,7 +80,23 @@ inline Sched make_sched(const HeadList &hl, int group, int n_blk) {
       s.cstart[t] = (uint8_t)i;
       s.csize[t] = (uint8_t)(j - i);
     }
+    ++chunks;
+    equal = equal && j - i == s.csize[0];
+    if (whole) {                        // the chunk's workgroups per XCD: whole rounds, or a last one nearly full
+      const int rest = s.ls * s.stripe * (j - i) % rule.round;
+      whole = rest == 0 || 4 * rest > 3 * rule.round;
+    }
     i = j;
+  }
+  if (chunks < 2 || whole) return s;
+  if (equal && 8 % chunks == 0) {
+    if (!rule.apart) return s;
+    s.order = ORDER_APART;
+    s.apart = 8 / chunks;
+    s.per_xcd = (n_blk + s.apart - 1) / s.apart * s.csize[0];
+  } else if (chunks <= rule.together) {
+    s.order = ORDER_TOGETHER;
+    s.per_xcd = (n_blk + 7) / 8 * hl.n;
   }
   return s;
 }
@@ -77,6 +105,16 @@ inline Sched make_sched(const HeadList &hl, int group, int n_blk) {
 __host__ __device__ inline bool decode_item(const Sched &s, int hw, int &slot, int &blk) {
   const int xcd = hw & 7;
   int seq = hw >> 3;
+  if (s.order != ORDER_BY_CHUNK) {
+    // `n` XCDs take the blocks of `heads` slots in serpentine order, the heaviest block of all heads first
+    const bool apart = s.order == ORDER_APART;
+    const int n = apart ? s.apart : 8, heads = apart ? s.csize[0] : s.n_heads;
+    const int c = xcd / n, sub = xcd - c * n, r = seq / heads;
+    slot = c * heads + seq - r * heads;
+    const int rank = r * n + ((r & 1) ? n - 1 - sub : sub);
+    blk = s.n_blk - 1 - rank;
+    return rank < s.n_blk;
+  }
   // every head contributes ls * stripe items per XCD, so the chunk follows from the head position
   const int per_head = s.ls * s.stripe;
   const int hpos = seq / per_head;

@@ -113,8 +113,46 @@ static int check_wide(const std::vector<int> &ha, const std::vector<int> &hb, in
   return 0;
 }
 
+// Every order of the items: each exactly once, inside the grid; equal chunks apart keep to their XCDs.
+static int check_order(const std::vector<int> &heads, int group, int n_blk, const OrderRule &rule, int order) {
+  HeadList hl;
+  memset(&hl, 0, sizeof(hl));
+  hl.n = (int)heads.size();
+  for (int i = 0; i < hl.n; ++i) hl.h[i] = heads[i];
+  const Sched s = make_sched(hl, group, n_blk, rule);
+  if (s.order != order) { printf("FAIL order %d instead of %d\n", s.order, order); return 1; }
+  std::vector<int> seen((size_t)hl.n * n_blk, 0), last(8, n_blk);
+  for (int hw = 0; hw < s.per_xcd * 8; ++hw) {
+    int slot = -1, blk = -1;
+    if (!decode_item(s, hw, slot, blk)) continue;
+    if (slot < 0 || slot >= hl.n || blk < 0 || blk >= n_blk) { printf("FAIL order out of range\n"); return 1; }
+    ++seen[(size_t)slot * n_blk + blk];
+    if (order == ORDER_BY_CHUNK) continue;
+    if (blk > last[hw & 7]) { printf("FAIL order: a heavier block after a lighter one\n"); return 1; }
+    last[hw & 7] = blk;
+    if (order == ORDER_APART && (hw & 7) / s.apart != s.cstart[slot] / s.csize[0]) { printf("FAIL order: XCD\n"); return 1; }
+  }
+  for (int n : seen)
+    if (n != 1) { printf("FAIL order %d: item seen %d times\n", order, n); return 1; }
+  printf("ok order %d items %zu\n", order, seen.size());
+  return 0;
+}
+
 int main() {
   int bad = 0;
+  const OrderRule any{1, 64, 0}, rounds{1, 64, 32}, apart_only{1, 2, 0};
+  for (int nb : {1, 2, 7, 8, 9, 63, 64, 257}) {
+    bad |= check_order({0, 4}, 4, nb, any, ORDER_APART);
+    bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15}, 4, nb, any, ORDER_APART);
+    bad |= check_order({7, 6, 5, 4, 3, 2, 1, 0}, 1, nb, any, ORDER_APART);
+    bad |= check_order({0, 1, 2, 4, 5}, 4, nb, any, ORDER_TOGETHER);
+    bad |= check_order({0, 4, 8}, 4, nb, any, ORDER_TOGETHER);
+    bad |= check_order({0, 4, 8}, 4, nb, apart_only, ORDER_BY_CHUNK);
+    bad |= check_order({0, 1, 2}, 4, nb, any, ORDER_BY_CHUNK);             // one K/V head
+    bad |= check_order({0, 4}, 4, nb, OrderRule{0, 0, 0}, ORDER_BY_CHUNK);
+  }
+  bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7}, 4, 64, rounds, ORDER_BY_CHUNK);   // 8 blocks x 4 heads an XCD
+  bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7}, 4, 48, rounds, ORDER_APART);
   for (int nb : {1, 4, 7, 33, 128})
     for (int take = 0; take < 3; ++take) {      // (shared, shared), (shared, each), (each, shared); four blocks: nb / 4
       bad |= check_wide({0, 1, 2, 4, 5, 6}, {3, 7}, 4, nb, nb, take == 2, take == 1);
