@@ -1539,11 +1539,9 @@ __global__ __launch_bounds__(256) void bs_select_kernel(int NB, int slot0, int t
 // or, where that would leave CUs idle, two of them do and all eight pool the 32 blocks' Q
 // (BSF_FEW_GROUPS).
 constexpr int BSF_WAVES = 8, BSF_SEL_FEW = 2;
-// Workgroups of 128 blocks that leave at least half of the 256 CUs idle.  Index build, all eight waves
-// selecting -> two, us: 8 heads of 313 blocks (24 workgroups) 125 -> 73 (top-k kernel 109 -> 61; 88 when
-// the two selecting waves pool alone), of 1024 (64) 289 -> 174, of 2048 (128) 470 -> 340; 32 heads of
-// 512 blocks (128) 208 -> 165; 1 head of 16384 (128) 2153 -> 1421.  Full chips gain nothing from the
-// shared pooling: 32 heads of 2048 blocks 620 -> 641 (top-k kernel).
+// Workgroups of 128 blocks that leave at least half of the 256 CUs idle (rows that bs_rows_kernel does not
+// take).  Index build, all eight waves selecting -> two: 1 head of 16384 blocks (128 workgroups) 2153 ->
+// 1421 us.  Full chips gain nothing from the shared pooling: 32 heads of 2048 blocks 620 -> 641 (top-k kernel).
 constexpr int BSF_FEW_GROUPS = 128;
 constexpr int BSF_CAP = 160;                        // candidates a row can hold
 constexpr int BSF_PITCH = 164;                      // entries between rows: a multiple of 4 (16-byte reads)
@@ -1982,6 +1980,125 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
   }
 }
 
+// The same selection for rows of up to BSR_MAX blocks whose logits fit LDS: a workgroup of 16 waves takes
+// 16 query blocks of one head.  Wave w pools block w; then the waves share the key blocks, 16 at a time
+// (logits bit for bit those of bs_topk_kernel), and put the 16 rows of logits into LDS; then wave w
+// selects row w, held in registers, by bisection on the order keys (counts by ballot), and writes the kept
+// blocks in order.  Bound by latency: one pooling, one or a few rounds of loads and MFMAs, one bisection of
+// about 20 counts, where bs_topk_kernel walks the key tiles one after the other with two selecting waves
+// and cuts its candidate lists on the way.  Index build with bs_topk_kernel -> with this one, top-100, us:
+// 1 head of 128 blocks 32 -> 21, 313 blocks 67 -> 26, 1024: 160 -> 63, 2048: 234 -> 100; 8 heads of 313 blocks
+// 72 -> 30, 2048: 338 -> 223; 32 heads of 128 blocks 42 -> 29, 512: 166 -> 113, 1024: 371 -> 280, 2048 (4096 workgroups,
+// one per CU at a time): 674 -> 763; top-37, whose lists are cut less often: 16 heads of 2048 (2048 workgroups)
+// 401 -> 396, 32 heads of 1024 (2048) 278 -> 275, of 2048 516 -> 752.
+constexpr int BSR_MAX = 2048, BSR_ROWS = 16, BSR_MAX_GROUPS = 2048;
+constexpr size_t bsr_lds(int NB) {                  // means; partial sums of the pooling, then the logits
+  const size_t part = (size_t)BSR_ROWS * 16 * BSF_POOL_PITCH, logits = (size_t)BSR_ROWS * ((NB + 63) / 64 * 64 + 16);
+  return (BSR_ROWS * BSF_POOL_PITCH + (part > logits ? part : logits)) * sizeof(float);
+}
+template <int E>                                    // logits a lane holds of its row: NB <= 64 E
+__global__ __launch_bounds__(64 * BSR_ROWS) void bs_rows_kernel(QKV x, HeadList hl, int NB, int NBp, int topk, KvMap km,
+                                                                const float *kpool, int32_t *blk_idx,
+                                                                int32_t *blk_cnt) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  float *mean = reinterpret_cast<float *>(lds), *work = mean + BSR_ROWS * BSF_POOL_PITCH;
+  const int slot = blockIdx.x;
+  const int64_t list0 = (int64_t)(slot + blockIdx.z * gridDim.x) * NB;
+  const int R0 = (gridDim.y - 1 - blockIdx.y) * BSR_ROWS;    // the longest rows of every head first
+  const int lane = threadIdx.x & 63, n = lane & 15, hq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  bsf_pool_blocks(x.q + blockIdx.z * x.q_sb + hl.h[slot] * x.q_sh, x.q_st, R0 + wave, 1, NB,
+                  work + 16 * wave * BSF_POOL_PITCH, mean + wave * BSF_POOL_PITCH, lane);
+  __syncthreads();
+  float q[32];                                               // Q_hat[R0 + n][32 hq + j]
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float4 e = *reinterpret_cast<const float4 *>(mean + n * BSF_POOL_PITCH + 32 * hq + 4 * j);
+    q[4 * j] = e.x; q[4 * j + 1] = e.y; q[4 * j + 2] = e.z; q[4 * j + 3] = e.w;
+  }
+  // (the partial sums, which the logits overwrite, were last read before the barrier)
+  const int pitch = (NB + 63) / 64 * 64 + 16;
+  const int n_half = min(R0 + BSR_ROWS - 1, NB - 1) / 16 + 1;   // groups of 16 key blocks with a causal one
+  const float *kr = kpool + ((int64_t)(blockIdx.z * km.n_kv + km.slot_kv[slot]) * NBp + n) * 128 + 32 * hq;
+  float4 a[8];
+  auto load = [&](int t) {                                   // kpool is padded to whole groups
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = *reinterpret_cast<const float4 *>(kr + (int64_t)t * (16 * 128) + 4 * i);
+  };
+  if (wave < n_half) load(wave);
+  for (int t = wave; t < n_half; t += BSR_ROWS) {
+    f32x4v c0 = f32x4v{0.f, 0.f, 0.f, 0.f}, c1 = c0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, q[4 * i], c0, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].y, q[4 * i + 1], c1, 0, 0, 0);
+      c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].z, q[4 * i + 2], c0, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].w, q[4 * i + 3], c1, 0, 0, 0);
+    }
+    if (t + BSR_ROWS < n_half) load(t + BSR_ROWS);
+    // register e: key block 16 t + 4 hq + e, query block R0 + n
+    *reinterpret_cast<float4 *>(work + n * pitch + 16 * t + 4 * hq) =
+        make_float4(c0[0] + c1[0], c0[1] + c1[1], c0[2] + c1[2], c0[3] + c1[3]);
+  }
+  __syncthreads();
+  const int row = R0 + wave;
+  if (row >= NB) return;
+  const int n_row = row + 1, k = min(topk, n_row);
+  unsigned key[E];                                           // 0: no candidate (not causal, NaN, -inf)
+  unsigned hi = 0u, lo = 0xffffffffu;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    key[e] = 0u;
+    if (64 * e < n_row) {
+      const float v = work[wave * pitch + 64 * e + lane];
+      if (64 * e + lane < n_row && v > -__builtin_inff()) key[e] = max(order_key(v), 1u);
+      hi = max(hi, key[e]);
+      lo = min(lo, key[e] - 1u);                             // no candidate: wraps to the top
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    hi = max(hi, (unsigned)__shfl_xor((int)hi, off));
+    lo = min(lo, (unsigned)__shfl_xor((int)lo, off));
+  }
+  hi = __builtin_amdgcn_readfirstlane(hi);
+  lo = __builtin_amdgcn_readfirstlane(lo) + 1u;
+  auto count_ge = [&](unsigned v) {
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (64 * e < n_row) c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[e] >= v));
+    return c;
+  };
+  const int valid = count_ge(1u), take = min(k, valid);
+  unsigned T = 1u;                                           // all candidates
+  if (valid > k) {
+    // at least k keys are >= lo, fewer than k are > hi
+    while (lo < hi) {
+      const unsigned mid = lo + ((hi - lo + 1u) >> 1);
+      const int c = count_ge(mid);
+      if (c >= k) lo = mid; else hi = mid - 1u;
+      if (c == k) break;
+    }
+    T = lo;
+  }
+  int quota = take - (T == 0xffffffffu ? 0 : count_ge(T + 1u));   // of the keys equal to T the first that are still needed
+  int32_t *out = blk_idx + (list0 + row) * topk;
+  int pos = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (64 * e < n_row) {
+      const unsigned long long eq = __builtin_amdgcn_ballot_w64(key[e] == T);
+      const bool keep = key[e] > T || (key[e] == T && __builtin_popcountll(eq & lanes_below(lane)) < quota);
+      const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
+      if (keep) out[pos + __builtin_popcountll(kept & lanes_below(lane))] = 64 * e + lane;
+      pos += __builtin_popcountll(kept);
+      quota -= __builtin_popcountll(eq);
+    }
+  for (int i = take + lane; i < topk; i += 64) out[i] = -1;
+  if (lane == 0) blk_cnt[list0 + row] = take;
+}
+
 // Processing order of the query blocks of one head: sorted by (first kept key block, block id).
 // One workgroup per head: the composite keys (first << 16 | block) of up to 32768 blocks are
 // sorted in LDS (4 bytes per block, up to 128 KiB) by a bitonic network (padded to a power of
@@ -2256,8 +2373,22 @@ hipError_t launch_build_bs(const QKV &x, int nb, const HeadList &hl, int topk, i
                          st, x, hl, NB, NBp, topk, km, (const float *)kpool, blk_idx, blk_cnt);
       return hipSuccess;
     };
+    auto rows_launch = [&](auto held) -> hipError_t {
+      constexpr int E = decltype(held)::value;
+      const size_t lds = bsr_lds(NB);
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs_rows_kernel<E>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((bs_rows_kernel<E>), dim3(hl.n, (NB + BSR_ROWS - 1) / BSR_ROWS, nb), dim3(64 * BSR_ROWS), lds,
+                         st, x, hl, NB, NBp, topk, km, (const float *)kpool, blk_idx, blk_cnt);
+      return hipSuccess;
+    };
     const bool few = nb * hl.n * ((NB + 16 * BSF_WAVES - 1) / (16 * BSF_WAVES)) <= BSF_FEW_GROUPS;
-    const hipError_t e = few ? topk_launch(std::integral_constant<int, BSF_SEL_FEW>{}, bsf_few_lds())
+    const bool by_rows = NB <= BSR_MAX && (int64_t)nb * hl.n * ((NB + BSR_ROWS - 1) / BSR_ROWS) <= BSR_MAX_GROUPS;
+    const hipError_t e = by_rows ? (NB <= 512    ? rows_launch(std::integral_constant<int, 8>{})
+                                    : NB <= 1024 ? rows_launch(std::integral_constant<int, 16>{})
+                                                 : rows_launch(std::integral_constant<int, 32>{}))
+                         : few ? topk_launch(std::integral_constant<int, BSF_SEL_FEW>{}, bsf_few_lds())
                              : topk_launch(std::integral_constant<int, BSF_WAVES>{}, bsf_lds(BSF_WAVES));
     if (e != hipSuccess) return e;
   } else {

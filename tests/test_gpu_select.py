@@ -100,3 +100,30 @@ def test_bs_few_and_many_rows_and_order(B, N, heads, topk):
         assert got[0][1][b] == n and bool((got[0][0][b, n:] == -1).all())
         # pooled values are sums of 64 bf16 numbers in float32: the logits agree to about 1e-6
         check_topk(got[0][0][b, :n].numpy(), score, n, tol=1e-5, relative=False)
+
+
+@pytest.mark.parametrize("kind", ["random", "special"])
+@pytest.mark.parametrize("N,heads,topk", [(32768, 66, 100), (32704, 66, 37), (65536, 33, 112), (131072, 17, 1)])
+def test_bs_rows_in_lds_and_candidate_lists_agree(B, N, heads, topk, kind):
+    """A head alone is selected from rows of logits in LDS (up to 512, 1024, 2048 blocks), in a list of
+    more than 2048 groups of 16 blocks by candidate lists: the same bits, ties (repeated keys), infinite and
+    NaN logits included."""
+    NB = N // 64
+    q, k, _ = random_qkv(64, heads, 1, N)
+    if kind == "special":
+        k = k.clone().view(1, NB, 64, 128)
+        k[:, 3::7] = k[:, 2:3]                                # equal logits
+        k[:, 11::13, 0, 5] = float("inf")                     # +inf or -inf by the sign of the pooled query
+        k[:, 17::29, 1, 7] = float("nan")
+        k = k.view(1, N, 128)
+    got = []
+    for hs in ([heads - 1], list(range(heads))):
+        idx = B.alloc_bs_index(len(hs), N, topk)
+        idx.blk_idx.fill_(-5)
+        ws = torch.empty(B.minf_bs_index_workspace_bytes(q, k, len(hs), topk), dtype=torch.uint8, device="cuda")
+        B.minf_build_bs_index(q, k, hs, topk, idx, ws)
+        torch.cuda.synchronize()
+        got.append((idx.blk_idx[-1].cpu(), idx.blk_cnt[-1].cpu()))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    live = torch.arange(topk)[None] < got[0][1][:, None]
+    assert bool((got[0][0][~live] == -1).all()) and bool((got[0][0][live] >= 0).all())
