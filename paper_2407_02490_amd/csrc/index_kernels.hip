@@ -41,8 +41,18 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 //  smallest (a chunk also meets 64 keys beyond its own, so small ones cost more work).  4 K/V heads
 //  of 40K tokens: 160 workgroups of 1024 keys took 69 us, 632 of 256 take 53.
 constexpr int VS_CHUNK = 1024, VS_CHUNK_SHORT = 256, VS_CHUNK_TINY = 128;
+constexpr int VS_CHUNK_MIN = 64;                   // pass 2 only, where even that fills no chip: 4 half tiles one after the other, not 6
 constexpr int VS_SHORT_N = 32768, VS_TINY_N = 8192;
 constexpr int VS_MIN_GROUPS = 512;
+// Chunks of 64 keys in pass 2 while they are at most 256 workgroups; 128 -> 64 keys, index build, us: 1 to 16 heads of
+// 4K tokens (64 to 256 workgroups of 64 keys) 33.7..36.0 -> 30.9..33.4, 32 heads of 2K (256) 35.4 -> 32.5; 32 heads of
+// 4K (512) 36.2 -> 36.8, 16 heads of 8K and 4 K/V heads (512) 39.8 -> 40.5.
+constexpr int VS_MAX_MIN_GROUPS = 256;
+// Partial sums combined in pass 2 itself instead of by a launch of their own, while they are few and few
+// workgroups repeat it (chunks of pass 1 x K/V groups <= 128): 1 to 16 heads of 4K (32 chunks, up to 4 groups)
+// 30.9..33.4 -> 29.9..31.9, 32 heads of 2K (16 chunks, 8 groups) 32.5 -> 30.8; 32 heads of 4K (32, 8) 36.8 -> 37.6,
+// 4 heads of 8K (64, 4) 38.9 -> 41.5.
+constexpr int VS_FOLD_CHUNKS = 32, VS_FOLD_READS = 128;
 
 struct KvMap {                      // pooling work list of the Block-Sparse build
   int32_t n_kv;                     // distinct KV heads used by the call
@@ -576,6 +586,26 @@ __device__ inline void vs_skew_reduce(const float (&p)[16], float *skew, float *
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// (row max, 1 / row sum) of estimating row `row` from the per-chunk pairs src[64 c], in the order of
+// vs_combine_kernel: 16 ranges of chunks, each summed in chunk order, then in range order.
+__device__ inline float2 vs_combine_row(const float2 *src, int n_chunks) {
+  float M = -INFINITY;
+#pragma unroll 16
+  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, src[64 * c].x);
+  if (M == -INFINITY) return make_float2(0.f, 0.f);
+  const int per = (n_chunks + 15) / 16;
+  float L = 0.f, part = 0.f;
+  int left = per;
+#pragma unroll 16
+  for (int c = 0; c < n_chunks; ++c) {
+    const float2 ml = src[64 * c];
+    part += ml.y * fast_exp2(ml.x - M);
+    if (--left == 0) { L += part; part = 0.f; left = per; }
+  }
+  L += part;
+  return make_float2(M, L > 0.f ? 1.0f / L : 0.f);
+}
+
 template <int PASS, int C>
 __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, VsGroups vg, int last_q, int n_chunks,
                                                        float *ml_part, const float *ml_fin,
@@ -600,6 +630,21 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
   const int N = x.N;
   const int r_min = 64 - last_q;
 
+  DmaLane dl;
+  dma_lane_init(dl, x.k_st, lane);
+  const int key_hi = N - chunk * C;                 // exclusive end of the owned keys
+  // pass 2, 32-key half tiles: the offsets of the chunk meet the half tiles 0 .. C/32 + 1; the chunk's own
+  // keys are the half tiles 0 .. C/32 - 1.  The first two go out before everything else (nothing below
+  // waits for anything younger before they are needed).
+  const int n_half = min(C / 32 + 2, key_hi / 32);
+  auto fetch_half = [&](int mm) {
+    vs_fetch_quarter<32>(kh, x.k_st, dl, key_hi - 32 * (mm + 1), lds + (mm % 3) * HALF_BYTES, wave);
+  };
+  if (PASS == 2) {
+    if (n_half > 0) fetch_half(0);
+    if (n_half > 1) fetch_half(1);
+  }
+
   // Q fragments: lane (n, h) holds Q[N-64 + 32 nb + n][16 ks + 8 h .. +7], which is the B operand
   // of K Q^T and the A operand of Q K^T alike
   bf16x8 q[2][8];
@@ -611,8 +656,6 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
   }
   LaneOfs lo;
   lane_offsets(lo, lane);
-  DmaLane dl;
-  dma_lane_init(dl, x.k_st, lane);
 
   // pass 1 state: lane (n, h) follows rows 32 nb + n over its half of the keys
   float m_run0 = -INFINITY, m_run1 = -INFINITY, l_run0 = 0.f, l_run1 = 0.f;
@@ -620,19 +663,27 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
   // exponent offset  max + log2(sum)  (+inf for a row that does not take part: P = 0)
   float off[2][16];
   if (PASS == 2) {
+    // lane = row, through this wave's LDS into the register layout.  Few chunks are combined here, by every
+    // workgroup; else vs_combine_kernel left the result in ml_fin.
+    const float2 ml = ml_fin ? reinterpret_cast<const float2 *>(ml_fin)[(int64_t)row0 * 64 + lane]
+                             : vs_combine_row(reinterpret_cast<const float2 *>(ml_part) + (int64_t)row0 * n_chunks * 64 + lane,
+                                              n_chunks);
+    dacc[lane] = (lane >= r_min && ml.y > 0.f) ? ml.x - __builtin_amdgcn_logf(ml.y) : INFINITY;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 32 * nb + 8 * (r >> 2) + 4 * h + (r & 3);
-        const float mx = ml_fin[(row0 * 64 + row) * 2 + 0], inv = ml_fin[(row0 * 64 + row) * 2 + 1];
-        off[nb][r] = (row >= r_min && inv > 0.f) ? mx - __builtin_amdgcn_logf(inv) : INFINITY;
+      for (int g = 0; g < 4; ++g) {
+        const float4 e = *reinterpret_cast<const float4 *>(dacc + 32 * nb + 8 * g + 4 * h);
+        off[nb][4 * g] = e.x; off[nb][4 * g + 1] = e.y; off[nb][4 * g + 2] = e.z; off[nb][4 * g + 3] = e.w;
       }
-    for (int i = lane; i < C + 2 * VS_DPAD + 32 * VS_SKEW_PITCH; i += 64) dacc[i] = 0.f;   // dacc and skew
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = lane; i < C + 2 * VS_DPAD + 32 * VS_SKEW_PITCH; i += 64) dacc[i] = 0.f;   // dacc and skew, read by this wave only
   }
-
-  const int key_hi = N - chunk * C;                 // exclusive end of the owned keys
 
   if (PASS == 1) {
     // 64-key tiles, two 16 KiB buffers; tiles are 64-aligned: wholly inside [0, N) or outside
@@ -720,13 +771,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
       }
     }
   } else {
-    // 32-key half tiles, two 8 KiB buffers.  The offsets of the chunk meet the half tiles
-    // 0 .. C/32 + 1; the chunk's own keys are the half tiles 0 .. C/32 - 1.
-    const int n_half = min(C / 32 + 2, key_hi / 32);
     auto tile_key = [&](int mm) { return key_hi - 32 * (mm + 1); };
-    auto fetch = [&](int mm) {
-      vs_fetch_quarter<32>(kh, x.k_st, dl, tile_key(mm), lds + (mm % 3) * HALF_BYTES, wave);
-    };
     // lane (n, h) reads K row n of the half tile: keys run along the lanes in index order
     int kofs[8];
 #pragma unroll
@@ -734,8 +779,6 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
     float carry[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) carry[r] = 0.f;
-    if (n_half > 0) fetch(0);
-    if (n_half > 1) fetch(1);
     for (int m = 0; m < n_half; ++m) {
       const int kt = tile_key(m);
       const char *tK = lds + (m % 3) * HALF_BYTES;
@@ -745,7 +788,7 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
       // older and has landed.
       if (m + 1 < n_half) MINF_WAIT_VMCNT(2); else MINF_WAIT_VMCNT(0);
       __syncthreads();
-      if (m + 2 < n_half) fetch(m + 2);
+      if (m + 2 < n_half) fetch_half(m + 2);
       if (!active) continue;
       const bool diag_tile = kt + 31 > N - 64;
       // s[nb]: register r holds row 32 nb + 8 (r / 4) + 4 h + r % 4, key kt + n
@@ -2159,7 +2202,7 @@ static int vs_ml_chunk_keys(int N) { return N <= VS_TINY_N ? VS_CHUNK_TINY : N <
 static int vs_sum_chunk_keys(int N, int n_groups) {
   for (const int keys : {VS_CHUNK, VS_CHUNK_SHORT})
     if (vs_chunks(N, keys) * n_groups >= VS_MIN_GROUPS) return keys;
-  return VS_CHUNK_TINY;
+  return vs_chunks(N, VS_CHUNK_MIN) * n_groups <= VS_MAX_MIN_GROUPS ? VS_CHUNK_MIN : VS_CHUNK_TINY;
 }
 static int vs_ml_chunks(int N) { return vs_chunks(N, vs_ml_chunk_keys(N)); }
 
@@ -2233,6 +2276,8 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
   const int nc = vs_ml_chunks(N), rows = hl.n * nb;
   const VsScratch w = vs_scratch(N, rows, nb == 1 || vs_prefilters(N, nv, ns), static_cast<char *>(ws));
   const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
+  // pass 2 writes the scores: it may read the partial sums only where these have a place of their own
+  const bool fold = nc <= VS_FOLD_CHUNKS && nc * vg.n <= VS_FOLD_READS && w.ml_part != w.colsum;
   // 48 KiB (three workgroups of four waves per CU; registers allow two) and 75 KiB (two per CU)
   auto score = [&](auto pass, auto chunk_keys, size_t lds) -> hipError_t {
     constexpr int P = decltype(pass)::value, C = decltype(chunk_keys)::value;
@@ -2242,7 +2287,7 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
       if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((vs_score_kernel<P, C>), dim3(vs_chunks(N, C), vg.n, nb), dim3(64 * VS_GROUP), lds, st, x, hl, vg,
-                       last_q, nc, w.ml_part, (const float *)w.ml_fin, w.colsum, w.diagsum);
+                       last_q, nc, w.ml_part, fold ? (const float *)nullptr : (const float *)w.ml_fin, w.colsum, w.diagsum);
     return hipSuccess;
   };
   auto pass1 = [&](auto c) { return score(std::integral_constant<int, 1>{}, c, 3 * VS_TILE_BYTES); };
@@ -2251,13 +2296,15 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
                  3 * HALF_BYTES + VS_GROUP * vs_wave_floats(decltype(c)::value) * sizeof(float));
   };
   auto by_chunk = [&](int keys, auto run) -> hipError_t {
-    return keys == VS_CHUNK_TINY    ? run(std::integral_constant<int, VS_CHUNK_TINY>{})
+    return keys == VS_CHUNK_MIN     ? run(std::integral_constant<int, VS_CHUNK_MIN>{})
+           : keys == VS_CHUNK_TINY  ? run(std::integral_constant<int, VS_CHUNK_TINY>{})
            : keys == VS_CHUNK_SHORT ? run(std::integral_constant<int, VS_CHUNK_SHORT>{})
                                     : run(std::integral_constant<int, VS_CHUNK>{});
   };
   hipError_t e = by_chunk(vs_ml_chunk_keys(N), pass1);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(vs_combine_kernel, dim3(rows), dim3(1024), 0, st, nc, (const float *)w.ml_part, w.ml_fin);
+  if (!fold)
+    hipLaunchKernelGGL(vs_combine_kernel, dim3(rows), dim3(1024), 0, st, nc, (const float *)w.ml_part, w.ml_fin);
   e = by_chunk(vs_sum_chunk_keys(N, vg.n * nb), pass2);
   if (e != hipSuccess) return e;
   // top-k of the line scores: prefilter by many workgroups, exact selection on what is left

@@ -127,3 +127,26 @@ def test_bs_rows_in_lds_and_candidate_lists_agree(B, N, heads, topk, kind):
     assert all(torch.equal(a, b) for a, b in zip(*got))
     live = torch.arange(topk)[None] < got[0][1][:, None]
     assert bool((got[0][0][~live] == -1).all()) and bool((got[0][0][live] >= 0).all())
+
+
+@pytest.mark.parametrize("N", [64, 128, 192, 1984, 2048, 4032, 4096])
+def test_vs_scores_of_short_rows_in_every_grid(B, N):
+    """Chunks of 64 or 128 keys in pass 2, partial sums combined there or by a launch of their own: the
+    line scores of a head have the same bits alone and in a list over eight K/V heads; indices as the oracle's."""
+    q, k, _ = random_qkv(66, 16, 8, N)
+    nv, ns, got = min(40, N), min(100, N), []
+    for hs in (list(range(16)), [13], [13, 2, 5]):
+        idx = B.alloc_vs_index(len(hs), nv, ns, N)
+        ws = torch.empty(B.minf_vs_index_workspace_bytes(q, k, len(hs), 64), dtype=torch.uint8, device="cuda")
+        B.minf_build_vs_index(q, k, hs, 64, nv, ns, idx, ws)
+        torch.cuda.synchronize()
+        scores = ws[:2 * len(hs) * N * 4].view(torch.int32)
+        r, pad = hs.index(13), (-len(hs) * N * 4) % 256 // 4            # the arrays start 256-byte aligned
+        col = scores[r * N:(r + 1) * N].cpu()
+        diag = ws[(len(hs) * N + pad) * 4:].view(torch.int32)[r * N:(r + 1) * N].cpu()
+        got.append((col, diag, idx.v_idx[r].cpu(), idx.s_idx[r].cpu(), idx.counts[r].cpu(), idx.cover_bits[r].cpu()))
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+    col, diag = O.vs_line_scores(O.vs_estimate(to_f64(q[13]), to_f64(k[6]), 64))
+    check_topk(got[0][2].numpy(), col, nv)
+    check_topk(got[0][3].numpy(), diag, ns)
