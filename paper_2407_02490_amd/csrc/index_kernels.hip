@@ -14,7 +14,7 @@
 //   integer image of the fp32 score (counts per range of keys, at most three
 //   passes over registers, or a radix select over memory), ties to the lower
 //   index, followed by an ordered compaction, so the kept indices come out
-//   ascending without a sort.  From 128K scores on, a prefilter by many
+//   ascending without a sort.  On rows beyond 40K scores a prefilter by many
 //   workgroups (group maxima -> a lower bound of the k-th largest -> the scores
 //   that reach it) leaves the select a few thousand candidates.
 // Block-Sparse (Alg. 3, first steps):
@@ -983,6 +983,7 @@ __device__ inline int vs_merge_runs(const int32_t *offs, int k, int N, int2 *run
 // the same in both cases: exact top-k, equal scores to the lower position.
 // ---------------------------------------------------------------------------
 constexpr int VS_SLICE = 16384;                     // scores per workgroup of the filter
+constexpr int VS_REG_SCORES = 40 * 1024;            // longest row that vs_select_kernel holds in registers
 struct VsSelState {                                 // per (head slot, which), in the workspace
   unsigned bound;                                   // order key of the lower bound
   int count;                                        // candidates taken so far (room counter)
@@ -994,13 +995,23 @@ __device__ inline float key_to_float(unsigned key) {
   return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
 
-// largest G = 2^g, 2 <= g <= 6, with N / G >= 4 k; -1 if there is none, or if the row is so short
-// that the three extra launches cost more than they save (below 128K scores)
+// largest G = 2^g, 2 <= g <= 6, with N / G >= 4 k; -1 if there is none
 inline int vs_log_group(int N, int k) {
-  if (N < 131072) return -1;
   for (int g = 6; g >= 2; --g)
     if ((int64_t)(N >> g) >= 4 * (int64_t)k) return g;
   return -1;
+}
+// Whether the prefilter runs, and with which groups.  Rows that the selection holds in registers do without;
+// longer ones take it if it serves both lists (a list without it selects from memory beside it, and the
+// three launches come on top), from 128K scores on also if it serves one.  Index build without -> with, us:
+// 1 head 41K (30, 2048) 98 -> 91, 64K (500, 1500) 120 -> 94, 96K (1000, 6096) 173 -> 119, 127K 206 -> 125;
+// 32 heads 41K 164 -> 159, 64K 187 -> 167, 96K 297 -> 250, 127K 405 -> 326; one list only, 1 head: 41K (3000, 200)
+// 97 -> 123, 64K (1000, 6096) 127 -> 151.
+struct VsFilter { int log_gv, log_gs; bool on; };
+inline VsFilter vs_filter(int N, int nv, int ns) {
+  VsFilter f{vs_log_group(N, nv < N ? nv : N), vs_log_group(N, ns < N ? ns : N), false};
+  f.on = N >= 131072 ? f.log_gv >= 0 || f.log_gs >= 0 : N > VS_REG_SCORES && f.log_gv >= 0 && f.log_gs >= 0;
+  return f;
 }
 
 // grid (ceil(N / 4096), heads, 2), 256 threads: thread t of a workgroup holds the scores
@@ -2244,17 +2255,13 @@ static VsScratch vs_scratch(int N, int rows, bool whole, char *base) {
   w.bytes = (size_t)(p - base);
   return w;
 }
-static bool vs_prefilters(int N, int nv, int ns) {
-  return vs_log_group(N, nv < N ? nv : N) >= 0 || vs_log_group(N, ns < N ? ns : N) >= 0;
-}
-
 size_t vs_index_ws_bytes(int N, int n_heads) { return vs_scratch(N, n_heads, true, nullptr).bytes; }
 
 int vs_index_batch(int N, int n_heads, int nv, int ns, size_t ws_bytes, int batch) {
   const size_t most = ws_bytes / ((size_t)n_heads * N * 2 * sizeof(float));
   int nb = (size_t)batch < most ? batch : (int)most;
   if (nb > 65535 / n_heads) nb = 65535 / n_heads;            // rows are a grid dimension
-  while (nb > 1 && vs_scratch(N, n_heads * nb, vs_prefilters(N, nv, ns), nullptr).bytes > ws_bytes) --nb;
+  while (nb > 1 && vs_scratch(N, n_heads * nb, vs_filter(N, nv, ns).on, nullptr).bytes > ws_bytes) --nb;
   return nb < 1 ? 1 : nb;
 }
 
@@ -2274,7 +2281,8 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
     vg.slot[g][vg.cnt[g]++] = (uint8_t)i;
   }
   const int nc = vs_ml_chunks(N), rows = hl.n * nb;
-  const VsScratch w = vs_scratch(N, rows, nb == 1 || vs_prefilters(N, nv, ns), static_cast<char *>(ws));
+  const VsFilter filter = vs_filter(N, nv, ns);
+  const VsScratch w = vs_scratch(N, rows, nb == 1 || filter.on, static_cast<char *>(ws));
   const int cap = vs_cand_cap(N), n_slices = vs_slices(N);
   // pass 2 writes the scores: it may read the partial sums only where these have a place of their own
   const bool fold = nc <= VS_FOLD_CHUNKS && nc * vg.n <= VS_FOLD_READS && w.ml_part != w.colsum;
@@ -2308,23 +2316,19 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
   e = by_chunk(vs_sum_chunk_keys(N, vg.n * nb), pass2);
   if (e != hipSuccess) return e;
   // top-k of the line scores: prefilter by many workgroups, exact selection on what is left
-  const int kv_ = nv < N ? nv : N, ks_ = ns < N ? ns : N;
-  const int log_gv = vs_log_group(N, kv_), log_gs = vs_log_group(N, ks_);
-  if (log_gv >= 0 || log_gs >= 0)
-    hipLaunchKernelGGL(vs_gmax_kernel, dim3((N + 4095) / 4096, rows, 2), dim3(256), 0, st, N, log_gv, log_gs,
+  if (filter.on) {
+    hipLaunchKernelGGL(vs_gmax_kernel, dim3((N + 4095) / 4096, rows, 2), dim3(256), 0, st, N, filter.log_gv, filter.log_gs,
                        (const float *)w.colsum, (const float *)w.diagsum, w.gmax_v, w.gmax_s);
-  const bool prefilter = log_gv >= 0 || log_gs >= 0;
-  if (prefilter)
-    hipLaunchKernelGGL(vs_bound_kernel, dim3(rows, 2), dim3(1024), 0, st, N, nv, ns, log_gv, log_gs,
+    hipLaunchKernelGGL(vs_bound_kernel, dim3(rows, 2), dim3(1024), 0, st, N, nv, ns, filter.log_gv, filter.log_gs,
                        (const float *)w.gmax_v, (const float *)w.gmax_s, w.state);
-  if (prefilter)
     hipLaunchKernelGGL(vs_filter_kernel, dim3(n_slices, rows, 2), dim3(256), 0, st, N, cap, n_slices,
                        (const float *)w.colsum, (const float *)w.diagsum, w.state, w.cand_val, w.cand_idx, w.seg);
+  }
   auto select = [&](auto held) {
     constexpr int E = decltype(held)::value;
     hipLaunchKernelGGL((vs_select_kernel<E>), dim3(rows, 2), dim3(1024), 0, st, N, nv, ns, (const float *)w.colsum,
                        (const float *)w.diagsum, v_idx, s_idx, cover, cover_bits, counts, cover_words, cap,
-                       prefilter ? n_slices : 0, (const VsSelState *)w.state, (const float *)w.cand_val,
+                       filter.on ? n_slices : 0, (const VsSelState *)w.state, (const float *)w.cand_val,
                        (const int32_t *)w.cand_idx, (const int2 *)w.seg, w.list_val, w.list_idx);
   };
   // scores a thread of the selection holds
