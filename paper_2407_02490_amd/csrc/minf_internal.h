@@ -174,7 +174,9 @@ __device__ inline bool decode_wg(const Sched &s, int &slot, int &blk) {
 // workspace: b n + s, n listed heads.
 constexpr int MAX_BATCH_LAUNCH = 16384;             // batch elements per launch (grid limit 65535)
 __device__ inline QKV at_batch(QKV x, int b) {
-  x.q += b * x.q_sb; x.k += b * x.k_sb; x.v += b * x.v_sb; x.o += b * x.o_sb;
+  if (b != 0) {                                     // single prompts skip the eight 64-bit products
+    x.q += b * x.q_sb; x.k += b * x.k_sb; x.v += b * x.v_sb; x.o += b * x.o_sb;
+  }
   return x;
 }
 
