@@ -6,6 +6,7 @@
 
 #include <mutex>
 
+#include "batch_rule.h"
 #include "minf_internal.h"
 
 using namespace minf;
@@ -92,8 +93,22 @@ QKV view(const minf_qkv *x, int b) {
   return v;
 }
 
-// Batch elements that may run at the same time: outputs laid over each other are written in batch order.
-int outputs_apart(const minf_qkv *x) { return x->o_stride[0] == 0 ? 1 : x->batch; }
+// Batch elements that may run at the same time (heads listed: up to `last`): all, or one if the rule
+// cannot tell their outputs apart.
+int outputs_apart(const minf_qkv *x, int last) {
+  auto layout = [&](const void *p, const int64_t *s, int heads) {
+    return BatchLayout{reinterpret_cast<uintptr_t>(p) / 2, s[0], s[1], s[2], x->batch, heads, x->seq_len};
+  };
+  const int kv = last / (x->n_q_heads / x->n_kv_heads) + 1;
+  return batch_apart(layout(x->q, x->q_stride, last + 1), layout(x->k, x->k_stride, kv), layout(x->v, x->v_stride, kv),
+                     layout(x->o, x->o_stride, last + 1)) ? x->batch : 1;
+}
+int last_head(const HeadList &hl) {
+  int last = 0;
+  for (int i = 0; i < hl.n; ++i)
+    if (hl.h[i] > last) last = hl.h[i];
+  return last;
+}
 
 // Calls launch(first batch element, how many) for groups of at most `most` elements.
 template <class Launch>
@@ -226,7 +241,7 @@ minf_status minf_ashape_attn(const minf_qkv *x, const int32_t *heads, int32_t n_
   n_init = n_init < x->seq_len ? n_init : x->seq_len;
   n_local = n_local < x->seq_len ? n_local : x->seq_len;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
+  return over_batch(x, outputs_apart(x, last_head(hl)), [&](int b, int nb) {
     return launch_ashape(view(x, b), nb, hl, n_init, n_local, st);
   });
 }
@@ -252,7 +267,7 @@ minf_status minf_vs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
       (uint64_t)x->seq_len * (uint64_t)x->v_stride[2] * 2u >= (1ull << 32))
     return MINF_ERR_SHAPE;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
+  return over_batch(x, outputs_apart(x, last_head(hl)), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
     return launch_vs(view(x, b), nb, hl, idx->v_idx + r * idx->nv, idx->cover + r * idx->ns * 2,
                              idx->cover_bits + r * idx->cover_words, idx->counts + r * 4, idx->nv,
@@ -271,7 +286,7 @@ minf_status minf_bs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
   if (idx->topk < 1) return MINF_ERR_BUDGET;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int64_t NB = x->seq_len / MINF_BLOCK;
-  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
+  return over_batch(x, outputs_apart(x, last_head(hl)), [&](int b, int nb) {
     const int64_t r = (int64_t)b * n_heads;
     return launch_bs(view(x, b), nb, hl, idx->blk_idx + r * NB * idx->topk, idx->blk_cnt + r * NB,
                      idx->order ? idx->order + r * NB : nullptr, idx->topk, st);
@@ -299,7 +314,7 @@ minf_status minf_vs_bs_attn(const minf_qkv *x, const int32_t *vs_heads, int32_t 
       if (vs_heads[i] == bs_heads[j]) return MINF_ERR_SHAPE;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int64_t NB = x->seq_len / MINF_BLOCK;
-  return over_batch(x, outputs_apart(x), [&](int b, int nb) {
+  return over_batch(x, outputs_apart(x, last_head(hv) > last_head(hb) ? last_head(hv) : last_head(hb)), [&](int b, int nb) {
     const int64_t rv = (int64_t)b * n_vs, rb = (int64_t)b * n_bs;
     return launch_vs_bs(view(x, b), nb, hv, vs->v_idx + rv * vs->nv, vs->cover + rv * vs->ns * 2,
                         vs->cover_bits + rv * vs->cover_words, vs->counts + rv * 4, vs->nv, vs->ns,

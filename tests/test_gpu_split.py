@@ -300,3 +300,34 @@ def test_batch_elements_are_the_calls_alone(B, nq, nkv, N, layout):
                 assert torch.equal(idx[7 + b * nq + r], alone[b][0][7 + r]), f"runs of element {b}, head {r}"
             for t, (got, want) in enumerate(zip(out, alone[b][1])):
                 assert torch.equal(got[b].view(torch.int16), want.view(torch.int16)), f"output {t} of element {b}"
+
+
+@pytest.mark.parametrize("step", [0, 1])
+def test_outputs_laid_over_each_other_come_out_in_batch_order(B, step):
+    """Outputs of a batch with stride 0, or one head apart: what a later element writes stays."""
+    nb, nq, N = 3, 2, 320
+    x = [random_qkv(500 + b, nq, 1, N) for b in range(nb)]
+    q, k, v = (torch.stack([e[t] for e in x]) for t in range(3))
+    vi, bi = B.alloc_vs_index(nb * nq, 60, 100, N), B.alloc_bs_index(nb * nq, N, 2)
+    B.minf_build_vs_index(q, k, [0, 1], 64, 60, 100, vi, torch.empty(
+        B.minf_vs_index_workspace_bytes(q, k, nq, 64), dtype=torch.uint8, device="cuda"))
+    B.minf_build_bs_index(q, k, [0, 1], 2, bi, torch.empty(
+        B.minf_bs_index_workspace_bytes(q, k, nq, 2), dtype=torch.uint8, device="cuda"))
+    v1, b1 = B.alloc_vs_index(nb, 60, 100, N), B.alloc_bs_index(nb, N, 2)          # head 0 of each element, head 1 of each
+    for t in ("v_idx", "s_idx", "cover", "cover_bits", "counts"):
+        getattr(v1, t).copy_(getattr(vi, t)[0::nq])
+    for t in ("blk_idx", "blk_cnt", "order"):
+        getattr(b1, t).copy_(getattr(bi, t)[1::nq])
+    calls = [lambda o: B.minf_vs_attn(q, k, v, o, [0, 1], vi), lambda o: B.minf_bs_attn(q, k, v, o, [0, 1], bi),
+             lambda o: B.minf_ashape_attn(q, k, v, o, [0, 1], 70, 100), lambda o: B.minf_dense_attn(q, k, v, o, [0, 1]),
+             lambda o: B.minf_vs_bs_attn(q, k, v, o, [0], v1, [1], b1)]
+    for i, call in enumerate(calls):
+        want = torch.empty_like(q)
+        call(want)
+        out = torch.full((step * (nb - 1) + nq, N, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        call(out.as_strided(q.shape, (step * N * 128, N * 128, 128, 1)))
+        torch.cuda.synchronize()
+        for b in range(nb):
+            for h in range(nq):
+                if (b, h) == max((c, g) for c in range(nb) for g in range(nq) if step * c + g == step * b + h):
+                    assert torch.equal(out[step * b + h], want[b, h]), f"call {i}, element {b}, head {h}"

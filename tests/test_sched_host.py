@@ -58,3 +58,8 @@ def test_kernel_rules_take_the_faster_kernel_at_measured_sizes():
     """tests/dispatch_check.cpp (host only): the rules of dispatch.h at sizes where both kernels
     were timed."""
     run_host_check("dispatch_check")
+
+
+def test_outputs_of_a_batch_that_the_rule_calls_apart_are_apart():
+    """tests/batch_rule_check.cpp (host only): batch_rule.h against the places of drawn and of ordinary layouts."""
+    run_host_check("batch_rule_check")
