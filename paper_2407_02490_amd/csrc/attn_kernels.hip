@@ -1288,7 +1288,8 @@ __device__ inline void dma_pair(const char *step_row0, unsigned rb, const DmaRow
                  :: "v"(rows.voff[2]), "v"(rows.voff[3]), "s"(base), "s"(m) : "memory");
 }
 // Gathered rows: lane L of block blk fetches chunk c of row (column id) 4 blk + L / 16 of the step;
-// the byte offset key * rb + 16 c fits 32 bits (checked on the host: N rb < 2^32), key < 2^24.  The
+// the byte offset key * rb + 16 c fits 32 bits (checked on the host: N rb < 2^32), key and rb fit 24 (a
+// product of 32 bits costs four times as much; vs_cols_pipelined leaves longer rows to the exact scheme).  The
 // list holds a step's 32 ids in the order a lane needs them (gather_pos), so that a lane's eight come
 // with two 16-byte reads, one step ahead (an LDS read and its wait in front of every one of a step's
 // 16 loads before: 32 heads of 128K tokens, 3000 columns, 200 slashes: 5.41 -> 5.32 ms);
@@ -2102,6 +2103,10 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
   const int qlast = q0 + BQ - 1;
+  if ((k_rb | v_rb) >> 24) {           // rows of 16 MiB and more (at most 255 tokens): the exact scheme addresses with 64 bits
+    st.l[0] = __builtin_nanf("");
+    return;
+  }
   int *cols = c.cols;
   int vpos = 64 * wave;
   while (vpos < c.n_v) {

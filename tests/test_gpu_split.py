@@ -331,3 +331,28 @@ def test_outputs_laid_over_each_other_come_out_in_batch_order(B, step):
             for h in range(nq):
                 if (b, h) == max((c, g) for c in range(nb) for g in range(nq) if step * c + g == step * b + h):
                     assert torch.equal(out[step * b + h], want[b, h]), f"call {i}, element {b}, head {h}"
+
+
+@pytest.mark.parametrize("nq,row", [(2, (1 << 23) - 8), (2, 1 << 23), (2, (1 << 23) + 136), (600, (1 << 23) + 136)])
+def test_gathered_rows_far_apart(B, nq, row):
+    """Token distances at and beyond 2^24 bytes (128 tokens in 2 GiB): four waves per block, one wave per
+    block (600 heads), and both kinds in one launch."""
+    N, heads = 128, [0, nq - 1]
+    q, k0, v0 = random_qkv(77, nq, 1, N)
+    store = torch.empty((N - 1) * row + 256, dtype=torch.bfloat16, device="cuda")
+    k, v = (store.as_strided((1, N, 128), (0, row, 1), at) for at in (0, 128))
+    k.copy_(k0), v.copy_(v0)
+    V, S = np.array([1, 2, 5, 17, 40, 63, 64, 65, 90, 126]), np.array([0, 70])
+    idx = B.vs_index_from_host([V] * 2, [S] * 2, N)
+    blocks = B.bs_index_from_host(np.zeros((1, 2, 1)), np.ones((1, 2)))
+    o, both = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    B.minf_vs_attn(q, k, v, o, heads, idx)
+    if nq > 2:
+        B.minf_vs_bs_attn(q, k, v, both, heads, idx, [1], blocks)
+    else:                                                        # one kind's list would take the other's head
+        both.copy_(o)
+    torch.cuda.synchronize()
+    for h in heads:
+        want = O.vs_attention(to_f64(q[h]), to_f64(k0[0]), to_f64(v0[0]), V, S, Bm=64)
+        assert_close_rows(o[h], want, f"head {h}")
+        assert torch.equal(both[h], o[h])
