@@ -100,6 +100,19 @@ inline bool ashape_split_pays(int n_q, int N, int n_local) {
   return items <= 512 || (n_local >= N && N >= 4096 && items <= 1024);
 }
 
+// Block-Sparse index of rows of up to 2048 blocks: a workgroup per 16 rows that keeps their logits in LDS
+// (bs_rows_kernel, one workgroup per CU at a time), or the candidate lists of bs_topk_kernel; same bits.
+// groups: workgroups of the first, over heads and batch elements.  The lists cost little where few entries
+// are kept (they are cut less often), the rows cost the same for every budget.  Index build, lists -> rows, us:
+//   top-1    1024 blocks, 24 heads (1536 groups) 226 -> 214, 32 (2048) 261 -> 275; 2048 blocks, 12 heads (1536)
+//            354 -> 311, 16 (2048) 386 -> 400, 24 (3072) 401 -> 576; 29 heads of 1036 blocks (1885) 235 -> 281
+//   top-37   24 heads of 1024 244 -> 215, 32 279 -> 274, 12 of 2048 368 -> 308, 29 of 1036 253 -> 276
+//   top-64   32 heads of 1024 302 -> 276, 16 of 2048 433 -> 397, 29 of 1036 283 -> 273, 24 of 2048 455 -> 578
+//   top-100  32 heads of 1024 371 -> 280, 16 of 2048 538 -> 402; 24 of 2048 (3072) 557 -> 581, 32 674 -> 761
+// Of 4851 points of 700 to 2100 groups the rows lose 9 % at most (top-1) where the rule takes them, 25 % with 2048 for
+// every budget; past 2048 groups they would still gain at top-80 and more.
+inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 ? 1536 : 2048); }
+
 // Order of a launch's work items (minf_internal.h: ORDER_*).  apart: chunks that are equal and 2, 4 or 8
 // get XCDs of their own; together: the largest number of other chunks that are mixed; round: workgroups an
 // XCD holds, if a chunk that fills whole rounds of them by itself loses by either (0: it does not).

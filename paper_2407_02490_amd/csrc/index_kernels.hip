@@ -2042,10 +2042,9 @@ __global__ __launch_bounds__(64 * BSF_WAVES) void bs_topk_kernel(QKV x, HeadList
 // about 20 counts, where bs_topk_kernel walks the key tiles one after the other with two selecting waves
 // and cuts its candidate lists on the way.  Index build with bs_topk_kernel -> with this one, top-100, us:
 // 1 head of 128 blocks 32 -> 21, 313 blocks 67 -> 26, 1024: 160 -> 63, 2048: 234 -> 100; 8 heads of 313 blocks
-// 72 -> 30, 2048: 338 -> 223; 32 heads of 128 blocks 42 -> 29, 512: 166 -> 113, 1024: 371 -> 280, 2048 (4096 workgroups,
-// one per CU at a time): 674 -> 763; top-37, whose lists are cut less often: 16 heads of 2048 (2048 workgroups)
-// 401 -> 396, 32 heads of 1024 (2048) 278 -> 275, of 2048 516 -> 752.
-constexpr int BSR_MAX = 2048, BSR_ROWS = 16, BSR_MAX_GROUPS = 2048;
+// 72 -> 30, 2048: 338 -> 223; 32 heads of 128 blocks 42 -> 29, 512: 166 -> 113, 1024: 371 -> 280.  Up to how many
+// workgroups: bs_rows_pay().
+constexpr int BSR_MAX = 2048, BSR_ROWS = 16;
 constexpr size_t bsr_lds(int NB) {                  // means; partial sums of the pooling, then the logits
   const size_t part = (size_t)BSR_ROWS * 16 * BSF_POOL_PITCH, logits = (size_t)BSR_ROWS * ((NB + 63) / 64 * 64 + 16);
   return (BSR_ROWS * BSF_POOL_PITCH + (part > logits ? part : logits)) * sizeof(float);
@@ -2435,7 +2434,7 @@ hipError_t launch_build_bs(const QKV &x, int nb, const HeadList &hl, int topk, i
       return hipSuccess;
     };
     const bool few = nb * hl.n * ((NB + 16 * BSF_WAVES - 1) / (16 * BSF_WAVES)) <= BSF_FEW_GROUPS;
-    const bool by_rows = NB <= BSR_MAX && (int64_t)nb * hl.n * ((NB + BSR_ROWS - 1) / BSR_ROWS) <= BSR_MAX_GROUPS;
+    const bool by_rows = NB <= BSR_MAX && bs_rows_pay((int64_t)nb * hl.n * ((NB + BSR_ROWS - 1) / BSR_ROWS), topk);
     const hipError_t e = by_rows ? (NB <= 512    ? rows_launch(std::integral_constant<int, 8>{})
                                     : NB <= 1024 ? rows_launch(std::integral_constant<int, 16>{})
                                                  : rows_launch(std::integral_constant<int, 32>{}))
