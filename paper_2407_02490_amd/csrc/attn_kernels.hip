@@ -2936,7 +2936,7 @@ hipError_t launch_bs(const QKV &x, int nb, const HeadList &hl, const int32_t *bl
                      const int32_t *order, int topk, hipStream_t st) {
   const int NB = x.N / BQ;
   const bool split = bs_split_pays(x.n_q, x.N, topk);
-  const Sched s = make_sched(hl, x.group, NB, split ? split_order(x.N) : bs_order(x.N));
+  const Sched s = make_sched(hl, x.group, NB, bs_order(x.N, topk, split));
   if (split) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(bs_split_kernel);

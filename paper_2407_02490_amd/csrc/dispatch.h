@@ -130,7 +130,11 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //           16K 1194 -> 1256; 8/8 32K 731 -> 783
 // Chunk after chunk -> together, 12 heads of 3 K/V heads unless stated:
 //   dense 4K 84 -> 77, 8K 217 -> 207, 16K 768 -> 698; A-shape 4K 85 -> 77, 8K..64K within 1 %
-//   BS    4K 88 -> 81, 8K 243 -> 212, 16K 591 -> 567, 32K 1226 -> 1372; 8 chunks of 16K 413 -> 529
+//   BS    4K 88 -> 81, 8K 243 -> 212, 16K 591 -> 567, 32K 1226 -> 1372; 8 chunks of 16K 413 -> 529; beyond 8K only for
+//         long lists: top-16  11K 72.2 -> 75.5, 10/5 9K 71.7 -> 77.0, 6/3 16K 72.6 -> 82.9;  top-37  15K 227 -> 232,
+//         5/5 9K 68.0 -> 73.4, 6/3 16K 145 -> 164;  top-64  10/5 9K 206 -> 186, 3/3 12K 94.8 -> 87.7, 6/3 16K 238 -> 261;
+//         top-100  11K 303 -> 262, 15K 512 -> 464, 10/5 9K 249 -> 205, 6/3 16K 345 -> 338, worst 3/3 16K 151 -> 157
+//         (some lists of a few blocks gain there too: top-8 11K 57.6 -> 50.8)
 //   VS, four blocks per workgroup: 8K 217 -> 205, 16K 735 -> 681, 32K 2213 -> 2134; others: 4K 91 -> 89,
 //         (500, 1500) 8K 220 -> 236; four-wave blocks of 7 chunks 8K 318 -> 328 (mixed layer)
 struct OrderRule {
@@ -143,7 +147,11 @@ inline OrderRule split_order(int N) {              // four waves per block, any 
 inline OrderRule vs_order(int N, bool share) {
   return share ? OrderRule{N <= 20480, N <= 32768 ? 64 : 0, XCD_CUS} : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
 }
-inline OrderRule bs_order(int N) { return OrderRule{N <= 32768, N <= 16384 ? 49152 / N : 0, 0}; }
+inline OrderRule bs_order(int N, int topk, bool split) {
+  OrderRule r = split ? split_order(N) : OrderRule{N <= 32768, N <= 16384 ? 49152 / N : 0, 0};
+  if (N > 8192 && (topk < 64 || (topk < 100 && N > 14336))) r.together = 0;
+  return r;
+}
 inline OrderRule ashape_order(int N) { return OrderRule{N <= 131072, N <= 65536 ? 64 : 0, 0}; }
 
 }  // namespace minf
