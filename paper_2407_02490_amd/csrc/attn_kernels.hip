@@ -2974,7 +2974,7 @@ hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_
     return hipGetLastError();
   }
   const bool split = vs_split_pays(x.n_q, x.N, nv, ns);
-  const Sched s = make_sched(hl, x.group, NB, split ? split_order(x.N) : vs_order(x.N, false));
+  const Sched s = make_sched(hl, x.group, NB, vs_order(x.n_q, x.N, nv, ns, split, false));
   if (split) {
     const size_t lds = SPLIT * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(vs_split_kernel);
@@ -2985,7 +2985,7 @@ hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_
     return hipGetLastError();
   }
   if (vs_share_pays(x.N, ns)) {
-    const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4, vs_order(x.N, true));
+    const Sched s4 = make_sched(hl, x.group, (NB + 3) / 4, vs_order(x.n_q, x.N, nv, ns, false, true));
     const size_t lds = 4 * RING_BYTES;
     const void *fn = reinterpret_cast<const void *>(vs_share_kernel);
     hipError_t e = set_lds(fn, lds);

@@ -127,7 +127,9 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //   VS, four blocks per workgroup: 32/8 4K 182 -> 135, 8K 517 -> 467; 16/8 13K 676 -> 581; 8/8 16K 599 -> 452, 20K 733 -> 678;
 //           16/8 26K 1871 -> 1970; 8/8 64K 3430 -> 3818; whole rounds: 16/4 16K 869 -> 867, 32K 2768 -> 2949
 //   VS, others: 8/8 4K 72 -> 54, 8K 189 -> 164; 4/4 8K 111 -> 87; (500, 1500) 16/4 8K 320 -> 257, 32/8 8K 518 -> 500,
-//           16K 1194 -> 1256; 8/8 32K 731 -> 783
+//           16K 1194 -> 1256; 8/8 32K 731 -> 783; (30, 64) 32/8 2816 tokens 64.6 -> 53.8, 3136 the same, 4800 71.7 -> 80.0,
+//           6784 103 -> 118, 7488 106 -> 130, 16/4 6208 45.9 -> 53.9, but 8/8 6464 48.8 -> 40.5; (30, 128) 32/8 4800
+//           109 -> 111, 6784 172 -> 170, 16/4 6208 82.7 -> 77.6; (256, 512) 32/8 4800 197 -> 174, 6784 291 -> 266
 // Chunk after chunk -> together, 12 heads of 3 K/V heads unless stated:
 //   dense 4K 84 -> 77, 8K 217 -> 207, 16K 768 -> 698; A-shape 4K 85 -> 77, 8K..64K within 1 %
 //   BS    4K 88 -> 81, 8K 243 -> 212, 16K 591 -> 567, 32K 1226 -> 1372; 8 chunks of 16K 413 -> 529; beyond 8K only for
@@ -137,6 +139,10 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //         (some lists of a few blocks gain there too: top-8 11K 57.6 -> 50.8)
 //   VS, four blocks per workgroup: 8K 217 -> 205, 16K 735 -> 681, 32K 2213 -> 2134; others: 4K 91 -> 89,
 //         (500, 1500) 8K 220 -> 236; four-wave blocks of 7 chunks 8K 318 -> 328 (mixed layer)
+//   VS, four waves per block, where the walk does not grow over the whole row: (500, 1500) 7/7 3712 67.8 -> 56.3,
+//         6/3 4608 62.6 -> 54.5, 7/7 4992 81.4 -> 88.1, 6/6 6912 96.1 -> 111, 5/5 8K 100 -> 110; (256, 256) 5/5 4032
+//         53.5 -> 42.7, 6848 63.5 -> 73.9, 3/3 11K 62.3 -> 72.0; where it does: (1000, 6096) 7/7 4992 82.1 -> 75.5,
+//         5/5 6144 84.9 -> 69.5, 8K 121 -> 116, 3/3 9344 108 -> 84.5, 6/3 9920 184 -> 192; (3000, 200) 3/3 9344 79.4 -> 67.4
 struct OrderRule {
   int apart, together, round;
 };
@@ -144,8 +150,14 @@ constexpr int XCD_CUS = 32;                        // workgroups of 128 KiB and 
 inline OrderRule split_order(int N) {              // four waves per block, any kind; three K/V heads of 16K fit the L2s
   return OrderRule{N <= 16384, 49152 / N, XCD_CUS};
 }
-inline OrderRule vs_order(int N, bool share) {
-  return share ? OrderRule{N <= 20480, N <= 32768 ? 64 : 0, XCD_CUS} : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
+inline OrderRule vs_order(int n_q, int N, int nv, int ns, bool split, bool share) {
+  OrderRule r = split   ? split_order(N)
+                : share ? OrderRule{N <= 20480, N <= 32768 ? 64 : 0, XCD_CUS}
+                        : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
+  // blocks of short walks weigh all the same
+  if (!split && !share && N > 3072 && (int64_t)n_q * (N / 64) > 1024 && nv + 4 * (int64_t)ns < 512) r.apart = 0;
+  if (split && N > 4608 && 16 * (int64_t)(nv > ns ? nv : ns) < 5 * (int64_t)N) r.together = 0;
+  return r;
 }
 inline OrderRule bs_order(int N, int topk, bool split) {
   OrderRule r = split ? split_order(N) : OrderRule{N <= 32768, N <= 16384 ? 49152 / N : 0, 0};
