@@ -2103,10 +2103,6 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
   const char *khb = reinterpret_cast<const char *>(c.kh), *vhb = reinterpret_cast<const char *>(c.vh);
   const unsigned k_rb = (unsigned)c.k_st * 2u, v_rb = (unsigned)c.v_st * 2u;
   const int qlast = q0 + BQ - 1;
-  if ((k_rb | v_rb) >> 24) {           // rows of 16 MiB and more (at most 255 tokens): the exact scheme addresses with 64 bits
-    st.l[0] = __builtin_nanf("");
-    return;
-  }
   int *cols = c.cols;
   int vpos = 64 * wave;
   while (vpos < c.n_v) {
@@ -2135,6 +2131,12 @@ __device__ inline void vs_cols_pipelined(const VsCtx &c, WaveState &st, const QA
     pipe.run();
     wave_lds_sync();
   }
+}
+
+// Rows of 16 MiB and more (at most 255 tokens): dma_pair_gather's product is short of their top bits, and
+// what it fetched (other places of the view) is thrown away for the exact scheme, which addresses with 64 bits.
+__device__ inline void discard_far_gathers(const VsCtx &c, WaveState &st) {
+  if ((uint64_t)(c.k_st | c.v_st) >> 23) st.l[0] = __builtin_nanf("");
 }
 
 // Optimistic pass of the Vertical-Slash kernel, software pipelined.
@@ -2202,6 +2204,7 @@ __device__ __forceinline__ void vs_item(const QKV &x, const HeadList &hl, const 
   mp.q0 = q0; mp.n_init = KEY_NONE; mp.n_local = 1; mp.lo = 0; mp.hi = 0;
 
   vs_pass_pipelined<NW>(c, st, lo, mp, wave, lane, lds);
+  discard_far_gathers(c, st);
   if (NW > 1) {
     if (split_finish<NW>(st, oh, x.o_st, q0, lds, wave, lane)) return;
   }
@@ -2419,7 +2422,7 @@ __device__ __forceinline__ void vs_share_item(const QKV &x, const HeadList &hl, 
       if (usable < n) break;
     }
     vs_cols_pipelined<1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
-    redo = needs_exact(st);
+    redo = needs_exact(st);        // (no far rows here: at least 3072 tokens)
     if (!redo) wave_finish(st, oh, x.o_st, q0, ring, lane);
   }
   // ---- blocks that must be redone exactly: the four waves share the steps of one after the other,
@@ -2894,6 +2897,7 @@ __global__ __launch_bounds__(256) void vs_ring_kernel(QKV x, HeadList hl, const 
   if (!active) return;       // no workgroup barrier below this line
   // ---- phase B: verticals, per wave
   vs_cols_pipelined<1>(c, st, qa, has_ref, lo, mp, dk, dv, 0, lane);
+  discard_far_gathers(c, st);
   if (needs_exact(st)) {
     load_q(st, qh, x.q_st, q0, lane);   // the pipelined pass kept Q in accumulator registers only
     reset_for_max_pass(st);
