@@ -142,7 +142,8 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //   VS, four waves per block, where the walk does not grow over the whole row: (500, 1500) 7/7 3712 67.8 -> 56.3,
 //         6/3 4608 62.6 -> 54.5, 7/7 4992 81.4 -> 88.1, 6/6 6912 96.1 -> 111, 5/5 8K 100 -> 110; (256, 256) 5/5 4032
 //         53.5 -> 42.7, 6848 63.5 -> 73.9, 3/3 11K 62.3 -> 72.0; where it does: (1000, 6096) 7/7 4992 82.1 -> 75.5,
-//         5/5 6144 84.9 -> 69.5, 8K 121 -> 116, 3/3 9344 108 -> 84.5, 6/3 9920 184 -> 192; (3000, 200) 3/3 9344 79.4 -> 67.4
+//         5/5 6144 84.9 -> 69.5, 8K 121 -> 116, 3/3 9344 108 -> 84.5, 6/3 9920 184 -> 192, 3/3 12160 146 -> 159, two
+//         prompts of 15744 407 -> 451; (3000, 200) 3/3 9344 79.4 -> 67.4
 struct OrderRule {
   int apart, together, round;
 };
@@ -156,7 +157,7 @@ inline OrderRule vs_order(int n_q, int N, int nv, int ns, bool split, bool share
                         : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
   // blocks of short walks weigh all the same
   if (!split && !share && N > 3072 && (int64_t)n_q * (N / 64) > 1024 && nv + 4 * (int64_t)ns < 512) r.apart = 0;
-  if (split && N > 4608 && 16 * (int64_t)(nv > ns ? nv : ns) < 5 * (int64_t)N) r.together = 0;
+  if (split && (N > 12032 || (N > 4608 && 16 * (int64_t)(nv > ns ? nv : ns) < 5 * (int64_t)N))) r.together = 0;
   return r;
 }
 inline OrderRule bs_order(int N, int topk, bool split) {
