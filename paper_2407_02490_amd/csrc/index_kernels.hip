@@ -2303,8 +2303,7 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
                  3 * HALF_BYTES + VS_GROUP * vs_wave_floats(decltype(c)::value) * sizeof(float));
   };
   auto by_chunk = [&](int keys, auto run) -> hipError_t {
-    return keys == VS_CHUNK_MIN     ? run(std::integral_constant<int, VS_CHUNK_MIN>{})
-           : keys == VS_CHUNK_TINY  ? run(std::integral_constant<int, VS_CHUNK_TINY>{})
+    return keys == VS_CHUNK_TINY    ? run(std::integral_constant<int, VS_CHUNK_TINY>{})
            : keys == VS_CHUNK_SHORT ? run(std::integral_constant<int, VS_CHUNK_SHORT>{})
                                     : run(std::integral_constant<int, VS_CHUNK>{});
   };
@@ -2312,7 +2311,8 @@ hipError_t launch_build_vs(const QKV &x, int nb, const HeadList &hl, int last_q,
   if (e != hipSuccess) return e;
   if (!fold)
     hipLaunchKernelGGL(vs_combine_kernel, dim3(rows), dim3(1024), 0, st, nc, (const float *)w.ml_part, w.ml_fin);
-  e = by_chunk(vs_sum_chunk_keys(N, vg.n * nb), pass2);
+  const int sum_keys = vs_sum_chunk_keys(N, vg.n * nb);
+  e = sum_keys == VS_CHUNK_MIN ? pass2(std::integral_constant<int, VS_CHUNK_MIN>{}) : by_chunk(sum_keys, pass2);
   if (e != hipSuccess) return e;
   // top-k of the line scores: prefilter by many workgroups, exact selection on what is left
   if (filter.on) {

@@ -52,3 +52,9 @@ def test_attention_kernels_use_no_scratch_memory(kernels):
     assert len(names) == 10
     for n in names:
         assert kernels[n][".private_segment_fixed_size"] == 0 and kernels[n][".vgpr_spill_count"] == 0, n
+
+
+def test_score_kernels_are_those_that_are_launched(kernels):
+    """Chunks of 64 keys belong to pass 2 only."""
+    score = sorted(n[n.index("ILi") + 3:].split("EEv")[0] for n in kernels if "vs_score_kernel" in n)
+    assert score == sorted(f"{p}ELi{c}" for p, c in ((1, 128), (1, 256), (1, 1024), (2, 64), (2, 128), (2, 256), (2, 1024)))
