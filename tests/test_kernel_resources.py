@@ -56,5 +56,5 @@ def test_attention_kernels_use_no_scratch_memory(kernels):
 
 def test_score_kernels_are_those_that_are_launched(kernels):
     """Chunks of 64 keys belong to pass 2 only."""
-    score = sorted(n[n.index("ILi") + 3:].split("EEv")[0] for n in kernels if "vs_score_kernel" in n)
+    score = sorted(n[n.index("ILi") + 3:].split("EEEv")[0] for n in kernels if "vs_score_kernel" in n)
     assert score == sorted(f"{p}ELi{c}" for p, c in ((1, 128), (1, 256), (1, 1024), (2, 64), (2, 128), (2, 256), (2, 1024)))
