@@ -25,8 +25,9 @@ def build_vs(B, q, k, heads, nv, ns):
     return idx
 
 
-# 8192 | 32768 | 40960 scores: the steps of what a thread holds; behind the last, from memory; from
-# 131072 on the candidates of the prefilter; the run bits come from LDS up to 262144
+# 8192 | 32768 | 40960 scores: the steps of what a thread holds; behind the last, the candidates of the
+# prefilter if it serves both lists, from 131072 on also if it serves one, else from memory; the run bits come
+# from LDS up to 262144
 @pytest.mark.parametrize("N,nv,ns", [(64, 64, 64), (128, 1, 1), (4096, 256, 512), (8192, 1000, 6096), (8256, 1000, 6096),
                                      (32768, 100, 1800), (32832, 3000, 200), (40960, 500, 1500), (41024, 500, 1500),
                                      (131072, 1000, 6096), (262144, 30, 2048), (262208, 30, 2048)])
@@ -46,6 +47,24 @@ def test_vs_selection_and_runs(B, N, nv, ns):
         col, diag = O.vs_line_scores(O.vs_estimate(to_f64(q[1]), to_f64(k[0]), 64))
         check_topk(idx.v_idx[1].cpu().numpy(), col, nv)
         check_topk(idx.s_idx[1].cpu().numpy(), diag, ns)
+
+
+@pytest.mark.parametrize("N,nv,ns", [(41024, 1000, 6096), (41024, 500, 1500), (65536, 1000, 6096), (97472, 1000, 6096),
+                                     (97536, 1000, 6096), (131072, 1000, 9000), (131072, 9000, 30), (131072, 40000, 40000)])
+def test_vs_selection_of_long_rows(B, N, nv, ns):
+    """Rows beyond what a thread holds, with the prefilter for both lists (97536: 4 x 6096 groups of 4), for one
+    of them (from 131072 on) and for none: exactly the largest line scores, which lie at the start of the
+    workspace, equal ones to the lower position."""
+    q, k, _ = random_qkv(67, 2, 1, N)
+    idx = B.alloc_vs_index(2, nv, ns, N)
+    ws = torch.empty(B.minf_vs_index_workspace_bytes(q, k, 2, 64), dtype=torch.uint8, device="cuda")
+    B.minf_build_vs_index(q, k, [0, 1], 64, nv, ns, idx, ws)
+    torch.cuda.synchronize()
+    scores = ws[:4 * N * 4].view(torch.float32).view(2, 2, N).cpu()
+    for which, (lines, n) in enumerate(((idx.v_idx, nv), (idx.s_idx, ns))):
+        for r in range(2):
+            best = torch.sort(scores[which, r], descending=True, stable=True).indices[:n]
+            assert torch.equal(lines[r].cpu(), torch.sort(best).values.int()), f"list {which}, row {r}"
 
 
 @pytest.mark.parametrize("N", [1024, 4160, 12352, 33024, 65600, 131072])

@@ -356,3 +356,81 @@ def test_gathered_rows_far_apart(B, nq, row):
         want = O.vs_attention(to_f64(q[h]), to_f64(k0[0]), to_f64(v0[0]), V, S, Bm=64)
         assert_close_rows(o[h], want, f"head {h}")
         assert torch.equal(both[h], o[h])
+
+
+def index_rows(idx):
+    """Arrays of an index with their valid runs, per row."""
+    runs = idx.counts[:, 2].tolist()
+    return [[t[r] for t in (idx.v_idx, idx.s_idx, idx.cover_bits, idx.counts)] + [idx.cover[r, :c]]
+            for r, c in enumerate(runs)]
+
+
+def build(B, q, k, heads, nv, ns, extra):
+    rows = len(heads) * (q.shape[0] if q.dim() == 4 else 1)
+    idx = B.alloc_vs_index(rows, nv, ns, q.shape[-2])
+    ws = torch.empty(extra * B.minf_vs_index_workspace_bytes(q, k, len(heads), 64), dtype=torch.uint8, device="cuda")
+    B.minf_build_vs_index(q, k, heads, 64, nv, ns, idx, ws)
+    return idx
+
+
+@pytest.mark.parametrize("engine", ["wave", "ring"])
+def test_batch_elements_with_four_blocks_per_workgroup(B, monkeypatch, engine):
+    """17 heads of 65 blocks are too many to split, 1400 slashes enough for vs_share_kernel: its batch
+    elements, those of the one launch with a Block-Sparse head, and of the ring engine, against calls alone."""
+    monkeypatch.setenv("MINF_VS_ENGINE", engine)
+    nb, nq, N, nv, ns, topk = 3, 17, 4160, 40, 1400, 5
+    x = [random_qkv(700 + b, nq, 1, N) for b in range(nb)]
+    q, k, v = (torch.stack([e[t] for e in x]) for t in range(3))
+    vs_heads, bs_heads = list(range(1, nq)), [0]
+
+    def run(q, k, v, n):
+        vi, bi = build(B, q, k, vs_heads, nv, ns, 4), B.alloc_bs_index(n, N, topk)
+        B.minf_build_bs_index(q, k, bs_heads, topk, bi, torch.empty(
+            4 * B.minf_bs_index_workspace_bytes(q, k, 1, topk), dtype=torch.uint8, device="cuda"))
+        o, both = torch.zeros_like(q), torch.zeros_like(q)
+        B.minf_vs_attn(q, k, v, o, vs_heads, vi)
+        B.minf_bs_attn(q, k, v, o, bs_heads, bi)
+        B.minf_vs_bs_attn(q, k, v, both, vs_heads, vi, bs_heads, bi)
+        torch.cuda.synchronize()
+        return o, both
+
+    o, both = run(q, k, v, nb)
+    if engine == "wave":
+        assert torch.equal(o, both)
+    for b in range(nb):
+        o1, both1 = run(q[b], k[b], v[b], 1)
+        assert torch.equal(o[b], o1) and torch.equal(both[b], both1), f"element {b}"
+
+
+@pytest.mark.parametrize("N,nv,ns", [(41024, 500, 1500), (41024, 1000, 6096), (131072, 1000, 9000), (131072, 30, 2048)])
+def test_batch_elements_of_rows_beyond_the_register_selection(B, N, nv, ns):
+    """Three elements that share a larger workspace, with the prefilter on both lists, on none and on one of
+    them: the index of calls alone."""
+    nb, heads = 3, [1, 0]
+    x = [random_qkv(800 + b, 2, 1, N) for b in range(nb)]
+    q, k = (torch.stack([e[t] for e in x]) for t in range(2))
+    got = index_rows(build(B, q, k, heads, nv, ns, 4))
+    for b in range(nb):
+        for r, want in enumerate(index_rows(build(B, q[b], k[b], heads, nv, ns, 1))):
+            assert all(torch.equal(a, w) for a, w in zip(got[b * len(heads) + r], want)), f"element {b}, row {r}"
+
+
+@pytest.mark.parametrize("N,nq,topk", [(32768, 22, 100), (135168, 2, 37)])
+def test_batch_elements_of_the_candidate_lists(B, N, nq, topk):
+    """Rows of logits for an element alone and candidate lists for three together (2112 workgroups of 16
+    rows), and lists of rows beyond 2048 blocks: the same index."""
+    nb, heads = 3, list(range(nq))
+    x = [random_qkv(900 + b, nq, 1, N) for b in range(nb)]
+    q, k = (torch.stack([e[t] for e in x]) for t in range(2))
+
+    def run(q, k, n):
+        idx = B.alloc_bs_index(n * nq, N, topk)
+        B.minf_build_bs_index(q, k, heads, topk, idx, torch.empty(
+            4 * B.minf_bs_index_workspace_bytes(q, k, nq, topk), dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return idx.blk_idx, idx.blk_cnt, idx.order
+
+    got = run(q, k, nb)
+    for b in range(nb):
+        for a, w in zip(got, run(q[b], k[b], 1)):
+            assert torch.equal(a[b * nq:(b + 1) * nq], w), f"element {b}"
