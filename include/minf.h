@@ -20,6 +20,11 @@
  *     any status other than MINF_OK and MINF_ERR_HIP nothing was launched.
  *     MINF_ERR_HIP means the runtime refused a launch; with batch > 1 the
  *     launches of earlier batch elements may already be enqueued then.
+ *   - The batch elements of an attention call run at the same time.  Where the
+ *     output of one lies over the output or over the inputs of another, or the
+ *     library cannot tell (it compares addresses, strides and sizes), they run
+ *     in batch order.  o may be q itself; within an element, o must not lie
+ *     over k, v or other rows of q.
  *   - Layout: q [batch, n_q_heads, seq_len, head_dim], k/v [batch, n_kv_heads,
  *     seq_len, head_dim], o like q; bf16; head_dim contiguous; strides in
  *     elements for (batch, head, token).  Query head h reads KV head
@@ -130,7 +135,8 @@ int32_t minf_vs_cover_words(int32_t seq_len);
  * only (512 bytes per head and 64-token block) when topk <= 112 and the sequence has fewer than
  * 65536 blocks: pooling of Q, block logits and selection are then fused and neither the pooled Q
  * nor a logit is stored.  Larger budgets also keep the pooled Q and stage the logits of a few
- * heads at a time: up to 2 GiB more. */
+ * heads at a time: up to 2 GiB more.  The sizes are one batch element's; a larger workspace lets
+ * more elements of a call run together (the whole ws_bytes may be written). */
 size_t minf_vs_index_workspace_bytes(const minf_qkv *x, int32_t n_heads, int32_t last_q);
 size_t minf_bs_index_workspace_bytes(const minf_qkv *x, int32_t n_heads, int32_t topk);
 
@@ -158,8 +164,8 @@ minf_status minf_build_vs_index(const minf_qkv *x, const int32_t *heads, int32_t
  * instead of `ws`.  Allocates nothing, frees nothing, synchronises nothing.
  * Inputs whose workspace need (minf_vs_index_workspace_bytes) exceeds
  * MINF_NOALLOC_SCRATCH_BYTES are refused with MINF_ERR_WORKSPACE; with
- * batch > 1 the batch elements use the array one after the other on the
- * stream.  All calls on one GPU share that GPU's array: calls that overlap
+ * batch > 1 as many batch elements as fit use the array at a time, the next
+ * ones after them on the stream.  All calls on one GPU share that GPU's array: calls that overlap
  * in time on one GPU (different streams, different threads) race; nothing in
  * the array needs clearing between calls (every word that is read was
  * written by the same call).  The array's device address is looked up on the
@@ -234,8 +240,10 @@ minf_status minf_bs_attn(const minf_qkv *x, const int32_t *heads, int32_t n_head
  * to one so that every part of the chip holds both kinds at once.  Sequences
  * of more than 8192 tokens for which one of the two calls would take a block
  * with several waves, or several blocks per workgroup, get the launches of the
- * two calls.  Faster than the two calls up to about 8K tokens; slower from 32K
- * on (the patterns disturb each other's cache reuse).
+ * two calls.  Up to 8K tokens up to twice as fast as the two calls on most
+ * layers, 5 to 12 % slower on a few (12 + 4 heads of 4 K/V heads at 4K tokens,
+ * 4 + 4 of 8 at 8K); slower from 32K on where it is one launch there (the
+ * patterns disturb each other's cache reuse).
  */
 minf_status minf_vs_bs_attn(const minf_qkv *x, const int32_t *vs_heads, int32_t n_vs, const minf_vs_index *vs,
                             const int32_t *bs_heads, int32_t n_bs, const minf_bs_index *bs, void *hip_stream);

@@ -959,10 +959,12 @@ struct AshapeLoop {
   }
 };
 
-// The first loads of a pass, in the order in which they are needed: K(0), K(1), V(0), K(2).  They go out
-// before the Q rows are awaited, and the pass starts on K(0) alone: with every load of the prologue
-// awaited behind Q, and a zero output update in the first iteration, windows of (0, 64) took 333 us
-// instead of 323 and (128, 1024) 714 instead of 705 (8 heads of 128K tokens); longer ones the same.
+// The first loads of a pass, in the order in which they are needed: K(0), K(1), V(0), K(2).  In ashape_kernel
+// they go out ahead of the Q rows: loads return in order, so the wait for Q is the wait for these too, and
+// the counted waits below find nothing left to wait for; one memory latency instead of two, and the first
+// iteration has no output update.  (Loads behind Q and a zero update: windows of (0, 64) 333 us instead of
+// 323, (128, 1024) 714 instead of 705, 8 heads of 128K tokens; longer ones the same.)  In vs_share_kernel Q
+// is there and a pass does start on K(0) alone.
 __device__ inline void ashape_first_loads(const AshapeCtx &c, const WaveDma &d) {
   const unsigned dst = lds_addr_of(c.lds) + d.lds_w;
   auto tile = [&](const char *w, unsigned rb, const DmaRows &rows, int t, unsigned to) {
@@ -2235,8 +2237,9 @@ __global__ __launch_bounds__(64) void vs_kernel(QKV x, HeadList hl, const int32_
 
 // Few work items: four waves per query block, each with a quarter of its steps (and its own ring;
 // 160 KiB, one workgroup per CU).  The time is the longest item's: 128 steps of 32 keys at 4K tokens
-// took 100 us as one wave and take 37 us as four (bound by the CU's load path, 1.3 us per step of
-// all four waves against 0.8 us for one wave alone).  The shares meet once, in split_finish.
+// took 100 us as one wave and take 37 us as four.  Bound by one in-order wave per SIMD that waits on its
+// loads: matrix pipelines busy a third of the time, 64 KiB per step of all four waves in 1.3 us = 50 GB/s
+// where the path into the LDS moves 140.  The shares meet once, in split_finish.
 constexpr int SPLIT = 4;
 __global__ __launch_bounds__(64 * SPLIT) void vs_split_kernel(QKV x, HeadList hl, const int32_t *v_idx,
                                                               const int32_t *cover, const uint32_t *cover_bits,
@@ -3009,10 +3012,12 @@ hipError_t launch_vs(const QKV &x, int nb, const HeadList &hl, const int32_t *v_
 
 // Longest row on which minf_vs_bs_attn interleaves the kinds also where one of them shares blocks among
 // waves; beyond it such layers take the launches of the two calls.  Short rows end with idle CUs, and
-// one launch ends once: both calls -> one launch, mixed recipe, us: 32 heads of 1K tokens 62 -> 52,
-// 8 of 2K 47 -> 30, 8 of 4K 83 -> 69, 32 of 4K 256 -> 216, of 8K 890 -> 588 (blocks that are redone
-// overlap with the other kind).  On long rows the kinds disturb each other's cache reuse: one wave per
-// block, one launch against two, 16K tokens 2048 against 2058 us, 32K 6352 against 5988.
+// one launch ends once: both calls -> one launch, mixed recipe, us (Vertical-Slash + Block-Sparse heads / K/V
+// heads): 26+6/8 1K 63 -> 47, 4K 250 -> 207, 8K 835 -> 562 (blocks that are redone overlap with the other kind),
+// 6+2/2 2K 48 -> 30, 4K 78 -> 65, 8K the same, 24+8/1 8K 1192 -> 739, 16+16/8 8K 1063 -> 956; not so where the
+// calls' own orders of the blocks gain more: 12+4/4 4K 119 -> 125, 4+4/8 8K 169 -> 189.  On long rows the kinds disturb each
+// other's cache reuse: one wave per block, one launch against two, 16K tokens 2048 against 2058 us, 32K 6352
+// against 5988.
 constexpr int ONE_LAUNCH_MAX_N = 8192;
 
 hipError_t launch_vs_bs(const QKV &x, int nb, const HeadList &hv, const int32_t *v_idx, const int32_t *cover,

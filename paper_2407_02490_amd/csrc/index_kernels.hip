@@ -634,8 +634,8 @@ __global__ __launch_bounds__(256, 2) void vs_score_kernel(QKV x, HeadList hl, Vs
   dma_lane_init(dl, x.k_st, lane);
   const int key_hi = N - chunk * C;                 // exclusive end of the owned keys
   // pass 2, 32-key half tiles: the offsets of the chunk meet the half tiles 0 .. C/32 + 1; the chunk's own
-  // keys are the half tiles 0 .. C/32 - 1.  The first two go out before everything else (nothing below
-  // waits for anything younger before they are needed).
+  // keys are the half tiles 0 .. C/32 - 1.  The first two go out ahead of the Q rows and the row statistics,
+  // whose waits (loads return in order) then cover them: one memory latency for all.
   const int n_half = min(C / 32 + 2, key_hi / 32);
   auto fetch_half = [&](int mm) {
     vs_fetch_quarter<32>(kh, x.k_st, dl, key_hi - 32 * (mm + 1), lds + (mm % 3) * HALF_BYTES, wave);

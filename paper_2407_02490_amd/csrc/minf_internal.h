@@ -181,11 +181,12 @@ __device__ inline bool decode_wg(const Sched &s, int &slot, int &blk) {
 // The batch elements of a call run in one launch: grid dimension y of the attention kernels, z of the index
 // kernels.  A launch per element leaves the chip to drain, and the index kernels of short prompts do not
 // fill it: two prompts of 40256 tokens, 16 heads, 3 % of 3.65 ms; pairs of short ones 188 -> 139 us and
-// 147 -> 112.  The kernels are chosen as for one element, so an element has the same bits alone.  Index row of (batch element b, list slot s) in the index arrays and the
-// workspace: b n + s, n listed heads.
+// 147 -> 112.  The kernels are chosen as for one element, so an element has the same bits alone.  Index row
+// of (batch element b, list slot s) in the index arrays and the workspace: b n + s, n listed heads.
+// (Outputs that meet: batch_rule.h.)
 constexpr int MAX_BATCH_LAUNCH = 16384;             // batch elements per launch (grid limit 65535)
 __device__ inline QKV at_batch(QKV x, int b) {
-  if (b != 0) {                                     // single prompts skip the eight 64-bit products
+  if (b != 0) {                                     // single prompts skip the four 64-bit products
     x.q += b * x.q_sb; x.k += b * x.k_sb; x.v += b * x.v_sb; x.o += b * x.o_sb;
   }
   return x;
