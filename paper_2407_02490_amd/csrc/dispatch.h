@@ -113,9 +113,10 @@ inline bool ashape_split_pays(int n_q, int N, int n_local) {
 // every budget; past 2048 groups they would still gain at top-80 and more.
 inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 ? 1536 : 2048); }
 
-// Order of a launch's work items (minf_internal.h: ORDER_*).  apart: chunks that are equal and 2, 4 or 8
-// get XCDs of their own; together: the largest number of other chunks that are mixed; round: workgroups an
-// XCD holds, if a chunk that fills whole rounds of them by itself loses by either (0: it does not).
+// Order of a launch's work items (minf_internal.h: ORDER_*).  apart: chunks that are equal and 2, 4 or 8 get XCDs
+// of their own, except for the numbers of chunks in the mask `but`; together: the largest number of other chunks
+// that are mixed; round: workgroups an XCD holds, if a chunk that fills whole rounds of them by itself loses by
+// either (0: it does not).
 // Chunk after chunk -> apart, us (query heads / K/V heads, tokens):
 //   dense   8/8 4K 72 -> 52, 8K 191 -> 163, 16K 673 -> 456, 32K 2295 -> 1746; 4/4 32K 1234 -> 884; 16/4 8K 301 -> 238;
 //           32/8 4K 171 -> 133, 8K 514 -> 467, 20K 2779 -> 2712; 8/2 8K..32K, 16/4 16K, 4/4 64K the same;
@@ -130,6 +131,13 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //           16K 1194 -> 1256; 8/8 32K 731 -> 783; (30, 64) 32/8 2816 tokens 64.6 -> 53.8, 3136 the same, 4800 71.7 -> 80.0,
 //           6784 103 -> 118, 7488 106 -> 130, 16/4 6208 45.9 -> 53.9, but 8/8 6464 48.8 -> 40.5; (30, 128) 32/8 4800
 //           109 -> 111, 6784 172 -> 170, 16/4 6208 82.7 -> 77.6; (256, 512) 32/8 4800 197 -> 174, 6784 291 -> 266
+//   VS, four waves per block where the walk does not grow over the whole row, two chunks, three and more rounds of items,
+//         4/2 heads: (256, 512) 8640 56.5 -> 61.2, 9600 65.3 -> 62.5, 13440 75.6 -> 88.3, 16000 88.6 -> 84.9; (3000, 200) 11840
+//         90.2 -> 100, 15680 116 -> 108; (500, 1500) 12160 143 -> 136, 13760 135 -> 151; longer walks (100, 1800) 12480
+//         162 -> 161, 13120 182 -> 170, 13760 163 -> 171, (30, 2048) 13120 181 -> 170; two rounds of items gain 0 to 3 %
+//         four chunks of short walks, three rounds: (256, 512) 8/4 4160 46.0 -> 48.9, 4480 51.0 -> 54.3, 4/4 8320 49.7 -> 56.2,
+//         9600 55.8 -> 59.6, 11.2K 58.7 -> 63.4, 11.5K 67.1 -> 62.3, 12.5K the same; of longer ones (3000, 200) 4/4 9280
+//         86.2 -> 78.7, (30, 2048) 8640 104 -> 94.1
 // Chunk after chunk -> together, 12 heads of 3 K/V heads unless stated:
 //   dense 4K 84 -> 77, 8K 217 -> 207, 16K 768 -> 698; A-shape 4K 85 -> 77, 8K..64K within 1 %
 //   BS    4K 88 -> 81, 8K 243 -> 212, 16K 591 -> 567, 32K 1226 -> 1372; 8 chunks of 16K 413 -> 529; beyond 8K only for
@@ -145,19 +153,25 @@ inline bool bs_rows_pay(int64_t groups, int topk) { return groups <= (topk < 64 
 //         5/5 6144 84.9 -> 69.5, 8K 121 -> 116, 3/3 9344 108 -> 84.5, 6/3 9920 184 -> 192, 3/3 12160 146 -> 159, two
 //         prompts of 15744 407 -> 451; (3000, 200) 3/3 9344 79.4 -> 67.4
 struct OrderRule {
-  int apart, together, round;
+  int apart, together, round, but = 0;
 };
 constexpr int XCD_CUS = 32;                        // workgroups of 128 KiB and more that an XCD holds
 inline OrderRule split_order(int N) {              // four waves per block, any kind; three K/V heads of 16K fit the L2s
   return OrderRule{N <= 16384, 49152 / N, XCD_CUS};
 }
 inline OrderRule vs_order(int n_q, int N, int nv, int ns, bool split, bool share) {
+  const int64_t walk = nv + 4 * (int64_t)ns;
   OrderRule r = split   ? split_order(N)
                 : share ? OrderRule{N <= 20480, N <= 32768 ? 64 : 0, XCD_CUS}
                         : OrderRule{N <= 8192, N <= 4096 ? 64 : 0, 0};
   // blocks of short walks weigh all the same
-  if (!split && !share && N > 3072 && (int64_t)n_q * (N / 64) > 1024 && nv + 4 * (int64_t)ns < 512) r.apart = 0;
-  if (split && (N > 12032 || (N > 4608 && 16 * (int64_t)(nv > ns ? nv : ns) < 5 * (int64_t)N))) r.together = 0;
+  if (!split && !share && N > 3072 && (int64_t)n_q * (N / 64) > 1024 && walk < 512) r.apart = 0;
+  const bool flat = 16 * (int64_t)(nv > ns ? nv : ns) < 5 * (int64_t)N;        // no walk grows over the whole row
+  if (split && (N > 12032 || (N > 4608 && flat))) r.together = 0;
+  if (split && flat && (int64_t)n_q * (N / 64) > 512) {
+    if (N > 8192 && N <= 14336 && walk < 7168) r.but |= 2;
+    if (N > 4096 && N <= 11264 && walk < 3072) r.but |= 4;
+  }
   return r;
 }
 inline OrderRule bs_order(int N, int topk, bool split) {

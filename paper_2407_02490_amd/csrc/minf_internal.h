@@ -90,7 +90,7 @@ inline Sched make_sched(const HeadList &hl, int group, int n_blk, const OrderRul
   }
   if (chunks < 2 || whole) return s;
   if (equal && 8 % chunks == 0) {
-    if (!rule.apart) return s;
+    if (!rule.apart || (rule.but & chunks)) return s;
     s.order = ORDER_APART;
     s.apart = 8 / chunks;
     s.per_xcd = (n_blk + s.apart - 1) / s.apart * s.csize[0];

@@ -140,7 +140,7 @@ static int check_order(const std::vector<int> &heads, int group, int n_blk, cons
 
 int main() {
   int bad = 0;
-  const OrderRule any{1, 64, 0}, rounds{1, 64, 32}, apart_only{1, 2, 0};
+  const OrderRule any{1, 64, 0}, rounds{1, 64, 32}, apart_only{1, 2, 0}, but_two{1, 64, 0, 2};
   for (int nb : {1, 2, 7, 8, 9, 63, 64, 257}) {
     bad |= check_order({0, 4}, 4, nb, any, ORDER_APART);
     bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15}, 4, nb, any, ORDER_APART);
@@ -150,6 +150,8 @@ int main() {
     bad |= check_order({0, 4, 8}, 4, nb, apart_only, ORDER_BY_CHUNK);
     bad |= check_order({0, 1, 2}, 4, nb, any, ORDER_BY_CHUNK);             // one K/V head
     bad |= check_order({0, 4}, 4, nb, OrderRule{0, 0, 0}, ORDER_BY_CHUNK);
+    bad |= check_order({0, 4}, 4, nb, but_two, ORDER_BY_CHUNK);
+    bad |= check_order({0, 1, 2, 3}, 1, nb, but_two, ORDER_APART);
   }
   bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7}, 4, 64, rounds, ORDER_BY_CHUNK);   // 8 blocks x 4 heads an XCD
   bad |= check_order({0, 1, 2, 3, 4, 5, 6, 7}, 4, 48, rounds, ORDER_APART);
